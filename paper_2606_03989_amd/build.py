@@ -19,11 +19,13 @@ SOURCES = ["gbp_kernels.hip", "gbp_adjoint.hip", "gbp_tree.hip", "gbp_transfer.h
 ARCH = os.environ.get("PIXVOD_ARCH", "gfx950")
 
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# Per-source flags. The persistent passes in gbp_kernels.hip loop over tiles
-# around a body that needs every register: hoisting loop-invariant values
-# (constants, addresses) out of such a loop only makes them spill, so machine
-# loop-invariant code motion is off there.
-SOURCE_FLAGS = {"gbp_kernels.hip": ["-mllvm", "-disable-machine-licm"]}
+# Per-source flags. The iteration's kernels spell out their fused multiply-adds
+# and are compiled with contraction off: the compiler then has no choice to
+# make differently in two kernels that have to agree bit for bit. The persistent
+# batch kernel loops over items around a body that needs every register:
+# hoisting loop-invariant values (constants, addresses) out of that loop only
+# makes them spill, so machine loop-invariant code motion is off there.
+SOURCE_FLAGS = {"gbp_kernels.hip": ["-ffp-contract=off", "-mllvm", "-disable-machine-licm"]}
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-unused-result"]
 
 

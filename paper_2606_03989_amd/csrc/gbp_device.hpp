@@ -4,6 +4,11 @@
 // planes; every per-pixel 6x6 / 7x7 solve, marginalisation and message is
 // evaluated in double precision (the information matrices span ~1 .. 1e8).
 //
+// The fused multiply-adds of the iteration's arithmetic are written out (its
+// kernels are compiled with contraction off), so that every kernel that
+// inlines a function gets the same bits: the schedules, a batch and a single
+// context, and the reverse sweep's recompute agree exactly.
+//
 // Tangent ordering [theta(3); rho(3); logdepth], Exp of Eq. (exp_err),
 // perturbations on the right (Eq. var), information form (eta, Lambda).
 #pragma once
@@ -40,6 +45,7 @@ struct Geo {
     int pitch;            // floats per row of every plane
     long plane;           // floats per plane (H * pitch)
     double fx, fy, cx, cy;
+    double ifx, ify;      // 1 / fx, 1 / fy
 };
 
 struct Strengths {
@@ -52,6 +58,8 @@ struct Strengths {
     double prior_ell;
     double prior_R[9];    // Exp(prior_xi)^-1 rotation
     double prior_t[3];    // Exp(prior_xi)^-1 translation
+    double prior_q[4];    // Exp(prior_xi): unit quaternion (vector, scalar)
+    double prior_p[3];    // and translation
     int prior_is_identity;
     int has_sigma_map;
     int has_prior_map;    // per-pixel log-depth prior means (in.prior_ell)
@@ -116,21 +124,21 @@ struct BatchLaunch {
 // SE(3)
 
 __device__ inline void skew_mul(const double w[3], const double v[3], double out[3]) {
-    out[0] = w[1] * v[2] - w[2] * v[1];
-    out[1] = w[2] * v[0] - w[0] * v[2];
-    out[2] = w[0] * v[1] - w[1] * v[0];
+    out[0] = fma(w[1], v[2], -(w[2] * v[1]));
+    out[1] = fma(w[2], v[0], -(w[0] * v[2]));
+    out[2] = fma(w[0], v[1], -(w[1] * v[0]));
 }
 
-// 1/x and 1/sqrt(x) in double precision: the hardware estimate refined by two
-// Newton steps (quadratic convergence from the ~2^-22 estimate to rounding)
+// 1/x in double precision: the hardware estimate (relative error e below 2^-22)
+// refined by one cubic step, y (1 + e + e^2), whose error e^3 is below 2^-66.
+// Four instructions in a chain of four, against five for two Newton steps.
 __device__ inline double rcp_nr(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, y, 1.0);
-    y = fma(y, e, y);
-    e = fma(-x, y, 1.0);
-    return fma(y, e, y);
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
 }
 
+// 1/sqrt(x): the hardware estimate refined by two Newton steps
 __device__ inline double rsqrt_nr(double x) {
     double y = __builtin_amdgcn_rsq(x);
     const double h = 0.5 * x;
@@ -288,6 +296,122 @@ __device__ inline void se3_between(const double Rj[9], const double tj[3], const
 }
 
 // ---------------------------------------------------------------------------
+// poses of the iteration kernels: unit quaternion q = (vector 3, scalar) and
+// translation t. An Exp is 39 FP64 operations and the residual between two
+// poses 75, against 80 and 95 with rotation matrices, and a pose is 7 values
+// instead of 12; the log needs no case near pi (half angles stay below pi / 2).
+
+// x / sin-type series in x = theta^2, truncation below 1e-19 for theta < 0.1
+__device__ inline void pose_exp(const double xi[6], double q[4], double t[3]) {
+    const double* w = xi;
+    const double* p = xi + 3;
+    const double th2 = fma(w[0], w[0], fma(w[1], w[1], w[2] * w[2]));
+    double a, c, C;   // sin(theta/2)/theta, cos(theta/2), (theta - sin(theta))/theta^3
+    if (th2 < 1e-2) {
+        a = fma(th2, fma(th2, fma(th2, fma(th2, 1.0 / 185794560.0, -1.0 / 645120.0), 1.0 / 3840.0), -1.0 / 48.0), 0.5);
+        c = fma(th2, fma(th2, fma(th2, fma(th2, 1.0 / 10321920.0, -1.0 / 46080.0), 1.0 / 384.0), -1.0 / 8.0), 1.0);
+        C = fma(th2, fma(th2, fma(th2, fma(th2, 1.0 / 39916800.0, -1.0 / 362880.0), 1.0 / 5040.0), -1.0 / 120.0), 1.0 / 6.0);
+    } else {
+        const double th = sqrt(th2);
+        double sh;
+        sincos(0.5 * th, &sh, &c);
+        a = sh / th;
+        C = (th - 2.0 * sh * c) / (th2 * th);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q[k] = a * w[k];
+    q[3] = c;
+    // V rho = rho + B (w x rho) + C w x (w x rho), B = (1 - cos(theta))/theta^2 = 2 a^2
+    double u1[3], u2[3];
+    skew_mul(w, p, u1);
+    skew_mul(w, u1, u2);
+    const double B = 2.0 * a * a;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] = fma(C, u2[k], fma(B, u1[k], p[k]));
+}
+
+__device__ inline void pose_rotation(const double q[4], double R[9]) {
+    const double x = q[0], y = q[1], z = q[2], s = q[3];
+    const double x2 = x + x, y2 = y + y, z2 = z + z;
+    const double xx = x2 * x, yy = y2 * y, zz = z2 * z;
+    R[0] = 1.0 - (yy + zz);
+    R[4] = 1.0 - (xx + zz);
+    R[8] = 1.0 - (xx + yy);
+    const double sz = s * z2, sy = s * y2, sx = s * x2;
+    R[1] = fma(x2, y, -sz);
+    R[3] = fma(x2, y, sz);
+    R[2] = fma(x2, z, sy);
+    R[6] = fma(x2, z, -sy);
+    R[5] = fma(y2, z, -sx);
+    R[7] = fma(y2, z, sx);
+}
+
+// xi = Log of the pose (q, t); -q is the same rotation as q.
+// theta/2 = asin|v|, theta = 2 |v| g(|v|^2) with g the series of asin(n)/n;
+// translation part rho = t - w x t / 2 + D w x (w x t)
+__device__ inline void pose_log(const double q[4], const double t[3], double xi[6]) {
+    const double n2 = fma(q[0], q[0], fma(q[1], q[1], q[2] * q[2]));
+    double f, D;   // theta / |v|, (1 - (theta/2) cot(theta/2))/theta^2
+    if (n2 < 2.5e-3) {
+        double g = 63.0 / 2816.0;
+        g = fma(g, n2, 35.0 / 1152.0);
+        g = fma(g, n2, 5.0 / 112.0);
+        g = fma(g, n2, 3.0 / 40.0);
+        g = fma(g, n2, 1.0 / 6.0);
+        g = fma(g, n2, 1.0);
+        f = q[3] < 0.0 ? -2.0 * g : 2.0 * g;
+        const double th2 = n2 * f * f;
+        D = fma(th2, fma(th2, fma(th2, 1.0 / 1209600.0, 1.0 / 30240.0), 1.0 / 720.0), 1.0 / 12.0);
+    } else {
+        const double sg = q[3] < 0.0 ? -1.0 : 1.0;
+        const double n = sqrt(n2), c = sg * q[3];
+        const double th = 2.0 * atan2(n, c);
+        f = sg * th / n;
+        D = (1.0 - 0.5 * th * c / n) / (th * th);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) xi[k] = f * q[k];
+    double u1[3], u2[3];
+    skew_mul(xi, t, u1);
+    skew_mul(xi, u1, u2);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) xi[3 + k] = fma(D, u2[k], fma(-0.5, u1[k], t[k]));
+}
+
+// Log(Tj^-1 Ti): the identity-factor residual of Eq. (regul)
+__device__ inline void pose_between(const double qj[4], const double tj[3], const double qi[4], const double ti[3],
+                                    double r[6]) {
+    double q[4], t[3], u1[3], u2[3];
+    const double d[3] = {ti[0] - tj[0], ti[1] - tj[1], ti[2] - tj[2]};
+    skew_mul(qj, qi, u1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q[k] = fma(qj[3], qi[k], fma(-qi[3], qj[k], -u1[k]));
+    q[3] = fma(qj[3], qi[3], fma(qj[0], qi[0], fma(qj[1], qi[1], qj[2] * qi[2])));
+    // Rj^T d = d - 2 s (v x d) + 2 v x (v x d)
+    skew_mul(qj, d, u1);
+    skew_mul(qj, u1, u2);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] = fma(2.0, fma(-qj[3], u1[k], u2[k]), d[k]);
+    pose_log(q, t, r);
+}
+
+// tau = Log(T Exp(m)) for T = (q, t)
+__device__ inline void pose_retract(const double q[4], const double t[3], const double m[6], double tau[6]) {
+    double qm[4], tm[3], q1[4], t1[3], u1[3], u2[3];
+    pose_exp(m, qm, tm);
+    skew_mul(q, qm, u1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q1[k] = fma(q[3], qm[k], fma(qm[3], q[k], u1[k]));
+    q1[3] = fma(q[3], qm[3], -fma(q[0], qm[0], fma(q[1], qm[1], q[2] * qm[2])));
+    // R tm = tm + 2 s (v x tm) + 2 v x (v x tm)
+    skew_mul(q, tm, u1);
+    skew_mul(q, u1, u2);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t1[k] = fma(2.0, fma(q[3], u1[k], u2[k]), tm[k] + t[k]);
+    pose_log(q1, t1, tau);
+}
+
+// ---------------------------------------------------------------------------
 // small symmetric linear algebra, packed upper storage
 
 // in-place LDL^T-free Cholesky of a packed 6x6 SPD matrix; A <- L (lower in the
@@ -403,6 +527,72 @@ __device__ inline void chol7_solve(const double L[28], const double inv_diag[7],
 // has a single entry in its last column)
 __device__ inline double chol7_var_last(const double inv_diag[7]) { return inv_diag[6] * inv_diag[6]; }
 
+// m = L^-1 eta for the packed SPD L (7x7) by LDL^T elimination with eta carried
+// along as a further row, and [L^-1]_66 = 1 / D_66; false on a non-positive
+// pivot. No square roots: seven reciprocals and about 160 FP64 operations,
+// against about 230 for Cholesky and two substitutions. Overwrites L and eta.
+__device__ inline bool ldl7_solve(double L[28], double eta[7], double m[7], double& var_last) {
+    bool ok = true;
+    double id[7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        const double d = L[s7(j, j)];
+        ok = ok && (d > 0.0);
+        id[j] = rcp_nr(fmax(d, 1e-300));
+        double l[7];
+#pragma unroll
+        for (int i = j + 1; i < 7; ++i) l[i] = L[s7(j, i)] * id[j];
+#pragma unroll
+        for (int i = j + 1; i < 7; ++i) {
+            eta[i] = fma(-l[i], eta[j], eta[i]);
+#pragma unroll
+            for (int k = i; k < 7; ++k) L[s7(i, k)] = fma(-l[i], L[s7(j, k)], L[s7(i, k)]);
+        }
+#pragma unroll
+        for (int i = j + 1; i < 7; ++i) L[s7(j, i)] = l[i];
+    }
+    var_last = id[6];
+#pragma unroll
+    for (int i = 6; i >= 0; --i) {
+        double x = eta[i] * id[i];
+#pragma unroll
+        for (int k = i + 1; k < 7; ++k) x = fma(-L[s7(i, k)], m[k], x);
+        m[i] = x;
+    }
+    return ok;
+}
+
+// the same for a packed 6x6 matrix (a quadtree node)
+__device__ inline bool ldl6_solve(double L[21], double eta[6], double m[6]) {
+    bool ok = true;
+    double id[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const double d = L[s6(j, j)];
+        ok = ok && (d > 0.0);
+        id[j] = rcp_nr(fmax(d, 1e-300));
+        double l[6];
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) l[i] = L[s6(j, i)] * id[j];
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) {
+            eta[i] = fma(-l[i], eta[j], eta[i]);
+#pragma unroll
+            for (int k = i; k < 6; ++k) L[s6(i, k)] = fma(-l[i], L[s6(j, k)], L[s6(i, k)]);
+        }
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) L[s6(j, i)] = l[i];
+    }
+#pragma unroll
+    for (int i = 5; i >= 0; --i) {
+        double x = eta[i] * id[i];
+#pragma unroll
+        for (int k = i + 1; k < 6; ++k) x = fma(-L[s6(i, k)], m[k], x);
+        m[i] = x;
+    }
+    return ok;
+}
+
 // ---------------------------------------------------------------------------
 // photometric and prior factors
 
@@ -452,14 +642,14 @@ struct PhotoPre {
 __device__ inline PhotoPre photometric_begin(const Geo& g, const Inputs& in, int u, int v, const double R[9],
                                              const double t[3], double ell) {
     PhotoPre p;
-    p.q0 = ((double)u - g.cx) / g.fx;
-    p.q1 = ((double)v - g.cy) / g.fy;
+    p.q0 = ((double)u - g.cx) * g.ifx;
+    p.q1 = ((double)v - g.cy) * g.ify;
     p.rho = exp(-ell);
-    p.a0 = R[0] * p.q0 + R[1] * p.q1 + R[2] + p.rho * t[0];
-    p.a1 = R[3] * p.q0 + R[4] * p.q1 + R[5] + p.rho * t[1];
-    const double a2 = R[6] * p.q0 + R[7] * p.q1 + R[8] + p.rho * t[2];
+    p.a0 = fma(p.rho, t[0], fma(R[0], p.q0, fma(R[1], p.q1, R[2])));
+    p.a1 = fma(p.rho, t[1], fma(R[3], p.q0, fma(R[4], p.q1, R[5])));
+    const double a2 = fma(p.rho, t[2], fma(R[6], p.q0, fma(R[7], p.q1, R[8])));
     p.iz = rcp_nr(a2 > 0.0 ? a2 : 1.0);
-    const double wx = g.fx * p.a0 * p.iz + g.cx, wy = g.fy * p.a1 * p.iz + g.cy;
+    const double wx = fma(g.fx * p.a0, p.iz, g.cx), wy = fma(g.fy * p.a1, p.iz, g.cy);
     p.valid = a2 > 0.0 && wx >= -WARP_EPS && wx <= (g.W - 1) + WARP_EPS && wy >= -WARP_EPS &&
               wy <= (g.H - 1) + WARP_EPS;
     const double x = p.valid ? fmin(fmax(wx, 0.0), (double)(g.W - 1)) : 0.0;
@@ -497,34 +687,35 @@ __device__ inline Photo photometric_end(const PhotoPre& p, const Geo& g, const S
     if (!SEL && !p.valid) return f;
     f.valid = true;
     const double fx = p.fx, fy = p.fy, iz = p.iz, rho = p.rho, q0 = p.q0, q1 = p.q1;
-    const double It = (1.0 - fy) * ((1.0 - fx) * p.s[0] + fx * p.s[1]) + fy * ((1.0 - fx) * p.s[2] + fx * p.s[3]);
-    const double gx = (1.0 - fy) * ((1.0 - fx) * p.s[4] + fx * p.s[5]) + fy * ((1.0 - fx) * p.s[6] + fx * p.s[7]);
-    const double gy = (1.0 - fy) * ((1.0 - fx) * p.s[8] + fx * p.s[9]) + fy * ((1.0 - fx) * p.s[10] + fx * p.s[11]);
+    const double w3 = fx * fy, w2 = fy - w3, w1 = fx - w3, w0 = (1.0 - fx) - w2;
+    const double It = fma(w3, (double)p.s[3], fma(w2, (double)p.s[2], fma(w1, (double)p.s[1], w0 * p.s[0])));
+    const double gx = fma(w3, (double)p.s[7], fma(w2, (double)p.s[6], fma(w1, (double)p.s[5], w0 * p.s[4])));
+    const double gy = fma(w3, (double)p.s[11], fma(w2, (double)p.s[10], fma(w1, (double)p.s[9], w0 * p.s[8])));
     f.r = (double)pin.Is - It;
     // c = -g^T dw/da  (row 3-vector)
     const double c0 = -gx * g.fx * iz, c1 = -gy * g.fy * iz;
-    const double c2 = (gx * g.fx * p.a0 + gy * g.fy * p.a1) * iz * iz;
+    const double c2 = -fma(c0, p.a0, c1 * p.a1) * iz;
     // J_theta = c.(-R [q]x d) = -(R^T c).(q x d) = -((R^T c) x q).d with b = R^T c
-    const double b0 = R[0] * c0 + R[3] * c1 + R[6] * c2;
-    const double b1 = R[1] * c0 + R[4] * c1 + R[7] * c2;
-    const double b2 = R[2] * c0 + R[5] * c1 + R[8] * c2;
-    f.J[0] = -(b1 * 1.0 - b2 * q1);
-    f.J[1] = -(b2 * q0 - b0 * 1.0);
-    f.J[2] = -(b0 * q1 - b1 * q0);
+    const double b0 = fma(R[0], c0, fma(R[3], c1, R[6] * c2));
+    const double b1 = fma(R[1], c0, fma(R[4], c1, R[7] * c2));
+    const double b2 = fma(R[2], c0, fma(R[5], c1, R[8] * c2));
+    f.J[0] = fma(b2, q1, -b1);
+    f.J[1] = fma(-b2, q0, b0);
+    f.J[2] = fma(b1, q0, -(b0 * q1));
     f.J[3] = rho * b0;
     f.J[4] = rho * b1;
     f.J[5] = rho * b2;
-    f.J[6] = -rho * (c0 * t[0] + c1 * t[1] + c2 * t[2]);
+    f.J[6] = -rho * fma(c0, t[0], fma(c1, t[1], c2 * t[2]));
     const double isig = s.has_sigma_map ? rcp_nr((double)pin.sigD) : s.inv_sigD;
     const double lamD = isig * isig;
     const double M = fabs(f.r) * isig;
     double kappa = 1.0;
     if constexpr (SEL) {
-        const double iM = rcp_nr(M > s.huber_k ? M : 1.0);
-        kappa = (M > s.huber_k) ? s.huber_k * iM * (2.0 - s.huber_k * iM) : 1.0;
+        const double kM = s.huber_k * rcp_nr(M > s.huber_k ? M : 1.0);
+        kappa = (M > s.huber_k) ? kM * (2.0 - kM) : 1.0;
     } else if (M > s.huber_k) {
-        const double iM = rcp_nr(M);
-        kappa = s.huber_k * iM * (2.0 - s.huber_k * iM);
+        const double kM = s.huber_k * rcp_nr(M);
+        kappa = kM * (2.0 - kM);
     }
     f.w = kappa * lamD;
     if constexpr (SEL) {
@@ -552,135 +743,144 @@ __device__ inline void add_photometric(const Photo& f, double L[28], double eta[
 #pragma unroll
     for (int a = 0; a < 7; ++a) {
         const double wJa = f.w * f.J[a];
-        eta[a] -= wJa * f.r;
+        eta[a] = fma(-wJa, f.r, eta[a]);
 #pragma unroll
-        for (int b = a; b < 7; ++b) L[s7(a, b)] += wJa * f.J[b];
+        for (int b = a; b < 7; ++b) L[s7(a, b)] = fma(wJa, f.J[b], L[s7(a, b)]);
     }
 }
 
-// Adds the prior factor (Eq. prior) at the linearisation point tau,
-// (R, t) = Exp(tau), ell to (L, eta).
-__device__ inline void add_prior(const Strengths& s, const double tau[6], const double R[9], const double t[3],
-                                 double ell, const PixelInputs& pin, double L[28], double eta[7]) {
-    // --- prior: r = [Log(Exp(prior)^-1 Exp(tau)); ell - prior_ell],
-    //     J = blockdiag(I + ad/2 + ad^2/12, 1)
-    double rp[6];
+// Information lamP J^T J (packed 6x6, written through put(r, c, value)) and
+// -lamP J^T r of a pose prior (Eq. prior) with residual r = (w, p) and
+// J = I + ad(r)/2 + ad(r)^2/12 = [[S, 0], [Q, S]],
+//   S = I + W/2 + W^2/12, Q = P/2 + (PW + WP)/12, W = [w]x, P = [p]x.
+// The products are expanded with [a]x [b]x = b a^T - (a.b) I, W w = P p = 0 and
+// n = w x p (P w = -n):
+//   S^T S = (a^2 + |w|^2/4) I + (a/6 + |w|^2/144 - 1/4) w w^T,  a = 1 - |w|^2/12,
+//   Q^T S = (1/12 + |w|^2/72) (w.p) I - P/2 - (w.p)/24 W - (1/6 + |w|^2/144) w p^T
+//           + p w^T/12 - (w.p)/144 w w^T,
+//   Q^T Q = (|p|^2/4 + (w.p)^2/36) I + (|w|^2/144 - 1/4) p p^T + |p|^2/144 w w^T
+//           - (w.p)/48 (w p^T + p w^T) + (p n^T + n p^T)/24,
+//   S^T w = w, Q^T p = (|p|^2 w - (w.p) p)/12, S^T p = a p - n/2 + (w.p)/12 w:
+// about 125 FP64 operations, against about 210 for the blocks and their
+// products.
+template <class Put>
+__device__ inline void pose_prior(double lamP, const double r[6], double eta[6], Put put) {
+    const double* w = r;
+    const double* p = r + 3;
+    const double th2 = fma(w[0], w[0], fma(w[1], w[1], w[2] * w[2]));
+    const double pp = fma(p[0], p[0], fma(p[1], p[1], p[2] * p[2]));
+    const double wp = fma(w[0], p[0], fma(w[1], p[1], w[2] * p[2]));
+    double n[3];
+    skew_mul(w, p, n);
+    constexpr double c12 = 1.0 / 12.0, c24 = 1.0 / 24.0, c144 = 1.0 / 144.0;
+    const double a = fma(-c12, th2, 1.0), t144 = c144 * th2, wp144 = c144 * wp;
+    const double alpha = fma(a, a, 0.25 * th2), beta = fma(a, 1.0 / 6.0, t144 - 0.25);
+    // lower right block S^T S and upper left block S^T S + Q^T Q
+    const double dq = fma(0.25, pp, fma(wp * (1.0 / 36.0), wp, alpha));
+    const double kpp = t144 - 0.25, kww = fma(c144, pp, beta), kwp = wp * (-1.0 / 48.0);
+    double lw[3], lp[3], ln[3], x[3], y[3], z[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        lw[k] = lamP * w[k];
+        lp[k] = lamP * p[k];
+        ln[k] = lamP * n[k];
+        z[k] = c24 * p[k];
+        x[k] = fma(kpp, p[k], fma(kwp, w[k], c24 * n[k]));
+        y[k] = fma(kww, w[k], kwp * p[k]);
+    }
+    const double lalpha = lamP * alpha, ldq = lamP * dq;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = i; j < 3; ++j) {
+            put(i, j, fma(lp[i], x[j], fma(lw[i], y[j], i == j ? fma(ln[i], z[j], ldq) : ln[i] * z[j])));
+            put(3 + i, 3 + j, i == j ? fma(lw[i], beta * w[j], lalpha) : lw[i] * (beta * w[j]));
+        }
+    // upper right block Q^T S: the skew part is -[s]x with s = p/2 + (w.p)/24 w
+    const double c1 = -(1.0 / 6.0) - t144, k1 = lamP * (wp * fma(1.0 / 72.0, th2, c12)), wp24 = c24 * wp;
+    double f[3], g[3], sk[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        f[k] = fma(c1, p[k], -wp144 * w[k]);
+        g[k] = c12 * w[k];
+        sk[k] = lamP * fma(wp24, w[k], 0.5 * p[k]);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            // -[s]x entry (i, j): +s_k for (0,1), (1,2), (2,0), -s_k for the transposes
+            const int k = 3 - i - j;
+            const double d = i == j ? k1 : ((j - i + 3) % 3 == 1 ? sk[k] : -sk[k]);
+            put(i, 3 + j, fma(lw[i], f[j], fma(lp[i], g[j], d)));
+        }
+    const double q1 = fma(c12, pp, 1.0), q2 = c12 * wp;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        eta[k] = fma(q2, lp[k], -q1 * lw[k]);
+        eta[3 + k] = fma(-a, lp[k], fma(0.5, ln[k], -q2 * lw[k]));
+    }
+}
+
+// residual of a pose prior: Log(Exp(prior_xi)^-1 T) for T = (q, t) = Exp(tau)
+__device__ inline void prior_residual(const Strengths& s, const double tau[6], const double q[4], const double t[3],
+                                      double rp[6]) {
     if (s.prior_is_identity) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) rp[k] = tau[k];
     } else {
-        double Rr[9], tr[3];
-        se3_compose(s.prior_R, s.prior_t, R, t, Rr, tr);
-        se3_log(Rr, tr, rp);
+        pose_between(s.prior_q, s.prior_p, q, t, rp);
     }
-    // J = [[S, 0], [Q, S]] with, for rp = (w, q), W = [w]x, P = [q]x and
-    // [a]x [b]x = b a^T - (a.b) I:
-    //   S = I + W/2 + W^2/12 = I + W/2 + (w w^T - |w|^2 I)/12,
-    //   Q = P/2 + (PW + WP)/12 = P/2 + (w q^T + q w^T - 2 (w.q) I)/12
-    double S[9], Q[9];
-    {
-        const double w0 = rp[0], w1 = rp[1], w2 = rp[2], p0 = rp[3], p1 = rp[4], p2 = rp[5];
-        const double w[3] = {w0, w1, w2}, q[3] = {p0, p1, p2};
-        const double Wm[9] = {0.0, -w2, w1, w2, 0.0, -w0, -w1, w0, 0.0};
-        const double Pm[9] = {0.0, -p2, p1, p2, 0.0, -p0, -p1, p0, 0.0};
-        const double th2 = w0 * w0 + w1 * w1 + w2 * w2;
-        const double wq = w0 * p0 + w1 * p1 + w2 * p2;
-        constexpr double c12 = 1.0 / 12.0;
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double I = (r == c) ? 1.0 : 0.0;
-                S[r * 3 + c] = I + 0.5 * Wm[r * 3 + c] + (w[r] * w[c] - I * th2) * c12;
-                Q[r * 3 + c] = 0.5 * Pm[r * 3 + c] + (w[r] * q[c] + q[r] * w[c] - 2.0 * I * wq) * c12;
-            }
-    }
-    // J^T J = [[S^T S + Q^T Q, Q^T S], [S^T Q, S^T S]],
-    // J^T rp = [S^T rp_w + Q^T rp_q; S^T rp_q]
-    const double lamP = s.lamP;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        double e0 = 0.0, e1 = 0.0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            e0 += S[k * 3 + a] * rp[k] + Q[k * 3 + a] * rp[3 + k];
-            e1 += S[k * 3 + a] * rp[3 + k];
-        }
-        eta[a] -= lamP * e0;
-        eta[3 + a] -= lamP * e1;
-#pragma unroll
-        for (int b = a; b < 3; ++b) {
-            double ss = 0.0, qq = 0.0;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                ss += S[k * 3 + a] * S[k * 3 + b];
-                qq += Q[k * 3 + a] * Q[k * 3 + b];
-            }
-            L[s7(a, b)] += lamP * (ss + qq);
-            L[s7(3 + a, 3 + b)] += lamP * ss;
-        }
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            double qs = 0.0;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) qs += Q[k * 3 + a] * S[k * 3 + b];
-            L[s7(a, 3 + b)] += lamP * qs;
-        }
-    }
+}
+
+// (L, eta) = the prior factor (Eq. prior) at the linearisation point tau,
+// (q, t) = Exp(tau), ell
+__device__ inline void prior_factor(const Strengths& s, const double tau[6], const double q[4], const double t[3],
+                                    double ell, const PixelInputs& pin, double L[28], double eta[7]) {
+    double rp[6];
+    prior_residual(s, tau, q, t, rp);
+    pose_prior(s.lamP, rp, eta, [&](int r, int c, double x) { L[s7(r, c)] = x; });
     const double pell = s.has_prior_map ? (double)pin.prior_ell : s.prior_ell;
-    eta[6] -= lamP * (ell - pell);
-    L[s7(6, 6)] += lamP;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) L[s7(k, 6)] = 0.0;
+    eta[6] = -s.lamP * (ell - pell);
+    L[s7(6, 6)] = s.lamP;
 }
 
-// the unary belief (photometric + prior) from a photometric factor's pieces
-template <bool SEL = false>
-__device__ inline void unary_from(const Strengths& s, const Photo& f, const double tau[6], const double R[9],
-                                  const double t[3], double ell, const PixelInputs& pin, double L[28],
-                                  double eta[7]) {
-#pragma unroll
-    for (int k = 0; k < 28; ++k) L[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 7; ++k) eta[k] = 0.0;
-    add_photometric<SEL>(f, L, eta);
-    add_prior(s, tau, R, t, ell, pin, L, eta);
-}
-
-// (L, eta) = photometric + prior factors of pixel (u, v) at tau, ell; returns
-// the valid-warp flag
+// (L, eta) = photometric + prior factors of pixel (u, v) at tau, ell, with
+// (q, t) = Exp(tau) and R the rotation matrix; returns the valid-warp flag. The
+// prior's arithmetic stands under the photometric samples' loads.
 template <bool SEL = false>
 __device__ inline bool unary_factors(const Geo& g, const Strengths& s, const Inputs& in, int u, int v,
-                                     const double tau[6], const double R[9], const double t[3],
+                                     const double tau[6], const double q[4], const double R[9], const double t[3],
                                      double ell, const PixelInputs& pin, double L[28], double eta[7]) {
-    const Photo f = photometric<SEL>(g, s, in, u, v, R, t, ell, pin);
-    unary_from<SEL>(s, f, tau, R, t, ell, pin, L, eta);
+    const PhotoPre pre = photometric_begin(g, in, u, v, R, t, ell);
+    prior_factor(s, tau, q, t, ell, pin, L, eta);
+    const Photo f = photometric_end<SEL>(pre, g, s, R, t, pin);
+    add_photometric<SEL>(f, L, eta);
     return f.valid;
-}
-
-template <bool SEL = false>
-__device__ inline bool unary_factors(const Geo& g, const Strengths& s, const Inputs& in, int u, int v,
-                                     const double tau[6], const double R[9], const double t[3],
-                                     double ell, double L[28], double eta[7]) {
-    return unary_factors<SEL>(g, s, in, u, v, tau, R, t, ell, load_pixel_inputs(g, s, in, u, v), L, eta);
 }
 
 // ---------------------------------------------------------------------------
 // marginals of a pixel belief
 
-// pose marginal (depth eliminated): P = L_pp - L_p6 L_6p / L_66
-__device__ inline void pose_marginal(const double L[28], const double eta[7], double P[21], double p[6]) {
-    const double i66 = rcp_nr(L[s7(6, 6)]);
+// pose marginal (depth eliminated): P = L_pp - L_p6 L_6p / L_66, with l66 = L_66
+__device__ inline void pose_marginal(const double L[28], const double eta[7], double l66, double P[21], double p[6]) {
+    const double i66 = rcp_nr(l66);
 #pragma unroll
     for (int r = 0; r < 6; ++r) {
         const double lr = L[s7(r, 6)] * i66;
-        p[r] = eta[r] - lr * eta[6];
+        p[r] = fma(-lr, eta[6], eta[r]);
 #pragma unroll
-        for (int c = r; c < 6; ++c) P[s6(r, c)] = L[s7(r, c)] - lr * L[s7(c, 6)];
+        for (int c = r; c < 6; ++c) P[s6(r, c)] = fma(-lr, L[s7(c, 6)], L[s7(r, c)]);
     }
 }
 
-// depth marginal (pose eliminated): D = L_66 - L_6p L_pp^-1 L_p6
+// depth marginal (pose eliminated): D = L_66 - L_6p L_pp^-1 L_p6 and the same
+// for eta, by LDL^T elimination of the pose block with the columns L_p6 and eta
+// carried along (no substitutions: about 135 FP64 operations against 210)
 __device__ inline bool depth_marginal(const double L[28], const double eta[7], double& D, double& dv) {
-    double A[21], idg[6], y[6], z[6];
+    double A[21], y[6], z[6];
 #pragma unroll
     for (int r = 0; r < 6; ++r) {
 #pragma unroll
@@ -688,17 +888,26 @@ __device__ inline bool depth_marginal(const double L[28], const double eta[7], d
         y[r] = L[s7(r, 6)];
         z[r] = eta[r];
     }
-    const bool ok = chol6(A, idg);
-    chol6_solve(A, idg, y);
-    chol6_solve(A, idg, z);
-    double sy = 0.0, sz = 0.0;
+    D = L[s7(6, 6)];
+    dv = eta[6];
+    bool ok = true;
 #pragma unroll
-    for (int r = 0; r < 6; ++r) {
-        sy += L[s7(r, 6)] * y[r];
-        sz += y[r] * eta[r];
+    for (int j = 0; j < 6; ++j) {
+        const double d = A[s6(j, j)];
+        ok = ok && (d > 0.0);
+        const double id = rcp_nr(fmax(d, 1e-300));
+        const double ty = y[j] * id;
+        D = fma(-ty, y[j], D);
+        dv = fma(-ty, z[j], dv);
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) {
+            const double l = A[s6(j, i)] * id;
+            y[i] = fma(-l, y[j], y[i]);
+            z[i] = fma(-l, z[j], z[i]);
+#pragma unroll
+            for (int k = i; k < 6; ++k) A[s6(i, k)] = fma(-l, A[s6(j, k)], A[s6(i, k)]);
+        }
     }
-    D = L[s7(6, 6)] - sy;
-    dv = eta[6] - sz;
     return ok;
 }
 
@@ -741,35 +950,6 @@ __device__ inline bool normal_active(const Geo& g, const Inputs& in, long pi, lo
     return isfinite(c);
 }
 
-__device__ inline void load_messages(const float* __restrict__ X, const Geo& g, long p, float mid[4][27],
-                                     float mn[4][2]) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-#pragma unroll
-        for (int k = 0; k < 27; ++k) mid[d][k] = X[(long)(P_MID + d * MID_STRIDE + k) * g.plane + p];
-        mn[d][0] = X[(long)(P_MN + 2 * d) * g.plane + p];
-        mn[d][1] = X[(long)(P_MN + 2 * d + 1) * g.plane + p];
-    }
-}
-
-// B += messages (embedded: identity -> pose block, normal -> depth entry)
-__device__ inline void add_messages(double L[28], double eta[7], const float mid[4][27], const float mn[4][2]) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-#pragma unroll
-        for (int a = 0; a < 6; ++a) eta[a] += (double)mid[d][a];
-#pragma unroll
-        for (int r = 0; r < 6; ++r)
-#pragma unroll
-            for (int c = r; c < 6; ++c) L[s7(r, c)] += (double)mid[d][6 + s6(r, c)];
-    }
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        eta[6] += (double)mn[d][0];
-        L[s7(6, 6)] += (double)mn[d][1];
-    }
-}
-
 // ---------------------------------------------------------------------------
 // factor-to-variable messages, split into the part the sender computes from
 // its variable-to-factor message (the "partial", independent of the
@@ -779,28 +959,43 @@ __device__ inline void add_messages(double L[28], double eta[7], const float mid
 // Identity factor (Eq. regul) with Jacobians +I / -I: for the sender's
 // variable-to-factor pose marginal (V, v) and A = lamR I + V,
 //   Lambda' = lamR I - lamR^2 A^-1,   h = lamR A^-1 v,   eta' = h - Lambda' r.
-// A^-1 comes from symmetric Gauss-Jordan elimination (the sweep operator on
-// each pivot in turn), which leaves -A^-1 in the packed storage; every pivot
-// is a Schur complement of A, so a non-positive one means A is not SPD.
+// A^-1 comes from symmetric Gauss-Jordan elimination with 2 x 2 pivot blocks
+// (the sweep operator on each block in turn), which leaves -A^-1 in the packed
+// storage; every pivot block is a Schur complement of A, so one that is not
+// positive definite means that A is not SPD. Three reciprocals in the chain
+// instead of six and 135 FP64 operations instead of 170; the determinant's
+// cancellation costs what the second scalar pivot's would.
 __device__ inline bool sweep6_neg_inverse(double A[21]) {
     bool ok = true;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const double D = A[s6(k, k)];
-        ok = ok && (D > 0.0);
-        const double iD = rcp_nr(D > 0.0 ? D : 1e-300);
-        double r[6];
+    for (int k = 0; k < 6; k += 2) {
+        const double a = A[s6(k, k)], b = A[s6(k, k + 1)], c = A[s6(k + 1, k + 1)];
+        const double det = fma(a, c, -(b * b));
+        ok = ok && (a > 0.0) && (det > 0.0);
+        const double id = rcp_nr(fmax(det, 1e-300));
+        const double k00 = c * id, k01 = -b * id, k11 = a * id;
+        double x[6], y[6];
 #pragma unroll
-        for (int i = 0; i < 6; ++i) r[i] = (i == k) ? 0.0 : A[s6(i, k)] * iD;
+        for (int i = 0; i < 6; ++i) {
+            if (i == k || i == k + 1) continue;
+            x[i] = fma(A[s6(i, k)], k00, A[s6(i, k + 1)] * k01);
+            y[i] = fma(A[s6(i, k)], k01, A[s6(i, k + 1)] * k11);
+        }
 #pragma unroll
         for (int i = 0; i < 6; ++i)
 #pragma unroll
             for (int j = i; j < 6; ++j)
-                if (i != k && j != k) A[s6(i, j)] = fma(-A[s6(i, k)], r[j], A[s6(i, j)]);
+                if (i != k && i != k + 1 && j != k && j != k + 1)
+                    A[s6(i, j)] = fma(-x[i], A[s6(j, k)], fma(-y[i], A[s6(j, k + 1)], A[s6(i, j)]));
 #pragma unroll
-        for (int i = 0; i < 6; ++i)
-            if (i != k) A[s6(i, k)] = r[i];
-        A[s6(k, k)] = -iD;
+        for (int i = 0; i < 6; ++i) {
+            if (i == k || i == k + 1) continue;
+            A[s6(i, k)] = x[i];
+            A[s6(i, k + 1)] = y[i];
+        }
+        A[s6(k, k)] = -k00;
+        A[s6(k, k + 1)] = -k01;
+        A[s6(k + 1, k + 1)] = -k11;
     }
     return ok;
 }

@@ -20,169 +20,223 @@ namespace cg = cooperative_groups;
 
 namespace pv {
 
-// belief mean, relinearisation (Eq. var) and first-order transport of the
-// stored messages into the new tangent space (Sec. 4.1)
-__device__ inline bool update_and_transport(double L[28], double eta[7], double tau[6], double& ell,
-                                            float mid[4][27], float mn[4][2], double& var_ll) {
-    double idg[7];
-    const bool ok = chol7(L, idg);
-    double m[7];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) m[k] = eta[k];
-    chol7_solve(L, idg, m);
-    var_ll = chol7_var_last(idg);
-    double R0[9], t0[3], Rm[9], tm[3], R1[9], t1[3];
-    se3_exp(tau, R0, t0);
-    se3_exp(m, Rm, tm);
-    se3_compose(R0, t0, Rm, tm, R1, t1);
-    se3_log(R1, t1, tau);
-    ell += m[6];
+// The four stored messages of a pixel in a fused pass. A pass needs each
+// message's information matrix three times (sum of the belief, transport,
+// what its sender subtracts), with a 7x7 solve between the first and the
+// second, and 4 x 29 values beside the FP64 algebra would leave one wave per
+// SIMD. The matrices of three directions are therefore kept in LDS, where they
+// are loaded straight from memory without passing through registers (63 planes
+// of 64 lanes, 16 KB per wave: eight waves fit a CU's 160 KB), the fourth and
+// everything else in registers: at most 256 registers, so that two waves share
+// a SIMD and fill each other's waits. Every lane reads only what it loaded
+// itself, so no barrier is needed.
+constexpr int LDS_DIRS = 3;
+constexpr int LDS_PLANES = LDS_DIRS * 21;
+constexpr int LDS_WAVE = LDS_PLANES * 64;   // floats per wave
+
+struct Messages {
+    float eta[4][6];     // identity messages
+    float lam3[21];      // information of direction 3
+    float mn[4][2];      // normal messages: eta, lambda
+    const float* lds;    // information of directions 0 .. 2: this lane's column of the wave's LDS planes
+
+    __device__ inline float lam(int d, int k) const { return d < LDS_DIRS ? lds[(d * 21 + k) * 64] : lam3[k]; }
+};
+
+// Plane access of the fused passes: the plane's base is uniform (scalar
+// registers and scalar arithmetic), the pixel a 32-bit byte offset, and a
+// neighbour's slot the same offset from a base moved by one element or one
+// row. (H * pitch is at most 2^28 elements.) A base runs through consecutive
+// planes and is opaque to the compiler at each, which otherwise forms 64-bit
+// addresses per lane (about 300 vector instructions more per pass).
+__device__ inline unsigned off_of(const Geo& g, int u, int v) { return (unsigned)((v * g.pitch + u) * 4); }
+__device__ inline long step_of(const Geo& g, int d) {
+    return d == DIR_L ? -1 : d == DIR_R ? 1 : d == DIR_U ? -(long)g.pitch : (long)g.pitch;
+}
+typedef __attribute__((address_space(1))) float GFloat;
+typedef __attribute__((address_space(1))) double GDouble;
+typedef __attribute__((address_space(1))) char GByte;
+
+template <class T>
+__device__ inline T* opaque(T* base) {
+    asm("" : "+s"(base));
+    return base;
+}
+__device__ inline GFloat* plane_of(const float* base, long elements) {
+    return opaque((GFloat*)const_cast<float*>(base + elements));
+}
+__device__ inline GDouble* plane_of(double* base) { return opaque((GDouble*)base); }
+// the pixel's offset for the accesses of one block of code: its widening to 64
+// bits has to be visible there for the access to take base and offset apart
+__device__ inline unsigned here(unsigned o) {
+    asm("" : "+v"(o));
+    return o;
+}
+// a pixel's element of a plane
+__device__ inline GFloat* at(GFloat* base, unsigned o) { return (GFloat*)((GByte*)base + o); }
+__device__ inline GDouble* at(GDouble* base, unsigned o) { return (GDouble*)((GByte*)base + 2UL * o); }
+__device__ inline float ld(const float* base, unsigned o) { return *at((GFloat*)const_cast<float*>(base), o); }
+// the base of the next plane
+template <class T>
+__device__ inline T* next(const Geo& g, T* base) {
+    return opaque(base + g.plane);
+}
+
+// issues the loads of a pixel's stored messages (or partials in flight) but
+// the information of direction 3. buf: the wave's LDS planes, lane: the lane
+// of the wave. The information matrices of the LDS directions may be read after
+// wait_lds_loads() only.
+__device__ inline void load_messages(const float* X, const Geo& g, unsigned o, float* buf, int lane, Messages& m) {
+    GFloat* b = plane_of(X, (long)P_MID * g.plane);
+    o = here(o);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
 #pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            double s = (double)mid[d][a];
-#pragma unroll
-            for (int b = 0; b < 6; ++b) s -= (double)mid[d][6 + s6(a, b)] * m[b];
-            mid[d][a] = (float)s;
+        for (int k = 0; k < 6; ++k) {
+            m.eta[d][k] = *at(b, o);
+            b = next(g, b);
         }
-        mn[d][0] = (float)((double)mn[d][0] - (double)mn[d][1] * m[6]);
+        if (d < LDS_DIRS) {
+#pragma unroll
+            for (int k = 0; k < 21; ++k) {
+                __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(b, o),
+                                                 (__attribute__((address_space(3))) void*)(buf + (d * 21 + k) * 64), 4,
+                                                 0, 0);
+                b = next(g, b);
+            }
+        }
     }
-    return ok;
-}
-
-// sender side: partial messages of pixel i towards each neighbour, from its
-// belief (L, eta) and its stored messages; written to the neighbour's slot
-__device__ inline void emit_partials(const Geo& g, const Strengths& s, const Inputs& in, int u, int v,
-                                     const double L[28], const double eta[7], const float mid[4][27],
-                                     const float mn[4][2], float* __restrict__ Y, bool& ok,
-                                     double* __restrict__ marg_out = nullptr) {
-    double P[21], p[6], D, dv;
-    pose_marginal(L, eta, P, p);
-    ok = depth_marginal(L, eta, D, dv) && ok;
-    const long pi = pix_of(g, u, v);
-    if (marg_out) {
-        // the marginals in the per-factor layout (k_pf_linearise): P 21, p 6,
-        // D, dv; then the belief they come from: L 28, eta 7 (the reverse
-        // sweep's tape, written non-temporally)
-#pragma unroll
-        for (int k = 0; k < 21; ++k) __builtin_nontemporal_store(P[k], &marg_out[(long)k * g.plane + pi]);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) __builtin_nontemporal_store(p[k], &marg_out[(long)(21 + k) * g.plane + pi]);
-        __builtin_nontemporal_store(D, &marg_out[27L * g.plane + pi]);
-        __builtin_nontemporal_store(dv, &marg_out[28L * g.plane + pi]);
-#pragma unroll
-        for (int k = 0; k < 28; ++k) __builtin_nontemporal_store(L[k], &marg_out[(long)(29 + k) * g.plane + pi]);
-#pragma unroll
-        for (int k = 0; k < 7; ++k) __builtin_nontemporal_store(eta[k], &marg_out[(long)(57 + k) * g.plane + pi]);
-    }
+    b = plane_of(X, (long)P_MN * g.plane);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        int nu, nv;
-        if (!neighbour(g, u, v, d, nu, nv)) continue;
-        const long pj = pix_of(g, nu, nv);
-        const int slot = opposite(d);
-        double V[21], vv[6], Lp[21], h[6];
+        m.mn[d][0] = *at(b, o);
+        b = next(g, b);
+        m.mn[d][1] = *at(b, o);
+        b = next(g, b);
+    }
+    m.lds = buf + lane;
+}
+
+// issues the loads of direction 3's information: late, so that they are not
+// held in registers beside the linearisation
+__device__ inline void load_lam3(const float* X, const Geo& g, unsigned o, Messages& m) {
+    GFloat* b = plane_of(X, (long)(P_MID + 3 * MID_STRIDE + 6) * g.plane);
+    o = here(o);
 #pragma unroll
-        for (int k = 0; k < 21; ++k) V[k] = P[k] - (double)mid[d][6 + k];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) vv[k] = p[k] - (double)mid[d][k];
-        ok = identity_partial(s.lamR, V, vv, Lp, h) && ok;
-        float* dst = Y + (long)(P_MID + slot * MID_STRIDE) * g.plane + pj;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) dst[k * g.plane] = (float)h[k];
-#pragma unroll
-        for (int k = 0; k < 21; ++k) dst[(6 + k) * g.plane] = (float)Lp[k];
-        float* dn = Y + (long)(P_MN + 2 * slot) * g.plane + pj;
-        if (normal_active(g, in, pi, pj, d) && s.lamN > 0.0) {
-            double lp, hn;
-            normal_partial(s.lamN, D - (double)mn[d][1], dv - (double)mn[d][0], lp, hn);
-            dn[0] = (float)hn;
-            dn[g.plane] = (float)lp;
-        } else {
-            dn[0] = 0.0f;
-            dn[g.plane] = 0.0f;
-        }
+    for (int k = 0; k < 21; ++k) {
+        m.lam3[k] = *at(b, o);
+        b = next(g, b);
     }
 }
 
-// adds one completed message (identity eta/Lambda, normal eta/lambda) of slot
-// d to the belief in FP64 and keeps its FP32 storage copy
-__device__ inline void accumulate_message(double L[28], double eta[7], const double id_eta[6], const float id_lam[21],
-                                          double n_eta, float n_lam, float mid_d[27], float mn_d[2]) {
+__device__ inline void load_point_at(const float* X, const Geo& g, unsigned o, float pt[7]) {
+    GFloat* b = plane_of(X, 0);
+    o = here(o);
 #pragma unroll
-    for (int a = 0; a < 6; ++a) {
-        eta[a] += id_eta[a];
-        mid_d[a] = (float)id_eta[a];
+    for (int k = 0; k < 7; ++k) {
+        pt[k] = *at(b, o);
+        b = next(g, b);
     }
+}
+
+// load_pixel_inputs without branches: a map that is not bound is read from the
+// keyframe image and not used
+__device__ inline PixelInputs load_inputs_at(const Strengths& s, const Inputs& in, unsigned o) {
+    PixelInputs r;
+    r.Is = ld(in.Is, o);
+    r.sigD = ld(s.has_sigma_map ? in.sigD : in.Is, o);
+    r.prior_ell = ld(s.has_prior_map ? in.prior_ell : in.Is, o);
+    return r;
+}
+
+__device__ inline void point_of(const float pt[7], double tau[6], double& ell) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) tau[k] = (double)pt[k];
+    ell = (double)pt[6];
+}
+
+// wait for this wave's loads into LDS: the compiler does not track them, so
+// the wait is explicit, and the memory clobber keeps the LDS reads after it
+__device__ inline void wait_lds_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// the information matrices are read from LDS again after this point instead of
+// being kept in registers from their previous use
+__device__ inline void reread_lds() { asm volatile("" ::: "memory"); }
+
+// wait for this wave's LDS reads, before its planes are loaded again
+__device__ inline void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// B += a stored message (embedded: identity -> pose block, normal -> depth entry)
+__device__ inline void add_message(double L[28], double eta[7], const Messages& m, int d) {
+#pragma unroll
+    for (int a = 0; a < 6; ++a) eta[a] += (double)m.eta[d][a];
 #pragma unroll
     for (int r = 0; r < 6; ++r)
 #pragma unroll
-        for (int c = r; c < 6; ++c) L[s7(r, c)] += (double)id_lam[s6(r, c)];
-#pragma unroll
-    for (int k = 0; k < 21; ++k) mid_d[6 + k] = id_lam[k];
-    eta[6] += n_eta;
-    L[s7(6, 6)] += (double)n_lam;
-    mn_d[0] = (float)n_eta;
-    mn_d[1] = n_lam;
+        for (int c = r; c < 6; ++c) L[s7(r, c)] += (double)m.lam(d, s6(r, c));
+    eta[6] += (double)m.mn[d][0];
+    L[s7(6, 6)] += (double)m.mn[d][1];
 }
 
-// receiver side: completes the partial in slot d with the residual at both
-// linearisation points, eta = h - Lambda' r, and adds it to the belief.
-// Lam_out (reverse-sweep tape) receives each new message's information (the
-// identity Lambda and the normal lambda, 22 FP32 planes per slot: they are
-// the partials' FP32 values, so the FP32 tape is exact)
-__device__ inline void complete_partials(const Geo& g, const Strengths& s, const Inputs& in,
-                                         const float* __restrict__ X, int u, int v, const double R[9],
-                                         const double t[3], double ell, double L[28], double eta[7],
-                                         float mid[4][27], float mn[4][2], float* __restrict__ Lam_out = nullptr) {
-    const long pi = pix_of(g, u, v);
+// first-order transport of a stored message by the mean step (Sec. 4.1)
+__device__ inline void transport_message(Messages& ms, int d, const double m[7]) {
+    double e[6];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        int nu, nv;
-        if (!neighbour(g, u, v, d, nu, nv)) {
+    for (int a = 0; a < 6; ++a) e[a] = (double)ms.eta[d][a];
 #pragma unroll
-            for (int k = 0; k < 27; ++k) mid[d][k] = 0.0f;
-            mn[d][0] = mn[d][1] = 0.0f;
-            if (Lam_out)
+    for (int r = 0; r < 6; ++r)
 #pragma unroll
-                for (int k = 0; k < LAM_STRIDE; ++k) __builtin_nontemporal_store(0.0f, &Lam_out[(long)(d * LAM_STRIDE + k) * g.plane + pi]);
-            continue;
+        for (int c = r; c < 6; ++c) {
+            const double l = (double)ms.lam(d, s6(r, c));
+            e[r] = fma(-l, m[c], e[r]);
+            if (r != c) e[c] = fma(-l, m[r], e[c]);
         }
-        const long pj = pix_of(g, nu, nv);
-        double tj[6], ellj, Rj[9], trj[3], r[6];
-        load_point(X, g, pj, tj, ellj);
-        se3_exp(tj, Rj, trj);
-        se3_between(Rj, trj, R, t, r);
-        const float* src = X + (long)(P_MID + d * MID_STRIDE) * g.plane + pi;
-        float part[27];
 #pragma unroll
-        for (int k = 0; k < 27; ++k) part[k] = src[k * g.plane];
-        double e6[6];
+    for (int a = 0; a < 6; ++a) ms.eta[d][a] = (float)e[a];
+    ms.mn[d][0] = (float)fma(-(double)ms.mn[d][1], m[6], (double)ms.mn[d][0]);
+}
+
+// receiver side: eta = h - Lambda' r of an identity partial (h, Lambda')
+template <class Lam>
+__device__ inline void complete_eta(const float h[6], Lam lam, const double r[6], double e[6]) {
 #pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            double e = (double)part[a];
+    for (int a = 0; a < 6; ++a) e[a] = (double)h[a];
 #pragma unroll
-            for (int b = 0; b < 6; ++b) e -= (double)part[6 + s6(a, b)] * r[b];
-            e6[a] = e;
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int c = i; c < 6; ++c) {
+            const double l = (double)lam(s6(i, c));
+            e[i] = fma(-l, r[c], e[i]);
+            if (i != c) e[c] = fma(-l, r[i], e[c]);
         }
-        double ne = 0.0;
-        float nl = 0.0f;
-        double rn;
-        if (s.lamN > 0.0 && normal_residual(g, in, pi, pj, d, ell, ellj, rn)) {
-            const float* sn = X + (long)(P_MN + 2 * d) * g.plane + pi;
-            nl = sn[g.plane];
-            ne = (double)sn[0] - (double)nl * rn;
-        }
-        accumulate_message(L, eta, e6, part + 6, ne, nl, mid[d], mn[d]);
-        if (Lam_out) {
-            // the reverse sweep's tape of the new messages' information, written
-            // non-temporally like the FP64 tape
-            float* o = Lam_out + (long)(d * LAM_STRIDE) * g.plane + pi;
+}
+
+// normal_residual of an active edge with a preloaded target c of the left/upper pixel
+__device__ inline double normal_residual_c(float c, int d, double ell_i, double ell_j) {
+    const bool recv_is_b = (d == DIR_L || d == DIR_U);
+    return recv_is_b ? (ell_i - ell_j + (double)c) : (ell_i - ell_j - (double)c);
+}
+
+// per-lane tape of the reverse sweep's recompute
+struct Tape {
+    float* lam;          // information of the new messages (88 FP32 planes: 21 + 1 per slot)
+    double* bel;         // belief of the update (35 FP64 planes)
+    float* canonical;    // canonical state after the update (not the last iteration of a segment)
+    double* marg;        // marginals and belief of the next emission (64 FP64 planes)
+};
+
+// the marginals in the per-factor layout (k_pf_linearise): P 21, p 6, D, dv;
+// then the belief they come from: L 28, eta 7. The tape is written
+// non-temporally: it is read back only by the reverse sweep.
+__device__ inline void tape_marginals(double* marg, const Geo& g, unsigned o, const double P[21], const double pm[6],
+                                      double D, double dv, const double L[28], const double eta[7]) {
+    GDouble* b = plane_of(marg);
+    o = here(o);
 #pragma unroll
-            for (int k = 0; k < 21; ++k) __builtin_nontemporal_store(part[6 + k], &o[k * g.plane]);
-            __builtin_nontemporal_store(nl, &o[21 * g.plane]);
-        }
+    for (int k = 0; k < 64; ++k) {
+        const double x = k < 21 ? P[k] : k < 27 ? pm[k - 21] : k == 27 ? D : k == 28 ? dv : k < 57 ? L[k - 29] : eta[k - 57];
+        __builtin_nontemporal_store(x, at(b, o));
+        b = next(g, b);
     }
 }
 
@@ -190,40 +244,41 @@ __device__ inline void complete_partials(const Geo& g, const Strengths& s, const
 // for passes whose output is not read again while it could stay cached: the
 // batch's passes over many sequences and a frame's final pass
 template <bool NT = false>
-__device__ inline void put(float* __restrict__ a, float v) {
+__device__ inline void put(GFloat* a, float v) {
     if constexpr (NT) __builtin_nontemporal_store(v, a);
     else *a = v;
 }
 
 template <bool NT = false>
-__device__ inline void store_point(float* __restrict__ Y, const Geo& g, long p, const double tau[6], double ell) {
-    if constexpr (NT) {
+__device__ inline void store_point(float* Y, const Geo& g, unsigned o, const double tau[6], double ell) {
+    GFloat* b = plane_of(Y, 0);
+    o = here(o);
 #pragma unroll
-        for (int k = 0; k < 6; ++k) put<true>(&Y[(P_TAU + k) * g.plane + p], (float)tau[k]);
-        put<true>(&Y[P_ELL * g.plane + p], (float)ell);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) Y[(P_TAU + k) * g.plane + p] = (float)tau[k];
-        Y[P_ELL * g.plane + p] = (float)ell;
+    for (int k = 0; k < 6; ++k) {
+        put<NT>(at(b, o), (float)tau[k]);
+        b = next(g, b);
     }
+    put<NT>(at(b, o), (float)ell);
 }
 
 template <bool NT = false>
-__device__ inline void store_messages(float* __restrict__ Y, const Geo& g, long p, const float mid[4][27],
-                                      const float mn[4][2]) {
+__device__ inline void store_messages(float* Y, const Geo& g, unsigned o, const Messages& m, const bool has[4]) {
+    GFloat* b = plane_of(Y, (long)P_MID * g.plane);
+    o = here(o);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        if constexpr (NT) {
 #pragma unroll
-            for (int k = 0; k < 27; ++k) put<true>(&Y[(long)(P_MID + d * MID_STRIDE + k) * g.plane + p], mid[d][k]);
-            put<true>(&Y[(long)(P_MN + 2 * d) * g.plane + p], mn[d][0]);
-            put<true>(&Y[(long)(P_MN + 2 * d + 1) * g.plane + p], mn[d][1]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 27; ++k) Y[(long)(P_MID + d * MID_STRIDE + k) * g.plane + p] = mid[d][k];
-            Y[(long)(P_MN + 2 * d) * g.plane + p] = mn[d][0];
-            Y[(long)(P_MN + 2 * d + 1) * g.plane + p] = mn[d][1];
+        for (int k = 0; k < 27; ++k) {
+            put<NT>(at(b, o), k < 6 ? m.eta[d][k] : (has[d] ? m.lam(d, k - 6) : 0.0f));
+            b = next(g, b);
         }
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        put<NT>(at(b, o), m.mn[d][0]);
+        b = next(g, b);
+        put<NT>(at(b, o), m.mn[d][1]);
+        b = next(g, b);
     }
 }
 
@@ -319,15 +374,25 @@ __global__ __launch_bounds__(256) void k_pf_linearise(Geo g, Strengths s, Inputs
     const int v = blockIdx.y * blockDim.y + threadIdx.y;
     if (u >= g.W || v >= g.H) return;
     const long p = pix_of(g, u, v);
-    double tau[6], ell, R[9], t[3], L[28], eta[7];
+    double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
     load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, t);
-    const bool val = unary_factors(g, s, in, u, v, tau, R, t, ell, L, eta);
-    float mid[4][27], mn[4][2];
-    load_messages(X, g, p, mid, mn);
-    add_messages(L, eta, mid, mn);
+    pose_exp(tau, q, t);
+    pose_rotation(q, R);
+    const bool val = unary_factors(g, s, in, u, v, tau, q, R, t, ell, load_pixel_inputs(g, s, in, u, v), L, eta);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const float* m = X + (long)(P_MID + d * MID_STRIDE) * g.plane + p;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) eta[a] += (double)m[a * g.plane];
+#pragma unroll
+        for (int r = 0; r < 6; ++r)
+#pragma unroll
+            for (int c = r; c < 6; ++c) L[s7(r, c)] += (double)m[(6 + s6(r, c)) * g.plane];
+        eta[6] += (double)X[(long)(P_MN + 2 * d) * g.plane + p];
+        L[s7(6, 6)] += (double)X[(long)(P_MN + 2 * d + 1) * g.plane + p];
+    }
     double P[21], pv_[6], D, dv;
-    pose_marginal(L, eta, P, pv_);
+    pose_marginal(L, eta, L[s7(6, 6)], P, pv_);
     const bool ok = depth_marginal(L, eta, D, dv);
 #pragma unroll
     for (int k = 0; k < 21; ++k) marg[(long)k * g.plane + p] = P[k];
@@ -350,9 +415,9 @@ __global__ __launch_bounds__(256, 2) void k_pf_messages(Geo g, Strengths s, Inpu
     const int v = blockIdx.y * blockDim.y + threadIdx.y;
     if (u >= g.W || v >= g.H) return;
     const long pi = pix_of(g, u, v);
-    double tau[6], ell, R[9], t[3];
+    double tau[6], ell, q[4], t[3];
     load_point(X, g, pi, tau, ell);
-    se3_exp(tau, R, t);
+    pose_exp(tau, q, t);
     bool ok = true;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
@@ -377,17 +442,11 @@ __global__ __launch_bounds__(256, 2) void k_pf_messages(Geo g, Strengths s, Inpu
             for (int k = 0; k < 6; ++k) part[k] = (float)h[k];
 #pragma unroll
             for (int k = 0; k < 21; ++k) part[6 + k] = (float)Lp[k];
-            double tj[6], ellj, Rj[9], trj[3], r[6];
+            double tj[6], ellj, qj[4], trj[3], r[6];
             load_point(X, g, pj, tj, ellj);
-            se3_exp(tj, Rj, trj);
-            se3_between(Rj, trj, R, t, r);
-#pragma unroll
-            for (int a = 0; a < 6; ++a) {
-                double e = (double)part[a];
-#pragma unroll
-                for (int b = 0; b < 6; ++b) e -= (double)part[6 + s6(a, b)] * r[b];
-                out[a] = e;
-            }
+            pose_exp(tj, qj, trj);
+            pose_between(qj, trj, q, t, r);
+            complete_eta(part, [&](int k) { return part[6 + k]; }, r, out);
 #pragma unroll
             for (int k = 0; k < 21; ++k) out[6 + k] = (double)part[6 + k];
             double rn;
@@ -397,7 +456,7 @@ __global__ __launch_bounds__(256, 2) void k_pf_messages(Geo g, Strengths s, Inpu
                 double lp, hn;
                 normal_partial(s.lamN, ls, vs, lp, hn);
                 const float fl = (float)lp, fh = (float)hn;
-                out[27] = (double)fh - (double)fl * rn;
+                out[27] = fma(-(double)fl, rn, (double)fh);
                 out[28] = (double)fl;
             }
             if (beta != 0.0f) {
@@ -422,35 +481,57 @@ __global__ __launch_bounds__(256, 2) void k_pf_messages(Geo g, Strengths s, Inpu
 
 // U: new belief from the recomputed unary and the new messages, relinearise,
 // transport, write the state in place
-__global__ __launch_bounds__(256) void k_pf_update(Geo g, Strengths s, Inputs in, float* __restrict__ X,
-                                                   const double* __restrict__ M, float* __restrict__ var_ll,
-                                                   float* __restrict__ valid, int* __restrict__ health) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y * blockDim.y + threadIdx.y;
-    if (u >= g.W || v >= g.H) return;
+__global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs in, float* __restrict__ X,
+                                                     const double* __restrict__ M, float* __restrict__ var_ll,
+                                                     float* __restrict__ valid, int* __restrict__ health) {
+    __shared__ float buf[LDS_WAVE];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
     const long p = pix_of(g, u, v);
-    double tau[6], ell, R[9], t[3], L[28], eta[7];
+    double tau[6], ell, q[4], R[9], t[3], L[28], eta[7], m[7], var;
     load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, t);
-    const bool val = unary_factors(g, s, in, u, v, tau, R, t, ell, L, eta);
-    float mid[4][27], mn[4][2];
+    pose_exp(tau, q, t);
+    pose_rotation(q, R);
+    const bool val = unary_factors(g, s, in, u, v, tau, q, R, t, ell, load_pixel_inputs(g, s, in, u, v), L, eta);
+    // the new messages: added to the belief in FP64, kept at storage precision
+    // (the information matrices are at storage precision already)
+    Messages ms;
+    float* lds = buf + threadIdx.x;
+    ms.lds = lds;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        double e6[6];
-        float lam[21];
+        const double* md = M + (long)(d * 29) * g.plane + p;
 #pragma unroll
-        for (int k = 0; k < 6; ++k) e6[k] = M[(long)(d * 29 + k) * g.plane + p];
+        for (int a = 0; a < 6; ++a) {
+            const double e = md[a * g.plane];
+            eta[a] += e;
+            ms.eta[d][a] = (float)e;
+        }
 #pragma unroll
-        for (int k = 0; k < 21; ++k) lam[k] = (float)M[(long)(d * 29 + 6 + k) * g.plane + p];
-        const double ne = M[(long)(d * 29 + 27) * g.plane + p];
-        const float nl = (float)M[(long)(d * 29 + 28) * g.plane + p];
-        accumulate_message(L, eta, e6, lam, ne, nl, mid[d], mn[d]);
+        for (int r = 0; r < 6; ++r)
+#pragma unroll
+            for (int c = r; c < 6; ++c) {
+                const double l = md[(6 + s6(r, c)) * g.plane];
+                L[s7(r, c)] += l;
+                if (d < LDS_DIRS) lds[(d * 21 + s6(r, c)) * 64] = (float)l;
+                else ms.lam3[s6(r, c)] = (float)l;
+            }
+        const double ne = md[27 * g.plane], nl = md[28 * g.plane];
+        eta[6] += ne;
+        L[s7(6, 6)] += nl;
+        ms.mn[d][0] = (float)ne;
+        ms.mn[d][1] = (float)nl;
     }
-    double var;
-    const bool ok = update_and_transport(L, eta, tau, ell, mid, mn, var);
+    reread_lds();
+    const bool ok = ldl7_solve(L, eta, m, var);
+    pose_retract(q, t, m, tau);
+    ell += m[6];
     round_point(tau, ell);
-    store_point(X, g, p, tau, ell);
-    store_messages(X, g, p, mid, mn);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) transport_message(ms, d, m);
+    const bool has[4] = {true, true, true, true};
+    store_point(X, g, off_of(g, u, v), tau, ell);
+    store_messages(X, g, off_of(g, u, v), ms, has);
     var_ll[p] = (float)var;
     valid[p] = val ? 1.0f : 0.0f;
     if (!ok) atomicOr(health, 1);
@@ -459,451 +540,292 @@ __global__ __launch_bounds__(256) void k_pf_update(Geo g, Strengths s, Inputs in
 // ---------------------------------------------------------------------------
 // fused schedule
 
-// prologue of one pixel: belief of the canonical state and the first partials
-__device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& g, const Strengths& s, const Inputs& in, const float* __restrict__ X,
-                                      float* __restrict__ Y, int* __restrict__ health, int u, int v,
-                                      double* __restrict__ marg_out = nullptr) {
-    const long p = pix_of(g, u, v);
-    double tau[6], ell, R[9], t[3], L[28], eta[7];
-    load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, t);
-    const PixelInputs pin = load_pixel_inputs(g, s, in, u, v);
-    unary_factors(g, s, in, u, v, tau, R, t, ell, pin, L, eta);
-    float mid[4][27], mn[4][2];
-    load_messages(X, g, p, mid, mn);
-    add_messages(L, eta, mid, mn);
-    bool ok = true;
-    emit_partials(g, s, in, u, v, L, eta, mid, mn, Y, ok, marg_out);
-    store_point(Y, g, p, tau, ell);
-    if (!ok) atomicOr(health, 1);
-}
-
-// one iteration of one pixel: complete, update, relinearise, then (not
-// FINAL) emit the next partials or (FINAL) write the canonical state and the
-// per-pixel outputs. Not FINAL, Yc (when given) also receives the canonical
-// state after the update, and marg_next the marginals of the next emission.
-template <bool FINAL>
-__device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g, const Strengths& s, const Inputs& in, const float* __restrict__ X,
-                                     float* __restrict__ Y, float* __restrict__ var_ll, float* __restrict__ valid,
-                                     int* __restrict__ health, int u, int v, float* __restrict__ Lam_out = nullptr,
-                                     double* __restrict__ bel_out = nullptr, float* __restrict__ Yc = nullptr,
-                                     double* __restrict__ marg_next = nullptr) {
-    const long p = pix_of(g, u, v);
-    double tau[6], ell, R[9], t[3], L[28], eta[7];
-    load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, t);
-    const bool val = unary_factors(g, s, in, u, v, tau, R, t, ell, L, eta);
-    float mid[4][27], mn[4][2];
-    complete_partials(g, s, in, X, u, v, R, t, ell, L, eta, mid, mn, Lam_out);
-    if (bel_out) {
-        // the belief of the update (unary + new messages): L 28, eta 7; the
-        // FP64 tape is written non-temporally (read back only by the reverse
-        // sweep, after the segment's recompute)
-#pragma unroll
-        for (int k = 0; k < 28; ++k) __builtin_nontemporal_store(L[k], &bel_out[(long)k * g.plane + p]);
-#pragma unroll
-        for (int k = 0; k < 7; ++k) __builtin_nontemporal_store(eta[k], &bel_out[(long)(28 + k) * g.plane + p]);
-    }
-    double var;
-    bool ok = update_and_transport(L, eta, tau, ell, mid, mn, var);
-    round_point(tau, ell);
-    store_point(Y, g, p, tau, ell);
-    if (FINAL) {
-        store_messages(Y, g, p, mid, mn);
-        var_ll[p] = (float)var;
-        valid[p] = val ? 1.0f : 0.0f;
-    } else {
-        if (Yc) {
-            store_point(Yc, g, p, tau, ell);
-            store_messages(Yc, g, p, mid, mn);
-        }
-        se3_exp(tau, R, t);
-        unary_factors(g, s, in, u, v, tau, R, t, ell, L, eta);
-        add_messages(L, eta, mid, mn);
-        emit_partials(g, s, in, u, v, L, eta, mid, mn, Y, ok, marg_next);
-    }
-    if (!ok) atomicOr(health, 1);
-}
-
-// ---------------------------------------------------------------------------
-// fused pass with its loads issued together
-//
-// With one wave per SIMD (the pass keeps ~450 registers live) nothing hides
-// memory latency, so the number of dependent round trips to memory sets the
-// pass time. Every load whose address does not depend on computed values
-// (own point, the four neighbours' points, the four partials and normal
-// partials in flight, the normal targets, the keyframe intensity and the
-// optional sigma and prior maps) is issued at once at the start; a missing
-// neighbour's loads read the pixel itself and are discarded. What remains
-// dependent are the bilinear samples at the two warps. The arithmetic and its
-// order are those of iterate_pixel.
-
-// preloaded normal targets of the four edges: c of the left/upper pixel a
-struct EdgeTargets {
-    float c[4];
-};
-
-// normal_residual with a preloaded target
-__device__ inline bool normal_residual_c(float c, int d, double ell_i, double ell_j, double& r_recv) {
-    if (!isfinite(c)) return false;
-    const bool recv_is_b = (d == DIR_L || d == DIR_U);
-    r_recv = recv_is_b ? (ell_i - ell_j + (double)c) : (ell_i - ell_j - (double)c);
-    return true;
-}
-
-// Linearisation points of the neighbours: either loaded from the state and
-// exponentiated by every pixel that needs them (SH = false), or, in the
-// 64 x 4 workgroups of the single-sequence pass (SH = true), exponentiated
-// once per point into a shared table of the workgroup's points and its
-// one-pixel halo (HALO_W x HALO_H points, FP64 R, t and ell per point,
-// structure of arrays): each point's Exp is then computed by one lane instead
-// of five, and the neighbours' points are not loaded per pixel.
-constexpr int HALO_W = 66, HALO_H = 6, HALO_N = HALO_W * HALO_H;
-constexpr int SH_FIELDS = 13;   // R 9, t 3, ell
-
-__device__ inline void sh_put(double* __restrict__ sh, int h, const double R[9], const double t[3], double ell) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) sh[k * HALO_N + h] = R[k];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) sh[(9 + k) * HALO_N + h] = t[k];
-    sh[12 * HALO_N + h] = ell;
-}
-
-// the halo ring of a 64 x 4 tile at (u0, v0), lane l < 140: its point, or
-// false outside the image
-__device__ inline bool halo_point(const Geo& g, int u0, int v0, int l, int& u, int& v, int& h) {
-    int hx, hy;
-    if (l < HALO_W) { hx = l - 1; hy = -1; }
-    else if (l < 2 * HALO_W) { hx = l - HALO_W - 1; hy = 4; }
-    else if (l < 2 * HALO_W + 4) { hx = -1; hy = l - 2 * HALO_W; }
-    else { hx = 64; hy = l - 2 * HALO_W - 4; }
-    u = u0 + hx;
-    v = v0 + hy;
-    h = (hy + 1) * HALO_W + (hx + 1);
-    return u >= 0 && u < g.W && v >= 0 && v < g.H;
-}
-
-// The stored messages of a pixel (eta 6 and Lambda 21 of the four identity
-// slots, eta and lambda of the four normal slots) are the 116 consecutive
-// planes from P_MID. The persistent single-sequence pass keeps them for the
-// next 64 x 4 tile in LDS, loaded straight from memory into LDS (no
-// registers) while the current tile computes: wave w loads tile row w, plane
-// k of lane l at buf[k * 256 + w * 64 + l]. Lanes outside the image load any
-// valid pixel; their values are not used.
-constexpr int MSG_PLANES = 116;
-static_assert(P_MN + 8 == P_MID + MSG_PLANES, "messages are contiguous planes");
-
-__device__ inline void prefetch_messages(const Geo& g, const float* __restrict__ X, float* buf, int u0, int v0,
-                                         int w, int lane) {
-    const int u = u0 + lane, v = v0 + w;
-    const long p = (u < g.W && v < g.H) ? pix_of(g, u, v) : 0;
-    const float* src = X + (long)P_MID * g.plane + p;
-    float* dst = buf + w * 64;
-#pragma unroll 4
-    for (int k = 0; k < MSG_PLANES; ++k)
-        __builtin_amdgcn_global_load_lds((const void*)(src + (long)k * g.plane),
-                                         (__attribute__((address_space(3))) void*)(dst + k * 256), 4, 0, 0);
-}
-
-// wait for this wave's loads into LDS: the compiler does not track them, so
-// the wait is explicit, and the memory clobber keeps the LDS reads after it
-__device__ inline void wait_lds_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-template <bool FINAL, bool SH, bool PIPE = false, bool NT = false>
-__device__ __attribute__((always_inline)) inline void iterate_pixel_pf(
-    const Geo& g, const Strengths& s, const Inputs& in, const float* __restrict__ X, float* __restrict__ Y,
-    float* __restrict__ var_ll, float* __restrict__ valid, int* __restrict__ health, int u, int v,
-    bool inside = true, double* __restrict__ sh = nullptr, int u0 = 0, int v0 = 0, int tid = 0,
-    float* mbuf = nullptr, bool pre = false, int nu0 = 0, int nv0 = 0) {
-    const long p = inside ? pix_of(g, u, v) : 0;
-    bool has[4];
-    long pn[4];
+// sender side: partial messages of a pixel towards each neighbour, from its
+// belief (L, eta) and its stored messages, written to the neighbours' slots;
+// act: which edges' normal-integration factors are active
+template <bool NT, bool TAPE>
+__device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned o, const bool has[4], const bool act[4],
+                                     const double L[28], const double eta[7], const Messages& ms,
+                                     float* __restrict__ Y, double* __restrict__ marg) {
+    double P[21], pm[6], D, dv, l66 = L[s7(6, 6)];
+    bool ok = depth_marginal(L, eta, D, dv);
+    // the depth marginal and what is sent of it are finished before the pose
+    // marginal takes the belief's registers
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        int nu, nv;
-        has[d] = inside && neighbour(g, u, v, d, nu, nv);
-        pn[d] = has[d] ? pix_of(g, nu, nv) : p;
+        if (!has[d]) continue;
+        GFloat* b = plane_of(Y, (long)(P_MN + 2 * opposite(d)) * g.plane + step_of(g, d));
+        const unsigned oh = here(o);
+        double lp, hn;
+        normal_partial(s.lamN, D - (double)ms.mn[d][1], dv - (double)ms.mn[d][0], lp, hn);
+        put<NT>(at(b, oh), act[d] ? (float)hn : 0.0f);
+        put<NT>(at(next(g, b), oh), act[d] ? (float)lp : 0.0f);
     }
-    // --- loads with computable addresses, all issued before any use
-    float pt[7], npt[4][7], mid[4][27], mn[4][2];
-    EdgeTargets ct;
-    PixelInputs pin;
-    double tau[6], ell, R[9], t[3];
-    if (inside) {
+    asm volatile("" : "+v"(l66), "+v"(D), "+v"(dv));
+    pose_marginal(L, eta, l66, P, pm);
+    if constexpr (TAPE) tape_marginals(marg, g, o, P, pm, D, dv, L, eta);
 #pragma unroll
-        for (int k = 0; k < 7; ++k) pt[k] = X[(long)(P_TAU + k) * g.plane + p];
-        if constexpr (!SH) {
+    for (int d = 0; d < 4; ++d) {
+        if (!has[d]) continue;
+        reread_lds();
+        const int slot = opposite(d);
+        double V[21], vv[6], Lp[21], h[6];
 #pragma unroll
-            for (int d = 0; d < 4; ++d)
+        for (int k = 0; k < 21; ++k) V[k] = P[k] - (double)ms.lam(d, k);
 #pragma unroll
-                for (int k = 0; k < 7; ++k) npt[d][k] = X[(long)(P_TAU + k) * g.plane + pn[d]];
+        for (int k = 0; k < 6; ++k) vv[k] = pm[k] - (double)ms.eta[d][k];
+        ok = identity_partial(s.lamR, V, vv, Lp, h) && ok;
+        GFloat* b = plane_of(Y, (long)(P_MID + slot * MID_STRIDE) * g.plane + step_of(g, d));
+        const unsigned oh = here(o);
+#pragma unroll
+        for (int k = 0; k < 27; ++k) {
+            put<NT>(at(b, oh), k < 6 ? (float)h[k] : (float)Lp[k - 6]);
+            b = next(g, b);
         }
-        if constexpr (!PIPE) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-#pragma unroll
-                for (int k = 0; k < 27; ++k) mid[d][k] = X[(long)(P_MID + d * MID_STRIDE + k) * g.plane + p];
-                mn[d][0] = X[(long)(P_MN + 2 * d) * g.plane + p];
-                mn[d][1] = X[(long)(P_MN + 2 * d + 1) * g.plane + p];
-            }
-        }
-        ct.c[DIR_L] = in.cxt[pn[DIR_L]];
-        ct.c[DIR_R] = in.cxt[p];
-        ct.c[DIR_U] = in.cyt[pn[DIR_U]];
-        ct.c[DIR_D] = in.cyt[p];
-        pin = load_pixel_inputs(g, s, in, u, v);
-        if constexpr (PIPE) {
-            // this tile's messages, prefetched into LDS during the previous tile
-            wait_lds_loads();
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-#pragma unroll
-                for (int k = 0; k < 27; ++k) mid[d][k] = mbuf[(d * MID_STRIDE + k) * 256 + tid];
-                mn[d][0] = mbuf[(P_MN - P_MID + 2 * d) * 256 + tid];
-                mn[d][1] = mbuf[(P_MN - P_MID + 2 * d + 1) * 256 + tid];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 6; ++k) tau[k] = (double)pt[k];
-        ell = (double)pt[6];
-        se3_exp(tau, R, t);
     }
-    if constexpr (SH) {
-        // the tile's points and its halo into the shared table
-        if (inside) sh_put(sh, (v - v0 + 1) * HALO_W + (u - u0 + 1), R, t, ell);
-        int hu, hv, hh;
-        if (tid < 2 * HALO_W + 8 && halo_point(g, u0, v0, tid, hu, hv, hh)) {
-            const long hp = pix_of(g, hu, hv);
-            double ht[6], hR[9], htr[3];
+    return ok;
+}
+
+// the pixel's neighbours: whether there is one, its offset (a missing
+// neighbour's is the pixel's own), and the normal targets of the edges
+__device__ inline void edges_of(const Geo& g, const Inputs& in, int u, int v, bool has[4], unsigned on[4], float c[4]) {
+    const unsigned o = off_of(g, u, v);
+    has[DIR_L] = u > 0;
+    has[DIR_R] = u + 1 < g.W;
+    has[DIR_U] = v > 0;
+    has[DIR_D] = v + 1 < g.H;
 #pragma unroll
-            for (int k = 0; k < 6; ++k) ht[k] = (double)X[(long)(P_TAU + k) * g.plane + hp];
-            const double hell = (double)X[(long)P_ELL * g.plane + hp];
-            se3_exp(ht, hR, htr);
-            sh_put(sh, hh, hR, htr, hell);
-        }
-        __syncthreads();
-    }
-    if (!inside) {
-        if constexpr (PIPE) {
-            wait_lds_loads();   // this lane's slots of the buffer are read (nothing) before they are refilled
-            if (pre) prefetch_messages(g, X, mbuf, nu0, nv0, tid >> 6, tid & 63);
-        }
-        return;
-    }
+    for (int d = 0; d < 4; ++d) on[d] = has[d] ? o + (unsigned)(4 * step_of(g, d)) : o;
+    c[DIR_L] = ld(in.cxt, on[DIR_L]);
+    c[DIR_R] = ld(in.cxt, o);
+    c[DIR_U] = ld(in.cyt, on[DIR_U]);
+    c[DIR_D] = ld(in.cyt, o);
+}
+
+// which edges' normal-integration factors are active
+__device__ inline void active_edges(const Strengths& s, const float c[4], bool act[4]) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) act[d] = isfinite(c[d]) && s.lamN > 0.0;
+}
+
+// prologue of one pixel: belief of the canonical state and the first partials
+template <bool NT, bool TAPE>
+__device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& g, const Strengths& s, const Inputs& in,
+                                                                     const float* __restrict__ X,
+                                                                     float* __restrict__ Y, int* __restrict__ health,
+                                                                     int u, int v, float* buf, int lane,
+                                                                     double* __restrict__ marg) {
+    const unsigned o = off_of(g, u, v);
+    Messages ms;
+    bool has[4];
+    unsigned on[4];
+    float c[4], pt[7];
+    load_point_at(X, g, o, pt);
+    const PixelInputs pin = load_inputs_at(s, in, o);
+    edges_of(g, in, u, v, has, on, c);
+    load_messages(X, g, o, buf, lane, ms);
+    double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
+    point_of(pt, tau, ell);
+    pose_exp(tau, q, t);
+    pose_rotation(q, R);
+    unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
+    wait_lds_loads();
+    load_lam3(X, g, o, ms);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) add_message(L, eta, ms, d);
+    bool act[4];
+    active_edges(s, c, act);
+    const bool ok = emit_partials<NT, TAPE>(g, s, o, has, act, L, eta, ms, Y, marg);
+    store_point<NT>(Y, g, o, tau, ell);
+    if (!ok) atomicOr(health, 1);
+}
+
+// one iteration of one pixel: complete the partials in flight, update and
+// relinearise, then (not FINAL) linearise again and emit the next partials or
+// (FINAL) write the canonical state and the per-pixel outputs. Every load
+// whose address does not depend on computed values is issued before its first
+// use; the bilinear samples at the two warps stand under the prior's
+// arithmetic. The point is stored after the second samples' arrival: a wait
+// for loads also waits for the stores issued before them. NT: non-temporal
+// stores; TAPE: also writes the reverse sweep's tape.
+template <bool FINAL, bool NT, bool TAPE>
+__device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g, const Strengths& s, const Inputs& in,
+                                                                    const float* __restrict__ X,
+                                                                    float* __restrict__ Y, float* __restrict__ var_ll,
+                                                                    float* __restrict__ valid,
+                                                                    int* __restrict__ health, int u, int v, float* buf,
+                                                                    int lane, const Tape& tape) {
+    const unsigned o = off_of(g, u, v);
+    Messages ms;
+    bool has[4];
+    unsigned on[4];
+    float c[4], pt[7], npt[4][7];
+    load_point_at(X, g, o, pt);
+    const PixelInputs pin = load_inputs_at(s, in, o);
+    edges_of(g, in, u, v, has, on, c);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) load_point_at(X, g, on[d], npt[d]);
+    load_messages(X, g, o, buf, lane, ms);
 
     // --- linearise at the current point
-    double L[28], eta[7];
-    const bool val = unary_factors(g, s, in, u, v, tau, R, t, ell, pin, L, eta);
-    if constexpr (PIPE && FINAL) {
-        if (pre) prefetch_messages(g, X, mbuf, nu0, nv0, tid >> 6, tid & 63);
-    }
+    double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
+    point_of(pt, tau, ell);
+    pose_exp(tau, q, t);
+    pose_rotation(q, R);
+    const bool val = unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
 
-    // --- complete the partials in flight (complete_partials)
-    const int hown = SH ? (v - v0 + 1) * HALO_W + (u - u0 + 1) : 0;
+    // --- complete the partials in flight with the residuals at both points
+    wait_lds_loads();
+    load_lam3(X, g, o, ms);
+    bool act[4];
+    active_edges(s, c, act);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         if (!has[d]) {
 #pragma unroll
-            for (int k = 0; k < 27; ++k) mid[d][k] = 0.0f;
-            mn[d][0] = mn[d][1] = 0.0f;
+            for (int k = 0; k < 6; ++k) ms.eta[d][k] = 0.0f;
+            ms.mn[d][0] = ms.mn[d][1] = 0.0f;
+            if constexpr (TAPE) {
+                GFloat* b = plane_of(tape.lam, (long)(d * LAM_STRIDE) * g.plane);
+#pragma unroll
+                for (int k = 0; k < LAM_STRIDE; ++k) {
+                    __builtin_nontemporal_store(0.0f, at(b, o));
+                    b = next(g, b);
+                }
+            }
             continue;
         }
-        double Rj[9], trj[3], ellj, r[6];
-        if constexpr (SH) {
-            const int hj = hown + (d == DIR_L ? -1 : d == DIR_R ? 1 : d == DIR_U ? -HALO_W : HALO_W);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) Rj[k] = sh[k * HALO_N + hj];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) trj[k] = sh[(9 + k) * HALO_N + hj];
-            ellj = sh[12 * HALO_N + hj];
-        } else {
-            double tj[6];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) tj[k] = (double)npt[d][k];
-            ellj = (double)npt[d][6];
-            se3_exp(tj, Rj, trj);
+        double tj[6], ellj, qj[4], trj[3], r[6], e[6];
+        point_of(npt[d], tj, ellj);
+        pose_exp(tj, qj, trj);
+        pose_between(qj, trj, q, t, r);
+        complete_eta(ms.eta[d], [&](int k) { return ms.lam(d, k); }, r, e);
+        double ne = 0.0, rn;
+        float nl = 0.0f;
+        if (act[d]) {
+            rn = normal_residual_c(c[d], d, ell, ellj);
+            nl = ms.mn[d][1];
+            ne = fma(-(double)nl, rn, (double)ms.mn[d][0]);
         }
-        se3_between(Rj, trj, R, t, r);
-        double e6[6];
 #pragma unroll
         for (int a = 0; a < 6; ++a) {
-            double e = (double)mid[d][a];
-#pragma unroll
-            for (int b = 0; b < 6; ++b) e -= (double)mid[d][6 + s6(a, b)] * r[b];
-            e6[a] = e;
+            eta[a] += e[a];
+            ms.eta[d][a] = (float)e[a];
         }
-        double ne = 0.0;
-        float nl = 0.0f;
-        double rn;
-        if (s.lamN > 0.0 && normal_residual_c(ct.c[d], d, ell, ellj, rn)) {
-            nl = mn[d][1];
-            ne = (double)mn[d][0] - (double)nl * rn;
-        }
-        float lam[21];
 #pragma unroll
-        for (int k = 0; k < 21; ++k) lam[k] = mid[d][6 + k];
-        accumulate_message(L, eta, e6, lam, ne, nl, mid[d], mn[d]);
+        for (int i = 0; i < 6; ++i)
+#pragma unroll
+            for (int k = i; k < 6; ++k) L[s7(i, k)] += (double)ms.lam(d, s6(i, k));
+        eta[6] += ne;
+        L[s7(6, 6)] += (double)nl;
+        ms.mn[d][0] = (float)ne;
+        ms.mn[d][1] = nl;
+        if constexpr (TAPE) {
+            // the new messages' information: the partials' FP32 values
+            GFloat* b = plane_of(tape.lam, (long)(d * LAM_STRIDE) * g.plane);
+#pragma unroll
+            for (int k = 0; k < LAM_STRIDE; ++k) {
+                __builtin_nontemporal_store(k < 21 ? ms.lam(d, k) : nl, at(b, o));
+                b = next(g, b);
+            }
+        }
+    }
+    if constexpr (TAPE) {
+        GDouble* b = plane_of(tape.bel);
+#pragma unroll
+        for (int k = 0; k < 35; ++k) {
+            __builtin_nontemporal_store(k < 28 ? L[k] : eta[k - 28], at(b, o));
+            b = next(g, b);
+        }
     }
 
-    // --- update, relinearise, transport
-    double var;
-    bool ok = update_and_transport(L, eta, tau, ell, mid, mn, var);
+    // --- update, relinearise (Eq. var), transport the stored messages
+    reread_lds();
+    double m[7], var;
+    bool ok = ldl7_solve(L, eta, m, var);
+    pose_retract(q, t, m, tau);
+    ell += m[6];
     round_point(tau, ell);
-    store_point<NT>(Y, g, p, tau, ell);
-    if (FINAL) {
-        store_messages<NT>(Y, g, p, mid, mn);
-        var_ll[p] = (float)var;
-        valid[p] = val ? 1.0f : 0.0f;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        if (has[d]) transport_message(ms, d, m);
+    reread_lds();
+    if constexpr (FINAL) {
+        store_point<NT>(Y, g, o, tau, ell);
+        store_messages<NT>(Y, g, o, ms, has);
+        *at((GFloat*)var_ll, o) = (float)var;
+        *at((GFloat*)valid, o) = val ? 1.0f : 0.0f;
     } else {
-        // --- linearise at the new point and send the next partials (emit_partials)
-        se3_exp(tau, R, t);
-        unary_factors(g, s, in, u, v, tau, R, t, ell, pin, L, eta);
-        if constexpr (PIPE) {
-            // the next tile's messages stream into LDS during the rest of this one
-            if (pre) prefetch_messages(g, X, mbuf, nu0, nv0, tid >> 6, tid & 63);
+        // --- linearise at the new point and send the next partials
+        pose_exp(tau, q, t);
+        pose_rotation(q, R);
+        unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
+        store_point<NT>(Y, g, o, tau, ell);
+        if constexpr (TAPE) {
+            store_point(tape.canonical, g, o, tau, ell);
+            store_messages(tape.canonical, g, o, ms, has);
         }
-        add_messages(L, eta, mid, mn);
-        double P[21], pm[6], D, dv;
-        pose_marginal(L, eta, P, pm);
-        ok = depth_marginal(L, eta, D, dv) && ok;
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            if (!has[d]) continue;
-            const long pj = pn[d];
-            const int slot = opposite(d);
-            double V[21], vv[6], Lp[21], h[6];
-#pragma unroll
-            for (int k = 0; k < 21; ++k) V[k] = P[k] - (double)mid[d][6 + k];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) vv[k] = pm[k] - (double)mid[d][k];
-            ok = identity_partial(s.lamR, V, vv, Lp, h) && ok;
-            float* dst = Y + (long)(P_MID + slot * MID_STRIDE) * g.plane + pj;
-            if constexpr (NT) {
-#pragma unroll
-                for (int k = 0; k < 6; ++k) put<true>(&dst[k * g.plane], (float)h[k]);
-#pragma unroll
-                for (int k = 0; k < 21; ++k) put<true>(&dst[(6 + k) * g.plane], (float)Lp[k]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 6; ++k) dst[k * g.plane] = (float)h[k];
-#pragma unroll
-                for (int k = 0; k < 21; ++k) dst[(6 + k) * g.plane] = (float)Lp[k];
-            }
-            float* dn = Y + (long)(P_MN + 2 * slot) * g.plane + pj;
-            if (isfinite(ct.c[d]) && s.lamN > 0.0) {
-                double lp, hn;
-                normal_partial(s.lamN, D - (double)mn[d][1], dv - (double)mn[d][0], lp, hn);
-                if constexpr (NT) {
-                    put<true>(&dn[0], (float)hn);
-                    put<true>(&dn[g.plane], (float)lp);
-                } else {
-                    dn[0] = (float)hn;
-                    dn[g.plane] = (float)lp;
-                }
-            } else if constexpr (NT) {
-                put<true>(&dn[0], 0.0f);
-                put<true>(&dn[g.plane], 0.0f);
-            } else {
-                dn[0] = 0.0f;
-                dn[g.plane] = 0.0f;
-            }
-        }
+        for (int d = 0; d < 4; ++d)
+            if (has[d]) add_message(L, eta, ms, d);
+        ok = emit_partials<NT, TAPE>(g, s, o, has, act, L, eta, ms, Y, tape.marg) && ok;
     }
     if (!ok) atomicOr(health, 1);
 }
 
-__global__ __launch_bounds__(256) void k_fu_prologue(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                     float* __restrict__ Y, int* __restrict__ health) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y * blockDim.y + threadIdx.y;
-    if (u >= g.W || v >= g.H) return;
-    prologue_pixel(g, s, in, X, Y, health, u, v);
+// Fused passes of one image: one wave per workgroup, 64 pixels of a row, so
+// that a SIMD takes the next row segment as soon as one of its two waves ends.
+// Bound by memory where the image fills the chip (640 x 480: 83.6 us per pass,
+// 302 MB of algorithmic bytes, whose copy at this card's 4.74 TB/s takes 64 us;
+// 127 us before, as one wave per SIMD of a persistent workgroup with 504
+// registers) and by one wave's chain of instructions and loads where it does
+// not (32 x 24: 17.0 us, 21.2 before; 4,218 vector instructions per wave, 6,234
+// before).
+__global__ __launch_bounds__(64, 2) void k_fu_prologue(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
+                                                       float* __restrict__ Y, int* __restrict__ health) {
+    __shared__ float buf[LDS_WAVE];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
+    prologue_pixel<false, false>(g, s, in, X, Y, health, u, v, buf, threadIdx.x, nullptr);
 }
 
-// Persistent: each workgroup (one per CU: the LDS of the shared table and the
-// message buffer fill a CU) takes the 64 x 4 tiles blockIdx, blockIdx +
-// gridDim, ... in turn, loading the next tile's messages into LDS while it
-// computes the current one. Every lane reaches the barriers of every tile;
-// lanes outside the image only help fill the shared table.
 template <bool FINAL>
-__global__ __launch_bounds__(256) void k_fu_iterate(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                    float* __restrict__ Y, float* __restrict__ var_ll,
-                                                    float* __restrict__ valid, int* __restrict__ health,
-                                                    int tiles_x, int ntiles) {
-    __shared__ double sh[SH_FIELDS * HALO_N];
-    __shared__ float mbuf[MSG_PLANES * 256];
-    const int tid = threadIdx.y * 64 + threadIdx.x;
-    int tile = blockIdx.x;
-    if (tile >= ntiles) return;
-    prefetch_messages(g, X, mbuf, (tile % tiles_x) * 64, (tile / tiles_x) * 4, threadIdx.y, threadIdx.x);
-    for (; tile < ntiles; tile += gridDim.x) {
-        const int next = tile + gridDim.x;
-        const int u0 = (tile % tiles_x) * 64, v0 = (tile / tiles_x) * 4;
-        const int u = u0 + threadIdx.x, v = v0 + threadIdx.y;
-        // everything the pass derives from the arguments and the lane index is
-        // made opaque per tile, so the compiler recomputes it inside the tile
-        // instead of hoisting it out of the loop (hundreds of plane and LDS
-        // addresses, which would not fit in registers)
-        int z = 0;
-        asm volatile("" : "+s"(z));
-        Geo gt = g;
-        gt.H += z;
-        gt.W += z;
-        gt.pitch += z;
-        gt.plane += z;
-        Inputs it = in;
-        it.Is += z;
-        it.cxt += z;
-        it.cyt += z;
-        it.sigD += z;
-        it.It += z;
-        it.Gx += z;
-        it.Gy += z;
-        it.prior_ell += z;
-        const int tz = tid + z;
-        __syncthreads();   // the previous tile's readers of the shared table are done
-        iterate_pixel_pf<FINAL, true, true, FINAL>(gt, s, it, X + z, Y + z, var_ll + z, valid + z, health, u + z, v + z,
-                                            u < g.W && v < g.H, sh, u0, v0, tz, mbuf, next < ntiles,
-                                            (next % tiles_x) * 64, (next / tiles_x) * 4);
-    }
+__global__ __launch_bounds__(64, 2) void k_fu_iterate(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
+                                                      float* __restrict__ Y, float* __restrict__ var_ll,
+                                                      float* __restrict__ valid, int* __restrict__ health) {
+    __shared__ float buf[LDS_WAVE];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
+    iterate_pixel<FINAL, FINAL, false>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, Tape{});
 }
 
 // the same passes for the reverse sweep's recompute: the prologue also writes
 // the belief of its state and its marginals, the final pass the new messages
 // computed from its source state and the belief they form with the unary
 // factors (exactly the values of k_pf_linearise, k_pf_messages, k_pf_update)
-__global__ __launch_bounds__(256) void k_fu_prologue_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                          float* __restrict__ Y, double* __restrict__ marg,
-                                                          int* __restrict__ health) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y * blockDim.y + threadIdx.y;
-    if (u >= g.W || v >= g.H) return;
-    prologue_pixel(g, s, in, X, Y, health, u, v, marg);
+__global__ __launch_bounds__(64, 2) void k_fu_prologue_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
+                                                            float* __restrict__ Y, double* __restrict__ marg,
+                                                            int* __restrict__ health) {
+    __shared__ float buf[LDS_WAVE];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
+    prologue_pixel<false, true>(g, s, in, X, Y, health, u, v, buf, threadIdx.x, marg);
 }
 
 // the rotated form of the recompute: the update of iteration k from its
-// partial state X (new messages into M, belief into bel, canonical state
-// k + 1 into Yc) and the prologue of iteration k + 1 (partials into Y,
-// marginals and belief into marg_next) in one pass; the same arithmetic as
-// k_fu_final_tape followed by k_fu_prologue_tape on the canonical state
-__global__ __launch_bounds__(256) void k_fu_rot_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                     float* __restrict__ Y, float* __restrict__ Yc,
-                                                     float* __restrict__ M, double* __restrict__ bel,
-                                                     double* __restrict__ marg_next, int* __restrict__ health) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y * blockDim.y + threadIdx.y;
-    if (u >= g.W || v >= g.H) return;
-    iterate_pixel<false>(g, s, in, X, Y, nullptr, nullptr, health, u, v, M, bel, Yc, marg_next);
-}
-
-__global__ __launch_bounds__(256) void k_fu_final_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                       float* __restrict__ Y, float* __restrict__ M,
-                                                       double* __restrict__ bel, float* __restrict__ var_ll,
-                                                       float* __restrict__ valid, int* __restrict__ health) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y * blockDim.y + threadIdx.y;
-    if (u >= g.W || v >= g.H) return;
-    iterate_pixel<true>(g, s, in, X, Y, var_ll, valid, health, u, v, M, bel);
+// partial state X (new messages into tape.lam, belief into tape.bel, canonical
+// state k + 1 into tape.canonical) and the prologue of iteration k + 1
+// (partials into Y, marginals and belief into tape.marg) in one pass; the same
+// arithmetic as k_fu_final_tape followed by k_fu_prologue_tape on the
+// canonical state
+template <bool FINAL>
+__global__ __launch_bounds__(64, 2) void k_fu_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
+                                                   float* __restrict__ Y, Tape tape, float* __restrict__ var_ll,
+                                                   float* __restrict__ valid, int* __restrict__ health) {
+    __shared__ float buf[LDS_WAVE];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
+    iterate_pixel<FINAL, false, true>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, tape);
 }
 
 // ---------------------------------------------------------------------------
@@ -1008,10 +930,11 @@ __global__ __launch_bounds__(256) void k_valid_only(Geo g, Strengths s, Inputs i
     const int v = blockIdx.y * blockDim.y + threadIdx.y;
     if (u >= g.W || v >= g.H) return;
     const long p = pix_of(g, u, v);
-    double tau[6], ell, R[9], t[3], L[28], eta[7];
+    double tau[6], ell, q[4], R[9], t[3];
     load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, t);
-    valid[p] = unary_factors(g, s, in, u, v, tau, R, t, ell, L, eta) ? 1.0f : 0.0f;
+    pose_exp(tau, q, t);
+    pose_rotation(q, R);
+    valid[p] = photometric_begin(g, in, u, v, R, t, ell).valid ? 1.0f : 0.0f;
 }
 
 // state exchange: pitched planes <-> dense planes
@@ -1058,25 +981,40 @@ __global__ void k_batch_frame_prep(const SeqDesc* __restrict__ seqs, const int2*
     frame_prep_pixel(d->g, d->frame, d->g.W, d->It, d->Gx, d->Gy, u, v);
 }
 
-__global__ __launch_bounds__(256) void k_batch_prologue(const SeqDesc* __restrict__ seqs, const int2* __restrict__ work,
+// the wave's LDS planes of a workgroup of any tile shape (batch_lds bytes of
+// dynamic LDS) and the lane in its wave
+__device__ inline float* batch_buf(int& lane) {
+    extern __shared__ float batch_lds_[];
+    const int tid = threadIdx.y * blockDim.x + threadIdx.x;
+    lane = tid & 63;
+    return batch_lds_ + __builtin_amdgcn_readfirstlane(tid >> 6) * LDS_WAVE;
+}
+
+static size_t batch_lds(int tile_x, int tile_y) {
+    return (size_t)((tile_x * tile_y + 63) / 64) * LDS_WAVE * sizeof(float);
+}
+
+__global__ __launch_bounds__(256, 2) void k_batch_prologue(const SeqDesc* __restrict__ seqs, const int2* __restrict__ work,
                                                         int parity, Strengths s, int* __restrict__ health) {
     const SeqDesc* d;
-    int u, v, item;
+    int u, v, item, lane;
+    float* buf = batch_buf(lane);
     if (!batch_pixel(seqs, work, d, u, v, item)) return;
     const float* X = parity ? d->X1 : d->X0;
     float* Y = parity ? d->X0 : d->X1;
-    prologue_pixel(d->g, s, d->in, X, Y, health, u, v);
+    prologue_pixel<false, false>(d->g, s, d->in, X, Y, health, u, v, buf, lane, nullptr);
 }
 
 template <bool FINAL>
-__global__ __launch_bounds__(256) void k_batch_iterate(const SeqDesc* __restrict__ seqs, const int2* __restrict__ work,
+__global__ __launch_bounds__(256, 2) void k_batch_iterate(const SeqDesc* __restrict__ seqs, const int2* __restrict__ work,
                                                        int parity, Strengths s, int* __restrict__ health) {
     const SeqDesc* d;
-    int u, v, item;
+    int u, v, item, lane;
+    float* buf = batch_buf(lane);
     if (!batch_pixel(seqs, work, d, u, v, item)) return;
     const float* X = parity ? d->X1 : d->X0;
     float* Y = parity ? d->X0 : d->X1;
-    iterate_pixel_pf<FINAL, false, false, true>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v);
+    iterate_pixel<FINAL, true, false>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v, buf, lane, Tape{});
 }
 
 // per sequence (blockIdx.y) and 64 x 4 tile of its image (blockIdx.x): the
@@ -1156,10 +1094,12 @@ __global__ void k_set_ints(int* __restrict__ p, int n, int value) {
 // b + 2G, ..., stays with the work list's range of its XCD. Every workgroup
 // reaches every barrier: pixels outside an image skip the arithmetic, not the
 // barrier.
-__global__ __launch_bounds__(256) void k_batch_persistent(const SeqDesc* __restrict__ seqs,
+__global__ __launch_bounds__(256, 2) void k_batch_persistent(const SeqDesc* __restrict__ seqs,
                                                           const int2* __restrict__ work, int n_work, int parity,
                                                           int n_passes, Strengths s, int* __restrict__ health) {
     cg::grid_group grid = cg::this_grid();
+    int lane;
+    float* buf = batch_buf(lane);
     for (int pass = 0; pass < n_passes; ++pass) {
         const int par = parity ^ (pass & 1);
         for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
@@ -1171,7 +1111,9 @@ __global__ __launch_bounds__(256) void k_batch_persistent(const SeqDesc* __restr
             if (u < d->g.W && v < d->g.H) {
                 const float* X = par ? d->X1 : d->X0;
                 float* Y = par ? d->X0 : d->X1;
-                iterate_pixel_pf<false, false, false, true>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v);
+                wait_lds_reads();   // of the wave's previous item
+                iterate_pixel<false, true, false>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v, buf, lane,
+                                                  Tape{});
             }
         }
         if (pass + 1 < n_passes) grid.sync();
@@ -1180,17 +1122,18 @@ __global__ __launch_bounds__(256) void k_batch_persistent(const SeqDesc* __restr
 
 hipError_t launch_batch_frame_step(const BatchLaunch& b, int n_iters, hipStream_t st) {
     const dim3 blk(b.tile_x, b.tile_y), grid(b.n_work);
+    const size_t lds = batch_lds(b.tile_x, b.tile_y);
     hipLaunchKernelGGL(k_clear_int, dim3(1), dim3(64), 0, st, b.health);
     hipLaunchKernelGGL(k_batch_frame_prep, grid, blk, 0, st, b.seqs, b.work);
     int parity = b.parity;
     if (n_iters > 0) {
-        hipLaunchKernelGGL(k_batch_prologue, grid, blk, 0, st, b.seqs, b.work, parity, b.s, b.health);
+        hipLaunchKernelGGL(k_batch_prologue, grid, blk, lds, st, b.seqs, b.work, parity, b.s, b.health);
         parity ^= 1;
         for (int it = 0; it < n_iters; ++it) {
             if (it == n_iters - 1)
-                hipLaunchKernelGGL(k_batch_iterate<true>, grid, blk, 0, st, b.seqs, b.work, parity, b.s, b.health);
+                hipLaunchKernelGGL(k_batch_iterate<true>, grid, blk, lds, st, b.seqs, b.work, parity, b.s, b.health);
             else
-                hipLaunchKernelGGL(k_batch_iterate<false>, grid, blk, 0, st, b.seqs, b.work, parity, b.s, b.health);
+                hipLaunchKernelGGL(k_batch_iterate<false>, grid, blk, lds, st, b.seqs, b.work, parity, b.s, b.health);
             parity ^= 1;
         }
     }
@@ -1215,7 +1158,7 @@ hipError_t launch_batch_keyframe(const BatchLaunch& b, int parity, hipStream_t s
 int batch_persistent_grid(const BatchLaunch& b) {
     int per_cu = 0, dev = 0, n_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_batch_persistent),
-                                                     b.tile_x * b.tile_y, 0) != hipSuccess)
+                                                     b.tile_x * b.tile_y, batch_lds(b.tile_x, b.tile_y)) != hipSuccess)
         return 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -1228,9 +1171,10 @@ int batch_persistent_grid(const BatchLaunch& b) {
 
 hipError_t launch_batch_frame_step_persistent(const BatchLaunch& b, int n_iters, int grid_blocks, hipStream_t st) {
     const dim3 blk(b.tile_x, b.tile_y), grid(b.n_work);
+    const size_t lds = batch_lds(b.tile_x, b.tile_y);
     hipLaunchKernelGGL(k_clear_int, dim3(1), dim3(64), 0, st, b.health);
     hipLaunchKernelGGL(k_batch_frame_prep, grid, blk, 0, st, b.seqs, b.work);
-    hipLaunchKernelGGL(k_batch_prologue, grid, blk, 0, st, b.seqs, b.work, b.parity, b.s, b.health);
+    hipLaunchKernelGGL(k_batch_prologue, grid, blk, lds, st, b.seqs, b.work, b.parity, b.s, b.health);
     const SeqDesc* seqs = b.seqs;
     const int2* work = b.work;
     int n_work = b.n_work, parity = b.parity ^ 1, n_passes = n_iters - 1;
@@ -1239,11 +1183,11 @@ hipError_t launch_batch_frame_step_persistent(const BatchLaunch& b, int n_iters,
     if (n_passes > 0) {
         void* args[] = {&seqs, &work, &n_work, &parity, &n_passes, &s, &health};
         hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_batch_persistent), dim3(grid_blocks),
-                                                  blk, args, 0, st);
+                                                  blk, args, (unsigned)lds, st);
         if (e != hipSuccess) return e;
     }
     const int fin = b.parity ^ 1 ^ (n_passes & 1);
-    hipLaunchKernelGGL(k_batch_iterate<true>, grid, blk, 0, st, b.seqs, b.work, fin, b.s, b.health);
+    hipLaunchKernelGGL(k_batch_iterate<true>, grid, blk, lds, st, b.seqs, b.work, fin, b.s, b.health);
     const int par = fin ^ 1;
     launch_batch_stats(b, par, st);
     return launch_batch_keyframe(b, par, st);
@@ -1251,16 +1195,17 @@ hipError_t launch_batch_frame_step_persistent(const BatchLaunch& b, int n_iters,
 
 hipError_t launch_batch_passes(const BatchLaunch& b, int n_iters, bool prologue, bool final_last, hipStream_t st) {
     const dim3 blk(b.tile_x, b.tile_y), grid(b.n_work);
+    const size_t lds = batch_lds(b.tile_x, b.tile_y);
     int parity = b.parity;
     if (prologue) {
-        hipLaunchKernelGGL(k_batch_prologue, grid, blk, 0, st, b.seqs, b.work, parity, b.s, b.health);
+        hipLaunchKernelGGL(k_batch_prologue, grid, blk, lds, st, b.seqs, b.work, parity, b.s, b.health);
         parity ^= 1;
     }
     for (int it = 0; it < n_iters; ++it) {
         if (final_last && it == n_iters - 1)
-            hipLaunchKernelGGL(k_batch_iterate<true>, grid, blk, 0, st, b.seqs, b.work, parity, b.s, b.health);
+            hipLaunchKernelGGL(k_batch_iterate<true>, grid, blk, lds, st, b.seqs, b.work, parity, b.s, b.health);
         else
-            hipLaunchKernelGGL(k_batch_iterate<false>, grid, blk, 0, st, b.seqs, b.work, parity, b.s, b.health);
+            hipLaunchKernelGGL(k_batch_iterate<false>, grid, blk, lds, st, b.seqs, b.work, parity, b.s, b.health);
         parity ^= 1;
     }
     return hipGetLastError();
@@ -1271,11 +1216,6 @@ hipError_t launch_batch_passes(const BatchLaunch& b, int n_iters, bool prologue,
 
 static dim3 grid2d(const Geo& g, dim3 b) { return dim3((g.W + b.x - 1) / b.x, (g.H + b.y - 1) / b.y); }
 static const dim3 kBlock(64, 1);
-// fused passes: 64 x 4 tiles keep the vertical neighbours' points and partials
-// in the same workgroup's cache lines (measured 1.15x against 1.24x of the
-// algorithmic bytes for 64 x 1 at 640x480, same duration)
-static const dim3 kBlockFused(64, 4);
-
 hipError_t launch_frame_prep(const Geo& g, const float* src, long src_pitch, float* It, float* Gx, float* Gy,
                              hipStream_t st, int* clear) {
     hipLaunchKernelGGL(k_frame_prep, grid2d(g, kBlock), kBlock, 0, st, g, src, src_pitch, It, Gx, Gy, clear);
@@ -1303,28 +1243,17 @@ hipError_t launch_pf_iteration(const Geo& g, const Strengths& s, const Inputs& i
 
 hipError_t launch_fu_prologue(const Geo& g, const Strengths& s, const Inputs& in, const float* X, float* Y,
                               int* health, hipStream_t st) {
-    hipLaunchKernelGGL(k_fu_prologue, grid2d(g, kBlockFused), kBlockFused, 0, st, g, s, in, X, Y, health);
+    hipLaunchKernelGGL(k_fu_prologue, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, Y, health);
     return hipGetLastError();
 }
 
 hipError_t launch_fu_iterate(const Geo& g, const Strengths& s, const Inputs& in, const float* X, float* Y,
                              bool final_pass, float* var_ll, float* valid, int* health, hipStream_t st) {
-    static int n_cu = 0;
-    if (n_cu == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-            n_cu = 256;
-    }
-    const dim3 t = grid2d(g, kBlockFused);
-    const int ntiles = (int)(t.x * t.y);
-    const dim3 grid((unsigned)std::min(ntiles, n_cu));
     if (final_pass)
-        hipLaunchKernelGGL(k_fu_iterate<true>, grid, kBlockFused, 0, st, g, s, in, X, Y, var_ll, valid, health,
-                           (int)t.x, ntiles);
+        hipLaunchKernelGGL(k_fu_iterate<true>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, Y, var_ll, valid, health);
     else
-        hipLaunchKernelGGL(k_fu_iterate<false>, grid, kBlockFused, 0, st, g, s, in, X, Y, var_ll, valid, health,
-                           (int)t.x, ntiles);
+        hipLaunchKernelGGL(k_fu_iterate<false>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, Y, var_ll, valid,
+                           health);
     return hipGetLastError();
 }
 
@@ -1333,16 +1262,18 @@ hipError_t launch_fu_segment_tape(const Geo& g, const Strengths& s, const Inputs
                                   float* M, long M_stride, double* bel, long bel_stride, float* var_ll, float* valid,
                                   int* health, hipStream_t st) {
     if (len < 1) return hipSuccess;
-    const dim3 grid = grid2d(g, kBlockFused);
-    hipLaunchKernelGGL(k_fu_prologue_tape, grid, kBlockFused, 0, st, g, s, in, X0, tA, marg, health);
+    const dim3 grid = grid2d(g, kBlock);
+    hipLaunchKernelGGL(k_fu_prologue_tape, grid, kBlock, 0, st, g, s, in, X0, tA, marg, health);
     float* t[2] = {tA, tB};
-    for (int k = 0; k + 1 < len; ++k)
-        hipLaunchKernelGGL(k_fu_rot_tape, grid, kBlockFused, 0, st, g, s, in, t[k & 1], t[(k + 1) & 1],
-                           seg + seg_stride * (k + 1), M + M_stride * k, bel + bel_stride * k,
-                           marg + marg_stride * (k + 1), health);
-    const int k = len - 1;
-    hipLaunchKernelGGL(k_fu_final_tape, grid, kBlockFused, 0, st, g, s, in, t[k & 1], t[(k + 1) & 1],
-                       M + M_stride * k, bel + bel_stride * k, var_ll, valid, health);
+    for (int k = 0; k < len; ++k) {
+        const Tape tape{M + M_stride * k, bel + bel_stride * k, seg + seg_stride * (k + 1), marg + marg_stride * (k + 1)};
+        if (k + 1 < len)
+            hipLaunchKernelGGL(k_fu_tape<false>, grid, kBlock, 0, st, g, s, in, t[k & 1], t[(k + 1) & 1], tape, var_ll,
+                               valid, health);
+        else
+            hipLaunchKernelGGL(k_fu_tape<true>, grid, kBlock, 0, st, g, s, in, t[k & 1], t[(k + 1) & 1], tape, var_ll,
+                               valid, health);
+    }
     return hipGetLastError();
 }
 

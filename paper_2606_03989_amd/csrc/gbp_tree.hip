@@ -94,64 +94,12 @@ __device__ inline bool identity_partial_from(double lamR, const double P[21], co
     return ok;
 }
 
-// pose prior of a node (Eq. prior) with precision lamP at Exp(tau) = (R, t):
-// r = Log(Exp(xi_hat)^-1 Exp(tau)), J = I + ad(r)/2 + ad(r)^2/12
-__device__ inline void node_prior(const Strengths& s, double lamP, const double tau[6], const double R[9],
+// (L, eta) = pose prior of a node (Eq. prior) with precision lamP at Exp(tau) = (q, t)
+__device__ inline void node_prior(const Strengths& s, double lamP, const double tau[6], const double q[4],
                                   const double t[3], double L[21], double eta[6]) {
     double rp[6];
-    if (s.prior_is_identity) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) rp[k] = tau[k];
-    } else {
-        double Rr[9], tr[3];
-        se3_compose(s.prior_R, s.prior_t, R, t, Rr, tr);
-        se3_log(Rr, tr, rp);
-    }
-    // J = [[A, 0], [B, A]]: A = I + W/2 + W^2/12, B = P/2 + (P W + W P)/12,
-    // W = [theta]x and P = [rho]x of r
-    const double w0 = rp[0], w1 = rp[1], w2 = rp[2], p0 = rp[3], p1 = rp[4], p2 = rp[5];
-    const double Wm[9] = {0.0, -w2, w1, w2, 0.0, -w0, -w1, w0, 0.0};
-    const double Pm[9] = {0.0, -p2, p1, p2, 0.0, -p0, -p1, p0, 0.0};
-    double A[9], B[9];
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double ww = 0.0, pw = 0.0, wp = 0.0;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                ww += Wm[r * 3 + k] * Wm[k * 3 + c];
-                pw += Pm[r * 3 + k] * Wm[k * 3 + c];
-                wp += Wm[r * 3 + k] * Pm[k * 3 + c];
-            }
-            A[r * 3 + c] = (r == c ? 1.0 : 0.0) + 0.5 * Wm[r * 3 + c] + ww * (1.0 / 12.0);
-            B[r * 3 + c] = 0.5 * Pm[r * 3 + c] + (pw + wp) * (1.0 / 12.0);
-        }
-    // column a of J: rows 0..2 from A (a < 3), rows 3..5 from B (a < 3) or A (a >= 3)
-    double J[36];
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            J[r * 6 + c] = A[r * 3 + c];
-            J[r * 6 + c + 3] = 0.0;
-            J[(r + 3) * 6 + c] = B[r * 3 + c];
-            J[(r + 3) * 6 + c + 3] = A[r * 3 + c];
-        }
-#pragma unroll
-    for (int a = 0; a < 6; ++a) {
-        double e = 0.0;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) e += J[k * 6 + a] * rp[k];
-        eta[a] = -lamP * e;
-#pragma unroll
-        for (int b = a; b < 6; ++b) {
-            double g = 0.0;
-#pragma unroll
-            for (int k = 0; k < 6; ++k) g += J[k * 6 + a] * J[k * 6 + b];
-            L[s6(a, b)] = lamP * g;
-        }
-    }
+    prior_residual(s, tau, q, t, rp);
+    pose_prior(lamP, rp, eta, [&](int r, int c, double x) { L[s6(r, c)] = x; });
 }
 
 // per-workgroup level of a node launch (uniform across the workgroup)
@@ -207,7 +155,7 @@ __device__ inline bool pixel_emit(const Geo& g, const Strengths& s, const Inputs
                                   const double L[28], const double eta[7], const float mup[27],
                                   const float mn[4][2], float* __restrict__ Y) {
     double P[21], p[6], D, dv;
-    pose_marginal(L, eta, P, p);
+    pose_marginal(L, eta, L[s7(6, 6)], P, p);
     bool ok = depth_marginal(L, eta, D, dv);
     const long pi = pix_of(g, u, v);
     float part[27];
@@ -245,10 +193,11 @@ __global__ __launch_bounds__(256) void k_tr_pixel_prologue(Geo g, TreeGeo t, Str
     const int v = blockIdx.y * blockDim.y + threadIdx.y;
     if (u >= g.W || v >= g.H) return;
     const long p = pix_of(g, u, v);
-    double tau[6], ell, R[9], tt[3], L[28], eta[7];
+    double tau[6], ell, q4[4], R[9], tt[3], L[28], eta[7];
     load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, tt);
-    unary_factors<true>(g, s, in, u, v, tau, R, tt, ell, L, eta);
+    pose_exp(tau, q4, tt);
+    pose_rotation(q4, R);
+    unary_factors<true>(g, s, in, u, v, tau, q4, R, tt, ell, load_pixel_inputs(g, s, in, u, v), L, eta);
     float mup[27], mn[4][2];
     load_part27(X + (long)TP_UP * g.plane, g.plane, p, mup);
 #pragma unroll
@@ -273,21 +222,23 @@ __global__ __launch_bounds__(256) void k_tr_pixel_iterate(Geo g, TreeGeo t, Stre
     const int v = blockIdx.y * blockDim.y + threadIdx.y;
     if (u >= g.W || v >= g.H) return;
     const long pi = pix_of(g, u, v);
-    double tau[6], ell, R[9], tt[3], L[28], eta[7];
+    double tau[6], ell, q4[4], R[9], tt[3], L[28], eta[7];
     load_point(X, g, pi, tau, ell);
-    se3_exp(tau, R, tt);
-    const bool val = unary_factors<true>(g, s, in, u, v, tau, R, tt, ell, L, eta);
+    const PixelInputs pin = load_pixel_inputs(g, s, in, u, v);
+    pose_exp(tau, q4, tt);
+    pose_rotation(q4, R);
+    const bool val = unary_factors<true>(g, s, in, u, v, tau, q4, R, tt, ell, pin, L, eta);
 
     // the parent's partial for this child slot, completed at both points
     float mup[27];
     {
         const long pn = (long)t.off[1] + (long)(v >> 1) * t.Wl[1] + (u >> 1);
         const int q = ((v & 1) << 1) | (u & 1);
-        double tp[6], Rp[9], trp[3], r[6];
+        double tp[6], qp[4], trp[3], r[6];
 #pragma unroll
         for (int k = 0; k < 6; ++k) tp[k] = (double)NX[(long)(TN_TAU + k) * t.nplane + pn];
-        se3_exp(tp, Rp, trp);
-        se3_between(Rp, trp, R, tt, r);
+        pose_exp(tp, qp, trp);
+        pose_between(qp, trp, q4, tt, r);
         float part[27];
         load_part27(NX + (long)(TN_CH + 27 * q) * t.nplane, t.nplane, pn, part);
         complete_identity<7>(part, r, L, eta, mup);
@@ -313,18 +264,9 @@ __global__ __launch_bounds__(256) void k_tr_pixel_iterate(Geo g, TreeGeo t, Stre
         }
     }
     // update: mean, relinearisation (Eq. var), transport of the stored messages
-    double idg[7], m[7];
-    bool ok = chol7(L, idg);
-#pragma unroll
-    for (int k = 0; k < 7; ++k) m[k] = eta[k];
-    chol7_solve(L, idg, m);
-    const double var = chol7_var_last(idg);
-    {
-        double R1[9], t1[3], Rm[9], tm[3];
-        se3_exp(m, Rm, tm);
-        se3_compose(R, tt, Rm, tm, R1, t1);
-        se3_log(R1, t1, tau);
-    }
+    double m[7], var;
+    bool ok = ldl7_solve(L, eta, m, var);
+    pose_retract(q4, tt, m, tau);
     ell += m[6];
     transport_identity(mup, m);
 #pragma unroll
@@ -342,8 +284,9 @@ __global__ __launch_bounds__(256) void k_tr_pixel_iterate(Geo g, TreeGeo t, Stre
         var_ll[pi] = (float)var;
         valid[pi] = val ? 1.0f : 0.0f;
     } else {
-        se3_exp(tau, R, tt);
-        unary_factors<true>(g, s, in, u, v, tau, R, tt, ell, L, eta);
+        pose_exp(tau, q4, tt);
+        pose_rotation(q4, R);
+        unary_factors<true>(g, s, in, u, v, tau, q4, R, tt, ell, pin, L, eta);
         add_identity<7>(mup, L, eta);
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
@@ -387,14 +330,14 @@ __global__ __launch_bounds__(kTreeThreads) void k_tr_node(Geo g, TreeGeo t, Stre
     if (i >= lv.H * lv.W) return;
     const int x = i % lv.W, y = i / lv.W;
     const long n = (long)lv.off + i;
-    double tau[6], R[9], tt[3], L[21], eta[6];
+    double tau[6], q4[4], tt[3], L[21], eta[6];
     float msg[5][27];
     bool ok = true;
     if (PROLOGUE) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) tau[k] = (double)NX[(long)(TN_TAU + k) * t.nplane + n];
-        se3_exp(tau, R, tt);
-        node_prior(s, lv.lamP, tau, R, tt, L, eta);
+        pose_exp(tau, q4, tt);
+        node_prior(s, lv.lamP, tau, q4, tt, L, eta);
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
             load_part27(NX + (long)(TN_UP + 27 * k) * t.nplane, t.nplane, n, msg[k]);
@@ -435,15 +378,15 @@ __global__ __launch_bounds__(kTreeThreads) void k_tr_node(Geo g, TreeGeo t, Stre
         }
 #pragma unroll
         for (int k = 0; k < 6; ++k) tau[k] = (double)tnf[k];
-        se3_exp(tau, R, tt);
-        node_prior(s, lv.lamP, tau, R, tt, L, eta);
+        pose_exp(tau, q4, tt);
+        node_prior(s, lv.lamP, tau, q4, tt, L, eta);
         // parent's partial for this child slot, completed in place
         if (has_par) {
-            double tp[6], Rp[9], trp[3], r[6];
+            double tp[6], qp[4], trp[3], r[6];
 #pragma unroll
             for (int k = 0; k < 6; ++k) tp[k] = (double)tpf[k];
-            se3_exp(tp, Rp, trp);
-            se3_between(Rp, trp, R, tt, r);
+            pose_exp(tp, qp, trp);
+            pose_between(qp, trp, q4, tt, r);
             complete_identity<6>(msg[0], r, L, eta, msg[0]);
         } else {
 #pragma unroll
@@ -457,25 +400,17 @@ __global__ __launch_bounds__(kTreeThreads) void k_tr_node(Geo g, TreeGeo t, Stre
                 for (int k = 0; k < 27; ++k) msg[1 + q][k] = 0.0f;
                 continue;
             }
-            double tc[6], Rc[9], trc[3], r[6];
+            double tc[6], qc[4], trc[3], r[6];
 #pragma unroll
             for (int k = 0; k < 6; ++k) tc[k] = (double)tcf[q][k];
-            se3_exp(tc, Rc, trc);
-            se3_between(Rc, trc, R, tt, r);
+            pose_exp(tc, qc, trc);
+            pose_between(qc, trc, q4, tt, r);
             complete_identity<6>(msg[1 + q], r, L, eta, msg[1 + q]);
         }
         // update: mean, relinearisation, transport
-        double idg[6], m[6];
-        ok = chol6(L, idg);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) m[k] = eta[k];
-        chol6_solve(L, idg, m);
-        {
-            double R1[9], t1[3], Rm[9], tm[3];
-            se3_exp(m, Rm, tm);
-            se3_compose(R, tt, Rm, tm, R1, t1);
-            se3_log(R1, t1, tau);
-        }
+        double m[6];
+        ok = ldl6_solve(L, eta, m);
+        pose_retract(q4, tt, m, tau);
 #pragma unroll
         for (int k = 0; k < 5; ++k) transport_identity(msg[k], m);
         round6(tau);
@@ -487,8 +422,8 @@ __global__ __launch_bounds__(kTreeThreads) void k_tr_node(Geo g, TreeGeo t, Stre
             if (!ok) atomicOr(health, 1);
             return;
         }
-        se3_exp(tau, R, tt);
-        node_prior(s, lv.lamP, tau, R, tt, L, eta);
+        pose_exp(tau, q4, tt);
+        node_prior(s, lv.lamP, tau, q4, tt, L, eta);
 #pragma unroll
         for (int k = 0; k < 5; ++k) add_identity<6>(msg[k], L, eta);
     }

@@ -258,15 +258,18 @@ __global__ __launch_bounds__(kThreads) void k_c_linearise(Geo g, Strengths s, In
     for (int k = 0; k < kLinPartials; ++k) red[k] = 0.0;
     if (u < g.W && v < g.H) {
         const long pi = pix_of(g, u, v);
-        double tau[6], R[9], t[3], L[28], eta[7];
+        double tau[6], q[4], R[9], t[3], L[28], eta[7];
         for (int k = 0; k < 6; ++k) tau[k] = cs->xi[k];
-        se3_exp(tau, R, t);
+        pose_exp(tau, q, t);
+        pose_rotation(q, R);
         const double ell = P.ell[pi];
-        // the photometric factor alone (zero prior weight); the log-depth prior
-        // is added here, the pose prior once per solve
-        Strengths sp = s;
-        sp.lamP = 0.0;
-        const bool val = unary_factors(g, sp, in, u, v, tau, R, t, ell, L, eta);
+        // the photometric factor alone; the log-depth prior is added here, the
+        // pose prior once per solve
+        for (int k = 0; k < 28; ++k) L[k] = 0.0;
+        for (int k = 0; k < 7; ++k) eta[k] = 0.0;
+        const Photo f = photometric(g, s, in, u, v, R, t, ell, load_pixel_inputs(g, s, in, u, v));
+        add_photometric(f, L, eta);
+        const bool val = f.valid;
         double diag = L[s7(6, 6)] + s.lamP, gl = eta[6] - s.lamP * (ell - s.prior_ell);
         if (s.lamN > 0.0) {
             for (int d = 0; d < 4; ++d) {
@@ -689,6 +692,8 @@ Geo cgeo(const pixvod_central* c) {
     g.fy = c->K.fy;
     g.cx = c->K.cx;
     g.cy = c->K.cy;
+    g.ifx = 1.0 / g.fx;
+    g.ify = 1.0 / g.fy;
     return g;
 }
 

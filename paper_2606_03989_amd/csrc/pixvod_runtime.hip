@@ -152,6 +152,8 @@ static Geo geo_of(const pixvod_ctx* c) {
     g.fy = c->K.fy;
     g.cx = c->K.cx;
     g.cy = c->K.cy;
+    g.ifx = 1.0 / g.fx;
+    g.ify = 1.0 / g.fy;
     return g;
 }
 
@@ -184,6 +186,26 @@ static bool finite_params(const pixvod_params* p) {
            p->init_inv_depth > 0 && p->damping >= 0 && p->damping < 1 && p->kf_max_frames >= 1;
 }
 
+// the prior pose mean in the two forms that the kernels take: the inverse as a
+// matrix and the pose itself as a quaternion and a translation
+static void set_prior_pose(Strengths& s, const double xi[6]) {
+    double T[16], Ti[16];
+    host_se3_exp(xi, T);
+    host_se3_inverse(T, Ti);
+    bool ident = true;
+    for (int k = 0; k < 6; ++k) ident = ident && (xi[k] == 0.0);
+    for (int r = 0; r < 3; ++r) {
+        for (int cc = 0; cc < 3; ++cc) s.prior_R[r * 3 + cc] = Ti[r * 4 + cc];
+        s.prior_t[r] = Ti[r * 4 + 3];
+        s.prior_p[r] = T[r * 4 + 3];
+    }
+    const double th = std::sqrt(xi[0] * xi[0] + xi[1] * xi[1] + xi[2] * xi[2]);
+    const double a = th > 1e-6 ? std::sin(0.5 * th) / th : 0.5 - th * th / 48.0;
+    for (int k = 0; k < 3; ++k) s.prior_q[k] = a * xi[k];
+    s.prior_q[3] = std::cos(0.5 * th);
+    s.prior_is_identity = ident ? 1 : 0;
+}
+
 Strengths pv::strengths_from(const pixvod_params& P, bool has_sigma_map) {
     Strengths s;
     std::memset(&s, 0, sizeof(s));
@@ -194,20 +216,9 @@ Strengths pv::strengths_from(const pixvod_params& P, bool has_sigma_map) {
     s.inv_sigD = 1.0 / (double)P.sigma_D;
     s.huber_k = P.huber_k;
     s.prior_ell = P.prior_log_depth;
-    bool ident = true;
     double xi[6];
-    for (int k = 0; k < 6; ++k) {
-        xi[k] = P.prior_xi[k];
-        ident = ident && (xi[k] == 0.0);
-    }
-    double T[16], Ti[16];
-    host_se3_exp(xi, T);
-    host_se3_inverse(T, Ti);
-    for (int r = 0; r < 3; ++r) {
-        for (int cc = 0; cc < 3; ++cc) s.prior_R[r * 3 + cc] = Ti[r * 4 + cc];
-        s.prior_t[r] = Ti[r * 4 + 3];
-    }
-    s.prior_is_identity = ident ? 1 : 0;
+    for (int k = 0; k < 6; ++k) xi[k] = P.prior_xi[k];
+    set_prior_pose(s, xi);
     s.has_sigma_map = has_sigma_map ? 1 : 0;
     return s;
 }
@@ -216,16 +227,7 @@ static Strengths strengths_of(const pixvod_ctx* c) {
     Strengths s = strengths_from(c->P, c->has_sigma);
     if (c->has_prior_pose) {
         // a prior pose mean set at run time (kept in double)
-        double T[16], Ti[16];
-        host_se3_exp(c->prior_xi, T);
-        host_se3_inverse(T, Ti);
-        bool ident = true;
-        for (int k = 0; k < 6; ++k) ident = ident && (c->prior_xi[k] == 0.0);
-        for (int r = 0; r < 3; ++r) {
-            for (int cc = 0; cc < 3; ++cc) s.prior_R[r * 3 + cc] = Ti[r * 4 + cc];
-            s.prior_t[r] = Ti[r * 4 + 3];
-        }
-        s.prior_is_identity = ident ? 1 : 0;
+        set_prior_pose(s, c->prior_xi);
     }
     s.has_prior_map = c->has_prior_map ? 1 : 0;
     return s;
@@ -1116,6 +1118,8 @@ static Geo geo_of_seq(const BatchSeq& q) {
     g.fy = q.K.fy;
     g.cx = q.K.cx;
     g.cy = q.K.cy;
+    g.ifx = 1.0 / g.fx;
+    g.ify = 1.0 / g.fy;
     return g;
 }
 

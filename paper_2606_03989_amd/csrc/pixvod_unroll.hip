@@ -91,6 +91,8 @@ static Geo ugeo(const pixvod_unroll* u) {
     g.fy = u->K.fy;
     g.cx = u->K.cx;
     g.cy = u->K.cy;
+    g.ifx = 1.0 / g.fx;
+    g.ify = 1.0 / g.fy;
     return g;
 }
 

@@ -1,0 +1,57 @@
+"""The fused pass at the edges of its row segments (64 pixels per wave, two
+waves per SIMD, message information in LDS) and its pose maps away from their
+series: one iteration from an identical FP32 state against the oracle, for both
+schedules. Tolerance: the parity rule of tests/parity.py (1e-5 of a plane's
+largest magnitude, or twice the oracle's own spread at FP32 storage)."""
+
+import numpy as np
+import pytest
+
+import synth
+from parity import check_iteration, from_oracle, iteration_spread, make_oracle, make_tracker, plane_errors, to_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(H, W, seed=3):
+    p = synth.tiny_pair(seed, H=H, W=W)
+    return dict(cam=p["cam"], I_s=p["I_s"], N_s=p["normals_s"], frames=[p["I_t"]], iters=8,
+                kw=dict(init_inv_depth=0.4, huber_k=10.0, sigma_P=0.1))
+
+
+def _one_iteration(w, schedule, label, setup=None):
+    frame = w["frames"][0]
+    o = make_oracle(w)
+    if setup is not None:
+        setup(o)
+    o.track(frame, 3)
+    s32 = from_oracle(o.get_state())
+    t = make_tracker(w, schedule)
+    if setup is not None:
+        setup(t)
+    t.track(frame, 0)
+    t.set_state(s32)
+    t.iterate(1)
+    o.set_state(to_oracle(s32))
+    o.set_frame(frame)
+    o.iterate(1)
+    err = plane_errors(t.get_state(), from_oracle(o.get_state()))
+    check_iteration(err, iteration_spread(w, s32, frame, setup=setup), label)
+
+
+@pytest.mark.parametrize("schedule", [0, 1])
+@pytest.mark.parametrize("shape", [(2, 63), (3, 64), (2, 65), (5, 128), (4, 129), (2, 193)])
+def test_row_segment_edges(shape, schedule):
+    _one_iteration(_workload(*shape), schedule, f"{shape}/{schedule}")
+
+
+@pytest.mark.parametrize("theta", [0.09, 0.2, 1.5, 3.0])
+def test_pose_maps_away_from_identity(theta):
+    """A prior pose turned by theta: the prior's residual, and the poses that it
+    pulls, leave the series around the identity."""
+    xi = np.array([0.6 * theta, -0.64 * theta, 0.48 * theta, 0.02, -0.01, 0.03])
+
+    def setup(x):
+        x.set_prior(xi)
+
+    _one_iteration(_workload(9, 70), 0, f"theta {theta}", setup)
