@@ -130,7 +130,8 @@ int pixvod_destroy(pixvod_ctx* ctx);
  * later work; NULL restores the context's own stream. */
 int pixvod_set_stream(pixvod_ctx* ctx, void* hip_stream);
 
-/* Selects PIXVOD_SCHED_FUSED (default) or PIXVOD_SCHED_PER_FACTOR.
+/* Selects PIXVOD_SCHED_FUSED (default) or PIXVOD_SCHED_PER_FACTOR. Damped
+ * iterations run as one kernel each under the latter.
  * PIXVOD_EINVAL for the fused schedule when params.damping != 0. */
 int pixvod_set_schedule(pixvod_ctx* ctx, int schedule);
 
@@ -249,7 +250,7 @@ enum {
     PIXVOD_PROF_FUSED_ITERATE = 0,    /* one fused iteration pass (not the last of a frame) */
     PIXVOD_PROF_FUSED_FINAL = 1,      /* the last fused pass of a frame */
     PIXVOD_PROF_FUSED_PROLOGUE = 2,   /* the per-frame prologue of the fused schedule */
-    PIXVOD_PROF_PER_FACTOR = 3,       /* one per-factor iteration (three kernels) */
+    PIXVOD_PROF_PER_FACTOR = 3,       /* one per-factor iteration (three kernels; one when damped) */
     PIXVOD_PROF_KINDS = 4
 };
 int pixvod_profile_enable(pixvod_ctx* ctx, int enable);

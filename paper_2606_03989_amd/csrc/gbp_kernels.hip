@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256) void k_pf_linearise(Geo g, Strengths s, Inputs
 // Lambda(21, already at storage precision), normal eta, normal lambda.
 __global__ __launch_bounds__(256, 2) void k_pf_messages(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                      const double* __restrict__ marg, double* __restrict__ M,
-                                                     float beta, int* __restrict__ health) {
+                                                     int* __restrict__ health) {
     const int u = blockIdx.x * blockDim.x + threadIdx.x;
     const int v = blockIdx.y * blockDim.y + threadIdx.y;
     if (u >= g.W || v >= g.H) return;
@@ -458,19 +458,6 @@ __global__ __launch_bounds__(256, 2) void k_pf_messages(Geo g, Strengths s, Inpu
                 const float fl = (float)lp, fh = (float)hn;
                 out[27] = fma(-(double)fl, rn, (double)fh);
                 out[28] = (double)fl;
-            }
-            if (beta != 0.0f) {
-                // damping towards the stored message; the blended Lambda is
-                // rounded to storage precision like every stored Lambda
-                const double b = beta, a = 1.0 - b;
-#pragma unroll
-                for (int k = 0; k < 6; ++k)
-                    out[k] = a * out[k] + b * X[(long)(P_MID + d * MID_STRIDE + k) * g.plane + pi];
-#pragma unroll
-                for (int k = 6; k < 27; ++k)
-                    out[k] = (double)(float)(a * out[k] + b * X[(long)(P_MID + d * MID_STRIDE + k) * g.plane + pi]);
-                out[27] = a * out[27] + b * X[(long)(P_MN + 2 * d) * g.plane + pi];
-                out[28] = (double)(float)(a * out[28] + b * X[(long)(P_MN + 2 * d + 1) * g.plane + pi]);
             }
         }
 #pragma unroll
@@ -826,6 +813,183 @@ __global__ __launch_bounds__(64, 2) void k_fu_tape(Geo g, Strengths s, Inputs in
     const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
     if (u >= g.W) return;
     iterate_pixel<FINAL, false, true>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, tape);
+}
+
+// ---------------------------------------------------------------------------
+// damped iterations
+//
+// A damped message mixes the new one with the one that the receiver holds, so
+// it cannot travel as a partial; the receiver computes it from the sender's
+// marginals (FP64 planes, as k_pf_linearise leaves them). One pass per
+// iteration: the pixel's four messages, its update and transport, and the
+// marginals of the new state for the next pass; state and marginals alternate
+// between two buffers. The per-factor kernels' arithmetic without their
+// message planes (928 bytes per pixel written and read back) and second
+// linearisation: 45 us per iteration at 320 x 240, where the three launches
+// took 87 us (72 with this pass's algebra). Bound by the latency of the four
+// senders' gathered loads: 1,200 waves on 1,024 SIMDs.
+template <bool FINAL>
+__global__ __launch_bounds__(64, 2) void k_damped_iterate(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
+                                                          const double* __restrict__ marg, float* __restrict__ Y,
+                                                          double* __restrict__ marg_next, float beta,
+                                                          float* __restrict__ var_ll, float* __restrict__ valid,
+                                                          int* __restrict__ health) {
+    __shared__ float buf[LDS_WAVE];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
+    const unsigned o = off_of(g, u, v);
+    bool has[4], act[4];
+    unsigned on[4];
+    float c[4], pt[7];
+    load_point_at(X, g, o, pt);
+    const PixelInputs pin = load_inputs_at(s, in, o);
+    edges_of(g, in, u, v, has, on, c);
+    active_edges(s, c, act);
+    double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
+    point_of(pt, tau, ell);
+    pose_exp(tau, q, t);
+    // the sum of the new messages first: the linearisation's registers come after
+    double Lm[28], em[7];
+#pragma unroll
+    for (int k = 0; k < 28; ++k) Lm[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) em[k] = 0.0;
+    bool ok = true;
+    Messages ms;
+    float* lds = buf + threadIdx.x;
+    ms.lds = lds;
+    const double b1 = (double)beta, a1 = 1.0 - b1;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        float lam[21];
+#pragma unroll
+        for (int k = 0; k < 21; ++k) lam[k] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) ms.eta[d][k] = 0.0f;
+        ms.mn[d][0] = ms.mn[d][1] = 0.0f;
+        if (has[d]) {
+            const int slot = opposite(d);
+            const unsigned oj = here(on[d]), oi = here(o);
+            float npt[7];
+            load_point_at(X, g, oj, npt);
+            // the sender's variable-to-factor message: its marginals less the
+            // message it holds from this factor
+            double V[21], vv[6], Lp[21], h[6], D, dv;
+            GDouble* mb = plane_of(const_cast<double*>(marg));
+            GFloat* xb = plane_of(X, (long)(P_MID + slot * MID_STRIDE + 6) * g.plane);
+#pragma unroll
+            for (int k = 0; k < 21; ++k) {
+                V[k] = *at(mb, oj) - (double)*at(xb, oj);
+                mb = next(g, mb);
+                xb = next(g, xb);
+            }
+            xb = plane_of(X, (long)(P_MID + slot * MID_STRIDE) * g.plane);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                vv[k] = *at(mb, oj) - (double)*at(xb, oj);
+                mb = next(g, mb);
+                xb = next(g, xb);
+            }
+            xb = plane_of(X, (long)(P_MN + 2 * slot) * g.plane);
+            D = *at(mb, oj) - (double)*at(next(g, xb), oj);
+            dv = *at(next(g, mb), oj) - (double)*at(xb, oj);
+            ok = identity_partial(s.lamR, V, vv, Lp, h) && ok;
+            float part[27];
+#pragma unroll
+            for (int k = 0; k < 27; ++k) part[k] = k < 6 ? (float)h[k] : (float)Lp[k - 6];
+            double tj[6], ellj, qj[4], trj[3], r[6], e[6];
+            point_of(npt, tj, ellj);
+            pose_exp(tj, qj, trj);
+            pose_between(qj, trj, q, t, r);
+            complete_eta(part, [&](int k) { return part[6 + k]; }, r, e);
+            double ne = 0.0;
+            float nl = 0.0f;
+            if (act[d]) {
+                double lp, hn;
+                normal_partial(s.lamN, D, dv, lp, hn);
+                nl = (float)lp;
+                ne = fma(-(double)nl, normal_residual_c(c[d], d, ell, ellj), (double)(float)hn);
+            }
+            // damping towards the stored message; the blended information is
+            // rounded to storage precision like every stored one
+            xb = plane_of(X, (long)(P_MID + d * MID_STRIDE) * g.plane);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                e[k] = fma(a1, e[k], b1 * (double)*at(xb, oi));
+                xb = next(g, xb);
+                em[k] += e[k];
+                ms.eta[d][k] = (float)e[k];
+            }
+#pragma unroll
+            for (int k = 0; k < 21; ++k) {
+                lam[k] = (float)fma(a1, (double)part[6 + k], b1 * (double)*at(xb, oi));
+                xb = next(g, xb);
+            }
+            xb = plane_of(X, (long)(P_MN + 2 * d) * g.plane);
+            ne = fma(a1, ne, b1 * (double)*at(xb, oi));
+            nl = (float)fma(a1, (double)nl, b1 * (double)*at(next(g, xb), oi));
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int k = i; k < 6; ++k) Lm[s7(i, k)] += (double)lam[s6(i, k)];
+            em[6] += ne;
+            Lm[s7(6, 6)] += (double)nl;
+            ms.mn[d][0] = (float)ne;
+            ms.mn[d][1] = nl;
+        }
+#pragma unroll
+        for (int k = 0; k < 21; ++k) {
+            if (d < LDS_DIRS) lds[(d * 21 + k) * 64] = lam[k];
+            else ms.lam3[k] = lam[k];
+        }
+        // kept as FP32 (and not as the FP64 values that its readers convert to)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(ms.eta[d][k]));
+        asm volatile("" : "+v"(ms.mn[d][0]), "+v"(ms.mn[d][1]));
+        if (d == 3)
+#pragma unroll
+            for (int k = 0; k < 21; ++k) asm volatile("" : "+v"(ms.lam3[k]));
+        reread_lds();
+    }
+    pose_rotation(q, R);
+    const bool val = unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
+#pragma unroll
+    for (int k = 0; k < 28; ++k) L[k] += Lm[k];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) eta[k] += em[k];
+    double m[7], var;
+    ok = ldl7_solve(L, eta, m, var) && ok;
+    pose_retract(q, t, m, tau);
+    ell += m[6];
+    round_point(tau, ell);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) transport_message(ms, d, m);
+    reread_lds();
+    if constexpr (FINAL) {
+        *at((GFloat*)var_ll, o) = (float)var;
+        *at((GFloat*)valid, o) = val ? 1.0f : 0.0f;
+    } else {
+        pose_exp(tau, q, t);
+        pose_rotation(q, R);
+        unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) add_message(L, eta, ms, d);
+        double D, dv, P[21], pm[6], l66 = L[s7(6, 6)];
+        ok = depth_marginal(L, eta, D, dv) && ok;
+        asm volatile("" : "+v"(l66), "+v"(D), "+v"(dv));
+        pose_marginal(L, eta, l66, P, pm);
+        GDouble* mb = plane_of(marg_next);
+        const unsigned oh = here(o);
+#pragma unroll
+        for (int k = 0; k < 29; ++k) {
+            *at(mb, oh) = k < 21 ? P[k] : k < 27 ? pm[k - 21] : k == 27 ? D : dv;
+            mb = next(g, mb);
+        }
+    }
+    const bool all[4] = {true, true, true, true};
+    store_point(Y, g, o, tau, ell);
+    store_messages(Y, g, o, ms, all);
+    if (!ok) atomicOr(health, 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1233,10 +1397,26 @@ hipError_t launch_init_state(const Geo& g, float* X, float ell0, hipStream_t st)
     return hipGetLastError();
 }
 
+hipError_t launch_damped(const Geo& g, const Strengths& s, const Inputs& in, float* const X[2], int cur,
+                         double* const marg[2], int n_iters, float beta, float* var_ll, float* valid, int* health,
+                         hipStream_t st) {
+    if (n_iters < 1) return hipSuccess;
+    hipLaunchKernelGGL(k_pf_linearise, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X[cur], marg[0], valid, health);
+    for (int it = 0; it < n_iters; ++it, cur ^= 1) {
+        if (it + 1 < n_iters)
+            hipLaunchKernelGGL(k_damped_iterate<false>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X[cur],
+                               marg[it & 1], X[cur ^ 1], marg[(it & 1) ^ 1], beta, var_ll, valid, health);
+        else
+            hipLaunchKernelGGL(k_damped_iterate<true>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X[cur],
+                               marg[it & 1], X[cur ^ 1], marg[(it & 1) ^ 1], beta, var_ll, valid, health);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_pf_iteration(const Geo& g, const Strengths& s, const Inputs& in, float* X, double* marg,
-                               double* M, float* var_ll, float* valid, float beta, int* health, hipStream_t st) {
+                               double* M, float* var_ll, float* valid, int* health, hipStream_t st) {
     hipLaunchKernelGGL(k_pf_linearise, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, marg, valid, health);
-    hipLaunchKernelGGL(k_pf_messages, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, marg, M, beta, health);
+    hipLaunchKernelGGL(k_pf_messages, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, marg, M, health);
     hipLaunchKernelGGL(k_pf_update, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, M, var_ll, valid, health);
     return hipGetLastError();
 }

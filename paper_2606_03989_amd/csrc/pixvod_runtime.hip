@@ -684,13 +684,21 @@ static int run_iterations(pixvod_ctx* c, int n) {
             if (rc) return rc;
         }
         if (!c->msg) {
-            int rc = dev_alloc(c, &c->msg, pl * 116);
+            // the messages, or (damped) the second copy of the marginals
+            int rc = dev_alloc(c, &c->msg, pl * (c->P.damping != 0.0f ? 29 : 116));
             if (rc) return rc;
         }
         hipEvent_t a = prof_begin(c);
-        for (int it = 0; it < n; ++it)
-            HIP_TRY(c, launch_pf_iteration(g, s, in, c->X[c->cur], c->marg, c->msg, c->var_ll, c->valid,
-                                           c->P.damping, c->health, c->stream));
+        if (c->P.damping != 0.0f) {
+            double* marg[2] = {c->marg, c->msg};
+            HIP_TRY(c, launch_damped(g, s, in, c->X, c->cur, marg, n, c->P.damping, c->var_ll, c->valid, c->health,
+                                     c->stream));
+            c->cur ^= n & 1;
+        } else {
+            for (int it = 0; it < n; ++it)
+                HIP_TRY(c, launch_pf_iteration(g, s, in, c->X[c->cur], c->marg, c->msg, c->var_ll, c->valid,
+                                               c->health, c->stream));
+        }
         prof_end(c, a, PIXVOD_PROF_PER_FACTOR, n);
     } else {
         int src = c->cur, dst = 1 - c->cur;

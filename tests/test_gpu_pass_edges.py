@@ -55,3 +55,27 @@ def test_pose_maps_away_from_identity(theta):
         x.set_prior(xi)
 
     _one_iteration(_workload(9, 70), 0, f"theta {theta}", setup)
+
+
+@pytest.mark.parametrize("shape", [(2, 2), (2, 63), (3, 65), (4, 129)])
+def test_damped_row_segment_edges(shape):
+    w = _workload(*shape)
+    w["kw"]["damping"] = 0.3
+    _one_iteration(w, 1, f"damped {shape}")
+
+
+@pytest.mark.parametrize("damping", [0.0, 0.3])
+@pytest.mark.parametrize("n", [2, 5])
+def test_one_call_equals_single_iterations(n, damping):
+    """n iterations in one call (rotated passes) leave the state of n calls of
+    one iteration (final passes only), bit for bit."""
+    w = _workload(5, 70)
+    w["kw"]["damping"] = damping
+    states = []
+    for calls, iters in ((1, n), (n, 1)):
+        t = make_tracker(w, 1 if damping else 0)
+        t.track(w["frames"][0], 2)
+        for _ in range(calls):
+            t.iterate(iters)
+        states.append(t.get_state())
+    np.testing.assert_array_equal(states[0], states[1])
