@@ -13,6 +13,7 @@
 //               the last pass writes the canonical messages back.
 #include "gbp_kernels.h"
 #include "gbp_device.hpp"
+#include "gbp_planes.hpp"
 
 #include <hip/hip_cooperative_groups.h>
 
@@ -42,45 +43,6 @@ struct Messages {
 
     __device__ inline float lam(int d, int k) const { return d < LDS_DIRS ? lds[(d * 21 + k) * 64] : lam3[k]; }
 };
-
-// Plane access of the fused passes: the plane's base is uniform (scalar
-// registers and scalar arithmetic), the pixel a 32-bit byte offset, and a
-// neighbour's slot the same offset from a base moved by one element or one
-// row. (H * pitch is at most 2^28 elements.) A base runs through consecutive
-// planes and is opaque to the compiler at each, which otherwise forms 64-bit
-// addresses per lane (about 300 vector instructions more per pass).
-__device__ inline unsigned off_of(const Geo& g, int u, int v) { return (unsigned)((v * g.pitch + u) * 4); }
-__device__ inline long step_of(const Geo& g, int d) {
-    return d == DIR_L ? -1 : d == DIR_R ? 1 : d == DIR_U ? -(long)g.pitch : (long)g.pitch;
-}
-typedef __attribute__((address_space(1))) float GFloat;
-typedef __attribute__((address_space(1))) double GDouble;
-typedef __attribute__((address_space(1))) char GByte;
-
-template <class T>
-__device__ inline T* opaque(T* base) {
-    asm("" : "+s"(base));
-    return base;
-}
-__device__ inline GFloat* plane_of(const float* base, long elements) {
-    return opaque((GFloat*)const_cast<float*>(base + elements));
-}
-__device__ inline GDouble* plane_of(double* base) { return opaque((GDouble*)base); }
-// the pixel's offset for the accesses of one block of code: its widening to 64
-// bits has to be visible there for the access to take base and offset apart
-__device__ inline unsigned here(unsigned o) {
-    asm("" : "+v"(o));
-    return o;
-}
-// a pixel's element of a plane
-__device__ inline GFloat* at(GFloat* base, unsigned o) { return (GFloat*)((GByte*)base + o); }
-__device__ inline GDouble* at(GDouble* base, unsigned o) { return (GDouble*)((GByte*)base + 2UL * o); }
-__device__ inline float ld(const float* base, unsigned o) { return *at((GFloat*)const_cast<float*>(base), o); }
-// the base of the next plane
-template <class T>
-__device__ inline T* next(const Geo& g, T* base) {
-    return opaque(base + g.plane);
-}
 
 // issues the loads of a pixel's stored messages (or partials in flight) but
 // the information of direction 3. buf: the wave's LDS planes, lane: the lane
@@ -129,43 +91,6 @@ __device__ inline void load_lam3(const float* X, const Geo& g, unsigned o, Messa
     }
 }
 
-__device__ inline void load_point_at(const float* X, const Geo& g, unsigned o, float pt[7]) {
-    GFloat* b = plane_of(X, 0);
-    o = here(o);
-#pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        pt[k] = *at(b, o);
-        b = next(g, b);
-    }
-}
-
-// load_pixel_inputs without branches: a map that is not bound is read from the
-// keyframe image and not used
-__device__ inline PixelInputs load_inputs_at(const Strengths& s, const Inputs& in, unsigned o) {
-    PixelInputs r;
-    r.Is = ld(in.Is, o);
-    r.sigD = ld(s.has_sigma_map ? in.sigD : in.Is, o);
-    r.prior_ell = ld(s.has_prior_map ? in.prior_ell : in.Is, o);
-    return r;
-}
-
-__device__ inline void point_of(const float pt[7], double tau[6], double& ell) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) tau[k] = (double)pt[k];
-    ell = (double)pt[6];
-}
-
-// wait for this wave's loads into LDS: the compiler does not track them, so
-// the wait is explicit, and the memory clobber keeps the LDS reads after it
-__device__ inline void wait_lds_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// the information matrices are read from LDS again after this point instead of
-// being kept in registers from their previous use
-__device__ inline void reread_lds() { asm volatile("" ::: "memory"); }
-
-// wait for this wave's LDS reads, before its planes are loaded again
-__device__ inline void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
 // B += a stored message (embedded: identity -> pose block, normal -> depth entry)
 __device__ inline void add_message(double L[28], double eta[7], const Messages& m, int d) {
 #pragma unroll
@@ -196,27 +121,6 @@ __device__ inline void transport_message(Messages& ms, int d, const double m[7])
     ms.mn[d][0] = (float)fma(-(double)ms.mn[d][1], m[6], (double)ms.mn[d][0]);
 }
 
-// receiver side: eta = h - Lambda' r of an identity partial (h, Lambda')
-template <class Lam>
-__device__ inline void complete_eta(const float h[6], Lam lam, const double r[6], double e[6]) {
-#pragma unroll
-    for (int a = 0; a < 6; ++a) e[a] = (double)h[a];
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int c = i; c < 6; ++c) {
-            const double l = (double)lam(s6(i, c));
-            e[i] = fma(-l, r[c], e[i]);
-            if (i != c) e[c] = fma(-l, r[i], e[c]);
-        }
-}
-
-// normal_residual of an active edge with a preloaded target c of the left/upper pixel
-__device__ inline double normal_residual_c(float c, int d, double ell_i, double ell_j) {
-    const bool recv_is_b = (d == DIR_L || d == DIR_U);
-    return recv_is_b ? (ell_i - ell_j + (double)c) : (ell_i - ell_j - (double)c);
-}
-
 // per-lane tape of the reverse sweep's recompute
 struct Tape {
     float* lam;          // information of the new messages (88 FP32 planes: 21 + 1 per slot)
@@ -238,15 +142,6 @@ __device__ inline void tape_marginals(double* marg, const Geo& g, unsigned o, co
         __builtin_nontemporal_store(x, at(b, o));
         b = next(g, b);
     }
-}
-
-// one float of state; NT: a non-temporal store (streamed past the caches),
-// for passes whose output is not read again while it could stay cached: the
-// batch's passes over many sequences and a frame's final pass
-template <bool NT = false>
-__device__ inline void put(GFloat* a, float v) {
-    if constexpr (NT) __builtin_nontemporal_store(v, a);
-    else *a = v;
 }
 
 template <bool NT = false>
@@ -571,28 +466,6 @@ __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned 
         }
     }
     return ok;
-}
-
-// the pixel's neighbours: whether there is one, its offset (a missing
-// neighbour's is the pixel's own), and the normal targets of the edges
-__device__ inline void edges_of(const Geo& g, const Inputs& in, int u, int v, bool has[4], unsigned on[4], float c[4]) {
-    const unsigned o = off_of(g, u, v);
-    has[DIR_L] = u > 0;
-    has[DIR_R] = u + 1 < g.W;
-    has[DIR_U] = v > 0;
-    has[DIR_D] = v + 1 < g.H;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) on[d] = has[d] ? o + (unsigned)(4 * step_of(g, d)) : o;
-    c[DIR_L] = ld(in.cxt, on[DIR_L]);
-    c[DIR_R] = ld(in.cxt, o);
-    c[DIR_U] = ld(in.cyt, on[DIR_U]);
-    c[DIR_D] = ld(in.cyt, o);
-}
-
-// which edges' normal-integration factors are active
-__device__ inline void active_edges(const Strengths& s, const float c[4], bool act[4]) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) act[d] = isfinite(c[d]) && s.lamN > 0.0;
 }
 
 // prologue of one pixel: belief of the canonical state and the first partials

@@ -6,8 +6,10 @@
 // factor into a partial message (independent of the receiver's linearisation
 // point); the receiver completes it with the factor residual at both points,
 // updates and relinearises its variable, then sends its next partials. Each
-// iteration is two launches over the same buffers, one lane per pixel and one
-// lane per node (all levels in one launch, each workgroup inside one level).
+// iteration is one launch over the same buffers: the first workgroups take the
+// nodes (one lane per node, all levels, each workgroup inside one level), the
+// others the pixels (one lane per pixel, 64 of a row). Both read only what the
+// previous iteration wrote.
 //
 // Where partials live: a variable's partial towards its parent, and a node's
 // partials towards its children, stay in the sender's own slots (coalesced
@@ -17,6 +19,7 @@
 // messages, each stored at the variable that receives it.
 #include "gbp_tree.h"
 #include "gbp_device.hpp"
+#include "gbp_planes.hpp"
 
 #include <cmath>
 
@@ -24,73 +27,60 @@ namespace pv {
 
 namespace {
 
-__device__ inline void load_part27(const float* __restrict__ base, long stride, long p, float part[27]) {
-#pragma unroll
-    for (int k = 0; k < 27; ++k) part[k] = base[(long)k * stride + p];
-}
-
-__device__ inline void store_msg27(float* __restrict__ base, long stride, long p, const float m[27]) {
-#pragma unroll
-    for (int k = 0; k < 27; ++k) base[(long)k * stride + p] = m[k];
-}
-
 // receiver-side completion of an identity partial (h, Lambda') with the
 // residual r seen by the receiver: eta = h - Lambda' r; the message is added
-// to the pose block of the belief and kept at storage precision
-template <int LD>
-__device__ inline void complete_identity(const float part[27], const double r[6], double* L, double* eta,
-                                         float msg[27]) {
+// to the pose block of the belief and its eta kept at storage precision
+template <int LD, class Lam>
+__device__ inline void complete_identity(float msg_eta[6], Lam lam, const double r[6], double* L, double* eta) {
+    double e[6];
+    complete_eta(msg_eta, lam, r, e);
 #pragma unroll
     for (int a = 0; a < 6; ++a) {
-        double e = (double)part[a];
-#pragma unroll
-        for (int b = 0; b < 6; ++b) e -= (double)part[6 + s6(a, b)] * r[b];
-        eta[a] += e;
-        msg[a] = (float)e;
+        eta[a] += e[a];
+        msg_eta[a] = (float)e[a];
     }
 #pragma unroll
-    for (int r_ = 0; r_ < 6; ++r_)
+    for (int i = 0; i < 6; ++i)
 #pragma unroll
-        for (int c = r_; c < 6; ++c) L[LD == 7 ? s7(r_, c) : s6(r_, c)] += (double)part[6 + s6(r_, c)];
-#pragma unroll
-    for (int k = 0; k < 21; ++k) msg[6 + k] = part[6 + k];
+        for (int c = i; c < 6; ++c) L[LD == 7 ? s7(i, c) : s6(i, c)] += (double)lam(s6(i, c));
 }
 
-template <int LD>
-__device__ inline void add_identity(const float m[27], double* L, double* eta) {
+template <int LD, class Lam>
+__device__ inline void add_identity(const float msg_eta[6], Lam lam, double* L, double* eta) {
 #pragma unroll
-    for (int a = 0; a < 6; ++a) eta[a] += (double)m[a];
+    for (int a = 0; a < 6; ++a) eta[a] += (double)msg_eta[a];
 #pragma unroll
     for (int r = 0; r < 6; ++r)
 #pragma unroll
-        for (int c = r; c < 6; ++c) L[LD == 7 ? s7(r, c) : s6(r, c)] += (double)m[6 + s6(r, c)];
+        for (int c = r; c < 6; ++c) L[LD == 7 ? s7(r, c) : s6(r, c)] += (double)lam(s6(r, c));
 }
 
 // first-order transport of a stored identity message by the mean step m
-__device__ inline void transport_identity(float msg[27], const double m[6]) {
+template <class Lam>
+__device__ inline void transport_identity(float msg_eta[6], Lam lam, const double m[6]) {
+    double e[6];
+    complete_eta(msg_eta, lam, m, e);
 #pragma unroll
-    for (int a = 0; a < 6; ++a) {
-        double s = (double)msg[a];
-#pragma unroll
-        for (int b = 0; b < 6; ++b) s -= (double)msg[6 + s6(a, b)] * m[b];
-        msg[a] = (float)s;
-    }
+    for (int a = 0; a < 6; ++a) msg_eta[a] = (float)e[a];
 }
 
 // sender-side partial of an identity factor from the sender's pose marginal
-// (P, p) minus the factor's stored message to the sender
-__device__ inline bool identity_partial_from(double lamR, const double P[21], const double p[6], const float back[27],
-                                             float part[27]) {
+// (P, p) minus the factor's stored message to the sender, to 27 planes from b
+template <class Lam>
+__device__ inline bool send_identity(double lamR, const double P[21], const double p[6], const float back_eta[6],
+                                     Lam back_lam, GFloat* b, long stride, unsigned o) {
     double V[21], v[6], Lp[21], h[6];
 #pragma unroll
-    for (int k = 0; k < 21; ++k) V[k] = P[k] - (double)back[6 + k];
+    for (int k = 0; k < 21; ++k) V[k] = P[k] - (double)back_lam(k);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) v[k] = p[k] - (double)back[k];
+    for (int k = 0; k < 6; ++k) v[k] = p[k] - (double)back_eta[k];
     const bool ok = identity_partial(lamR, V, v, Lp, h);
+    o = here(o);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) part[k] = (float)h[k];
-#pragma unroll
-    for (int k = 0; k < 21; ++k) part[6 + k] = (float)Lp[k];
+    for (int k = 0; k < 27; ++k) {
+        put(at(b, o), k < 6 ? (float)h[k] : (float)Lp[k - 6]);
+        b = next(stride, b);
+    }
     return ok;
 }
 
@@ -149,288 +139,357 @@ __device__ inline void round6(double tau[6]) {
 // ---------------------------------------------------------------------------
 // pixels
 
+// a pixel's stored messages: of the edge to its parent (27 values) and of its
+// four normal-integration factors
+struct PixelMessages {
+    float eta[6], lam[21];
+    float mn[4][2];
+};
+
 // sender side of a pixel: partial towards the parent (own slot) and the
 // normal-integration partials (neighbours' slots) from the belief (L, eta)
-__device__ inline bool pixel_emit(const Geo& g, const Strengths& s, const Inputs& in, int u, int v,
-                                  const double L[28], const double eta[7], const float mup[27],
-                                  const float mn[4][2], float* __restrict__ Y) {
-    double P[21], p[6], D, dv;
-    pose_marginal(L, eta, L[s7(6, 6)], P, p);
+__device__ inline bool pixel_emit(const Geo& g, const Strengths& s, unsigned o, const bool has[4], const bool act[4],
+                                  const double L[28], const double eta[7], const PixelMessages& ms, float* Y) {
+    double P[21], p[6], D, dv, l66 = L[s7(6, 6)];
     bool ok = depth_marginal(L, eta, D, dv);
-    const long pi = pix_of(g, u, v);
-    float part[27];
-    ok = identity_partial_from(s.lamR, P, p, mup, part) && ok;
-    store_msg27(Y + (long)TP_UP * g.plane, g.plane, pi, part);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        int nu, nv;
-        if (!neighbour(g, u, v, d, nu, nv)) continue;
-        const long pj = pix_of(g, nu, nv);
-        float* dn = Y + (long)(TP_MN + 2 * opposite(d)) * g.plane + pj;
-        if (normal_active(g, in, pi, pj, d) && s.lamN > 0.0) {
-            double lp, hn;
-            normal_partial(s.lamN, D - (double)mn[d][1], dv - (double)mn[d][0], lp, hn);
-            dn[0] = (float)hn;
-            dn[g.plane] = (float)lp;
-        } else {
-            dn[0] = 0.0f;
-            dn[g.plane] = 0.0f;
-        }
+        if (!has[d]) continue;
+        GFloat* b = plane_of(Y, (long)(TP_MN + 2 * opposite(d)) * g.plane + step_of(g, d));
+        const unsigned oh = here(o);
+        double lp, hn;
+        normal_partial(s.lamN, D - (double)ms.mn[d][1], dv - (double)ms.mn[d][0], lp, hn);
+        put(at(b, oh), act[d] ? (float)hn : 0.0f);
+        put(at(next(g, b), oh), act[d] ? (float)lp : 0.0f);
     }
+    asm volatile("" : "+v"(l66), "+v"(D), "+v"(dv));
+    pose_marginal(L, eta, l66, P, p);
+    ok = send_identity(s.lamR, P, p, ms.eta, [&](int k) { return ms.lam[k]; }, plane_of(Y, (long)TP_UP * g.plane),
+                       g.plane, o) && ok;
     return ok;
 }
 
-__device__ inline void pixel_store_point(float* __restrict__ Y, const Geo& g, long p, const double tau[6], double ell) {
+__device__ inline void pixel_store_point(float* Y, const Geo& g, unsigned o, const double tau[6], double ell) {
+    GFloat* b = plane_of(Y, 0);
+    o = here(o);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) Y[(P_TAU + k) * g.plane + p] = (float)tau[k];
-    Y[P_ELL * g.plane + p] = (float)ell;
-}
-
-__global__ __launch_bounds__(256) void k_tr_pixel_prologue(Geo g, TreeGeo t, Strengths s, Inputs in,
-                                                           const float* __restrict__ X, float* __restrict__ Y,
-                                                           int* __restrict__ health) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y * blockDim.y + threadIdx.y;
-    if (u >= g.W || v >= g.H) return;
-    const long p = pix_of(g, u, v);
-    double tau[6], ell, q4[4], R[9], tt[3], L[28], eta[7];
-    load_point(X, g, p, tau, ell);
-    pose_exp(tau, q4, tt);
-    pose_rotation(q4, R);
-    unary_factors<true>(g, s, in, u, v, tau, q4, R, tt, ell, load_pixel_inputs(g, s, in, u, v), L, eta);
-    float mup[27], mn[4][2];
-    load_part27(X + (long)TP_UP * g.plane, g.plane, p, mup);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        mn[d][0] = X[(long)(TP_MN + 2 * d) * g.plane + p];
-        mn[d][1] = X[(long)(TP_MN + 2 * d + 1) * g.plane + p];
-        eta[6] += (double)mn[d][0];
-        L[s7(6, 6)] += (double)mn[d][1];
+    for (int k = 0; k < 7; ++k) {
+        put(at(b, o), k < 6 ? (float)tau[k] : (float)ell);
+        b = next(g, b);
     }
-    add_identity<7>(mup, L, eta);
-    const bool ok = pixel_emit(g, s, in, u, v, L, eta, mup, mn, Y);
-    pixel_store_point(Y, g, p, tau, ell);
-    if (!ok) atomicOr(health, 1);
 }
 
-template <bool FINAL>
-__global__ __launch_bounds__(256) void k_tr_pixel_iterate(Geo g, TreeGeo t, Strengths s, Inputs in,
-                                                          const float* __restrict__ X, const float* __restrict__ NX,
-                                                          float* __restrict__ Y, float* __restrict__ var_ll,
-                                                          float* __restrict__ valid, int* __restrict__ health) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y * blockDim.y + threadIdx.y;
-    if (u >= g.W || v >= g.H) return;
-    const long pi = pix_of(g, u, v);
+template <bool PROLOGUE, bool FINAL>
+__device__ __attribute__((always_inline)) inline void pixel_pass(const Geo& g, const TreeGeo& t, const Strengths& s,
+                                                                 const Inputs& in, const float* X, const float* NX,
+                                                                 float* Y, float* var_ll, float* valid, int* health,
+                                                                 int u, int v) {
+    const unsigned o = off_of(g, u, v);
+    bool has[4], act[4];
+    unsigned on[4];
+    float c[4], pt[7], ellj[4];
+    load_point_at(X, g, o, pt);
+    const PixelInputs pin = load_inputs_at(s, in, o);
+    edges_of(g, in, u, v, has, on, c);
+    active_edges(s, c, act);
+    PixelMessages ms;
+    // normal messages or partials; the parent edge's message (prologue) or the
+    // parent's partial for this child slot
+    const float* ub = PROLOGUE ? X + (long)TP_UP * g.plane : NX;
+    const long us = PROLOGUE ? g.plane : t.nplane;
+    const long pn = (long)t.off[1] + (long)(v >> 1) * t.Wl[1] + (u >> 1);
+    const long ul = PROLOGUE ? 0 : pn + (long)(TN_CH + 27 * (((v & 1) << 1) | (u & 1))) * t.nplane;
+    float tpf[6];
+    if constexpr (!PROLOGUE) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) ellj[d] = ld(X + (long)P_ELL * g.plane, on[d]);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) tpf[k] = NX[(long)(TN_TAU + k) * t.nplane + pn];
+    }
+    {
+        GFloat* b = plane_of(X, (long)TP_MN * g.plane);
+        const unsigned oh = here(o);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            ms.mn[d][0] = *at(b, oh);
+            b = next(g, b);
+            ms.mn[d][1] = *at(b, oh);
+            b = next(g, b);
+        }
+        const GFloat* q = PROLOGUE ? at((GFloat*)const_cast<float*>(ub), oh) : (GFloat*)const_cast<float*>(ub) + ul;
+#pragma unroll
+        for (int k = 0; k < 27; ++k) {
+            const float x = q[(long)k * us];
+            if (k < 6) ms.eta[k] = x;
+            else ms.lam[k - 6] = x;
+        }
+    }
+    const auto lam = [&](int k) { return ms.lam[k]; };
     double tau[6], ell, q4[4], R[9], tt[3], L[28], eta[7];
-    load_point(X, g, pi, tau, ell);
-    const PixelInputs pin = load_pixel_inputs(g, s, in, u, v);
+    point_of(pt, tau, ell);
     pose_exp(tau, q4, tt);
     pose_rotation(q4, R);
     const bool val = unary_factors<true>(g, s, in, u, v, tau, q4, R, tt, ell, pin, L, eta);
-
-    // the parent's partial for this child slot, completed at both points
-    float mup[27];
-    {
-        const long pn = (long)t.off[1] + (long)(v >> 1) * t.Wl[1] + (u >> 1);
-        const int q = ((v & 1) << 1) | (u & 1);
-        double tp[6], qp[4], trp[3], r[6];
+    bool ok = true;
+    if constexpr (!PROLOGUE) {
+        // the parent's partial, completed at both points
+        {
+            double tp[6], qp[4], trp[3], r[6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) tp[k] = (double)NX[(long)(TN_TAU + k) * t.nplane + pn];
-        pose_exp(tp, qp, trp);
-        pose_between(qp, trp, q4, tt, r);
-        float part[27];
-        load_part27(NX + (long)(TN_CH + 27 * q) * t.nplane, t.nplane, pn, part);
-        complete_identity<7>(part, r, L, eta, mup);
-    }
-    // normal-integration partials in this pixel's slots
-    float mn[4][2];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        mn[d][0] = mn[d][1] = 0.0f;
-        int nu, nv;
-        if (!neighbour(g, u, v, d, nu, nv)) continue;
-        const long pj = pix_of(g, nu, nv);
-        const double ellj = (double)X[(long)P_ELL * g.plane + pj];
-        double rn;
-        if (s.lamN > 0.0 && normal_residual(g, in, pi, pj, d, ell, ellj, rn)) {
-            const float* sn = X + (long)(TP_MN + 2 * d) * g.plane + pi;
-            const float nl = sn[g.plane];
-            const double ne = (double)sn[0] - (double)nl * rn;
-            eta[6] += ne;
-            L[s7(6, 6)] += (double)nl;
-            mn[d][0] = (float)ne;
-            mn[d][1] = nl;
+            for (int k = 0; k < 6; ++k) tp[k] = (double)tpf[k];
+            pose_exp(tp, qp, trp);
+            pose_between(qp, trp, q4, tt, r);
+            complete_identity<7>(ms.eta, lam, r, L, eta);
         }
-    }
-    // update: mean, relinearisation (Eq. var), transport of the stored messages
-    double m[7], var;
-    bool ok = ldl7_solve(L, eta, m, var);
-    pose_retract(q4, tt, m, tau);
-    ell += m[6];
-    transport_identity(mup, m);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) mn[d][0] = (float)((double)mn[d][0] - (double)mn[d][1] * m[6]);
-    round6(tau);
-    ell = (double)(float)ell;
-    pixel_store_point(Y, g, pi, tau, ell);
-    if (FINAL) {
-        store_msg27(Y + (long)TP_UP * g.plane, g.plane, pi, mup);
+        // normal-integration partials in this pixel's slots
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            Y[(long)(TP_MN + 2 * d) * g.plane + pi] = mn[d][0];
-            Y[(long)(TP_MN + 2 * d + 1) * g.plane + pi] = mn[d][1];
+            if (act[d] && has[d]) {
+                const double rn = normal_residual_c(c[d], d, ell, (double)ellj[d]);
+                const double ne = fma(-(double)ms.mn[d][1], rn, (double)ms.mn[d][0]);
+                eta[6] += ne;
+                L[s7(6, 6)] += (double)ms.mn[d][1];
+                ms.mn[d][0] = (float)ne;
+            } else {
+                ms.mn[d][0] = ms.mn[d][1] = 0.0f;
+            }
         }
-        var_ll[pi] = (float)var;
-        valid[pi] = val ? 1.0f : 0.0f;
-    } else {
+        // update: mean, relinearisation (Eq. var), transport of the stored messages
+        double m[7], var;
+        ok = ldl7_solve(L, eta, m, var);
+        pose_retract(q4, tt, m, tau);
+        ell += m[6];
+        transport_identity(ms.eta, lam, m);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) ms.mn[d][0] = (float)fma(-(double)ms.mn[d][1], m[6], (double)ms.mn[d][0]);
+        round6(tau);
+        ell = (double)(float)ell;
+        if constexpr (FINAL) {
+            pixel_store_point(Y, g, o, tau, ell);
+            GFloat* b = plane_of(Y, (long)TP_UP * g.plane);
+            const unsigned oh = here(o);
+#pragma unroll
+            for (int k = 0; k < 35; ++k) {   // TP_MN follows TP_UP
+                put(at(b, oh), k < 6 ? ms.eta[k] : k < 27 ? ms.lam[k - 6] : ms.mn[(k - 27) >> 1][(k - 27) & 1]);
+                b = next(g, b);
+            }
+            *at((GFloat*)var_ll, oh) = (float)var;
+            *at((GFloat*)valid, oh) = val ? 1.0f : 0.0f;
+            if (!ok) atomicOr(health, 1);
+            return;
+        }
         pose_exp(tau, q4, tt);
         pose_rotation(q4, R);
         unary_factors<true>(g, s, in, u, v, tau, q4, R, tt, ell, pin, L, eta);
-        add_identity<7>(mup, L, eta);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            eta[6] += (double)mn[d][0];
-            L[s7(6, 6)] += (double)mn[d][1];
-        }
-        ok = pixel_emit(g, s, in, u, v, L, eta, mup, mn, Y) && ok;
     }
+    add_identity<7>(ms.eta, lam, L, eta);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        eta[6] += (double)ms.mn[d][0];
+        L[s7(6, 6)] += (double)ms.mn[d][1];
+    }
+    pixel_store_point(Y, g, o, tau, ell);
+    ok = pixel_emit(g, s, o, has, act, L, eta, ms, Y) && ok;
     if (!ok) atomicOr(health, 1);
 }
 
 // ---------------------------------------------------------------------------
 // nodes
 
-// sender side of a node: partials towards its parent and its children, in
-// its own slots
-__device__ inline bool node_emit(const TreeGeo& t, const Level& lv, int x, int y, long n, const double L[21],
-                                 const double eta[6], const float msg[5][27], float* __restrict__ NY) {
-    bool ok = true;
-    float part[27];
-    if (lv.l < t.L) {
-        ok = identity_partial_from(lv.lamR_up, L, eta, msg[0], part) && ok;
-        store_msg27(NY + (long)TN_UP * t.nplane, t.nplane, n, part);
+// The messages of a node's five edges (0: parent, 1 .. 4: children). As in the
+// grid's pass, the information matrices of three of them stay in LDS, where
+// they are loaded without passing through registers, so that the node fits 256
+// registers and two waves share a SIMD.
+constexpr int NODE_LDS = 3 * 21 * 64;   // floats per wave: edges 1 .. 3
+
+struct NodeMessages {
+    float eta[5][6];
+    float lam0[21], lam4[21];
+    const float* lds;
+
+    __device__ inline float lam(int e, int k) const {
+        return e == 0 ? lam0[k] : e == 4 ? lam4[k] : lds[((e - 1) * 21 + k) * 64];
     }
+};
+
+template <bool PROLOGUE, bool FINAL>
+__device__ __attribute__((always_inline)) inline void node_pass(const Geo& g, const TreeGeo& t, const Strengths& s,
+                                                                const float* X, const float* NX, float* NY,
+                                                                int* health, float* buf) {
+    const Level lv = level_of_block(t, (int)blockIdx.x);
+    const int lane = (int)threadIdx.x;
+    const int i = ((int)blockIdx.x - lv.b0) * kTreeThreads + lane;
+    if (i >= lv.H * lv.W) return;
+    const int x = i % lv.W, y = i / lv.W;
+    const unsigned n = (unsigned)(lv.off + i);
+    const unsigned o = n * 4u;
+    // --- every load issued before any use: the node's pose, the parent's pose
+    // and its partial for this child slot, the children's poses and partials
+    // towards this node (the prologue: the node's own stored messages). A
+    // missing parent or child reads the node itself or the first child; its
+    // values are not used.
+    const bool has_par = lv.l < t.L;
+    bool has[5];
+    has[0] = has_par;
+    unsigned oc[4];   // byte offsets of the children in their planes
+    const bool pix = lv.l == 1;
+    const float* cb = pix ? X : NX;
+    const long cs = pix ? g.plane : t.nplane;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int cx = 2 * x + (q & 1), cy = 2 * y + (q >> 1);
-        if (cx >= lv.Wc || cy >= lv.Hc) continue;
-        ok = identity_partial_from(lv.lamR_down, L, eta, msg[1 + q], part) && ok;
-        store_msg27(NY + (long)(TN_CH + 27 * q) * t.nplane, t.nplane, n, part);
+        has[1 + q] = cx < lv.Wc && cy < lv.Hc;
+        const int cxc = has[1 + q] ? cx : 2 * x, cyc = has[1 + q] ? cy : 2 * y;
+        oc[q] = pix ? off_of(g, cxc, cyc) : (unsigned)(lv.offc + cyc * lv.Wc + cxc) * 4u;
     }
-    return ok;
-}
-
-template <bool PROLOGUE, bool FINAL>
-__global__ __launch_bounds__(kTreeThreads) void k_tr_node(Geo g, TreeGeo t, Strengths s,
-                                                          const float* __restrict__ X, const float* __restrict__ NX,
-                                                          float* __restrict__ NY, int* __restrict__ health) {
-    const Level lv = level_of_block(t, (int)blockIdx.x);
-    const int i = ((int)blockIdx.x - lv.b0) * kTreeThreads + (int)threadIdx.x;
-    if (i >= lv.H * lv.W) return;
-    const int x = i % lv.W, y = i / lv.W;
-    const long n = (long)lv.off + i;
-    double tau[6], q4[4], tt[3], L[21], eta[6];
-    float msg[5][27];
-    bool ok = true;
-    if (PROLOGUE) {
+    const unsigned op = has_par ? (unsigned)(lv.offp + (y >> 1) * lv.Wp + (x >> 1)) : n;
+    float tnf[6], tpf[6], tcf[4][6];
+    NodeMessages ms;
+    ms.lds = buf + lane;
+    {
+        GFloat* b = plane_of(NX, (long)TN_TAU * t.nplane);
+        const unsigned oh = here(o), oph = here(op * 4u);
 #pragma unroll
-        for (int k = 0; k < 6; ++k) tau[k] = (double)NX[(long)(TN_TAU + k) * t.nplane + n];
-        pose_exp(tau, q4, tt);
-        node_prior(s, lv.lamP, tau, q4, tt, L, eta);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            load_part27(NX + (long)(TN_UP + 27 * k) * t.nplane, t.nplane, n, msg[k]);
-            add_identity<6>(msg[k], L, eta);
+        for (int k = 0; k < 6; ++k) {
+            tnf[k] = *at(b, oh);
+            if constexpr (!PROLOGUE) tpf[k] = *at(b, oph);
+            b = next(t.nplane, b);
         }
-    } else {
-        // --- every load issued before any use (its address depends only on
-        // the node index): the node's pose, the parent's pose and its partial
-        // for this child slot, the children's poses and partials towards this
-        // node. A missing parent or child reads the node itself; its values
-        // are discarded.
-        float tnf[6], tpf[6], tcf[4][6];
-        const bool has_par = lv.l < t.L;
-        const long pp = has_par ? (long)lv.offp + (long)(y >> 1) * lv.Wp + (x >> 1) : n;
-        const int qn = ((y & 1) << 1) | (x & 1);
-        bool has_c[4];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) tnf[k] = NX[(long)(TN_TAU + k) * t.nplane + n];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) tpf[k] = NX[(long)(TN_TAU + k) * t.nplane + pp];
-        load_part27(NX + (long)(TN_CH + 27 * qn) * t.nplane, t.nplane, pp, msg[0]);
+    }
+    if constexpr (!PROLOGUE) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int cx = 2 * x + (q & 1), cy = 2 * y + (q >> 1);
-            has_c[q] = cx < lv.Wc && cy < lv.Hc;
-            const int cxc = has_c[q] ? cx : 2 * x, cyc = has_c[q] ? cy : 2 * y;
-            if (lv.l == 1) {
-                const long pc = pix_of(g, cxc, cyc);
+            GFloat* b = plane_of(cb, 0);   // the pose planes are the first of both
+            const unsigned oh = here(oc[q]);
 #pragma unroll
-                for (int k = 0; k < 6; ++k) tcf[q][k] = X[(long)(P_TAU + k) * g.plane + pc];
-                load_part27(X + (long)TP_UP * g.plane, g.plane, pc, msg[1 + q]);
-            } else {
-                const long nc = (long)lv.offc + (long)cyc * lv.Wc + cxc;
-#pragma unroll
-                for (int k = 0; k < 6; ++k) tcf[q][k] = NX[(long)(TN_TAU + k) * t.nplane + nc];
-                load_part27(NX + (long)TN_UP * t.nplane, t.nplane, nc, msg[1 + q]);
+            for (int k = 0; k < 6; ++k) {
+                tcf[q][k] = *at(b, oh);
+                b = next(cs, b);
             }
         }
+    }
+    {
+        // edge 0: own slot (prologue) or the parent's slot of this child
+        const int qn = ((y & 1) << 1) | (x & 1);
+        const GFloat* q = (GFloat*)const_cast<float*>(NX) +
+                          (PROLOGUE ? (long)TN_UP * t.nplane + n : (long)(TN_CH + 27 * qn) * t.nplane + op);
 #pragma unroll
-        for (int k = 0; k < 6; ++k) tau[k] = (double)tnf[k];
-        pose_exp(tau, q4, tt);
-        node_prior(s, lv.lamP, tau, q4, tt, L, eta);
-        // parent's partial for this child slot, completed in place
-        if (has_par) {
-            double tp[6], qp[4], trp[3], r[6];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) tp[k] = (double)tpf[k];
-            pose_exp(tp, qp, trp);
-            pose_between(qp, trp, q4, tt, r);
-            complete_identity<6>(msg[0], r, L, eta, msg[0]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 27; ++k) msg[0][k] = 0.0f;
+        for (int k = 0; k < 27; ++k) {
+            const float v = q[(long)k * t.nplane];
+            if (k < 6) ms.eta[0][k] = v;
+            else ms.lam0[k - 6] = v;
         }
-        // children's partials towards this node
+    }
+    static_assert(TN_UP == 6 && TP_UP == 7, "planes of the upward partials");
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (!has_c[q]) {
+    for (int e = 1; e < 5; ++e) {
+        GFloat* b = PROLOGUE ? plane_of(NX, (long)(TN_CH + 27 * (e - 1)) * t.nplane)
+                             : plane_of(cb, (pix ? (long)TP_UP : (long)TN_UP) * cs);
+        const long st = PROLOGUE ? t.nplane : cs;
+        const unsigned oh = here(PROLOGUE ? o : oc[e - 1]);
 #pragma unroll
-                for (int k = 0; k < 27; ++k) msg[1 + q][k] = 0.0f;
+        for (int k = 0; k < 27; ++k) {
+            if (k < 6) ms.eta[e][k] = *at(b, oh);
+            else if (e == 4) ms.lam4[k - 6] = *at(b, oh);
+            else
+                __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(b, oh),
+                                                 (__attribute__((address_space(3))) void*)(buf + ((e - 1) * 21 + k - 6) * 64),
+                                                 4, 0, 0);
+            b = next(st, b);
+        }
+    }
+    double tau[6], q4[4], tt[3], L[21], eta[6];
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) tau[k] = (double)tnf[k];
+    pose_exp(tau, q4, tt);
+    node_prior(s, lv.lamP, tau, q4, tt, L, eta);
+    wait_lds_loads();
+    if constexpr (!PROLOGUE) {
+#pragma unroll
+        for (int e = 0; e < 5; ++e) {
+            if (!has[e]) {
+#pragma unroll
+                for (int k = 0; k < 6; ++k) ms.eta[e][k] = 0.0f;
                 continue;
             }
-            double tc[6], qc[4], trc[3], r[6];
+            double tj[6], qj[4], trj[3], r[6];
 #pragma unroll
-            for (int k = 0; k < 6; ++k) tc[k] = (double)tcf[q][k];
-            pose_exp(tc, qc, trc);
-            pose_between(qc, trc, q4, tt, r);
-            complete_identity<6>(msg[1 + q], r, L, eta, msg[1 + q]);
+            for (int k = 0; k < 6; ++k) tj[k] = (double)(e == 0 ? tpf[k] : tcf[e == 0 ? 0 : e - 1][k]);
+            pose_exp(tj, qj, trj);
+            pose_between(qj, trj, q4, tt, r);
+            complete_identity<6>(ms.eta[e], [&](int k) { return ms.lam(e, k); }, r, L, eta);
         }
+        reread_lds();
         // update: mean, relinearisation, transport
         double m[6];
         ok = ldl6_solve(L, eta, m);
         pose_retract(q4, tt, m, tau);
 #pragma unroll
-        for (int k = 0; k < 5; ++k) transport_identity(msg[k], m);
+        for (int e = 0; e < 5; ++e)
+            if (has[e]) transport_identity(ms.eta[e], [&](int k) { return ms.lam(e, k); }, m);
         round6(tau);
-        if (FINAL) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) NY[(long)(TN_TAU + k) * t.nplane + n] = (float)tau[k];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) store_msg27(NY + (long)(TN_UP + 27 * k) * t.nplane, t.nplane, n, msg[k]);
-            if (!ok) atomicOr(health, 1);
-            return;
-        }
-        pose_exp(tau, q4, tt);
-        node_prior(s, lv.lamP, tau, q4, tt, L, eta);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) add_identity<6>(msg[k], L, eta);
+        reread_lds();
     }
+    {
+        GFloat* b = plane_of(NY, (long)TN_TAU * t.nplane);
+        const unsigned oh = here(o);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) NY[(long)(TN_TAU + k) * t.nplane + n] = (float)tau[k];
-    ok = node_emit(t, lv, x, y, n, L, eta, msg, NY) && ok;
+        for (int k = 0; k < 6; ++k) {
+            put(at(b, oh), (float)tau[k]);
+            b = next(t.nplane, b);
+        }
+    }
+    if constexpr (FINAL) {
+        GFloat* b = plane_of(NY, (long)TN_UP * t.nplane);
+        const unsigned oh = here(o);
+#pragma unroll
+        for (int e = 0; e < 5; ++e)   // TN_CH follows TN_UP
+#pragma unroll
+            for (int k = 0; k < 27; ++k) {
+                put(at(b, oh), k < 6 ? ms.eta[e][k] : has[e] ? ms.lam(e, k - 6) : 0.0f);
+                b = next(t.nplane, b);
+            }
+    } else {
+        if constexpr (!PROLOGUE) {
+            pose_exp(tau, q4, tt);
+            node_prior(s, lv.lamP, tau, q4, tt, L, eta);
+        }
+#pragma unroll
+        for (int e = 0; e < 5; ++e)
+            if (PROLOGUE || has[e]) add_identity<6>(ms.eta[e], [&](int k) { return ms.lam(e, k); }, L, eta);
+        // partials towards the parent and the children, in the node's own slots
+#pragma unroll
+        for (int e = 0; e < 5; ++e) {
+            if (!has[e]) continue;
+            reread_lds();
+            ok = send_identity(e == 0 ? lv.lamR_up : lv.lamR_down, L, eta, ms.eta[e],
+                               [&](int k) { return ms.lam(e, k); }, plane_of(NY, (long)(TN_UP + 27 * e) * t.nplane),
+                               t.nplane, o) && ok;
+        }
+    }
     if (!ok) atomicOr(health, 1);
+}
+
+// One iteration (or the prologue) of the whole tree: workgroups 0 .. nblocks - 1
+// take the nodes, the others the pixels, 64 of a row, tiles_x per row. The two
+// parts are independent within an iteration; in one launch the nodes' longer
+// waves start first and the pixels fill the SIMDs beside them.
+// 640 x 480: 64 us per iteration; 102 us as two launches (47 us of pixels, 55 us
+// of nodes at one wave per SIMD). The copy of its 238 MB at this card's
+// 4.74 TB/s takes 50 us.
+template <bool PROLOGUE, bool FINAL>
+__global__ __launch_bounds__(kTreeThreads, 2) void k_tr_pass(Geo g, TreeGeo t, Strengths s, Inputs in, const float* X,
+                                                             const float* NX, float* Y, float* NY, float* var_ll,
+                                                             float* valid, int* health, int tiles_x) {
+    __shared__ float buf[NODE_LDS];
+    if ((int)blockIdx.x < t.nblocks) {
+        node_pass<PROLOGUE, FINAL>(g, t, s, X, NX, NY, health, buf);
+        return;
+    }
+    const int b = (int)blockIdx.x - t.nblocks;
+    const int u = (b % tiles_x) * 64 + (int)threadIdx.x, v = b / tiles_x;
+    if (u < g.W) pixel_pass<PROLOGUE, FINAL>(g, t, s, in, X, NX, Y, var_ll, valid, health, u, v);
 }
 
 __global__ void k_tr_clear(float* __restrict__ p, long n) {
@@ -486,33 +545,24 @@ bool make_tree_geo(int H, int W, double sigma_P, double sigma_R, TreeGeo* t) {
     return true;
 }
 
-static const dim3 kTreeBlock(64, 4);
-static dim3 tree_grid2d(const Geo& g) {
-    return dim3((g.W + kTreeBlock.x - 1) / kTreeBlock.x, (g.H + kTreeBlock.y - 1) / kTreeBlock.y);
-}
-
 hipError_t launch_tree_prologue(const Geo& g, const TreeGeo& t, const Strengths& s, const Inputs& in,
                                 const float* X, const float* NX, float* Y, float* NY, int* health, hipStream_t st) {
-    hipLaunchKernelGGL(k_tr_pixel_prologue, tree_grid2d(g), kTreeBlock, 0, st, g, t, s, in, X, Y, health);
-    hipLaunchKernelGGL((k_tr_node<true, false>), dim3(t.nblocks), dim3(kTreeThreads), 0, st, g, t, s, X, NX, NY,
-                       health);
+    const int tx = (g.W + 63) / 64;
+    hipLaunchKernelGGL((k_tr_pass<true, false>), dim3(t.nblocks + tx * g.H), dim3(kTreeThreads), 0, st, g, t, s, in, X,
+                       NX, Y, NY, nullptr, nullptr, health, tx);
     return hipGetLastError();
 }
 
 hipError_t launch_tree_iterate(const Geo& g, const TreeGeo& t, const Strengths& s, const Inputs& in,
                                const float* X, const float* NX, float* Y, float* NY, bool final_pass,
                                float* var_ll, float* valid, int* health, hipStream_t st) {
-    if (final_pass) {
-        hipLaunchKernelGGL(k_tr_pixel_iterate<true>, tree_grid2d(g), kTreeBlock, 0, st, g, t, s, in, X, NX, Y, var_ll,
-                           valid, health);
-        hipLaunchKernelGGL((k_tr_node<false, true>), dim3(t.nblocks), dim3(kTreeThreads), 0, st, g, t, s, X, NX, NY,
-                           health);
-    } else {
-        hipLaunchKernelGGL(k_tr_pixel_iterate<false>, tree_grid2d(g), kTreeBlock, 0, st, g, t, s, in, X, NX, Y,
-                           var_ll, valid, health);
-        hipLaunchKernelGGL((k_tr_node<false, false>), dim3(t.nblocks), dim3(kTreeThreads), 0, st, g, t, s, X, NX, NY,
-                           health);
-    }
+    const int tx = (g.W + 63) / 64;
+    if (final_pass)
+        hipLaunchKernelGGL((k_tr_pass<false, true>), dim3(t.nblocks + tx * g.H), dim3(kTreeThreads), 0, st, g, t, s,
+                           in, X, NX, Y, NY, var_ll, valid, health, tx);
+    else
+        hipLaunchKernelGGL((k_tr_pass<false, false>), dim3(t.nblocks + tx * g.H), dim3(kTreeThreads), 0, st, g, t, s,
+                           in, X, NX, Y, NY, var_ll, valid, health, tx);
     return hipGetLastError();
 }
 

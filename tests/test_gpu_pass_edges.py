@@ -1,5 +1,5 @@
-"""The fused pass at the edges of its row segments (64 pixels per wave, two
-waves per SIMD, message information in LDS) and its pose maps away from their
+"""The passes at the edges of their row segments (64 pixels per wave, two
+waves per SIMD, message information in LDS) and the pose maps away from their
 series: one iteration from an identical FP32 state against the oracle, for both
 schedules. Tolerance: the parity rule of tests/parity.py (1e-5 of a plane's
 largest magnitude, or twice the oracle's own spread at FP32 storage)."""
@@ -8,7 +8,8 @@ import numpy as np
 import pytest
 
 import synth
-from parity import check_iteration, from_oracle, iteration_spread, make_oracle, make_tracker, plane_errors, to_oracle
+from parity import (check_iteration, from_oracle, iteration_spread, make_oracle, make_tracker, plane_errors,
+                    to_oracle, tree_from_oracle, tree_to_oracle)
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +80,33 @@ def test_one_call_equals_single_iterations(n, damping):
             t.iterate(iters)
         states.append(t.get_state())
     np.testing.assert_array_equal(states[0], states[1])
+
+
+@pytest.mark.parametrize("shape", [(2, 63), (3, 65), (18, 128), (33, 129), (130, 2)])
+def test_quadtree_workgroup_edges(shape):
+    """Quadtree: pixel row segments and node levels around multiples of 64,
+    levels with missing children; one iteration against the oracle, and one call
+    of three iterations equal to three calls of one."""
+    w = _workload(*shape)
+    frame = w["frames"][0]
+    o = make_oracle(w, 1)
+    o.track(frame, 3)
+    s32 = tree_from_oracle(o.get_state())
+    t = make_tracker(w, 0, topology=1)
+    t.track(frame, 0)
+    t.set_state(s32)
+    t.iterate(1)
+    o.set_state(tree_to_oracle(s32))
+    o.set_frame(frame)
+    o.iterate(1)
+    spread = iteration_spread(w, s32, frame, topology=1)
+    for part, g, r in zip(("pixels", "nodes"), t.get_state(), tree_from_oracle(o.get_state())):
+        check_iteration(plane_errors(g, r), spread[part], f"{shape} {part}")
+    states = []
+    for calls, iters in ((1, 3), (3, 1)):
+        t.set_state(s32)
+        for _ in range(calls):
+            t.iterate(iters)
+        states.append(t.get_state())
+    for a, b in zip(*states):
+        np.testing.assert_array_equal(a, b)
