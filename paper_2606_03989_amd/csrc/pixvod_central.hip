@@ -58,7 +58,7 @@ constexpr int kLinPartials = 29;   // A (21), g_xi (6), r.r, valid count
 constexpr int kCgPartials = 9;     // r.u, w.u, r.r, sum b_i u_i (6)
 constexpr int kCgThreads = 256;    // work-items per workgroup of the CG launches
 constexpr int kCgPx = 2;           // pixels per work-item and round in those launches
-constexpr int kCgMaxBlocks = 1024; // most workgroups of those launches (a multiple of 8)
+constexpr int kCgMaxBlocks = 768;  // most workgroups of those launches (a multiple of 8): three per CU
 constexpr int kCgChunk = 16;       // CG iterations launched between convergence checks
 
 // solver state in device memory
@@ -82,8 +82,8 @@ struct CgIter {
     int done, iters;
 };
 
-struct Planes {            // per-pixel FP64 planes (pitched)
-    double *ell, *diag, *b, *gl, *x, *p;
+struct Planes {            // per-pixel FP64 planes (pitched); idiag = 1 / D_ii
+    double *ell, *idiag, *b, *gl, *x, *p;
     double *r[2], *w[2], *s[2];   // read by neighbours: two alternating sets
 };
 
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void k_c_linearise(Geo g, Strengths s, In
                 }
             }
         }
-        P.diag[pi] = diag;
+        P.idiag[pi] = rcp_nr(diag);
         for (int k = 0; k < 6; ++k) P.b[(long)k * g.plane + pi] = L[s7(k, 6)];
         P.gl[pi] = gl;
         P.x[pi] = 0.0;
@@ -336,60 +336,153 @@ __global__ __launch_bounds__(kThreads) void k_c_lin_final(Strengths s, int nb, c
 // takes range (b mod 8) * (nbx / 8) + b / 8 (nbx, the grid, a multiple of 8):
 // workgroups are dealt to the eight XCDs in turn, so each XCD gets adjacent
 // ranges and finds most of their vertical neighbours in its own L2. Rounds
-// stride over the image when the grid is smaller than it. The first round's
-// own-pixel loads are issued before the scalar step, which does not depend on
-// them; the neighbours' (L1 and L2 hits: other work-items load them as their
-// own) after it.
+// stride over the image when the grid is smaller than it.
+//
+// Since D u = r, w = M u needs no diagonal: w = r - lamN sum u_j + b.u_pose,
+// and 1 / D_ii is kept instead of it. A pixel's horizontal neighbours are the
+// adjacent lanes (pixels of a range are consecutive), whose new u comes by a
+// lane exchange; the lanes at the ends of a wave and the vertical neighbours'
+// u are recomputed from their stored r, w, s.
 
 __device__ inline int cg_range(int b, int nbx) { return (b & 7) * (nbx >> 3) + (b >> 3); }
 
-struct CgPix {             // what an iteration needs of one pixel's own planes
-    int u, v, act;
-    double x, p, r, w, s, diag, b[6];
+struct CgPix {             // what an iteration needs of one pixel
+    int act;
+    long pi;
+    double x, p, r, w, s, idiag, b[6];
+    // r, w, s, 1 / D of the vertical neighbours and (first and last lane of a
+    // wave) of the left or right one
+    double nr[3], nw[3], ns[3], nd[3];
 };
 
 __device__ inline void cg_load(const Geo& g, const Planes& P, const unsigned char* __restrict__ act, int cur,
-                               bool first, int i, CgPix& a) {
-    a.u = i % g.W;
-    a.v = i / g.W;
-    const long pi = pix_of(g, a.u, a.v);
+                               bool first, int i, int N, CgPix& a) {
+    const int ic = i < N ? i : N - 1;
+    const int u = ic % g.W, v = ic / g.W;
+    const long pi = pix_of(g, u, v);
+    a.pi = pi;
     a.act = act[pi];
-    a.x = P.x[pi];
-    a.p = first ? 0.0 : P.p[pi];
     a.r = P.r[cur][pi];
     a.w = P.w[cur][pi];
     a.s = first ? 0.0 : P.s[cur][pi];
-    a.diag = P.diag[pi];
+    a.idiag = P.idiag[pi];
+    // a missing neighbour's loads read the pixel itself; its value is not used
+    const int lane = threadIdx.x & 63;
+    const long pj[3] = {v > 0 ? pi - g.pitch : pi, v + 1 < g.H ? pi + g.pitch : pi,
+                        lane == 0 ? (u > 0 ? pi - 1 : pi) : (u + 1 < g.W ? pi + 1 : pi)};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (k == 2 && lane != 0 && lane != 63) break;
+        a.nr[k] = P.r[cur][pj[k]];
+        a.nw[k] = P.w[cur][pj[k]];
+        a.ns[k] = first ? 0.0 : P.s[cur][pj[k]];
+        a.nd[k] = P.idiag[pj[k]];
+    }
+    a.x = P.x[pi];
+    a.p = first ? 0.0 : P.p[pi];
 #pragma unroll
     for (int k = 0; k < 6; ++k) a.b[k] = P.b[(long)k * g.plane + pi];
 }
 
-// one pixel's new residual and preconditioned residual from its stored r, w,
-// s (explicit FMAs, so that a pixel and its neighbours evaluate the same
-// expression bit for bit)
-__device__ inline double cg_new_r(double r, double w, double s_prev, double alpha, double beta, bool first,
-                                  double& s_new) {
-    s_new = first ? w : fma(beta, s_prev, w);
+// one pixel's new residual from its stored r, w, s (explicit FMAs, so that a
+// pixel and its neighbours evaluate the same expression bit for bit)
+__device__ inline double cg_new_r(double r, double w, double s_prev, double alpha, double beta, double& s_new) {
+    s_new = fma(beta, s_prev, w);
     return fma(-alpha, s_new, r);
 }
 
-// w = M u at one pixel: the diagonal, the active normal edges and the pose
-// column, with the partial sums of r.u, w.u, r.r and b_k u
-__device__ inline void cg_apply_pixel(double diag, const double b[6], const double un[4], int act, double lamN,
-                                      const double upose[6], double r, double u, double& w, double red[kCgPartials]) {
-    double q = diag * u;
+// the sums of kCgPartials values over the workgroup into column `block` of
+// part (kCgPartials rows of kCgMaxBlocks). The first eight are reduced
+// together: in three steps a lane keeps half of its values and takes the other
+// lane's part of that half, so that 16 lane exchanges do the work of 54.
+__device__ inline void cg_block_reduce(double v[kCgPartials], double* __restrict__ part, int block) {
+    static_assert(kCgPartials == 9, "eight sums and one");
+    __shared__ double sh[kCgThreads / 64][kCgPartials];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double h[8];
 #pragma unroll
-    for (int d = 0; d < 4; ++d)
-        if (act & (1 << d)) q -= lamN * un[d];
+    for (int k = 0; k < 8; ++k) h[k] = v[k];
+#pragma unroll
+    for (int n = 4, m = 32; n > 0; n >>= 1, m >>= 1) {
+        const bool up = lane & m;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const double give = up ? h[k] : h[n + k], keep = up ? h[n + k] : h[k];
+            h[k] = keep + __shfl_xor(give, m, 64);
+        }
+    }
+    double t8 = v[8];
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) t8 += __shfl_xor(t8, m, 64);
+#pragma unroll
+    for (int m = 4; m > 0; m >>= 1) h[0] += __shfl_xor(h[0], m, 64);
+    // lanes 8 j hold sum j (bit-reversed: the first step's bit is the top one)
+    if ((lane & 7) == 0) sh[w][lane >> 3] = h[0];
+    if (lane == 0) sh[w][8] = t8;
+    __syncthreads();
+    if (threadIdx.x < kCgPartials) {
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < kCgThreads / 64; ++j) t += sh[j][threadIdx.x];
+        part[(long)threadIdx.x * kCgMaxBlocks + block] = t;
+    }
+}
+
+// the totals over nb workgroups' records in one fixed order, wave w takes the
+// sums w and w + 4, the first wave the last one as well; tot is in LDS and
+// complete after the next barrier
+__device__ inline void cg_totals(const double* __restrict__ part, int nb, double* tot) {
+    static_assert(kCgThreads / 64 == 4 && kCgPartials == 9, "two sums per wave and one more");
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const double* row = part + (long)w * kCgMaxBlocks;
+    double t[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < kCgMaxBlocks / 64; ++j) {
+        const int b = lane + 64 * j;
+        if (b < nb) {
+            t[0] += row[b];
+            t[1] += row[4 * kCgMaxBlocks + b];
+            if (w == 0) t[2] += row[8 * kCgMaxBlocks + b];
+        }
+    }
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) t[k] += __shfl_xor(t[k], m, 64);
+    if (lane == 0) {
+        tot[w] = t[0];
+        tot[4 + w] = t[1];
+        if (w == 0) tot[8] = t[2];
+    }
+}
+
+// the new vectors, w = M u and the partial sums of one pixel; un: the
+// neighbours' new u, up the pose's
+__device__ inline void cg_apply_pixel(const double b[6], const double un[4], int act, double lamN,
+                                      const double upose[6], double r, double u, double& w, double red[kCgPartials]) {
+    double q = r;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) q = fma(-lamN, (act & (1 << d)) ? un[d] : 0.0, q);
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-        q += b[k] * upose[k];
-        red[3 + k] += b[k] * u;
+        q = fma(b[k], upose[k], q);
+        red[3 + k] = fma(b[k], u, red[3 + k]);
     }
     w = q;
-    red[0] += r * u;
-    red[1] += q * u;
-    red[2] += r * r;
+    red[0] = fma(r, u, red[0]);
+    red[1] = fma(q, u, red[1]);
+    red[2] = fma(r, r, red[2]);
+}
+
+// the four neighbours' u at a wave's pixels from the own u and the loaded
+// neighbours' (DIR_U, DIR_D, edge lane)
+__device__ inline void cg_neighbours(double u, const double uv[3], double un[4]) {
+    const int lane = threadIdx.x & 63;
+    const double l = __shfl_up(u, 1, 64), r = __shfl_down(u, 1, 64);
+    un[DIR_L] = lane == 0 ? uv[2] : l;
+    un[DIR_R] = lane == 63 ? uv[2] : r;
+    un[DIR_U] = uv[0];
+    un[DIR_D] = uv[1];
 }
 
 // CG start: u_0 = P^-1 r_0 and w_0 = M u_0 (planes of set 0), partial sums
@@ -417,30 +510,19 @@ __global__ __launch_bounds__(kCgThreads) void k_c_cg_init(Geo g, Strengths s, Pl
 #pragma unroll
         for (int j = 0; j < kCgPx; ++j) {
             const int i = rb * round + j * kCgThreads + threadIdx.x;
+            CgPix c;
+            cg_load(g, P, act, 0, true, i, N, c);
+            double uv[3], un[4], w;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) uv[k] = c.nr[k] * c.nd[k];
+            const double u = c.r * c.idiag;
+            cg_neighbours(u, uv, un);
             if (i >= N) continue;
-            const int u = i % g.W, v = i / g.W;
-            const long pi = pix_of(g, u, v);
-            const double r = P.r[0][pi], diag = P.diag[pi];
-            double b[6], un[4];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) b[k] = P.b[(long)k * g.plane + pi];
-            const int ea = s.lamN > 0.0 ? act[pi] : 0;
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                un[d] = 0.0;
-                if (ea & (1 << d)) {
-                    int nu, nv;
-                    neighbour(g, u, v, d, nu, nv);
-                    const long pj = pix_of(g, nu, nv);
-                    un[d] = P.r[0][pj] / P.diag[pj];
-                }
-            }
-            double w;
-            cg_apply_pixel(diag, b, un, ea, s.lamN, up, r, r / diag, w, red);
-            P.w[0][pi] = w;
+            cg_apply_pixel(c.b, un, s.lamN > 0.0 ? c.act : 0, s.lamN, up, c.r, u, w, red);
+            P.w[0][c.pi] = w;
         }
     }
-    block_reduce<kCgPartials, kCgThreads>(red, part_out);
+    cg_block_reduce(red, part_out, blockIdx.x);
 }
 
 // CG iteration k (planes of set cur in, set 1 - cur out): the scalar step
@@ -449,7 +531,13 @@ __global__ __launch_bounds__(kCgThreads) void k_c_cg_init(Geo g, Strengths s, Pl
 //   (k = 0: beta = 0, alpha = gamma / delta),
 // then p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s, u = P^-1 r,
 // w = M u and the partial sums for the next step. The scalar step runs on the
-// first work-item of each workgroup and reaches the others via LDS.
+// first wave of each workgroup, a lane per pose component, and reaches the
+// others via LDS. Every load of the launch (the previous partial sums, the pose block and its
+// inverse, the scalar record, the first round's pixels and neighbours) is
+// issued before the first wait: the launch is bound by its chain of latencies
+// (the waves wait on memory for 71% of their life), not by the 42 MB that it
+// moves at 640 x 480: 14.7 us per launch, 15.4 us with the scalar step in one
+// lane, its record loaded after the partial sums and 1 / D formed by division.
 __global__ __launch_bounds__(kCgThreads, 3) void k_c_cg_iter(Geo g, Strengths s, const CgState* __restrict__ cs,
                                                              Planes P, const unsigned char* __restrict__ act,
                                                              const CgIter* __restrict__ rin,
@@ -457,131 +545,137 @@ __global__ __launch_bounds__(kCgThreads, 3) void k_c_cg_iter(Geo g, Strengths s,
                                                              const double* __restrict__ part_in,
                                                              double* __restrict__ part_out, int cur, double tol2,
                                                              int first, int* __restrict__ done_flag) {
-    __shared__ double sh_u[6];
+    __shared__ double sh_tot[kCgPartials];
     __shared__ double sh_ab[2];
-    __shared__ int sh_done;
-    if (rin->done) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            *rout = *rin;
-            if (done_flag) *done_flag = 1;
-        }
-        return;
-    }
+    __shared__ double sh_A[42];     // the pose block and its inverse
+    __shared__ CgIter sh_st;
+    static_assert(sizeof(CgIter) % 8 == 0 && sizeof(CgIter) / 8 <= 64, "the record fits one wave");
+    static_assert(offsetof(CgState, Ainv) == offsetof(CgState, A) + 21 * sizeof(double), "A and its inverse");
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (wv == 1 && lane < 42) sh_A[lane] = cs->A[lane];
+    if (wv == 2 && lane < (int)(sizeof(CgIter) / 8))
+        reinterpret_cast<double*>(&sh_st)[lane] = reinterpret_cast<const double*>(rin)[lane];
+    cg_totals(part_in, gridDim.x, sh_tot);
     const int N = g.H * g.W;
     const int round = kCgThreads * kCgPx;
     int rb = cg_range(blockIdx.x, gridDim.x);
     CgPix a[kCgPx];
 #pragma unroll
-    for (int j = 0; j < kCgPx; ++j) {
-        const int i = rb * round + j * kCgThreads + threadIdx.x;
-        if (i < N) cg_load(g, P, act, cur, first != 0, i, a[j]);
-    }
-    double tot[kCgPartials];
-    final_sum<kCgPartials, kCgThreads>(part_in, gridDim.x, tot);
-    if (threadIdx.x == 0) {
-        CgIter st = *rin;
-        double w[6];
-        sym6_mul(cs->A, st.u, w);
-        for (int k = 0; k < 6; ++k) w[k] += tot[3 + k];
-        const double gamma = tot[0] + dot6(st.r, st.u);
-        const double delta = tot[1] + dot6(w, st.u);
-        const double rr = tot[2] + dot6(st.r, st.r);
-        if (!first) {
-            st.iters += 1;
-            if (rr <= tol2 * cs->rr0) st.done = 1;
+    for (int j = 0; j < kCgPx; ++j)
+        cg_load(g, P, act, cur, first != 0, rb * round + j * kCgThreads + tid, N, a[j]);
+    const double rr0 = cs->rr0;
+    __syncthreads();
+    if (wv == 0) {
+        // lane k < 6: component k of the pose's part (the other lanes repeat
+        // component 5 and add nothing)
+        CgIter& st = sh_st;
+        const int k = lane < 6 ? lane : 5;
+        const bool own = lane < 6;
+        const double u = st.u[k], r = st.r[k];
+        double w = sh_tot[3 + k];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) w = fma(sh_A[s6(k, c)], st.u[c], w);
+        double gamma = own ? r * u : 0.0, delta = own ? w * u : 0.0, rr = own ? r * r : 0.0;
+#pragma unroll
+        for (int m = 4; m > 0; m >>= 1) {
+            gamma += __shfl_xor(gamma, m, 64);
+            delta += __shfl_xor(delta, m, 64);
+            rr += __shfl_xor(rr, m, 64);
         }
-        st.rr = rr;
-        double alpha = 0.0, beta = 0.0;
-        if (!st.done) {
-            beta = first ? 0.0 : gamma / st.gamma;
-            alpha = first ? gamma / delta : gamma / (delta - beta * gamma / st.alpha);
-            for (int k = 0; k < 6; ++k) {
-                st.p[k] = first ? st.u[k] : fma(beta, st.p[k], st.u[k]);
-                st.s[k] = first ? w[k] : fma(beta, st.s[k], w[k]);
-                st.x[k] = fma(alpha, st.p[k], st.x[k]);
-                st.r[k] = fma(-alpha, st.s[k], st.r[k]);
+        gamma = __shfl(gamma, 0, 64) + sh_tot[0];
+        delta = __shfl(delta, 0, 64) + sh_tot[1];
+        rr = __shfl(rr, 0, 64) + sh_tot[2];
+        const int was = st.done, iters = st.iters;
+        const int done = (was || (!first && rr <= tol2 * rr0)) ? 1 : 0;
+        if (!done) {
+            const double beta = first ? 0.0 : gamma * rcp_nr(st.gamma);
+            const double alpha = first ? gamma * rcp_nr(delta) : gamma * rcp_nr(delta - beta * gamma * rcp_nr(st.alpha));
+            const double pk = fma(beta, st.p[k], u), sk = fma(beta, st.s[k], w);
+            const double rk = fma(-alpha, sk, r), xk = fma(alpha, pk, st.x[k]);
+            double un = 0.0;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) un = fma(sh_A[21 + s6(k, c)], __shfl(rk, c, 64), un);
+            __builtin_amdgcn_wave_barrier();   // every lane has read the record
+            if (own) {
+                st.p[k] = pk;
+                st.s[k] = sk;
+                st.x[k] = xk;
+                st.r[k] = rk;
+                st.u[k] = un;
             }
-            sym6_mul(cs->Ainv, st.r, st.u);
-            st.gamma = gamma;
-            st.alpha = alpha;
+            if (lane == 0) {
+                sh_ab[0] = alpha;
+                sh_ab[1] = beta;
+                st.gamma = gamma;
+                st.alpha = alpha;
+            }
         }
-        for (int k = 0; k < 6; ++k) sh_u[k] = st.u[k];
-        sh_ab[0] = alpha;
-        sh_ab[1] = beta;
-        sh_done = st.done;
-        if (blockIdx.x == 0) {
-            *rout = st;
-            if (done_flag) *done_flag = st.done;
+        if (lane == 0 && !was) {
+            st.rr = rr;
+            if (!first) st.iters = iters + 1;
+            st.done = done;
         }
     }
     __syncthreads();
-    if (sh_done) return;
+    const int done = sh_st.done;
+    if (blockIdx.x == 0 && wv == 1) {
+        if (lane < (int)(sizeof(CgIter) / 8))
+            reinterpret_cast<double*>(rout)[lane] = reinterpret_cast<const double*>(&sh_st)[lane];
+        if (lane == 0 && done_flag) *done_flag = done;
+    }
+    if (done) return;
     const double alpha = sh_ab[0], beta = sh_ab[1], lamN = s.lamN;
     const int nxt = 1 - cur;
     double up[6];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) up[k] = sh_u[k];
+    for (int k = 0; k < 6; ++k) up[k] = sh_st.u[k];
     double red[kCgPartials];
 #pragma unroll
     for (int k = 0; k < kCgPartials; ++k) red[k] = 0.0;
     while (true) {
 #pragma unroll
         for (int j = 0; j < kCgPx; ++j) {
-            const int i = rb * round + j * kCgThreads + threadIdx.x;
-            if (i >= N) continue;
+            const int i = rb * round + j * kCgThreads + tid;
             const CgPix& c = a[j];
-            const long pi = pix_of(g, c.u, c.v);
-            double un[4];
-            const int ea = lamN > 0.0 ? c.act : 0;
+            double uv[3], un[4], sj;
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                un[d] = 0.0;
-                if (ea & (1 << d)) {
-                    int nu, nv;
-                    neighbour(g, c.u, c.v, d, nu, nv);
-                    const long pj = pix_of(g, nu, nv);
-                    double sj;
-                    const double rj = cg_new_r(P.r[cur][pj], P.w[cur][pj], first ? 0.0 : P.s[cur][pj], alpha, beta,
-                                               first != 0, sj);
-                    un[d] = rj / P.diag[pj];
-                }
-            }
-            const double u_old = c.r / c.diag;
-            const double pn = first ? u_old : fma(beta, c.p, u_old);
-            double sv;
-            const double r = cg_new_r(c.r, c.w, c.s, alpha, beta, first != 0, sv);
-            double w;
-            cg_apply_pixel(c.diag, c.b, un, ea, lamN, up, r, r / c.diag, w, red);
-            P.x[pi] = fma(alpha, pn, c.x);
-            P.p[pi] = pn;
-            P.s[nxt][pi] = sv;
-            P.r[nxt][pi] = r;
-            P.w[nxt][pi] = w;
+            for (int k = 0; k < 3; ++k) uv[k] = cg_new_r(c.nr[k], c.nw[k], c.ns[k], alpha, beta, sj) * c.nd[k];
+            const double pn = fma(beta, c.p, c.r * c.idiag);
+            double sv, w;
+            const double r = cg_new_r(c.r, c.w, c.s, alpha, beta, sv);
+            const double u = r * c.idiag;
+            cg_neighbours(u, uv, un);
+            if (i >= N) continue;
+            cg_apply_pixel(c.b, un, lamN > 0.0 ? c.act : 0, lamN, up, r, u, w, red);
+            P.x[c.pi] = fma(alpha, pn, c.x);
+            P.p[c.pi] = pn;
+            P.s[nxt][c.pi] = sv;
+            P.r[nxt][c.pi] = r;
+            P.w[nxt][c.pi] = w;
         }
         rb += gridDim.x;
         if (rb * round >= N) break;
 #pragma unroll
-        for (int j = 0; j < kCgPx; ++j) {
-            const int i = rb * round + j * kCgThreads + threadIdx.x;
-            if (i < N) cg_load(g, P, act, cur, first != 0, i, a[j]);
-        }
+        for (int j = 0; j < kCgPx; ++j)
+            cg_load(g, P, act, cur, first != 0, rb * round + j * kCgThreads + tid, N, a[j]);
     }
-    block_reduce<kCgPartials, kCgThreads>(red, part_out);
+    cg_block_reduce(red, part_out, blockIdx.x);
 }
 
 // after the last launched iteration: the stop test of the last update (if the
 // solve had not stopped) and the solve's results into the solver state
 __global__ __launch_bounds__(kCgThreads) void k_c_cg_end(CgState* __restrict__ cs, const CgIter* __restrict__ rin,
                                                          const double* __restrict__ part_in, int nbx, double tol2) {
+    __shared__ double sh_tot[kCgPartials];
+    cg_totals(part_in, nbx, sh_tot);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
     CgIter st = *rin;
     if (!st.done) {
-        double tot[kCgPartials];
-        final_sum<kCgPartials, kCgThreads>(part_in, nbx, tot);
-        st.rr = tot[2] + dot6(st.r, st.r);
+        st.rr = sh_tot[2] + dot6(st.r, st.r);
         st.iters += 1;
         if (st.rr <= tol2 * cs->rr0) st.done = 1;
     }
-    if (threadIdx.x != 0) return;
     for (int k = 0; k < 6; ++k) cs->x[k] = st.x[k];
     cs->rr = st.rr;
     cs->done = st.done;
@@ -702,7 +796,7 @@ Planes cplanes(const pixvod_central* c) {
     double* b = c->planes;
     Planes P;
     P.ell = b;
-    P.diag = b + pl;
+    P.idiag = b + pl;
     P.b = b + 2 * pl;
     P.gl = b + 8 * pl;
     P.x = b + 9 * pl;
