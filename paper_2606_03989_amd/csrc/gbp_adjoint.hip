@@ -13,13 +13,13 @@
 //   k_adj_update       reverse of the update at every pixel: cotangents of its
 //                      four new messages (Mb, 116 planes) and of its unary
 //                      information and point (Ub, 42 planes);
-//   k_adj_edges        one lane per (pixel, direction): the pixel as the sender
+//   k_adj_edges        one wave per direction: the pixel as the sender
 //                      of its outgoing message and the receiver of its incoming
 //                      one on that edge: cotangents of its marginals, of the
 //                      residual's pose and log-depth arguments, and of the
 //                      stored message the sender subtracted (gathered from the
 //                      neighbours' Mb, no atomics; the four directions of a
-//                      pixel are summed with lane shuffles);
+//                      pixel are summed through LDS);
 //   k_adj_belief       reverse of the marginals and of the unary factors:
 //                      completes Xb (cotangent of X) and accumulates the
 //                      per-pixel parameter gradients. Every stored message
@@ -30,18 +30,14 @@
 //                      of a read-modify-write of all four slots.
 #include "gbp_adjoint.h"
 #include "gbp_adjoint.hpp"
+#include "gbp_planes.hpp"
 
 namespace pv {
 
 constexpr int MSG_STRIDE = 29;   // per direction: eta 6, Lambda 21, normal eta, normal lambda
 constexpr int UB_TAU = 35;       // Ub: L_bar 28, eta_bar 7, tau_bar 6, ell_bar 1
 constexpr int UB_ELL = 41;
-constexpr int EB_P = 0;          // Eb: P_bar 21, p_bar 6, D_bar, dv_bar, eps_bar 6, ell_bar
-constexpr int EB_PV = 21;
-constexpr int EB_D = 27;
-constexpr int EB_DV = 28;
-constexpr int EB_EPS = 29;
-constexpr int EB_ELL = 35;
+constexpr int EB_EPS = 29;       // Eb: P_bar 21, p_bar 6, D_bar, dv_bar, eps_bar 6, ell_bar
 
 __device__ inline bool pixel_2d(const Geo& g, int& u, int& v) {
     u = blockIdx.x * blockDim.x + threadIdx.x;
@@ -49,59 +45,127 @@ __device__ inline bool pixel_2d(const Geo& g, int& u, int& v) {
     return u < g.W && v < g.H;
 }
 
-// reverse of the update (k_pf_update): belief from the unary and the new
-// messages, mean m, relinearisation, transport of the messages
-__global__ __launch_bounds__(256, 2) void k_adj_update(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                    const float* __restrict__ M, const double* __restrict__ bel,
-                                                    const float* __restrict__ Xb, const float* __restrict__ Cb,
-                                                    float* __restrict__ Mb, float* __restrict__ Ub) {
-    int u, v;
-    if (!pixel_2d(g, u, v)) return;
-    const long p = pix_of(g, u, v);
-    const long pl = g.plane;
-    double tau[6], ell, R[9], t[3], L[28], eta[7];
-    load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, t);
-    // the belief of the update (unary + new messages), kept by the recompute
+// The reverse kernels go through phases: x is finished before what follows, and
+// the loads of a phase are not issued before it, so that a kernel's registers
+// are its phases' maximum and not their sum.
+template <int N>
+__device__ inline void phase(double (&x)[N]) {
 #pragma unroll
-    for (int k = 0; k < 28; ++k) L[k] = bel[(long)k * pl + p];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) eta[k] = bel[(long)(28 + k) * pl + p];
-    double idg[7], m[7];
-    chol7(L, idg);
-#pragma unroll
-    for (int k = 0; k < 7; ++k) m[k] = eta[k];
-    chol7_solve(L, idg, m);
-    double Rm[9], tm[3], R1[9], t1[3], tn[6];
-    se3_exp(m, Rm, tm);
-    se3_compose(R, t, Rm, tm, R1, t1);
-    se3_log(R1, t1, tn);
+    for (int k = 0; k < N; ++k) asm volatile("" : "+v"(x[k]) : : "memory");
+}
 
-    // transport eta' = eta - Lambda m_p, ne' = ne - nl m6: contribution to m_bar
+// a pointer that is the same in every lane, in scalar registers
+template <class T>
+__device__ inline T* uniform(T* p) {
+    const unsigned long a = (unsigned long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return (T*)(((unsigned long)hi << 32) | lo);
+}
+
+// n planes from `base` at offset o
+template <int N>
+__device__ inline void load_planes(const float* base, long stride, unsigned o, float x[N]) {
+    GFloat* b = plane_of(base, 0);
+    o = here(o);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        x[k] = *at(b, o);
+        b = next(stride, b);
+    }
+}
+template <int N>
+__device__ inline void load_planes(const double* base, long stride, unsigned o, double x[N]) {
+    GDouble* b = plane_of(const_cast<double*>(base));
+    o = here(o);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        x[k] = *at(b, o);
+        b = next(stride, b);
+    }
+}
+template <int N>
+__device__ inline void store_planes(float* base, long stride, unsigned o, const double x[N]) {
+    GFloat* b = plane_of(base, 0);
+    o = here(o);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        *at(b, o) = (float)x[k];
+        b = next(stride, b);
+    }
+}
+
+// reverse of the update (k_pf_update): belief from the unary and the new
+// messages, mean m, relinearisation, transport of the messages. Bound by one
+// wave's chain of loads and FP64 steps: every load goes out at the start (the
+// information cotangents of the four slots straight into LDS, 84 planes), and
+// the transport's sums, which do not need the solve, stand under the belief's
+// loads. 320 x 240, beside the recompute: 43.8 us, 51.3 with the loads behind
+// the solve and Cholesky factors.
+__global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs in, const float* X, const float* M,
+                                                      const double* bel, const float* Xb, const float* Cb, float* Mb,
+                                                      float* Ub) {
+    __shared__ float buf[84 * 64];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
+    const unsigned o = off_of(g, u, v);
+    const long pl = g.plane;
+    const bool has[4] = {u > 0, u + 1 < g.W, v > 0, v + 1 < g.H};
+    float xe[4][6], xn[8], ml[4][LAM_STRIDE], ce[6], cn[2];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        load_planes<LAM_STRIDE>(M + (long)d * LAM_STRIDE * pl, pl, o, ml[d]);
+        load_planes<6>(Xb + (long)(P_MID + d * MID_STRIDE) * pl, pl, o, xe[d]);
+    }
+    load_planes<8>(Xb + (long)P_MN * pl, pl, o, xn);
+    load_planes<6>(Cb, pl, o, ce);
+    load_planes<2>(Cb + 27 * pl, pl, o, cn);
+    // the belief of the update (unary + new messages), kept by the recompute
+    double L[28], m[7];
+    load_planes<28>(bel, pl, o, L);
+    load_planes<7>(bel + 28 * pl, pl, o, m);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        GFloat* b = plane_of(Xb, (long)(P_MID + d * MID_STRIDE + 6) * pl);
+        const unsigned oh = here(o);
+#pragma unroll
+        for (int k = 0; k < 21; ++k) {
+            __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(b, oh),
+                                             (__attribute__((address_space(3))) void*)(buf + (d * 21 + k) * 64), 4, 0,
+                                             0);
+            b = next(g, b);
+        }
+    }
+    // transport eta' = eta - Lambda m_p, ne' = ne - nl m6: contribution to
+    // m_bar (the tape's information of a missing edge is zero)
     double mb[7] = {0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        int nu, nv;
-        if (!neighbour(g, u, v, d, nu, nv)) continue;
-        const float* md = M + (long)d * LAM_STRIDE * pl + p;
-        const float* xb = Xb + (long)(P_MID + d * MID_STRIDE) * pl + p;
-        const float* cb = Cb + p;
-        double Lam[21], eb[6], y[6];
+        double eb[6], y[6];
 #pragma unroll
-        for (int k = 0; k < 21; ++k) Lam[k] = (double)md[k * pl];
+        for (int a = 0; a < 6; ++a) eb[a] = (double)xe[d][a] + (double)ce[a];
+        const float zero[6] = {0, 0, 0, 0, 0, 0};
+        complete_eta(zero, [&](int k) { return ml[d][k]; }, eb, y);   // y = -Lambda eb
 #pragma unroll
-        for (int a = 0; a < 6; ++a) eb[a] = (double)xb[a * pl] + (double)cb[a * pl];
-        sym_mv6(Lam, eb, y);
-#pragma unroll
-        for (int a = 0; a < 6; ++a) mb[a] -= y[a];
-        mb[6] -= (double)md[21 * pl] * ((double)Xb[(long)(P_MN + 2 * d) * pl + p] + (double)cb[27 * pl]);
+        for (int a = 0; a < 6; ++a) mb[a] += y[a];
+        mb[6] = fma(-(double)ml[d][21], (double)xn[2 * d] + (double)cn[0], mb[6]);
     }
+    phase(mb);
+    float pt[7], xp[7];
+    load_point_at(X, g, o, pt);
+    load_planes<7>(Xb, pl, o, xp);
+    double tau[6], ell, q[4], t[3], id[7], tn[6];
+    point_of(pt, tau, ell);
+    pose_exp(tau, q, t);
+    ldl7_factor(L, id);
+    ldl7_substitute(L, id, m);
+    pose_retract(q, t, m, tn);
     // relinearisation tau' = Log(Exp(tau) Exp(m_p)):
     //   d tau' = Jl(tau')^-1 Jl(tau) d tau + Jr(tau')^-1 Jr(m_p) d m_p
     double tnb[6], a6[6], taub[6], b6[6], mpb[6];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) tnb[k] = (double)Xb[(long)(P_TAU + k) * pl + p];
-    const double ellnb = (double)Xb[(long)P_ELL * pl + p];
+    for (int k = 0; k < 6; ++k) tnb[k] = (double)xp[k];
+    const double ellnb = (double)xp[6];
     jac_invT_apply(tn, 1.0, tnb, a6);
     jac_T_apply(tau, 1.0, a6, taub);
     jac_invT_apply(tn, -1.0, tnb, b6);
@@ -109,256 +173,319 @@ __global__ __launch_bounds__(256, 2) void k_adj_update(Geo g, Strengths s, Input
 #pragma unroll
     for (int k = 0; k < 6; ++k) mb[k] += mpb[k];
     mb[6] += ellnb;
-    // m = B^-1 beta
-    double betab[7], Bb[28];
+    // m = B^-1 beta: betab = B^-1 m_bar, B_bar = -sym(betab m^T)
+    phase(mb);
+    float cl[21];
+    load_planes<21>(Cb + 6 * pl, pl, o, cl);
+    load_planes<6>(Cb, pl, o, ce);
+    load_planes<2>(Cb + 27 * pl, pl, o, cn);
+    load_planes<8>(Xb + (long)P_MN * pl, pl, o, xn);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) load_planes<6>(Xb + (long)(P_MID + d * MID_STRIDE) * pl, pl, o, xe[d]);
+    double betab[7];
 #pragma unroll
     for (int k = 0; k < 7; ++k) betab[k] = mb[k];
-    chol7_solve(L, idg, betab);
+    ldl7_substitute(L, id, betab);
+    wait_lds_loads();
+    double Bb[28];
 #pragma unroll
     for (int k = 0; k < 28; ++k) Bb[k] = 0.0;
     sym_outer_acc7(Bb, betab, m, -1.0);
 
     // cotangents of the four new messages: transport + belief
+    const float* lds = buf + threadIdx.x;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        float* o = Mb + (long)d * MSG_STRIDE * pl + p;
-        int nu, nv;
-        if (!neighbour(g, u, v, d, nu, nv)) {
-#pragma unroll
-            for (int k = 0; k < MSG_STRIDE; ++k) o[k * pl] = 0.0f;
-            continue;
-        }
-        const float* xb = Xb + (long)(P_MID + d * MID_STRIDE) * pl + p;
-        const float* cb = Cb + p;
+        GFloat* b = plane_of(Mb, (long)d * MSG_STRIDE * pl);
+        const unsigned oh = here(o);
         double eb[6];
 #pragma unroll
         for (int a = 0; a < 6; ++a) {
-            eb[a] = (double)xb[a * pl] + (double)cb[a * pl];
-            o[a * pl] = (float)(eb[a] + betab[a]);
+            eb[a] = (double)xe[d][a] + (double)ce[a];
+            *at(b, oh) = has[d] ? (float)(eb[a] + betab[a]) : 0.0f;
+            b = next(g, b);
         }
 #pragma unroll
         for (int r = 0; r < 6; ++r)
 #pragma unroll
             for (int c = r; c < 6; ++c) {
-                const double tr = (r == c) ? eb[r] * m[r] : eb[r] * m[c] + eb[c] * m[r];
-                o[(6 + s6(r, c)) * pl] =
-                    (float)(((double)xb[(6 + s6(r, c)) * pl] + (double)cb[(6 + s6(r, c)) * pl]) - tr + Bb[s7(r, c)]);
+                const int k = s6(r, c);
+                const double tr = (r == c) ? eb[r] * m[r] : fma(eb[r], m[c], eb[c] * m[r]);
+                const double x = ((double)lds[(d * 21 + k) * 64] + (double)cl[k]) - tr + Bb[s7(r, c)];
+                *at(b, oh) = has[d] ? (float)x : 0.0f;
+                b = next(g, b);
             }
-        const double neb = (double)Xb[(long)(P_MN + 2 * d) * pl + p] + (double)cb[27 * pl];
-        const double nlb = (double)Xb[(long)(P_MN + 2 * d + 1) * pl + p] + (double)cb[28 * pl];
-        o[27 * pl] = (float)(neb + betab[6]);
-        o[28 * pl] = (float)(nlb - neb * m[6] + Bb[s7(6, 6)]);
+        const double neb = (double)xn[2 * d] + (double)cn[0];
+        const double nlb = (double)xn[2 * d + 1] + (double)cn[1];
+        *at(b, oh) = has[d] ? (float)(neb + betab[6]) : 0.0f;
+        b = next(g, b);
+        *at(b, oh) = has[d] ? (float)(fma(-neb, m[6], nlb) + Bb[s7(6, 6)]) : 0.0f;
     }
-    float* ub = Ub + p;
-#pragma unroll
-    for (int k = 0; k < 28; ++k) ub[k * pl] = (float)Bb[k];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) ub[(28 + k) * pl] = (float)betab[k];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) ub[(UB_TAU + k) * pl] = (float)taub[k];
-    ub[UB_ELL * pl] = (float)ellnb;
+    store_planes<28>(Ub, pl, o, Bb);
+    store_planes<7>(Ub + 28 * pl, pl, o, betab);
+    store_planes<6>(Ub + (long)UB_TAU * pl, pl, o, taub);
+    store_planes<1>(Ub + (long)UB_ELL * pl, pl, o, &ellnb);
 }
 
-// reverse of the message step (k_pf_messages), one lane per (pixel j,
-// direction d): j as the receiver of the message in its slot d (residual
-// cotangent) and as the sender of the message into its neighbour in direction
-// d (its marginals and the stored message it subtracted). The four lanes of a
-// pixel are adjacent; their contributions to j's marginal and perturbation
-// cotangents are summed with lane shuffles and written by the d = 0 lane.
-// Writes the sender part of j's slot-d cotangent to Xbo.
-__global__ __launch_bounds__(256, 2) void k_adj_edges(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                   const double* __restrict__ marg, const float* __restrict__ M,
-                                                   const float* __restrict__ Mb, float* __restrict__ Xbo,
-                                                   float* __restrict__ Eb, double* __restrict__ gN) {
-    const int d = threadIdx.x & 3;
-    const int u = blockIdx.x * (blockDim.x >> 2) + (threadIdx.x >> 2);
-    const int v = blockIdx.y;
-    // every lane of a pixel takes part in the shuffles; lanes past the row end
-    // work on a clamped copy and write nothing
-    const bool inside = u < g.W;
-    const int uc = inside ? u : g.W - 1;
-    const long pj = pix_of(g, uc, v);
+// reverse of the message step (k_pf_messages): wave d of a workgroup takes
+// direction d of 64 pixels j of a row, j as the receiver of the message in its
+// slot d (residual cotangent) and as the sender of the message into its
+// neighbour in direction d (its marginals and the stored message it
+// subtracted). The four waves' contributions to j's marginal and perturbation
+// cotangents are summed through LDS in a fixed order. Writes the sender part
+// of j's slot-d cotangent to Xbo. (A direction per wave, not per lane: the
+// planes of one direction are read 64 pixels at a time, the direction's cases
+// are uniform, and the sums take 37 LDS writes instead of 148 lane exchanges:
+// 57.8 against 73.9 us at 320 x 240, beside the recompute.)
+constexpr int EDGE_SUMS = 37;   // P_bar 21, p_bar 6, D_bar, dv_bar, eps_bar 6, ell_bar, lamN_bar
+constexpr int EDGE_HALF = 20;   // summed in two parts: 41 KB of LDS, three workgroups per CU
+static_assert(EDGE_SUMS % 4 == 1 && EDGE_HALF % 4 == 0 && EDGE_SUMS <= 2 * EDGE_HALF, "the last sum is wave 0's");
+
+__global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs in, const float* X,
+                                                      const double* marg, const float* M, const float* Mb, float* Xbo,
+                                                      float* Eb, double* gN) {
+    __shared__ double sh[EDGE_HALF][4][64];
+    const int lane = threadIdx.x;
+    const int d = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int u = blockIdx.x * 64 + lane, v = blockIdx.y;
     const long pl = g.plane;
-    double acc[37];   // P_bar 21, p_bar 6, D_bar, dv_bar, eps_bar 6, ell_bar, lamN_bar
-#pragma unroll
-    for (int k = 0; k < 37; ++k) acc[k] = 0.0;
-    float* xo = Xbo + (long)(P_MID + d * MID_STRIDE) * pl + pj;
-    float* xn = Xbo + (long)(P_MN + 2 * d) * pl + pj;
+    // the direction's planes, own and of the opposite slot
+    const int od = opposite(d);
+    const float* Md = uniform(M + (long)d * LAM_STRIDE * pl);
+    const float* Mo = uniform(M + (long)od * LAM_STRIDE * pl);
+    const float* Mbd = uniform(Mb + (long)d * MSG_STRIDE * pl);
+    const float* Mbo = uniform(Mb + (long)od * MSG_STRIDE * pl);
+    const float* Xd = uniform(X + (long)(P_MID + d * MID_STRIDE) * pl);
+    const float* Xnd = uniform(X + (long)(P_MN + 2 * d) * pl);
+    float* Xbd = uniform(Xbo + (long)(P_MID + d * MID_STRIDE) * pl);
+    float* Xbn = uniform(Xbo + (long)(P_MN + 2 * d) * pl);
+    const unsigned oj = off_of(g, u < g.W ? u : g.W - 1, v);
     int nu, nv;
-    if (neighbour(g, uc, v, d, nu, nv)) {
-        double tau[6], ell, R[9], t[3];
-        load_point(X, g, pj, tau, ell);
-        se3_exp(tau, R, t);
-        const long pi = pix_of(g, nu, nv);
-        const int o = opposite(d);
-        const float* Mj = M + (long)d * LAM_STRIDE * pl + pj;
-        const float* Mbj = Mb + (long)d * MSG_STRIDE * pl + pj;
-        const float* Mi = M + (long)o * LAM_STRIDE * pl + pi;
-        const float* Mbi = Mb + (long)o * MSG_STRIDE * pl + pi;
+    const bool inside = u < g.W;
+    const bool edge = inside && neighbour(g, u, v, d, nu, nv);
+    double acc[EDGE_SUMS];
+#pragma unroll
+    for (int k = 0; k < EDGE_SUMS; ++k) acc[k] = 0.0;
+    if (edge) {
+        const unsigned oi = oj + (unsigned)(4 * step_of(g, d));
+        float pj[7], pi[7], Mj[LAM_STRIDE], Mi[LAM_STRIDE], ej[6], ei[6], nej[1], nei[2];
+        load_point_at(X, g, oj, pj);
+        load_point_at(X, g, oi, pi);
+        load_planes<LAM_STRIDE>(Md, pl, oj, Mj);
+        load_planes<6>(Mbd, pl, oj, ej);
+        load_planes<LAM_STRIDE>(Mo, pl, oi, Mi);
+        load_planes<6>(Mbo, pl, oi, ei);
+        load_planes<1>(Mbd + 27 * pl, pl, oj, nej);
+        load_planes<2>(Mbo + 27 * pl, pl, oi, nei);
+        const float ct = d == DIR_L ? ld(in.cxt, oi) : d == DIR_R ? ld(in.cxt, oj) : d == DIR_U ? ld(in.cyt, oi) : ld(in.cyt, oj);
         // residual of the message into j from i, r = Log(Exp(tau_i)^-1 Exp(tau_j));
         // the message into i from j uses -r
-        double ti[6], elli, Ri[9], tri[3], r[6];
-        load_point(X, g, pi, ti, elli);
-        se3_exp(ti, Ri, tri);
-        se3_between(Ri, tri, R, t, r);
-        // eta_new = h - Lp r on both sides: receiver r_bar = -Lp_j eb_j, sender
-        // r_bar = -Lp_i eb_i with d(-r) = -d r, so eps_j += Jr(r)^-T (Lp_i eb_i - Lp_j eb_j)
-        double rb[6];
-        {
-            double Lam[21], e[6], y1[6], y2[6];
-#pragma unroll
-            for (int k = 0; k < 21; ++k) Lam[k] = (double)Mj[k * pl];
-#pragma unroll
-            for (int a = 0; a < 6; ++a) e[a] = (double)Mbj[a * pl];
-            sym_mv6(Lam, e, y1);
-#pragma unroll
-            for (int k = 0; k < 21; ++k) Lam[k] = (double)Mi[k * pl];
-#pragma unroll
-            for (int a = 0; a < 6; ++a) e[a] = (double)Mbi[a * pl];
-            sym_mv6(Lam, e, y2);
-#pragma unroll
-            for (int a = 0; a < 6; ++a) rb[a] = y2[a] - y1[a];
-        }
-        jac_invT_apply(r, -1.0, rb, acc + 29);
-
-        // sender: the partial of the message into i from j's variable-to-factor
-        // message (j's marginal minus j's stored message from this factor)
-        double V[21], vv[6], Lpb[21], hb[6], Vb[21], vb[6];
-#pragma unroll
-        for (int k = 0; k < 21; ++k) {
-            V[k] = marg[(long)k * pl + pj] - (double)X[(long)(P_MID + d * MID_STRIDE + 6 + k) * pl + pj];
-            Lpb[k] = (double)Mbi[(6 + k) * pl];
-        }
-#pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            vv[a] = marg[(long)(21 + a) * pl + pj] - (double)X[(long)(P_MID + d * MID_STRIDE + a) * pl + pj];
-            hb[a] = (double)Mbi[a * pl];
-        }
-        // eta_i = h - Lp (-r): Lp_bar += sym(hb r^T)
-        sym_outer_acc6(Lpb, hb, r, 1.0);
-        identity_partial_adjoint(s.lamR, V, vv, Lpb, hb, Vb, vb);
-#pragma unroll
-        for (int k = 0; k < 21; ++k) acc[k] = Vb[k];
-#pragma unroll
-        for (int a = 0; a < 6; ++a) acc[21 + a] = vb[a];
-        if (inside) {
-#pragma unroll
-            for (int k = 0; k < 21; ++k) xo[(6 + k) * pl] = (float)(-Vb[k]);
-#pragma unroll
-            for (int a = 0; a < 6; ++a) xo[a * pl] = (float)(-vb[a]);
-        }
-
+        double tau[6], ell, q[4], t[3], ti[6], elli, qi[4], tri[3], r[6];
+        point_of(pj, tau, ell);
+        point_of(pi, ti, elli);
+        pose_exp(tau, q, t);
+        pose_exp(ti, qi, tri);
+        pose_between(qi, tri, q, t, r);
         // normal-integration factor of the edge
         double nsb = 0.0, nlsb = 0.0;
-        double rn_j, rn_i;
-        if (s.lamN > 0.0 && normal_residual(g, in, pj, pi, d, ell, elli, rn_j)) {
-            normal_residual(g, in, pi, pj, o, elli, ell, rn_i);
+        if (isfinite(ct) && s.lamN > 0.0) {
+            double dm[2];
+            load_planes<2>(marg + 27 * pl, pl, oj, dm);
+            float xn[2];
+            load_planes<2>(Xnd, pl, oj, xn);
+            const double rn_i = normal_residual_c(ct, od, elli, ell);
             // ne_new = h - lp rn: receiver j and sender j (rn_i depends on ell_j with -1)
-            acc[35] = -(double)Mj[21 * pl] * (double)Mbj[27 * pl] + (double)Mi[21 * pl] * (double)Mbi[27 * pl];
-            const double neb = (double)Mbi[27 * pl], nlb = (double)Mbi[28 * pl];
-            const double ls = marg[27L * pl + pj] - (double)X[(long)(P_MN + 2 * d + 1) * pl + pj];
-            const double vs = marg[28L * pl + pj] - (double)X[(long)(P_MN + 2 * d) * pl + pj];
+            const double neb = (double)nei[0], nlb = (double)nei[1];
+            acc[35] = fma(-(double)Mj[21], (double)nej[0], (double)Mi[21] * neb);
             double lsb, vsb, lnb;
-            normal_partial_adjoint(s.lamN, ls, vs, nlb - neb * rn_i, neb, lsb, vsb, lnb);
+            normal_partial_adjoint(s.lamN, dm[0] - (double)xn[1], dm[1] - (double)xn[0], fma(-neb, rn_i, nlb), neb,
+                                   lsb, vsb, lnb);
             acc[27] = lsb;
             acc[28] = vsb;
             acc[36] = lnb;
             nsb = -vsb;
             nlsb = -lsb;
         }
-        if (inside) {
-            xn[0] = (float)nsb;
-            xn[pl] = (float)nlsb;
+        {
+            const double ns2[2] = {nsb, nlsb};
+            store_planes<2>(Xbn, pl, oj, ns2);
         }
+        // eta_new = h - Lp r on both sides: receiver r_bar = -Lp_j eb_j, sender
+        // r_bar = -Lp_i eb_i with d(-r) = -d r, so eps_j += Jr(r)^-T (Lp_i eb_i - Lp_j eb_j)
+        double hb[6];
+        {
+            double rb[6], e[6], y[6];
+            const float zero[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int a = 0; a < 6; ++a) {
+                e[a] = (double)ej[a];
+                hb[a] = (double)ei[a];
+            }
+            complete_eta(zero, [&](int k) { return Mj[k]; }, e, rb);    // -Lp_j eb_j
+            complete_eta(zero, [&](int k) { return Mi[k]; }, hb, y);    // -Lp_i eb_i
+#pragma unroll
+            for (int a = 0; a < 6; ++a) rb[a] -= y[a];
+            double eps[6];
+            jac_invT_apply(r, -1.0, rb, eps);
+            phase(eps);
+#pragma unroll
+            for (int a = 0; a < 6; ++a) acc[29 + a] = eps[a];
+        }
+        // sender: the partial of the message into i from j's variable-to-factor
+        // message (j's marginal minus j's stored message from this factor)
+        double V[21], vv[6], Lpb[21], Vb[21], vb[6];
+        load_planes<21>(marg, pl, oj, V);
+        load_planes<6>(marg + 21 * pl, pl, oj, vv);
+        {
+            float xm[27], lb[21];
+            load_planes<27>(Xd, pl, oj, xm);
+            load_planes<21>(Mbo + 6 * pl, pl, oi, lb);
+#pragma unroll
+            for (int k = 0; k < 21; ++k) {
+                V[k] -= (double)xm[6 + k];
+                Lpb[k] = (double)lb[k];
+            }
+#pragma unroll
+            for (int a = 0; a < 6; ++a) vv[a] -= (double)xm[a];
+        }
+        // eta_i = h - Lp (-r): Lp_bar += sym(hb r^T)
+        sym_outer_acc6(Lpb, hb, r, 1.0);
+        identity_partial_adjoint(s.lamR, V, vv, Lpb, hb, Vb, vb);
+        GFloat* b = plane_of(Xbd, 0);
+        const unsigned oh = here(oj);
+#pragma unroll
+        for (int k = 0; k < 27; ++k) {
+            *at(b, oh) = (float)-(k < 6 ? vb[k] : Vb[k - 6]);
+            b = next(g, b);
+        }
+#pragma unroll
+        for (int k = 0; k < 21; ++k) acc[k] = Vb[k];
+#pragma unroll
+        for (int a = 0; a < 6; ++a) acc[21 + a] = vb[a];
     } else if (inside) {
-        for (int k = 0; k < MID_STRIDE; ++k) xo[k * pl] = 0.0f;
-        xn[0] = xn[pl] = 0.0f;
-    }
-    // sum over the four directions of the pixel (lanes 4q .. 4q + 3)
+        GFloat* b = plane_of(Xbd, 0);
+        const unsigned oh = here(oj);
 #pragma unroll
-    for (int k = 0; k < 37; ++k) {
-        acc[k] += __shfl_xor(acc[k], 1, 4);
-        acc[k] += __shfl_xor(acc[k], 2, 4);
-    }
-    if (d == 0 && inside) {
-        float* eb = Eb + pj;
-#pragma unroll
-        for (int k = 0; k < 21; ++k) eb[(EB_P + k) * pl] = (float)acc[k];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            eb[(EB_PV + k) * pl] = (float)acc[21 + k];
-            eb[(EB_EPS + k) * pl] = (float)acc[29 + k];
+        for (int k = 0; k < 27; ++k) {
+            *at(b, oh) = 0.0f;
+            b = next(g, b);
         }
-        eb[EB_D * pl] = (float)acc[27];
-        eb[EB_DV * pl] = (float)acc[28];
-        eb[EB_ELL * pl] = (float)acc[35];
-        gN[pj] += acc[36];
+        const double zero2[2] = {0.0, 0.0};
+        store_planes<2>(Xbn, pl, oj, zero2);
+    }
+    // the sums over the four waves, every fourth by each wave, to the planes of
+    // Eb (and, wave 0's last, to gN)
+    const long pj = pix_of(g, inside ? u : g.W - 1, v);
+#pragma unroll
+    for (int part = 0; part < EDGE_SUMS; part += EDGE_HALF) {
+        if (part) __syncthreads();
+#pragma unroll
+        for (int k = part; k < part + EDGE_HALF && k < EDGE_SUMS; ++k) sh[k - part][d][lane] = acc[k];
+        __syncthreads();
+        if (!inside) continue;
+#pragma unroll
+        for (int j = 0; j < EDGE_HALF; j += 4) {
+            const int k = part + j + d;
+            if (part + j + 4 > EDGE_SUMS && d > 0) break;
+            const double(*q)[64] = sh[j + d];
+            const double x = (q[0][lane] + q[1][lane]) + (q[2][lane] + q[3][lane]);
+            if (part + j + 4 > EDGE_SUMS) {
+                gN[pj] += x;
+                break;
+            }
+            Eb[(long)k * pl + pj] = (float)x;
+        }
     }
 }
 
 // reverse of the marginals and of the unary factors; completes Xbo (point
-// planes) and writes the slot-common part Cbo
-__global__ __launch_bounds__(256) void k_adj_belief(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                    const double* __restrict__ marg, const float* __restrict__ Ub,
-                                                    const float* __restrict__ Eb,
-                                                    float* __restrict__ Xbo, float* __restrict__ Cbo,
-                                                    double* __restrict__ gsig, double* __restrict__ gk) {
-    int u, v;
-    if (!pixel_2d(g, u, v)) return;
-    const long p = pix_of(g, u, v);
+// planes) and writes the slot-common part Cbo. Two phases (marginals, unary),
+// each with its own loads, so that the kernel fits 256 registers and two waves
+// share a SIMD (29.8 us at 320 x 240, beside the recompute; 36.2 with 400).
+__global__ __launch_bounds__(64, 2) void k_adj_belief(Geo g, Strengths s, Inputs in, const float* X,
+                                                      const double* marg, const float* Ub, const float* Eb, float* Xbo,
+                                                      float* Cbo, double* gsig, double* gk) {
+    __shared__ float buf[14 * 64];
+    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    if (u >= g.W) return;
+    const unsigned o = off_of(g, u, v);
     const long pl = g.plane;
-    double tau[6], ell, R[9], t[3], L[28], eta[7];
-    load_point(X, g, p, tau, ell);
-    se3_exp(tau, R, t);
-    // the belief of the marginals (unary + stored messages), kept by the recompute
+    // the cotangents of the point, needed last, wait in LDS: tau_bar 6 and
+    // ell_bar of the update, eps_bar 6 and ell_bar of the edges
+    {
+        GFloat* b = plane_of(Ub, (long)UB_TAU * pl);
+        GFloat* c = plane_of(Eb, (long)EB_EPS * pl);
+        const unsigned oh = here(o);
 #pragma unroll
-    for (int k = 0; k < 28; ++k) L[k] = marg[(long)(29 + k) * pl + p];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) eta[k] = marg[(long)(57 + k) * pl + p];
-    const float* eb = Eb + p;
-    double Pb[21], pb[6];
-#pragma unroll
-    for (int k = 0; k < 21; ++k) Pb[k] = (double)eb[(EB_P + k) * pl];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) pb[k] = (double)eb[(EB_PV + k) * pl];
-    double BbS[28], ebS[7];
-#pragma unroll
-    for (int k = 0; k < 28; ++k) BbS[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 7; ++k) ebS[k] = 0.0;
-    marginals_adjoint(L, eta, Pb, pb, (double)eb[EB_D * pl], (double)eb[EB_DV * pl], BbS, ebS);
-
-    const float* ub = Ub + p;
-    double Lb[28], etab[7], epsb[6], taub[6];
-#pragma unroll
-    for (int k = 0; k < 28; ++k) Lb[k] = (double)ub[k * pl] + BbS[k];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) etab[k] = (double)ub[(28 + k) * pl] + ebS[k];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        epsb[k] = (double)eb[(EB_EPS + k) * pl];
-        taub[k] = (double)ub[(UB_TAU + k) * pl];
+        for (int k = 0; k < 7; ++k) {
+            __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(b, oh),
+                                             (__attribute__((address_space(3))) void*)(buf + k * 64), 4, 0, 0);
+            __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(c, oh),
+                                             (__attribute__((address_space(3))) void*)(buf + (7 + k) * 64), 4, 0, 0);
+            b = next(g, b);
+            c = next(g, c);
+        }
     }
-    double ellb = (double)ub[UB_ELL * pl] + (double)eb[EB_ELL * pl];
-    double sigb = 0.0, kb = 0.0;
+    double Lb[28], etab[7];
+    {
+        // the belief of the marginals (unary + stored messages), kept by the recompute
+        double L[28], eta[7], Pb[21], pb[6], BbS[28], ebS[7];
+        float eb[29];
+        load_planes<28>(marg + 29 * pl, pl, o, L);
+        load_planes<7>(marg + 57 * pl, pl, o, eta);
+        load_planes<29>(Eb, pl, o, eb);
+#pragma unroll
+        for (int k = 0; k < 21; ++k) Pb[k] = (double)eb[k];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) pb[k] = (double)eb[21 + k];
+#pragma unroll
+        for (int k = 0; k < 28; ++k) BbS[k] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) ebS[k] = 0.0;
+        marginals_adjoint(L, eta, Pb, pb, (double)eb[27], (double)eb[28], BbS, ebS);
+        // every stored message enters the belief: one slot-common cotangent
+        double c[29];
+#pragma unroll
+        for (int a = 0; a < 6; ++a) c[a] = ebS[a];
+#pragma unroll
+        for (int r = 0; r < 6; ++r)
+#pragma unroll
+            for (int k = r; k < 6; ++k) c[6 + s6(r, k)] = BbS[s7(r, k)];
+        c[27] = ebS[6];
+        c[28] = BbS[s7(6, 6)];
+        store_planes<29>(Cbo, pl, o, c);
+        phase(BbS);
+        float ub[35];
+        load_planes<35>(Ub, pl, o, ub);
+#pragma unroll
+        for (int k = 0; k < 28; ++k) Lb[k] = (double)ub[k] + BbS[k];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) etab[k] = (double)ub[28 + k] + ebS[k];
+    }
+    phase(Lb);
+    phase(etab);
+    float pt[7];
+    load_point_at(X, g, o, pt);
+    double tau[6], ell, q[4], R[9], t[3], epsb[6], taub[6];
+    point_of(pt, tau, ell);
+    pose_exp(tau, q, t);
+    pose_rotation(q, R);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) epsb[k] = taub[k] = 0.0;
+    double ellb = 0.0, sigb = 0.0, kb = 0.0;
     unary_adjoint(g, s, in, u, v, tau, R, t, ell, Lb, etab, epsb, taub, ellb, sigb, kb);
-    double te[6];
+    wait_lds_loads();
+    const float* lds = buf + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) epsb[k] += (double)lds[(7 + k) * 64];
+    double te[7];
     jac_T_apply(tau, -1.0, epsb, te);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) Xbo[(long)(P_TAU + k) * pl + p] = (float)(taub[k] + te[k]);
-    Xbo[(long)P_ELL * pl + p] = (float)ellb;
-    // every stored message enters the belief: one slot-common cotangent
-    float* cb = Cbo + p;
-#pragma unroll
-    for (int a = 0; a < 6; ++a) cb[a * pl] = (float)ebS[a];
-#pragma unroll
-    for (int r = 0; r < 6; ++r)
-#pragma unroll
-        for (int c = r; c < 6; ++c) cb[(6 + s6(r, c)) * pl] = (float)BbS[s7(r, c)];
-    cb[27 * pl] = (float)ebS[6];
-    cb[28 * pl] = (float)BbS[s7(6, 6)];
-    gsig[p] += sigb;
-    gk[p] += kb;
+    for (int k = 0; k < 6; ++k) te[k] += taub[k] + (double)lds[k * 64];
+    te[6] = ellb + ((double)lds[6 * 64] + (double)lds[13 * 64]);
+    store_planes<7>(Xbo, pl, o, te);
+    *at(plane_of(gsig), here(o)) += sigb;
+    *at(plane_of(gk), here(o)) += kb;
 }
 
 // cotangents of the per-frame outputs: pose mean (Eq. estimator_avg) and the
@@ -430,14 +557,13 @@ static dim3 adj_grid(const Geo& g) { return dim3((g.W + 63) / 64, (g.H + 3) / 4)
 hipError_t launch_adj_update(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const float* M,
                              const double* bel, const float* Xb, const float* Cb, float* Mb, float* Ub,
                              hipStream_t st) {
-    hipLaunchKernelGGL(k_adj_update, adj_grid(g), kAdjBlock, 0, st, g, s, in, X, M, bel, Xb, Cb, Mb, Ub);
+    hipLaunchKernelGGL(k_adj_update, dim3((g.W + 63) / 64, g.H), dim3(64), 0, st, g, s, in, X, M, bel, Xb, Cb, Mb, Ub);
     return hipGetLastError();
 }
 
 hipError_t launch_adj_edges(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const double* marg,
                             const float* M, const float* Mb, float* Xbo, float* Eb, double* gN, hipStream_t st) {
-    // one lane per (pixel, direction): 64 pixels of a row per 256-lane workgroup
-    hipLaunchKernelGGL(k_adj_edges, dim3((g.W + 63) / 64, g.H), dim3(256), 0, st, g, s, in, X, marg, M, Mb, Xbo, Eb,
+    hipLaunchKernelGGL(k_adj_edges, dim3((g.W + 63) / 64, g.H), dim3(64, 4), 0, st, g, s, in, X, marg, M, Mb, Xbo, Eb,
                        gN);
     return hipGetLastError();
 }
@@ -445,7 +571,8 @@ hipError_t launch_adj_edges(const Geo& g, const Strengths& s, const Inputs& in, 
 hipError_t launch_adj_belief(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const double* marg,
                              const float* Ub, const float* Eb, float* Xbo, float* Cbo, double* gsig, double* gk,
                              hipStream_t st) {
-    hipLaunchKernelGGL(k_adj_belief, adj_grid(g), kAdjBlock, 0, st, g, s, in, X, marg, Ub, Eb, Xbo, Cbo, gsig, gk);
+    hipLaunchKernelGGL(k_adj_belief, dim3((g.W + 63) / 64, g.H), dim3(64), 0, st, g, s, in, X, marg, Ub, Eb, Xbo, Cbo,
+                       gsig, gk);
     return hipGetLastError();
 }
 

@@ -179,7 +179,7 @@ __device__ inline void unary_adjoint(const Geo& g, const Strengths& s, const Inp
                                      const double Lb[28], const double eb[7], double eps_bar[6],
                                      double tau_bar[6], double& ell_bar, double& sig_bar, double& k_bar) {
     // --- photometric (Eq. distrb_photo, warp Eq. warp)
-    const double q0 = ((double)u - g.cx) / g.fx, q1 = ((double)v - g.cy) / g.fy;
+    const double q0 = ((double)u - g.cx) * g.ifx, q1 = ((double)v - g.cy) * g.ify;
     const double qt[3] = {q0, q1, 1.0};
     const double rho = exp(-ell);
     const double a0 = R[0] * q0 + R[1] * q1 + R[2] + rho * t[0];
@@ -336,6 +336,11 @@ __device__ inline void unary_adjoint(const Geo& g, const Strengths& s, const Inp
         se3_compose(s.prior_R, s.prior_t, R, t, Rr, tr);
         se3_log(Rr, tr, rp);
     }
+    // the photometric part is finished before the prior's blocks take its
+    // registers
+#pragma unroll
+    for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(rp[k]), "+v"(eps_bar[k]));
+    asm volatile("" : "+v"(rp[0]), "+v"(ell_bar), "+v"(sig_bar), "+v"(k_bar));
     // J = [[S, 0], [Q, S]] as in unary_factors: S = I + W/2 + W^2/12,
     // Q = P/2 + (PW + WP)/12 with W = [w]x, P = [q]x, rp = (w, q)
     const double w0 = rp[0], w1 = rp[1], w2 = rp[2], p0 = rp[3], p1 = rp[4], p2 = rp[5];

@@ -483,49 +483,42 @@ __device__ inline void chol6_inverse(const double L[21], const double inv_diag[6
         }
 }
 
-__device__ inline bool chol7(double A[28], double inv_diag[7]) {
+// in-place LDL^T of a packed 7x7 SPD matrix: L(i, j) stored at s7(j, i),
+// id = 1 / D; false on a non-positive pivot
+__device__ inline bool ldl7_factor(double L[28], double id[7]) {
     bool ok = true;
 #pragma unroll
     for (int j = 0; j < 7; ++j) {
-        double d = A[s7(j, j)];
-#pragma unroll
-        for (int k = 0; k < j; ++k) d -= A[s7(j, k)] * A[s7(j, k)];
+        const double d = L[s7(j, j)];
         ok = ok && (d > 0.0);
-        const double dd = d > 0.0 ? d : 1e-300;
-        const double il = rsqrt_nr(dd);
-        A[s7(j, j)] = dd * il;
-        inv_diag[j] = il;
+        id[j] = rcp_nr(fmax(d, 1e-300));
+        double l[7];
 #pragma unroll
-        for (int i = j + 1; i < 7; ++i) {
-            double s = A[s7(i, j)];
+        for (int i = j + 1; i < 7; ++i) l[i] = L[s7(j, i)] * id[j];
 #pragma unroll
-            for (int k = 0; k < j; ++k) s -= A[s7(i, k)] * A[s7(j, k)];
-            A[s7(i, j)] = s * il;
-        }
+        for (int i = j + 1; i < 7; ++i)
+#pragma unroll
+            for (int k = i; k < 7; ++k) L[s7(i, k)] = fma(-l[i], L[s7(j, k)], L[s7(i, k)]);
+#pragma unroll
+        for (int i = j + 1; i < 7; ++i) L[s7(j, i)] = l[i];
     }
     return ok;
 }
 
-__device__ inline void chol7_solve(const double L[28], const double inv_diag[7], double b[7]) {
+// b <- the solution with the factor of ldl7_factor
+__device__ inline void ldl7_substitute(const double L[28], const double id[7], double b[7]) {
 #pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        double s = b[i];
+    for (int j = 0; j < 7; ++j)
 #pragma unroll
-        for (int k = 0; k < i; ++k) s -= L[s7(i, k)] * b[k];
-        b[i] = s * inv_diag[i];
-    }
+        for (int i = j + 1; i < 7; ++i) b[i] = fma(-L[s7(j, i)], b[j], b[i]);
 #pragma unroll
     for (int i = 6; i >= 0; --i) {
-        double s = b[i];
+        double x = b[i] * id[i];
 #pragma unroll
-        for (int k = i + 1; k < 7; ++k) s -= L[s7(k, i)] * b[k];
-        b[i] = s * inv_diag[i];
+        for (int k = i + 1; k < 7; ++k) x = fma(-L[s7(i, k)], b[k], x);
+        b[i] = x;
     }
 }
-
-// [A^-1]_66 from the Cholesky factor: |L^-T e_6|^2 = 1 / L66^2 (last row of L^-1
-// has a single entry in its last column)
-__device__ inline double chol7_var_last(const double inv_diag[7]) { return inv_diag[6] * inv_diag[6]; }
 
 // m = L^-1 eta for the packed SPD L (7x7) by LDL^T elimination with eta carried
 // along as a further row, and [L^-1]_66 = 1 / D_66; false on a non-positive
