@@ -18,12 +18,13 @@ struct PoseBar {
 // Cb: the slot-common cotangent of the stored messages (29 FP32 planes, a
 // slot's layout: eta 6, Lambda 21, normal eta, normal lambda), added to every
 // existing slot of Xb by its reader
-// M: the tape of the new messages' information, LAM_STRIDE FP32 planes per slot
-hipError_t launch_adj_update(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const float* M,
+// Xn: the canonical state after the iteration, whose messages hold the new
+// messages' information
+hipError_t launch_adj_update(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const float* Xn,
                              const double* bel, const float* Xb, const float* Cb, float* Mb, float* Ub,
                              hipStream_t st);
 hipError_t launch_adj_edges(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const double* marg,
-                            const float* M, const float* Mb, float* Xbo, float* Eb, double* gN, hipStream_t st);
+                            const float* Xn, const float* Mb, float* Xbo, float* Eb, double* gN, hipStream_t st);
 hipError_t launch_adj_belief(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const double* marg,
                              const float* Ub, const float* Eb, float* Xbo, float* Cbo, double* gsig, double* gk,
                              hipStream_t st);

@@ -7,9 +7,9 @@
 // update + relinearise + transport; Sec. 3.4 and Sec. 4.1), given the
 // cotangent Xb' of X':
 //   forward recompute  the fused passes that recompute X also keep its belief
-//                      and marginals (64 planes), the information of its new
-//                      messages (88 FP32 planes: exact, they are the FP32
-//                      partials' values) and the belief of the update (35);
+//                      and depth marginal (37 FP64 planes) and the belief of
+//                      the update (35); the information of the new messages
+//                      is read from the state X' (the transport keeps it);
 //   k_adj_update       reverse of the update at every pixel: cotangents of its
 //                      four new messages (Mb, 116 planes) and of its unary
 //                      information and point (Ub, 42 planes);
@@ -100,9 +100,9 @@ __device__ inline void store_planes(float* base, long stride, unsigned o, const 
 // wave's chain of loads and FP64 steps: every load goes out at the start (the
 // information cotangents of the four slots straight into LDS, 84 planes), and
 // the transport's sums, which do not need the solve, stand under the belief's
-// loads. 320 x 240, beside the recompute: 43.8 us, 51.3 with the loads behind
+// loads. 320 x 240, beside the recompute: 40.4 us, 51.3 with the loads behind
 // the solve and Cholesky factors.
-__global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs in, const float* X, const float* M,
+__global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs in, const float* X, const float* Xn,
                                                       const double* bel, const float* Xb, const float* Cb, float* Mb,
                                                       float* Ub) {
     __shared__ float buf[84 * 64];
@@ -111,12 +111,14 @@ __global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs
     const unsigned o = off_of(g, u, v);
     const long pl = g.plane;
     const bool has[4] = {u > 0, u + 1 < g.W, v > 0, v + 1 < g.H};
-    float xe[4][6], xn[8], ml[4][LAM_STRIDE], ce[6], cn[2];
+    float xe[4][6], xn[8], ml[4][21], ce[6], cn[2];
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        load_planes<LAM_STRIDE>(M + (long)d * LAM_STRIDE * pl, pl, o, ml[d]);
+        load_planes<21>(Xn + (long)(P_MID + d * MID_STRIDE + 6) * pl, pl, o, ml[d]);
         load_planes<6>(Xb + (long)(P_MID + d * MID_STRIDE) * pl, pl, o, xe[d]);
     }
+    float nn[8];
+    load_planes<8>(Xn + (long)P_MN * pl, pl, o, nn);
     load_planes<8>(Xb + (long)P_MN * pl, pl, o, xn);
     load_planes<6>(Cb, pl, o, ce);
     load_planes<2>(Cb + 27 * pl, pl, o, cn);
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs
         }
     }
     // transport eta' = eta - Lambda m_p, ne' = ne - nl m6: contribution to
-    // m_bar (the tape's information of a missing edge is zero)
+    // m_bar (a missing edge's information is zero in the state)
     double mb[7] = {0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs
         complete_eta(zero, [&](int k) { return ml[d][k]; }, eb, y);   // y = -Lambda eb
 #pragma unroll
         for (int a = 0; a < 6; ++a) mb[a] += y[a];
-        mb[6] = fma(-(double)ml[d][21], (double)xn[2 * d] + (double)cn[0], mb[6]);
+        mb[6] = fma(-(double)nn[2 * d + 1], (double)xn[2 * d] + (double)cn[0], mb[6]);
     }
     phase(mb);
     float pt[7], xp[7];
@@ -236,23 +238,31 @@ __global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs
 // of j's slot-d cotangent to Xbo. (A direction per wave, not per lane: the
 // planes of one direction are read 64 pixels at a time, the direction's cases
 // are uniform, and the sums take 37 LDS writes instead of 148 lane exchanges:
-// 57.8 against 73.9 us at 320 x 240, beside the recompute.)
-constexpr int EDGE_SUMS = 37;   // P_bar 21, p_bar 6, D_bar, dv_bar, eps_bar 6, ell_bar, lamN_bar
-constexpr int EDGE_HALF = 20;   // summed in two parts: 41 KB of LDS, three workgroups per CU
-static_assert(EDGE_SUMS % 4 == 1 && EDGE_HALF % 4 == 0 && EDGE_SUMS <= 2 * EDGE_HALF, "the last sum is wave 0's");
+// 59.6 against 73.9 us at 320 x 240, beside the recompute. The first sums go to
+// LDS early: kept in registers, they made the pose marginal spill.)
+constexpr int EDGE_SUMS = 37;    // D_bar, dv_bar, eps_bar 6, ell_bar, lamN_bar, P_bar 21, p_bar 6
+constexpr int EDGE_FIRST = 10;   // those put into LDS as soon as they are known
+constexpr int EDGE_PART = 24;    // summed in two parts: 48 KB of LDS, three workgroups per CU
+constexpr int EDGE_LAMN = 9;     // lamN_bar, which goes to gN
+static_assert(EDGE_PART % 4 == 0 && EDGE_SUMS <= 2 * EDGE_PART && EDGE_LAMN < EDGE_FIRST && EDGE_FIRST < EDGE_PART,
+              "two parts, lamN_bar in the first");
+// the plane of Eb (P_bar 21, p_bar 6, D_bar, dv_bar, eps_bar 6, ell_bar) of a sum
+__device__ inline int edge_plane(int k) { return k < EDGE_LAMN ? 27 + k : k - EDGE_FIRST; }
 
 __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs in, const float* X,
-                                                      const double* marg, const float* M, const float* Mb, float* Xbo,
+                                                      const double* marg, const float* Xn, const float* Mb, float* Xbo,
                                                       float* Eb, double* gN) {
-    __shared__ double sh[EDGE_HALF][4][64];
+    __shared__ double sh[EDGE_PART][4][64];
     const int lane = threadIdx.x;
     const int d = __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int u = blockIdx.x * 64 + lane, v = blockIdx.y;
     const long pl = g.plane;
     // the direction's planes, own and of the opposite slot
     const int od = opposite(d);
-    const float* Md = uniform(M + (long)d * LAM_STRIDE * pl);
-    const float* Mo = uniform(M + (long)od * LAM_STRIDE * pl);
+    const float* Ld = uniform(Xn + (long)(P_MID + d * MID_STRIDE + 6) * pl);
+    const float* Lo = uniform(Xn + (long)(P_MID + od * MID_STRIDE + 6) * pl);
+    const float* Nd = uniform(Xn + (long)(P_MN + 2 * d + 1) * pl);
+    const float* No = uniform(Xn + (long)(P_MN + 2 * od + 1) * pl);
     const float* Mbd = uniform(Mb + (long)d * MSG_STRIDE * pl);
     const float* Mbo = uniform(Mb + (long)od * MSG_STRIDE * pl);
     const float* Xd = uniform(X + (long)(P_MID + d * MID_STRIDE) * pl);
@@ -263,17 +273,17 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
     int nu, nv;
     const bool inside = u < g.W;
     const bool edge = inside && neighbour(g, u, v, d, nu, nv);
-    double acc[EDGE_SUMS];
+    double acc[EDGE_SUMS];   // in the order of the sums
 #pragma unroll
     for (int k = 0; k < EDGE_SUMS; ++k) acc[k] = 0.0;
     if (edge) {
         const unsigned oi = oj + (unsigned)(4 * step_of(g, d));
-        float pj[7], pi[7], Mj[LAM_STRIDE], Mi[LAM_STRIDE], ej[6], ei[6], nej[1], nei[2];
+        float pj[7], pi[7], Mj[21], Mi[21], ej[6], ei[6], nej[1], nei[2];
         load_point_at(X, g, oj, pj);
         load_point_at(X, g, oi, pi);
-        load_planes<LAM_STRIDE>(Md, pl, oj, Mj);
+        load_planes<21>(Ld, pl, oj, Mj);
         load_planes<6>(Mbd, pl, oj, ej);
-        load_planes<LAM_STRIDE>(Mo, pl, oi, Mi);
+        load_planes<21>(Lo, pl, oi, Mi);
         load_planes<6>(Mbo, pl, oi, ei);
         load_planes<1>(Mbd + 27 * pl, pl, oj, nej);
         load_planes<2>(Mbo + 27 * pl, pl, oi, nei);
@@ -290,19 +300,20 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
         double nsb = 0.0, nlsb = 0.0;
         if (isfinite(ct) && s.lamN > 0.0) {
             double dm[2];
-            load_planes<2>(marg + 27 * pl, pl, oj, dm);
+            load_planes<2>(marg, pl, oj, dm);
+            const float lj = ld(Nd, oj), li = ld(No, oi);
             float xn[2];
             load_planes<2>(Xnd, pl, oj, xn);
             const double rn_i = normal_residual_c(ct, od, elli, ell);
             // ne_new = h - lp rn: receiver j and sender j (rn_i depends on ell_j with -1)
             const double neb = (double)nei[0], nlb = (double)nei[1];
-            acc[35] = fma(-(double)Mj[21], (double)nej[0], (double)Mi[21] * neb);
+            acc[8] = fma(-(double)lj, (double)nej[0], (double)li * neb);
             double lsb, vsb, lnb;
             normal_partial_adjoint(s.lamN, dm[0] - (double)xn[1], dm[1] - (double)xn[0], fma(-neb, rn_i, nlb), neb,
                                    lsb, vsb, lnb);
-            acc[27] = lsb;
-            acc[28] = vsb;
-            acc[36] = lnb;
+            acc[0] = lsb;
+            acc[1] = vsb;
+            acc[EDGE_LAMN] = lnb;
             nsb = -vsb;
             nlsb = -lsb;
         }
@@ -329,13 +340,19 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
             jac_invT_apply(r, -1.0, rb, eps);
             phase(eps);
 #pragma unroll
-            for (int a = 0; a < 6; ++a) acc[29 + a] = eps[a];
+            for (int a = 0; a < 6; ++a) acc[2 + a] = eps[a];
         }
+#pragma unroll
+        for (int k = 0; k < EDGE_FIRST; ++k) sh[k][d][lane] = acc[k];
         // sender: the partial of the message into i from j's variable-to-factor
         // message (j's marginal minus j's stored message from this factor)
         double V[21], vv[6], Lpb[21], Vb[21], vb[6];
-        load_planes<21>(marg, pl, oj, V);
-        load_planes<6>(marg + 21 * pl, pl, oj, vv);
+        {
+            double L[28], eta[7];
+            load_planes<28>(marg + 2 * pl, pl, oj, L);
+            load_planes<7>(marg + 30 * pl, pl, oj, eta);
+            pose_marginal(L, eta, L[s7(6, 6)], V, vv);
+        }
         {
             float xm[27], lb[21];
             load_planes<27>(Xd, pl, oj, xm);
@@ -359,9 +376,9 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
             b = next(g, b);
         }
 #pragma unroll
-        for (int k = 0; k < 21; ++k) acc[k] = Vb[k];
+        for (int k = 0; k < 21; ++k) acc[EDGE_FIRST + k] = Vb[k];
 #pragma unroll
-        for (int a = 0; a < 6; ++a) acc[21 + a] = vb[a];
+        for (int a = 0; a < 6; ++a) acc[EDGE_FIRST + 21 + a] = vb[a];
     } else if (inside) {
         GFloat* b = plane_of(Xbd, 0);
         const unsigned oh = here(oj);
@@ -372,28 +389,26 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
         }
         const double zero2[2] = {0.0, 0.0};
         store_planes<2>(Xbn, pl, oj, zero2);
+#pragma unroll
+        for (int k = 0; k < EDGE_FIRST; ++k) sh[k][d][lane] = 0.0;
     }
     // the sums over the four waves, every fourth by each wave, to the planes of
-    // Eb (and, wave 0's last, to gN)
+    // Eb and to gN
     const long pj = pix_of(g, inside ? u : g.W - 1, v);
 #pragma unroll
-    for (int part = 0; part < EDGE_SUMS; part += EDGE_HALF) {
+    for (int part = 0; part < EDGE_SUMS; part += EDGE_PART) {
         if (part) __syncthreads();
 #pragma unroll
-        for (int k = part; k < part + EDGE_HALF && k < EDGE_SUMS; ++k) sh[k - part][d][lane] = acc[k];
+        for (int k = part ? part : EDGE_FIRST; k < part + EDGE_PART && k < EDGE_SUMS; ++k) sh[k - part][d][lane] = acc[k];
         __syncthreads();
-        if (!inside) continue;
 #pragma unroll
-        for (int j = 0; j < EDGE_HALF; j += 4) {
+        for (int j = 0; j < EDGE_PART && part + j < EDGE_SUMS; j += 4) {
             const int k = part + j + d;
-            if (part + j + 4 > EDGE_SUMS && d > 0) break;
+            if (k >= EDGE_SUMS || !inside) break;
             const double(*q)[64] = sh[j + d];
             const double x = (q[0][lane] + q[1][lane]) + (q[2][lane] + q[3][lane]);
-            if (part + j + 4 > EDGE_SUMS) {
-                gN[pj] += x;
-                break;
-            }
-            Eb[(long)k * pl + pj] = (float)x;
+            if (k == EDGE_LAMN) gN[pj] += x;
+            else Eb[(long)edge_plane(k) * pl + pj] = (float)x;
         }
     }
 }
@@ -401,7 +416,7 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
 // reverse of the marginals and of the unary factors; completes Xbo (point
 // planes) and writes the slot-common part Cbo. Two phases (marginals, unary),
 // each with its own loads, so that the kernel fits 256 registers and two waves
-// share a SIMD (29.8 us at 320 x 240, beside the recompute; 36.2 with 400).
+// share a SIMD (24.2 us at 320 x 240, beside the recompute; 36.2 with 400).
 __global__ __launch_bounds__(64, 2) void k_adj_belief(Geo g, Strengths s, Inputs in, const float* X,
                                                       const double* marg, const float* Ub, const float* Eb, float* Xbo,
                                                       float* Cbo, double* gsig, double* gk) {
@@ -431,8 +446,8 @@ __global__ __launch_bounds__(64, 2) void k_adj_belief(Geo g, Strengths s, Inputs
         // the belief of the marginals (unary + stored messages), kept by the recompute
         double L[28], eta[7], Pb[21], pb[6], BbS[28], ebS[7];
         float eb[29];
-        load_planes<28>(marg + 29 * pl, pl, o, L);
-        load_planes<7>(marg + 57 * pl, pl, o, eta);
+        load_planes<28>(marg + 2 * pl, pl, o, L);
+        load_planes<7>(marg + 30 * pl, pl, o, eta);
         load_planes<29>(Eb, pl, o, eb);
 #pragma unroll
         for (int k = 0; k < 21; ++k) Pb[k] = (double)eb[k];
@@ -554,16 +569,16 @@ __global__ void k_plane_to_dense(Geo g, const double* __restrict__ src, float* _
 static const dim3 kAdjBlock(64, 4);
 static dim3 adj_grid(const Geo& g) { return dim3((g.W + 63) / 64, (g.H + 3) / 4); }
 
-hipError_t launch_adj_update(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const float* M,
+hipError_t launch_adj_update(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const float* Xn,
                              const double* bel, const float* Xb, const float* Cb, float* Mb, float* Ub,
                              hipStream_t st) {
-    hipLaunchKernelGGL(k_adj_update, dim3((g.W + 63) / 64, g.H), dim3(64), 0, st, g, s, in, X, M, bel, Xb, Cb, Mb, Ub);
+    hipLaunchKernelGGL(k_adj_update, dim3((g.W + 63) / 64, g.H), dim3(64), 0, st, g, s, in, X, Xn, bel, Xb, Cb, Mb, Ub);
     return hipGetLastError();
 }
 
 hipError_t launch_adj_edges(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const double* marg,
-                            const float* M, const float* Mb, float* Xbo, float* Eb, double* gN, hipStream_t st) {
-    hipLaunchKernelGGL(k_adj_edges, dim3((g.W + 63) / 64, g.H), dim3(64, 4), 0, st, g, s, in, X, marg, M, Mb, Xbo, Eb,
+                            const float* Xn, const float* Mb, float* Xbo, float* Eb, double* gN, hipStream_t st) {
+    hipLaunchKernelGGL(k_adj_edges, dim3((g.W + 63) / 64, g.H), dim3(64, 4), 0, st, g, s, in, X, marg, Xn, Mb, Xbo, Eb,
                        gN);
     return hipGetLastError();
 }

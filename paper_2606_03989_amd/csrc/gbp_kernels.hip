@@ -121,24 +121,26 @@ __device__ inline void transport_message(Messages& ms, int d, const double m[7])
     ms.mn[d][0] = (float)fma(-(double)ms.mn[d][1], m[6], (double)ms.mn[d][0]);
 }
 
-// per-lane tape of the reverse sweep's recompute
+// per-lane tape of the reverse sweep's recompute. The new messages'
+// information is not on it: it is the next canonical state's, unchanged by the
+// transport.
 struct Tape {
-    float* lam;          // information of the new messages (88 FP32 planes: 21 + 1 per slot)
     double* bel;         // belief of the update (35 FP64 planes)
     float* canonical;    // canonical state after the update (not the last iteration of a segment)
-    double* marg;        // marginals and belief of the next emission (64 FP64 planes)
+    double* marg;        // depth marginal and belief of the next emission (37 FP64 planes)
 };
 
-// the marginals in the per-factor layout (k_pf_linearise): P 21, p 6, D, dv;
-// then the belief they come from: L 28, eta 7. The tape is written
-// non-temporally: it is read back only by the reverse sweep.
-__device__ inline void tape_marginals(double* marg, const Geo& g, unsigned o, const double P[21], const double pm[6],
-                                      double D, double dv, const double L[28], const double eta[7]) {
+// the depth marginal D, dv and the belief of an emission: L 28, eta 7 (the
+// pose marginal is one division and 27 multiply-adds of the belief and is
+// formed again by its reader). The tape is written non-temporally: it is read
+// back only by the reverse sweep.
+__device__ inline void tape_marginals(double* marg, const Geo& g, unsigned o, double D, double dv, const double L[28],
+                                      const double eta[7]) {
     GDouble* b = plane_of(marg);
     o = here(o);
 #pragma unroll
-    for (int k = 0; k < 64; ++k) {
-        const double x = k < 21 ? P[k] : k < 27 ? pm[k - 21] : k == 27 ? D : k == 28 ? dv : k < 57 ? L[k - 29] : eta[k - 57];
+    for (int k = 0; k < 37; ++k) {
+        const double x = k == 0 ? D : k == 1 ? dv : k < 30 ? L[k - 2] : eta[k - 30];
         __builtin_nontemporal_store(x, at(b, o));
         b = next(g, b);
     }
@@ -444,8 +446,8 @@ __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned 
         put<NT>(at(next(g, b), oh), act[d] ? (float)lp : 0.0f);
     }
     asm volatile("" : "+v"(l66), "+v"(D), "+v"(dv));
+    if constexpr (TAPE) tape_marginals(marg, g, o, D, dv, L, eta);
     pose_marginal(L, eta, l66, P, pm);
-    if constexpr (TAPE) tape_marginals(marg, g, o, P, pm, D, dv, L, eta);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         if (!has[d]) continue;
@@ -545,14 +547,6 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 #pragma unroll
             for (int k = 0; k < 6; ++k) ms.eta[d][k] = 0.0f;
             ms.mn[d][0] = ms.mn[d][1] = 0.0f;
-            if constexpr (TAPE) {
-                GFloat* b = plane_of(tape.lam, (long)(d * LAM_STRIDE) * g.plane);
-#pragma unroll
-                for (int k = 0; k < LAM_STRIDE; ++k) {
-                    __builtin_nontemporal_store(0.0f, at(b, o));
-                    b = next(g, b);
-                }
-            }
             continue;
         }
         double tj[6], ellj, qj[4], trj[3], r[6], e[6];
@@ -580,15 +574,6 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
         L[s7(6, 6)] += (double)nl;
         ms.mn[d][0] = (float)ne;
         ms.mn[d][1] = nl;
-        if constexpr (TAPE) {
-            // the new messages' information: the partials' FP32 values
-            GFloat* b = plane_of(tape.lam, (long)(d * LAM_STRIDE) * g.plane);
-#pragma unroll
-            for (int k = 0; k < LAM_STRIDE; ++k) {
-                __builtin_nontemporal_store(k < 21 ? ms.lam(d, k) : nl, at(b, o));
-                b = next(g, b);
-            }
-        }
     }
     if constexpr (TAPE) {
         GDouble* b = plane_of(tape.bel);
@@ -660,9 +645,8 @@ __global__ __launch_bounds__(64, 2) void k_fu_iterate(Geo g, Strengths s, Inputs
 }
 
 // the same passes for the reverse sweep's recompute: the prologue also writes
-// the belief of its state and its marginals, the final pass the new messages
-// computed from its source state and the belief they form with the unary
-// factors (exactly the values of k_pf_linearise, k_pf_messages, k_pf_update)
+// the belief of its state and its depth marginal, the final pass the belief of
+// the update (exactly the values of k_pf_linearise, k_pf_messages, k_pf_update)
 __global__ __launch_bounds__(64, 2) void k_fu_prologue_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                             float* __restrict__ Y, double* __restrict__ marg,
                                                             int* __restrict__ health) {
@@ -673,11 +657,13 @@ __global__ __launch_bounds__(64, 2) void k_fu_prologue_tape(Geo g, Strengths s, 
 }
 
 // the rotated form of the recompute: the update of iteration k from its
-// partial state X (new messages into tape.lam, belief into tape.bel, canonical
-// state k + 1 into tape.canonical) and the prologue of iteration k + 1
-// (partials into Y, marginals and belief into tape.marg) in one pass; the same
-// arithmetic as k_fu_final_tape followed by k_fu_prologue_tape on the
-// canonical state
+// partial state X (belief into tape.bel, canonical state k + 1 into
+// tape.canonical) and the prologue of iteration k + 1 (partials into Y, depth
+// marginal and belief into tape.marg) in one pass; the same arithmetic as the
+// final form followed by k_fu_prologue_tape on the canonical state. Bound by its
+// stores: 320 x 240, beside the reverse kernels, 68.5 us with 1,560 bytes
+// written per pixel; 76.9 with 2,128 (the messages' information and the pose
+// marginal on the tape as well).
 template <bool FINAL>
 __global__ __launch_bounds__(64, 2) void k_fu_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                    float* __restrict__ Y, Tape tape, float* __restrict__ var_ll,
@@ -1312,14 +1298,14 @@ hipError_t launch_fu_iterate(const Geo& g, const Strengths& s, const Inputs& in,
 
 hipError_t launch_fu_segment_tape(const Geo& g, const Strengths& s, const Inputs& in, const float* X0, float* seg,
                                   long seg_stride, int len, float* tA, float* tB, double* marg, long marg_stride,
-                                  float* M, long M_stride, double* bel, long bel_stride, float* var_ll, float* valid,
-                                  int* health, hipStream_t st) {
+                                  double* bel, long bel_stride, float* var_ll, float* valid, int* health,
+                                  hipStream_t st) {
     if (len < 1) return hipSuccess;
     const dim3 grid = grid2d(g, kBlock);
     hipLaunchKernelGGL(k_fu_prologue_tape, grid, kBlock, 0, st, g, s, in, X0, tA, marg, health);
     float* t[2] = {tA, tB};
     for (int k = 0; k < len; ++k) {
-        const Tape tape{M + M_stride * k, bel + bel_stride * k, seg + seg_stride * (k + 1), marg + marg_stride * (k + 1)};
+        const Tape tape{bel + bel_stride * k, seg + seg_stride * (k + 1), marg + marg_stride * (k + 1)};
         if (k + 1 < len)
             hipLaunchKernelGGL(k_fu_tape<false>, grid, kBlock, 0, st, g, s, in, t[k & 1], t[(k + 1) & 1], tape, var_ll,
                                valid, health);

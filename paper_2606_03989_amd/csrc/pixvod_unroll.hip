@@ -26,8 +26,7 @@ using namespace pv;
 
 namespace {
 constexpr int MSG_PLANES = 116;  // 4 x (eta 6, Lambda 21, normal eta, normal lambda): cotangents (FP64)
-constexpr int LAM_PLANES = 88;   // 4 x (Lambda 21, normal lambda): the tape of new messages (FP32)
-constexpr int MARG_PLANES = 64;  // pose marginal 21 + 6, depth marginal 2, their belief 28 + 7
+constexpr int MARG_PLANES = 37;  // depth marginal 2, its belief 28 + 7
 constexpr int BEL_PLANES = 35;   // belief of the update: 28 + 7
 constexpr int UB_PLANES = 42;
 constexpr int EB_PLANES = 36;
@@ -48,13 +47,11 @@ struct pixvod_unroll {
     float *var_ll = nullptr, *valid = nullptr;
     double *marg = nullptr, *bel = nullptr;
     float *Mb = nullptr, *Ub = nullptr, *Eb = nullptr;   // reverse-sweep cotangents, FP32 storage
-    float* M = nullptr;
     // the reverse sweep recomputes the next segment on a side stream while
     // the current one is reversed: a second set of recompute buffers (and of
     // frame-prep planes, for segments of the next frame)
     float *seg2 = nullptr, *tmp2 = nullptr, *sink2 = nullptr, *It2 = nullptr, *Gx2 = nullptr, *Gy2 = nullptr;
     double *marg2 = nullptr, *bel2 = nullptr;
-    float* M2 = nullptr;
     hipStream_t side = nullptr;
     std::vector<hipEvent_t> evs;      // two per segment of a reverse sweep
 
@@ -137,8 +134,8 @@ static bool ualloc(T** p, size_t n) {
 
 static void urelease(pixvod_unroll* u) {
     void* bufs[] = {u->Is, u->cxt, u->cyt, u->sig, u->It, u->Gx, u->Gy, u->frames, u->stage, u->X0, u->Xw[0],
-                    u->Xw[1], u->tape, u->Xend, u->seg, u->var_ll, u->valid, u->marg, u->M, u->bel, u->Mb, u->Ub, u->Eb,
-                    u->Cb[0], u->Cb[1], u->seg2, u->tmp2, u->sink2, u->It2, u->Gx2, u->Gy2, u->marg2, u->M2, u->bel2,
+                    u->Xw[1], u->tape, u->Xend, u->seg, u->var_ll, u->valid, u->marg, u->bel, u->Mb, u->Ub, u->Eb,
+                    u->Cb[0], u->Cb[1], u->seg2, u->tmp2, u->sink2, u->It2, u->Gx2, u->Gy2, u->marg2, u->bel2,
                     u->Xb[0], u->Xb[1], u->gsig, u->gN, u->gk, u->partial, u->stats, u->health};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -222,7 +219,6 @@ int pixvod_unroll_create(int H, int W, const pixvod_intrinsics* K, const pixvod_
               ualloc(&u->Xw[0], S) && ualloc(&u->Xw[1], S) && ualloc(&u->tape, S * (size_t)max_frames * spf) &&
               ualloc(&u->Xend, S) && ualloc(&u->seg, S * (size_t)ckpt_every) && ualloc(&u->var_ll, pl) &&
               ualloc(&u->valid, pl) && ualloc(&u->marg, pl * MARG_PLANES * (size_t)ckpt_every) &&
-              ualloc(&u->M, pl * LAM_PLANES * (size_t)ckpt_every) &&
               ualloc(&u->bel, pl * BEL_PLANES * (size_t)ckpt_every) &&
               ualloc(&u->Mb, pl * MSG_PLANES) && ualloc(&u->Ub, pl * UB_PLANES) && ualloc(&u->Eb, pl * EB_PLANES) &&
               ualloc(&u->Xb[0], S) && ualloc(&u->Xb[1], S) && ualloc(&u->gsig, pl) && ualloc(&u->gN, pl) &&
@@ -231,7 +227,6 @@ int pixvod_unroll_create(int H, int W, const pixvod_intrinsics* K, const pixvod_
               ualloc(&u->seg2, S * (size_t)ckpt_every) && ualloc(&u->tmp2, S) && ualloc(&u->sink2, S) &&
               ualloc(&u->It2, pl) && ualloc(&u->Gx2, pl) && ualloc(&u->Gy2, pl) &&
               ualloc(&u->marg2, pl * MARG_PLANES * (size_t)ckpt_every) &&
-              ualloc(&u->M2, pl * LAM_PLANES * (size_t)ckpt_every) &&
               ualloc(&u->bel2, pl * BEL_PLANES * (size_t)ckpt_every) &&
               ualloc(&u->stats, (size_t)max_frames * 8 + 8) && ualloc(&u->health, 1);
     if (ok) ok = hipHostMalloc((void**)&u->h_stats, ((size_t)max_frames * 8 + 8) * sizeof(double)) == hipSuccess;
@@ -402,12 +397,10 @@ int pixvod_unroll_backward(pixvod_unroll* u, const double* xi_bar, const float* 
     const int S_ = u->seg_per_frame, T = F * S_;
     struct Set {
         float *seg, *tmp, *sink;
-        double* marg;
-        float* M;
-        double* bel;
+        double *marg, *bel;
     };
-    const Set sets[2] = {{u->seg, u->Xw[0], u->Xw[1], u->marg, u->M, u->bel},
-                         {u->seg2, u->tmp2, u->sink2, u->marg2, u->M2, u->bel2}};
+    const Set sets[2] = {{u->seg, u->Xw[0], u->Xw[1], u->marg, u->bel},
+                         {u->seg2, u->tmp2, u->sink2, u->marg2, u->bel2}};
     Inputs ins[2] = {in, in};
     ins[1].It = u->It2;
     ins[1].Gx = u->Gx2;
@@ -435,15 +428,13 @@ int pixvod_unroll_backward(pixvod_unroll* u, const double* xi_bar, const float* 
             UHIP(launch_frame_prep(g, u->frames + N * f, u->W, const_cast<float*>(I.It), const_cast<float*>(I.Gx),
                                    const_cast<float*>(I.Gy), u->side));
         // states of the segment: seg[0] = checkpoint, seg[i] after i
-        // iterations; the recompute also keeps, per iteration, the marginals
-        // and the new messages of its source state (one prologue, then one
-        // rotated pass per iteration; the last state is not needed and goes
-        // to a work buffer)
+        // iterations; the recompute also keeps, per iteration, the beliefs of
+        // its emission and its update (one prologue, then one rotated pass per
+        // iteration; the last state stays in a work buffer of the set)
         const int len = seg_len(u, sg);
         UHIP(hipMemcpyAsync(B.seg, ckpt(u, f, sg), S * sizeof(float), hipMemcpyDeviceToDevice, u->side));
         UHIP(launch_fu_segment_tape(g, s, I, B.seg, B.seg, (long)S, len, B.tmp, B.sink, B.marg,
-                                    (long)(pl * MARG_PLANES), B.M, (long)(pl * LAM_PLANES), B.bel,
-                                    (long)(pl * BEL_PLANES), u->var_ll, u->valid, u->health, u->side));
+                                    (long)(pl * MARG_PLANES), B.bel, (long)(pl * BEL_PLANES), u->var_ll, u->valid, u->health, u->side));
         UHIP(hipEventRecord(evC[i], u->side));
         return PIXVOD_OK;
     };
@@ -475,13 +466,15 @@ int pixvod_unroll_backward(pixvod_unroll* u, const double* xi_bar, const float* 
             UHIP(launch_adj_inject(g, xend, u->Xb[cur], xb, rb, u->stream));
         }
         UHIP(hipStreamWaitEvent(u->stream, evC[i], 0));
-        for (int k = seg_len(u, sg) - 1; k >= 0; --k) {
+        const int len = seg_len(u, sg);
+        for (int k = len - 1; k >= 0; --k) {
             const float* X = B.seg + S * k;
+            // the state after the iteration: its messages' information is the new messages'
+            const float* Xn = k + 1 < len ? X + S : (len & 1 ? B.sink : B.tmp);
             const double* marg = B.marg + pl * MARG_PLANES * k;
-            const float* M = B.M + pl * LAM_PLANES * k;
             const double* bel = B.bel + pl * BEL_PLANES * k;
-            UHIP(launch_adj_update(g, s, I, X, M, bel, u->Xb[cur], u->Cb[cur], u->Mb, u->Ub, u->stream));
-            UHIP(launch_adj_edges(g, s, I, X, marg, M, u->Mb, u->Xb[cur ^ 1], u->Eb, u->gN, u->stream));
+            UHIP(launch_adj_update(g, s, I, X, Xn, bel, u->Xb[cur], u->Cb[cur], u->Mb, u->Ub, u->stream));
+            UHIP(launch_adj_edges(g, s, I, X, marg, Xn, u->Mb, u->Xb[cur ^ 1], u->Eb, u->gN, u->stream));
             UHIP(launch_adj_belief(g, s, I, X, marg, u->Ub, u->Eb, u->Xb[cur ^ 1], u->Cb[cur ^ 1], u->gsig, u->gk,
                                    u->stream));
             cur ^= 1;
