@@ -106,7 +106,8 @@ __global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs
                                                       const double* bel, const float* Xb, const float* Cb, float* Mb,
                                                       float* Ub) {
     __shared__ float buf[84 * 64];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
     const unsigned o = off_of(g, u, v);
     const long pl = g.plane;
@@ -255,7 +256,8 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
     __shared__ double sh[EDGE_PART][4][64];
     const int lane = threadIdx.x;
     const int d = __builtin_amdgcn_readfirstlane(threadIdx.y);
-    const int u = blockIdx.x * 64 + lane, v = blockIdx.y;
+    int u, v;
+    segment_pixel(lane, u, v);
     const long pl = g.plane;
     // the direction's planes, own and of the opposite slot
     const int od = opposite(d);
@@ -421,7 +423,8 @@ __global__ __launch_bounds__(64, 2) void k_adj_belief(Geo g, Strengths s, Inputs
                                                       const double* marg, const float* Ub, const float* Eb, float* Xbo,
                                                       float* Cbo, double* gsig, double* gk) {
     __shared__ float buf[14 * 64];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
     const unsigned o = off_of(g, u, v);
     const long pl = g.plane;

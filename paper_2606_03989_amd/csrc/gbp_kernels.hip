@@ -44,15 +44,18 @@ struct Messages {
     __device__ inline float lam(int d, int k) const { return d < LDS_DIRS ? lds[(d * 21 + k) * 64] : lam3[k]; }
 };
 
-// issues the loads of a pixel's stored messages (or partials in flight) but
-// the information of direction 3. buf: the wave's LDS planes, lane: the lane
+// issues the loads of a pixel's messages but the information of direction 3.
+// at_: where each slot is read, the pixel itself for stored messages and the
+// neighbour that sends it for partials in flight (a missing neighbour's is the
+// pixel's own: finite and not used). buf: the wave's LDS planes, lane: the lane
 // of the wave. The information matrices of the LDS directions may be read after
 // wait_lds_loads() only.
-__device__ inline void load_messages(const float* X, const Geo& g, unsigned o, float* buf, int lane, Messages& m) {
+__device__ inline void load_messages(const float* X, const Geo& g, const unsigned at_[4], float* buf, int lane,
+                                     Messages& m) {
     GFloat* b = plane_of(X, (long)P_MID * g.plane);
-    o = here(o);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
+        const unsigned o = here(at_[d]);
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             m.eta[d][k] = *at(b, o);
@@ -71,6 +74,7 @@ __device__ inline void load_messages(const float* X, const Geo& g, unsigned o, f
     b = plane_of(X, (long)P_MN * g.plane);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
+        const unsigned o = here(at_[d]);
         m.mn[d][0] = *at(b, o);
         b = next(g, b);
         m.mn[d][1] = *at(b, o);
@@ -369,7 +373,8 @@ __global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs 
                                                      const double* __restrict__ M, float* __restrict__ var_ll,
                                                      float* __restrict__ valid, int* __restrict__ health) {
     __shared__ float buf[LDS_WAVE];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
     const long p = pix_of(g, u, v);
     double tau[6], ell, q[4], R[9], t[3], L[28], eta[7], m[7], var;
@@ -425,7 +430,12 @@ __global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs 
 // fused schedule
 
 // sender side: partial messages of a pixel towards each neighbour, from its
-// belief (L, eta) and its stored messages, written to the neighbours' slots;
+// belief (L, eta) and its stored messages. They are written at the sender's
+// pixel, in the planes of the receiver's slot, and the receiver reads them at
+// its neighbour: a wave then stores whole cache lines. (Stored at the receiver,
+// a horizontal neighbour's line is written in two pieces by two waves, which
+// costs more than reading it twice: the pass's loads and stores alone, 1920 x
+// 1080, take 575 us with the stores shifted and 430 with the loads shifted.)
 // act: which edges' normal-integration factors are active
 template <bool NT, bool TAPE>
 __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned o, const bool has[4], const bool act[4],
@@ -438,7 +448,7 @@ __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned 
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         if (!has[d]) continue;
-        GFloat* b = plane_of(Y, (long)(P_MN + 2 * opposite(d)) * g.plane + step_of(g, d));
+        GFloat* b = plane_of(Y, (long)(P_MN + 2 * opposite(d)) * g.plane);
         const unsigned oh = here(o);
         double lp, hn;
         normal_partial(s.lamN, D - (double)ms.mn[d][1], dv - (double)ms.mn[d][0], lp, hn);
@@ -459,7 +469,7 @@ __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned 
 #pragma unroll
         for (int k = 0; k < 6; ++k) vv[k] = pm[k] - (double)ms.eta[d][k];
         ok = identity_partial(s.lamR, V, vv, Lp, h) && ok;
-        GFloat* b = plane_of(Y, (long)(P_MID + slot * MID_STRIDE) * g.plane + step_of(g, d));
+        GFloat* b = plane_of(Y, (long)(P_MID + slot * MID_STRIDE) * g.plane);
         const unsigned oh = here(o);
 #pragma unroll
         for (int k = 0; k < 27; ++k) {
@@ -471,7 +481,7 @@ __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned 
 }
 
 // prologue of one pixel: belief of the canonical state and the first partials
-template <bool NT, bool TAPE>
+template <bool TAPE>
 __device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& g, const Strengths& s, const Inputs& in,
                                                                      const float* __restrict__ X,
                                                                      float* __restrict__ Y, int* __restrict__ health,
@@ -485,7 +495,8 @@ __device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& 
     load_point_at(X, g, o, pt);
     const PixelInputs pin = load_inputs_at(s, in, o);
     edges_of(g, in, u, v, has, on, c);
-    load_messages(X, g, o, buf, lane, ms);
+    const unsigned own[4] = {o, o, o, o};
+    load_messages(X, g, own, buf, lane, ms);
     double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
     point_of(pt, tau, ell);
     pose_exp(tau, q, t);
@@ -497,8 +508,8 @@ __device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& 
     for (int d = 0; d < 4; ++d) add_message(L, eta, ms, d);
     bool act[4];
     active_edges(s, c, act);
-    const bool ok = emit_partials<NT, TAPE>(g, s, o, has, act, L, eta, ms, Y, marg);
-    store_point<NT>(Y, g, o, tau, ell);
+    const bool ok = emit_partials<false, TAPE>(g, s, o, has, act, L, eta, ms, Y, marg);
+    store_point<false>(Y, g, o, tau, ell);
     if (!ok) atomicOr(health, 1);
 }
 
@@ -508,15 +519,20 @@ __device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& 
 // whose address does not depend on computed values is issued before its first
 // use; the bilinear samples at the two warps stand under the prior's
 // arithmetic. The point is stored after the second samples' arrival: a wait
-// for loads also waits for the stores issued before them. NT: non-temporal
-// stores; TAPE: also writes the reverse sweep's tape.
-template <bool FINAL, bool NT, bool TAPE>
+// for loads also waits for the stores issued before them. TAPE: also writes the
+// reverse sweep's tape. The state is stored non-temporally: no line of it is
+// used again before the pass ends, and what is left in the L2 has to be written
+// back then (256 x 256: 19.7 us against 21.2; 1920 x 1080: 459 against 475; 64
+// mixed sequences: 1,747 against 1,785). Beside the reverse kernels, which read
+// the state soon, it is not (320 x 240: the pass with tape 66.5 us, 71 with).
+template <bool FINAL, bool TAPE>
 __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g, const Strengths& s, const Inputs& in,
                                                                     const float* __restrict__ X,
                                                                     float* __restrict__ Y, float* __restrict__ var_ll,
                                                                     float* __restrict__ valid,
                                                                     int* __restrict__ health, int u, int v, float* buf,
                                                                     int lane, const Tape& tape) {
+    constexpr bool NT = !TAPE;
     const unsigned o = off_of(g, u, v);
     Messages ms;
     bool has[4];
@@ -527,7 +543,7 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
     edges_of(g, in, u, v, has, on, c);
 #pragma unroll
     for (int d = 0; d < 4; ++d) load_point_at(X, g, on[d], npt[d]);
-    load_messages(X, g, o, buf, lane, ms);
+    load_messages(X, g, on, buf, lane, ms);
 
     // --- linearise at the current point
     double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
@@ -538,7 +554,7 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 
     // --- complete the partials in flight with the residuals at both points
     wait_lds_loads();
-    load_lam3(X, g, o, ms);
+    load_lam3(X, g, on[3], ms);
     bool act[4];
     active_edges(s, c, act);
 #pragma unroll
@@ -620,18 +636,19 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 
 // Fused passes of one image: one wave per workgroup, 64 pixels of a row, so
 // that a SIMD takes the next row segment as soon as one of its two waves ends.
-// Bound by memory where the image fills the chip (640 x 480: 83.6 us per pass,
+// Bound by memory where the image fills the chip (640 x 480: 80 us per pass,
 // 302 MB of algorithmic bytes, whose copy at this card's 4.74 TB/s takes 64 us;
-// 127 us before, as one wave per SIMD of a persistent workgroup with 504
+// 1920 x 1080: 459 us, copy 431; 127 and 830 us before, as one wave per SIMD of a persistent workgroup with 504
 // registers) and by one wave's chain of instructions and loads where it does
 // not (32 x 24: 17.0 us, 21.2 before; 4,218 vector instructions per wave, 6,234
 // before).
 __global__ __launch_bounds__(64, 2) void k_fu_prologue(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                        float* __restrict__ Y, int* __restrict__ health) {
     __shared__ float buf[LDS_WAVE];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
-    prologue_pixel<false, false>(g, s, in, X, Y, health, u, v, buf, threadIdx.x, nullptr);
+    prologue_pixel<false>(g, s, in, X, Y, health, u, v, buf, threadIdx.x, nullptr);
 }
 
 template <bool FINAL>
@@ -639,9 +656,10 @@ __global__ __launch_bounds__(64, 2) void k_fu_iterate(Geo g, Strengths s, Inputs
                                                       float* __restrict__ Y, float* __restrict__ var_ll,
                                                       float* __restrict__ valid, int* __restrict__ health) {
     __shared__ float buf[LDS_WAVE];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
-    iterate_pixel<FINAL, FINAL, false>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, Tape{});
+    iterate_pixel<FINAL, false>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, Tape{});
 }
 
 // the same passes for the reverse sweep's recompute: the prologue also writes
@@ -651,9 +669,10 @@ __global__ __launch_bounds__(64, 2) void k_fu_prologue_tape(Geo g, Strengths s, 
                                                             float* __restrict__ Y, double* __restrict__ marg,
                                                             int* __restrict__ health) {
     __shared__ float buf[LDS_WAVE];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
-    prologue_pixel<false, true>(g, s, in, X, Y, health, u, v, buf, threadIdx.x, marg);
+    prologue_pixel<true>(g, s, in, X, Y, health, u, v, buf, threadIdx.x, marg);
 }
 
 // the rotated form of the recompute: the update of iteration k from its
@@ -669,9 +688,10 @@ __global__ __launch_bounds__(64, 2) void k_fu_tape(Geo g, Strengths s, Inputs in
                                                    float* __restrict__ Y, Tape tape, float* __restrict__ var_ll,
                                                    float* __restrict__ valid, int* __restrict__ health) {
     __shared__ float buf[LDS_WAVE];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
-    iterate_pixel<FINAL, false, true>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, tape);
+    iterate_pixel<FINAL, true>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, tape);
 }
 
 // ---------------------------------------------------------------------------
@@ -684,7 +704,7 @@ __global__ __launch_bounds__(64, 2) void k_fu_tape(Geo g, Strengths s, Inputs in
 // marginals of the new state for the next pass; state and marginals alternate
 // between two buffers. The per-factor kernels' arithmetic without their
 // message planes (928 bytes per pixel written and read back) and second
-// linearisation: 45 us per iteration at 320 x 240, where the three launches
+// linearisation: 41 us per iteration at 320 x 240, where the three launches
 // took 87 us (72 with this pass's algebra). Bound by the latency of the four
 // senders' gathered loads: 1,200 waves on 1,024 SIMDs.
 template <bool FINAL>
@@ -694,7 +714,8 @@ __global__ __launch_bounds__(64, 2) void k_damped_iterate(Geo g, Strengths s, In
                                                           float* __restrict__ var_ll, float* __restrict__ valid,
                                                           int* __restrict__ health) {
     __shared__ float buf[LDS_WAVE];
-    const int u = blockIdx.x * 64 + threadIdx.x, v = blockIdx.y;
+    int u, v;
+    segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
     const unsigned o = off_of(g, u, v);
     bool has[4], act[4];
@@ -1025,7 +1046,7 @@ __global__ __launch_bounds__(256, 2) void k_batch_prologue(const SeqDesc* __rest
     if (!batch_pixel(seqs, work, d, u, v, item)) return;
     const float* X = parity ? d->X1 : d->X0;
     float* Y = parity ? d->X0 : d->X1;
-    prologue_pixel<false, false>(d->g, s, d->in, X, Y, health, u, v, buf, lane, nullptr);
+    prologue_pixel<false>(d->g, s, d->in, X, Y, health, u, v, buf, lane, nullptr);
 }
 
 template <bool FINAL>
@@ -1037,7 +1058,7 @@ __global__ __launch_bounds__(256, 2) void k_batch_iterate(const SeqDesc* __restr
     if (!batch_pixel(seqs, work, d, u, v, item)) return;
     const float* X = parity ? d->X1 : d->X0;
     float* Y = parity ? d->X0 : d->X1;
-    iterate_pixel<FINAL, true, false>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v, buf, lane, Tape{});
+    iterate_pixel<FINAL, false>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v, buf, lane, Tape{});
 }
 
 // per sequence (blockIdx.y) and 64 x 4 tile of its image (blockIdx.x): the
@@ -1135,7 +1156,7 @@ __global__ __launch_bounds__(256, 2) void k_batch_persistent(const SeqDesc* __re
                 const float* X = par ? d->X1 : d->X0;
                 float* Y = par ? d->X0 : d->X1;
                 wait_lds_reads();   // of the wave's previous item
-                iterate_pixel<false, true, false>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v, buf, lane,
+                iterate_pixel<false, false>(d->g, s, d->in, X, Y, d->var_ll, d->valid, health, u, v, buf, lane,
                                                   Tape{});
             }
         }
