@@ -92,6 +92,8 @@ struct SeqDesc {
     float* Is;            // keyframe-prep outputs (same planes as in.Is, in.cxt, in.cyt)
     float* cxt;
     float* cyt;
+    float* inv_depth;     // output maps (dense H * W) of the current step, or NULL
+    float* inv_var;
     int tile_base;        // natural index of the sequence's first work item
     int tiles_x;          // tiles per image row
     int n_tiles;

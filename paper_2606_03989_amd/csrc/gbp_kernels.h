@@ -58,6 +58,9 @@ hipError_t launch_copy_plane(const Geo& g, const float* dense, float* plane, hip
 // per-sequence statistics, keyframe test and re-anchoring (canonical state
 // ends in buffer parity ^ (n > 0 ? (n + 1) & 1 : 0))
 hipError_t launch_batch_frame_step(const BatchLaunch& b, int n_iters, hipStream_t st);
+// the output maps of every sequence that asks for them (canonical state in
+// buffer `parity`), to device memory or pinned host memory
+hipError_t launch_batch_outputs(const BatchLaunch& b, int parity, hipStream_t st);
 // p[0 .. n) = value
 hipError_t launch_set_ints(int* p, int n, int value, hipStream_t st);
 // keyframe test of the frame just tracked and, if b.reanchor, re-anchoring of

@@ -638,7 +638,7 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 // that a SIMD takes the next row segment as soon as one of its two waves ends.
 // Bound by memory where the image fills the chip (640 x 480: 80 us per pass,
 // 302 MB of algorithmic bytes, whose copy at this card's 4.74 TB/s takes 64 us;
-// 1920 x 1080: 459 us, copy 431; 127 and 830 us before, as one wave per SIMD of a persistent workgroup with 504
+// 1920 x 1080: 459 us, copy 431; 127 us at 640 x 480 before, as one wave per SIMD of a persistent workgroup with 504
 // registers) and by one wave's chain of instructions and loads where it does
 // not (32 x 24: 17.0 us, 21.2 before; 4,218 vector instructions per wave, 6,234
 // before).
@@ -954,17 +954,21 @@ __global__ __launch_bounds__(RED_THREADS) void k_frame_final(int nblocks, const 
     if (health && threadIdx.x == 0) result[8] = (double)*health;
 }
 
-// output maps: inverse depth and its delta-method variance (dense H x W)
+// a pixel's output maps: inverse depth and its delta-method variance
+__device__ inline void output_pixel(const Geo& g, const float* X, const float* var_ll, int have_var, long p, long o,
+                                    float* inv_depth, float* inv_var) {
+    const double rho = exp(-(double)X[(long)P_ELL * g.plane + p]);
+    if (inv_depth) inv_depth[o] = (float)rho;
+    if (inv_var) inv_var[o] = have_var ? (float)(rho * rho * (double)var_ll[p]) : __int_as_float(0x7fc00000);
+}
+
+// the output maps (dense H x W)
 __global__ void k_outputs(Geo g, const float* __restrict__ X, const float* __restrict__ var_ll, int have_var,
                           float* __restrict__ inv_depth, float* __restrict__ inv_var) {
     const int u = blockIdx.x * blockDim.x + threadIdx.x;
     const int v = blockIdx.y * blockDim.y + threadIdx.y;
     if (u >= g.W || v >= g.H) return;
-    const long p = pix_of(g, u, v);
-    const double rho = exp(-(double)X[(long)P_ELL * g.plane + p]);
-    const long o = (long)v * g.W + u;
-    if (inv_depth) inv_depth[o] = (float)rho;
-    if (inv_var) inv_var[o] = have_var ? (float)(rho * rho * (double)var_ll[p]) : __int_as_float(0x7fc00000);
+    output_pixel(g, X, var_ll, have_var, pix_of(g, u, v), (long)v * g.W + u, inv_depth, inv_var);
 }
 
 // valid-warp flags of the current state without iterating (n_iters == 0)
@@ -1080,6 +1084,17 @@ __global__ __launch_bounds__(RED_THREADS) void k_batch_final(const SeqDesc* __re
     image_stats(partial + (long)d->stat_base * 8, stat_tiles(d->g.H, d->g.W), result + (long)blockIdx.x * 8);
 }
 
+// the output maps of the sequences that ask for them, sequence blockIdx.y: in
+// dense order, so that maps in pinned host memory leave the chip in whole lines
+__global__ __launch_bounds__(256) void k_batch_outputs(const SeqDesc* __restrict__ seqs, int parity) {
+    const SeqDesc* d = &seqs[blockIdx.y];
+    if (!d->inv_depth && !d->inv_var) return;
+    const float* X = parity ? d->X1 : d->X0;
+    const int W = d->g.W, N = d->g.H * W;
+    for (int i = blockIdx.x * 256 + (int)threadIdx.x; i < N; i += gridDim.x * 256)
+        output_pixel(d->g, X, d->var_ll, 1, pix_of(d->g, i % W, i / W), i, d->inv_depth, d->inv_var);
+}
+
 static void launch_batch_stats(const BatchLaunch& b, int parity, hipStream_t st) {
     hipLaunchKernelGGL(k_batch_stats, dim3(b.max_stat_tiles, b.n_seq), dim3(RED_THREADS), 0, st, b.seqs, parity,
                        b.partial);
@@ -1183,6 +1198,13 @@ hipError_t launch_batch_frame_step(const BatchLaunch& b, int n_iters, hipStream_
     }
     launch_batch_stats(b, parity, st);
     return launch_batch_keyframe(b, parity, st);
+}
+
+hipError_t launch_batch_outputs(const BatchLaunch& b, int parity, hipStream_t st) {
+    // a statistics tile is 256 pixels of the largest image
+    const int blocks = b.max_stat_tiles < 64 ? b.max_stat_tiles : 64;
+    hipLaunchKernelGGL(k_batch_outputs, dim3(blocks, b.n_seq), dim3(256), 0, st, b.seqs, parity);
+    return hipGetLastError();
 }
 
 hipError_t launch_set_ints(int* p, int n, int value, hipStream_t st) {

@@ -18,6 +18,7 @@
 #include "gbp_kernels.h"
 #include "gbp_transfer.h"
 #include "gbp_tree.h"
+#include "host_maps.hpp"
 #include "runtime_internal.h"
 
 using namespace pv;
@@ -48,9 +49,10 @@ struct pixvod_ctx {
     unsigned* zbuf = nullptr;            // depth-transfer z-buffer (allocated on first use)
     double* marg = nullptr;
     double* msg = nullptr;
-    double *partial = nullptr, *result = nullptr;
+    double* partial = nullptr;
     int* health = nullptr;
-    double* h_result = nullptr;
+    double* h_result = nullptr;          // pinned: the frame reductions are written here
+    MapStage maps;                       // output maps on their way to host memory
     bool have_kf = false, have_frame = false, has_sigma = false, have_track = false, have_var = false;
     double T_w_kf[16];
     double xi_last[6];
@@ -302,10 +304,11 @@ static void prof_collect(pixvod_ctx* c) {
 static void release(pixvod_ctx* c) {
     void* bufs[] = {c->X[0], c->X[1], c->NX[0], c->NX[1], c->Is, c->cxt, c->cyt, c->sig, c->It, c->Gx, c->Gy, c->prior_ell, c->var_ll,
                     c->valid, c->frame_stage, c->kf_stage, c->out_stage, c->dense_state, c->zbuf, c->marg, c->msg,
-                    c->partial, c->result, c->health};
+                    c->partial, c->health};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     if (c->h_result) (void)hipHostFree(c->h_result);
+    c->maps.release();
     for (auto& t : c->tgraph) {
         if (t.exec) (void)hipGraphExecDestroy(t.exec);
         for (hipEvent_t e : t.ev) (void)hipEventDestroy(e);
@@ -399,7 +402,6 @@ int pixvod_create(int H, int W, const pixvod_intrinsics* K, const pixvod_params*
     if (!rc) rc = dev_alloc(c, &c->kf_stage, N * 4);
     if (!rc) rc = dev_alloc(c, &c->out_stage, N * 2);
     if (!rc) rc = dev_alloc(c, &c->partial, (size_t)nb * 8);
-    if (!rc) rc = dev_alloc(c, &c->result, 9);
     if (!rc) rc = dev_alloc(c, &c->health, 1);
     if (!rc && hipHostMalloc((void**)&c->h_result, 9 * sizeof(double)) != hipSuccess) rc = PIXVOD_ENOMEM;
     if (!rc && hipStreamCreateWithFlags(&c->own_stream, hipStreamNonBlocking) != hipSuccess) rc = PIXVOD_EHIP;
@@ -765,7 +767,7 @@ static std::vector<unsigned char> track_graph_key(const pixvod_ctx* c, int n_ite
     const Inputs in = inputs_of(c);
     const void* ptrs[] = {in.Is,     in.cxt,   in.cyt,      in.sigD,   in.It,     in.Gx,       in.Gy,
                           in.prior_ell, c->X[0], c->X[1], c->var_ll, c->valid, c->health, c->partial,
-                          c->result};
+                          c->h_result};
     key_put(k, ptrs);
     key_put(k, n_iters);
     key_put(k, c->prof);
@@ -816,7 +818,7 @@ static int track_graph_capture(pixvod_ctx* c, pixvod_ctx::TrackGraph& t, int src
     t.kind.push_back(PIXVOD_PROF_FUSED_FINAL);
     t.launches.push_back(1);
     if (le == hipSuccess)
-        le = launch_frame_stats(g, c->X[cur], c->valid, 1, c->partial, c->result, c->stream, c->health);
+        le = launch_frame_stats(g, c->X[cur], c->valid, 1, c->partial, c->h_result, c->stream, c->health);
     hipGraph_t gr = nullptr;
     const hipError_t ce = hipStreamEndCapture(c->stream, &gr);
     if (le != hipSuccess || ce != hipSuccess) {
@@ -900,17 +902,26 @@ int pixvod_track(pixvod_ctx* c, const float* frame, int where, int n_iters, pixv
             rc = run_iterations(c, n_iters);
             if (rc) return rc;
         }
-        HIP_TRY(c, launch_frame_stats(g, c->X[c->cur], c->valid, 1, c->partial, c->result, c->stream, c->health));
+        HIP_TRY(c, launch_frame_stats(g, c->X[c->cur], c->valid, 1, c->partial, c->h_result, c->stream, c->health));
     }
+    MapJob jobs[2];
+    int n_jobs = 0;
     if (out->inv_depth || out->inv_depth_var) {
         float* d_inv = out->inv_depth;
         float* d_var = out->inv_depth_var;
+        bool staged = false;
         if (out->out_where == PIXVOD_HOST) {
-            d_inv = out->inv_depth ? c->out_stage : nullptr;
-            d_var = out->inv_depth_var ? c->out_stage + N : nullptr;
+            // the maps in pinned memory, or in device memory and copied
+            float* pinned = c->maps.reserve(2 * N);
+            staged = pinned != nullptr;
+            float* stage = staged ? pinned : c->out_stage;
+            d_inv = out->inv_depth ? stage : nullptr;
+            d_var = out->inv_depth_var ? stage + N : nullptr;
+            if (staged && d_inv) jobs[n_jobs++] = {out->inv_depth, d_inv, N};
+            if (staged && d_var) jobs[n_jobs++] = {out->inv_depth_var, d_var, N};
         }
         HIP_TRY(c, launch_outputs(g, c->X[c->cur], c->var_ll, c->have_var ? 1 : 0, d_inv, d_var, c->stream));
-        if (out->out_where == PIXVOD_HOST) {
+        if (out->out_where == PIXVOD_HOST && !staged) {
             if (out->inv_depth)
                 HIP_TRY(c, hipMemcpyAsync(out->inv_depth, c->out_stage, N * sizeof(float), hipMemcpyDeviceToHost,
                                           c->stream));
@@ -919,8 +930,9 @@ int pixvod_track(pixvod_ctx* c, const float* frame, int where, int n_iters, pixv
                                           hipMemcpyDeviceToHost, c->stream));
         }
     }
-    HIP_TRY(c, hipMemcpyAsync(c->h_result, c->result, 9 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    MapCopier copier(jobs, n_jobs);
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    copier.run();
     if (!c->pending.empty() || !c->graph_pending.empty()) prof_collect(c);
 
     const double inv_n = 1.0 / (double)N;
@@ -1096,6 +1108,8 @@ struct pixvod_batch {
     SeqDesc* h_desc = nullptr;           // pinned staging of the descriptors
     int *d_fsk = nullptr;                // per sequence: frames since the keyframe (device keyframe test)
     unsigned *d_flags = nullptr, *h_flags = nullptr;
+    MapStage maps;                       // output maps on their way to host memory
+    std::vector<MapJob> jobs;            // their copies of the present step (room for two per sequence)
     bool persistent = false;             // iteration block as one cooperative launch
     int persistent_grid = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -1164,6 +1178,7 @@ static void batch_release(pixvod_batch* b) {
     if (b->h_health) (void)hipHostFree(b->h_health);
     if (b->h_flags) (void)hipHostFree(b->h_flags);
     if (b->h_desc) (void)hipHostFree(b->h_desc);
+    b->maps.release();
     if (b->ev0) (void)hipEventDestroy(b->ev0);
     if (b->ev1) (void)hipEventDestroy(b->ev1);
     if (b->own_stream) (void)hipStreamDestroy(b->own_stream);
@@ -1289,6 +1304,7 @@ int pixvod_batch_create(int n, const int* H, const int* W, const pixvod_intrinsi
     b->n = n;
     b->P = P;
     b->seq.resize(n);
+    b->jobs.reserve(2 * (size_t)n);
     int rc = PIXVOD_OK;
     auto alloc = [&](float** p, size_t cnt) {
         if (rc) return;
@@ -1476,6 +1492,37 @@ static int batch_step(pixvod_batch* b, const float* const* frames, const float* 
             d.normals = reanchor ? normals[i] : nullptr;
         }
     }
+    // where the step's output maps go: device memory as given, host memory
+    // through the batch's pinned memory or (no room there) device staging
+    b->jobs.clear();
+    size_t n_host = 0;
+    bool any_maps = false;
+    for (int i = 0; i < b->n; ++i) {
+        const pixvod_track_out& o = outs[i];
+        const size_t N = (size_t)b->seq[i].H * b->seq[i].W;
+        any_maps = any_maps || o.inv_depth || o.inv_depth_var;
+        if (o.out_where == PIXVOD_HOST) n_host += (o.inv_depth ? N : 0) + (o.inv_depth_var ? N : 0);
+    }
+    float* pinned = n_host ? b->maps.reserve(n_host) : nullptr;
+    const bool staged = pinned != nullptr;
+    for (int i = 0; i < b->n; ++i) {
+        BatchSeq& q = b->seq[i];
+        SeqDesc& d = b->descs[i];
+        const pixvod_track_out& o = outs[i];
+        const size_t N = (size_t)q.H * q.W;
+        d.inv_depth = o.inv_depth;
+        d.inv_var = o.inv_depth_var;
+        if (o.out_where != PIXVOD_HOST) continue;
+        float* const host[2] = {o.inv_depth, o.inv_depth_var};
+        float** const dev[2] = {&d.inv_depth, &d.inv_var};
+        for (int k = 0; k < 2; ++k) {
+            if (!host[k]) continue;
+            *dev[k] = staged ? pinned : q.out_stage + k * N;
+            if (!staged) continue;
+            b->jobs.push_back({host[k], pinned, N});
+            pinned += N;
+        }
+    }
     std::memcpy(b->h_desc, b->descs.data(), sizeof(SeqDesc) * b->n);
     HIP_TRY_B(b, hipMemcpyAsync(b->d_seqs, b->h_desc, sizeof(SeqDesc) * b->n, hipMemcpyHostToDevice, b->stream));
     if (b->persistent) {
@@ -1499,30 +1546,23 @@ static int batch_step(pixvod_batch* b, const float* const* frames, const float* 
                                 b->stream));
     HIP_TRY_B(b, hipMemcpyAsync(b->h_health, b->d_health, sizeof(int), hipMemcpyDeviceToHost, b->stream));
     HIP_TRY_B(b, hipMemcpyAsync(b->h_flags, b->d_flags, sizeof(unsigned) * b->n, hipMemcpyDeviceToHost, b->stream));
-    for (int i = 0; i < b->n; ++i) {
-        BatchSeq& q = b->seq[i];
-        pixvod_track_out* o = &outs[i];
-        if (!o->inv_depth && !o->inv_depth_var) continue;
+    // re-anchoring keeps the log-depths and the variance plane: the maps are
+    // those of the frame just tracked
+    if (any_maps) HIP_TRY_B(b, launch_batch_outputs(batch_launch_args(b), b->parity, b->stream));
+    for (int i = 0; i < b->n && !staged; ++i) {
+        const BatchSeq& q = b->seq[i];
+        const pixvod_track_out* o = &outs[i];
+        if (o->out_where != PIXVOD_HOST) continue;
         const size_t N = (size_t)q.H * q.W;
-        float* di = o->inv_depth;
-        float* dv = o->inv_depth_var;
-        if (o->out_where == PIXVOD_HOST) {
-            di = o->inv_depth ? q.out_stage : nullptr;
-            dv = o->inv_depth_var ? q.out_stage + N : nullptr;
-        }
-        // re-anchoring keeps the log-depths and the variance plane: the maps
-        // are those of the frame just tracked
-        HIP_TRY_B(b, launch_outputs(geo_of_seq(q), q.X[b->parity], q.var_ll, 1, di, dv, b->stream));
-        if (o->out_where == PIXVOD_HOST) {
-            if (o->inv_depth)
-                HIP_TRY_B(b, hipMemcpyAsync(o->inv_depth, q.out_stage, N * sizeof(float), hipMemcpyDeviceToHost,
-                                            b->stream));
-            if (o->inv_depth_var)
-                HIP_TRY_B(b, hipMemcpyAsync(o->inv_depth_var, q.out_stage + N, N * sizeof(float),
-                                            hipMemcpyDeviceToHost, b->stream));
-        }
+        if (o->inv_depth)
+            HIP_TRY_B(b, hipMemcpyAsync(o->inv_depth, q.out_stage, N * sizeof(float), hipMemcpyDeviceToHost, b->stream));
+        if (o->inv_depth_var)
+            HIP_TRY_B(b, hipMemcpyAsync(o->inv_depth_var, q.out_stage + N, N * sizeof(float), hipMemcpyDeviceToHost,
+                                        b->stream));
     }
+    MapCopier copier(b->jobs.data(), (int)b->jobs.size());
     HIP_TRY_B(b, hipStreamSynchronize(b->stream));
+    copier.run();
     float ms = 0.0f;
     if (hipEventElapsedTime(&ms, b->ev0, b->ev1) == hipSuccess) b->last_ms = ms;
     for (int i = 0; i < b->n; ++i) {
