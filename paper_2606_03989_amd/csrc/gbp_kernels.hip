@@ -108,21 +108,25 @@ __device__ inline void add_message(double L[28], double eta[7], const Messages& 
 }
 
 // first-order transport of a stored message by the mean step (Sec. 4.1)
-__device__ inline void transport_message(Messages& ms, int d, const double m[7]) {
+template <class Lam>
+__device__ inline void transport(float eta[6], float mn[2], Lam lam, const double m[7]) {
     double e[6];
 #pragma unroll
-    for (int a = 0; a < 6; ++a) e[a] = (double)ms.eta[d][a];
+    for (int a = 0; a < 6; ++a) e[a] = (double)eta[a];
 #pragma unroll
     for (int r = 0; r < 6; ++r)
 #pragma unroll
         for (int c = r; c < 6; ++c) {
-            const double l = (double)ms.lam(d, s6(r, c));
+            const double l = (double)lam(s6(r, c));
             e[r] = fma(-l, m[c], e[r]);
             if (r != c) e[c] = fma(-l, m[r], e[c]);
         }
 #pragma unroll
-    for (int a = 0; a < 6; ++a) ms.eta[d][a] = (float)e[a];
-    ms.mn[d][0] = (float)fma(-(double)ms.mn[d][1], m[6], (double)ms.mn[d][0]);
+    for (int a = 0; a < 6; ++a) eta[a] = (float)e[a];
+    mn[0] = (float)fma(-(double)mn[1], m[6], (double)mn[0]);
+}
+__device__ inline void transport_message(Messages& ms, int d, const double m[7]) {
+    transport(ms.eta[d], ms.mn[d], [&](int k) { return ms.lam(d, k); }, m);
 }
 
 // per-lane tape of the reverse sweep's recompute. The new messages'
@@ -436,7 +440,37 @@ __global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs 
 // a horizontal neighbour's line is written in two pieces by two waves, which
 // costs more than reading it twice: the pass's loads and stores alone, 1920 x
 // 1080, take 575 us with the stores shifted and 430 with the loads shifted.)
-// act: which edges' normal-integration factors are active
+// mn, eta, lam: the pixel's stored messages of direction d; act: whether its
+// normal-integration factor is active
+template <bool NT>
+__device__ inline void emit_normal(const Geo& g, const Strengths& s, unsigned o, int d, double D, double dv,
+                                   const float mn[2], bool act, float* Y) {
+    GFloat* b = plane_of(Y, (long)(P_MN + 2 * opposite(d)) * g.plane);
+    const unsigned oh = here(o);
+    double lp, hn;
+    normal_partial(s.lamN, D - (double)mn[1], dv - (double)mn[0], lp, hn);
+    put<NT>(at(b, oh), act ? (float)hn : 0.0f);
+    put<NT>(at(next(g, b), oh), act ? (float)lp : 0.0f);
+}
+template <bool NT, class Lam>
+__device__ inline bool emit_identity(const Geo& g, const Strengths& s, unsigned o, int d, const double P[21],
+                                     const double p[6], const float eta[6], Lam lam, float* Y) {
+    double V[21], vv[6], Lp[21], h[6];
+#pragma unroll
+    for (int k = 0; k < 21; ++k) V[k] = P[k] - (double)lam(k);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) vv[k] = p[k] - (double)eta[k];
+    const bool ok = identity_partial(s.lamR, V, vv, Lp, h);
+    GFloat* b = plane_of(Y, (long)(P_MID + opposite(d) * MID_STRIDE) * g.plane);
+    const unsigned oh = here(o);
+#pragma unroll
+    for (int k = 0; k < 27; ++k) {
+        put<NT>(at(b, oh), k < 6 ? (float)h[k] : (float)Lp[k - 6]);
+        b = next(g, b);
+    }
+    return ok;
+}
+
 template <bool NT, bool TAPE>
 __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned o, const bool has[4], const bool act[4],
                                      const double L[28], const double eta[7], const Messages& ms,
@@ -446,15 +480,8 @@ __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned 
     // the depth marginal and what is sent of it are finished before the pose
     // marginal takes the belief's registers
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        if (!has[d]) continue;
-        GFloat* b = plane_of(Y, (long)(P_MN + 2 * opposite(d)) * g.plane);
-        const unsigned oh = here(o);
-        double lp, hn;
-        normal_partial(s.lamN, D - (double)ms.mn[d][1], dv - (double)ms.mn[d][0], lp, hn);
-        put<NT>(at(b, oh), act[d] ? (float)hn : 0.0f);
-        put<NT>(at(next(g, b), oh), act[d] ? (float)lp : 0.0f);
-    }
+    for (int d = 0; d < 4; ++d)
+        if (has[d]) emit_normal<NT>(g, s, o, d, D, dv, ms.mn[d], act[d], Y);
     asm volatile("" : "+v"(l66), "+v"(D), "+v"(dv));
     if constexpr (TAPE) tape_marginals(marg, g, o, D, dv, L, eta);
     pose_marginal(L, eta, l66, P, pm);
@@ -462,20 +489,7 @@ __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned 
     for (int d = 0; d < 4; ++d) {
         if (!has[d]) continue;
         reread_lds();
-        const int slot = opposite(d);
-        double V[21], vv[6], Lp[21], h[6];
-#pragma unroll
-        for (int k = 0; k < 21; ++k) V[k] = P[k] - (double)ms.lam(d, k);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) vv[k] = pm[k] - (double)ms.eta[d][k];
-        ok = identity_partial(s.lamR, V, vv, Lp, h) && ok;
-        GFloat* b = plane_of(Y, (long)(P_MID + slot * MID_STRIDE) * g.plane);
-        const unsigned oh = here(o);
-#pragma unroll
-        for (int k = 0; k < 27; ++k) {
-            put<NT>(at(b, oh), k < 6 ? (float)h[k] : (float)Lp[k - 6]);
-            b = next(g, b);
-        }
+        ok = emit_identity<NT>(g, s, o, d, P, pm, ms.eta[d], [&](int k) { return ms.lam(d, k); }, Y) && ok;
     }
     return ok;
 }
@@ -640,8 +654,8 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 // 302 MB of algorithmic bytes, whose copy at this card's 4.74 TB/s takes 64 us;
 // 1920 x 1080: 459 us, copy 431; 127 us at 640 x 480 before, as one wave per SIMD of a persistent workgroup with 504
 // registers) and by one wave's chain of instructions and loads where it does
-// not (32 x 24: 17.0 us, 21.2 before; 4,218 vector instructions per wave, 6,234
-// before).
+// not (256 x 256: 19.7 us, 27 before; 4,218 vector instructions per wave, 6,234
+// before; the smallest images take k_fu_split).
 __global__ __launch_bounds__(64, 2) void k_fu_prologue(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                        float* __restrict__ Y, int* __restrict__ health) {
     __shared__ float buf[LDS_WAVE];
@@ -692,6 +706,188 @@ __global__ __launch_bounds__(64, 2) void k_fu_tape(Geo g, Strengths s, Inputs in
     segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
     iterate_pixel<FINAL, true>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x, tape);
+}
+
+// The pass of an image that leaves the chip idle: four waves per 64 pixels, a
+// direction each. A wave completes, transports and sends on its own direction's
+// message; what they all need, the linearisations, the solve and the marginals,
+// each computes for itself from the same values in the same order, so that the
+// pass agrees with iterate_pixel bit for bit. Bound by one wave's chain, which
+// the split shortens: 32 x 24, 10.2 us per pass and 16.8 in one wave; with tape,
+// 48 x 48, 13.1 and 23.3.
+
+template <bool FINAL, bool TAPE>
+__global__ __launch_bounds__(256, 2) void k_fu_split(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
+                                                     float* __restrict__ Y, Tape tape, float* __restrict__ var_ll,
+                                                     float* __restrict__ valid, int* __restrict__ health) {
+    constexpr bool NT = !TAPE;
+    __shared__ float lam_[4 * 21 * 64];   // the four directions' information
+    __shared__ double done_[4][7][64];    // the completed messages: eta 6, normal eta
+    __shared__ float msg_[4][8][64];      // the transported messages: eta 6, normal eta; normal lambda
+    const int lane = threadIdx.x;
+    const int d = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    int u, v;
+    segment_pixel(lane, u, v);
+    // lanes past the row's end repeat its last pixel and store nothing
+    const bool inside = u < g.W;
+    if (!inside) u = g.W - 1;
+    const unsigned o = off_of(g, u, v);
+    bool has[4];
+    unsigned on[4];
+    float c[4], pt[7], npt[7], eta_d[6], mn[2];
+    load_point_at(X, g, o, pt);
+    const PixelInputs pin = load_inputs_at(s, in, o);
+    edges_of(g, in, u, v, has, on, c);
+    const unsigned od = d == 0 ? on[0] : d == 1 ? on[1] : d == 2 ? on[2] : on[3];
+    const bool has_d = d == 0 ? has[0] : d == 1 ? has[1] : d == 2 ? has[2] : has[3];
+    const float c_d = d == 0 ? c[0] : d == 1 ? c[1] : d == 2 ? c[2] : c[3];
+    load_point_at(X, g, od, npt);
+    {
+        GFloat* b = plane_of(X, (long)(P_MID + d * MID_STRIDE) * g.plane);
+        const unsigned oh = here(od);
+#pragma unroll
+        for (int k = 0; k < 27; ++k) {
+            if (k < 6) eta_d[k] = *at(b, oh);
+            else
+                __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(b, oh),
+                                                 (__attribute__((address_space(3))) void*)(lam_ + (d * 21 + k - 6) * 64),
+                                                 4, 0, 0);
+            b = next(g, b);
+        }
+        b = plane_of(X, (long)(P_MN + 2 * d) * g.plane);
+        mn[0] = *at(b, oh);
+        mn[1] = *at(next(g, b), oh);
+    }
+    const auto lam = [&](int dd, int k) { return lam_[(dd * 21 + k) * 64 + lane]; };
+    const auto own = [&](int k) { return lam_[(d * 21 + k) * 64 + lane]; };
+
+    // --- linearise at the current point, complete the direction's partial
+    double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
+    point_of(pt, tau, ell);
+    pose_exp(tau, q, t);
+    pose_rotation(q, R);
+    const bool val = unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
+    const bool act = isfinite(c_d) && s.lamN > 0.0;
+    wait_lds_loads();
+    if (has_d) {
+        double tj[6], ellj, qj[4], trj[3], r[6], e[6];
+        point_of(npt, tj, ellj);
+        pose_exp(tj, qj, trj);
+        pose_between(qj, trj, q, t, r);
+        complete_eta(eta_d, own, r, e);
+        double ne = 0.0;
+        float nl = 0.0f;
+        if (act) {
+            nl = mn[1];
+            ne = fma(-(double)nl, normal_residual_c(c_d, d, ell, ellj), (double)mn[0]);
+        }
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            done_[d][a][lane] = e[a];
+            eta_d[a] = (float)e[a];
+        }
+        done_[d][6][lane] = ne;
+        mn[0] = (float)ne;
+        mn[1] = nl;
+    } else {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) eta_d[a] = 0.0f;
+        mn[0] = mn[1] = 0.0f;
+    }
+    msg_[d][7][lane] = mn[1];
+    __syncthreads();
+#pragma unroll
+    for (int dd = 0; dd < 4; ++dd) {
+        if (!has[dd]) continue;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) eta[a] += done_[dd][a][lane];
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+#pragma unroll
+            for (int k = i; k < 6; ++k) L[s7(i, k)] += (double)lam(dd, s6(i, k));
+        eta[6] += done_[dd][6][lane];
+        L[s7(6, 6)] += (double)msg_[dd][7][lane];
+    }
+    if constexpr (TAPE) {
+        if (d == 0 && inside) {
+            GDouble* b = plane_of(tape.bel);
+            const unsigned oh = here(o);
+#pragma unroll
+            for (int k = 0; k < 35; ++k) {
+                __builtin_nontemporal_store(k < 28 ? L[k] : eta[k - 28], at(b, oh));
+                b = next(g, b);
+            }
+        }
+    }
+
+    // --- update, relinearise (Eq. var), transport the direction's message
+    double m[7], var;
+    bool ok = ldl7_solve(L, eta, m, var);
+    pose_retract(q, t, m, tau);
+    ell += m[6];
+    round_point(tau, ell);
+    if (has_d) transport(eta_d, mn, own, m);
+    // the stored form of the direction's message, to `S`
+    const auto store_own = [&](float* S) {
+        GFloat* b = plane_of(S, (long)(P_MID + d * MID_STRIDE) * g.plane);
+        const unsigned oh = here(o);
+#pragma unroll
+        for (int k = 0; k < 27; ++k) {
+            put<NT>(at(b, oh), k < 6 ? eta_d[k] : has_d ? own(k - 6) : 0.0f);
+            b = next(g, b);
+        }
+        b = plane_of(S, (long)(P_MN + 2 * d) * g.plane);
+        put<NT>(at(b, oh), mn[0]);
+        put<NT>(at(next(g, b), oh), mn[1]);
+    };
+    if constexpr (FINAL) {
+        if (inside) {
+            store_own(Y);
+            if (d == 0) {
+                store_point<NT>(Y, g, o, tau, ell);
+                *at((GFloat*)var_ll, o) = (float)var;
+                *at((GFloat*)valid, o) = val ? 1.0f : 0.0f;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) msg_[d][a][lane] = eta_d[a];
+        msg_[d][6][lane] = mn[0];
+        // --- linearise at the new point and send the direction's next partial
+        pose_exp(tau, q, t);
+        pose_rotation(q, R);
+        unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
+        if (inside && d == 0) store_point<NT>(Y, g, o, tau, ell);
+        if constexpr (TAPE) {
+            if (inside) {
+                store_own(tape.canonical);
+                if (d == 1) store_point<NT>(tape.canonical, g, o, tau, ell);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int dd = 0; dd < 4; ++dd) {
+            if (!has[dd]) continue;
+#pragma unroll
+            for (int a = 0; a < 6; ++a) eta[a] += (double)msg_[dd][a][lane];
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int k = i; k < 6; ++k) L[s7(i, k)] += (double)lam(dd, s6(i, k));
+            eta[6] += (double)msg_[dd][6][lane];
+            L[s7(6, 6)] += (double)msg_[dd][7][lane];
+        }
+        double P[21], pm[6], D, dv;
+        ok = depth_marginal(L, eta, D, dv) && ok;
+        if constexpr (TAPE)
+            if (d == 2 && inside) tape_marginals(tape.marg, g, o, D, dv, L, eta);
+        pose_marginal(L, eta, L[s7(6, 6)], P, pm);
+        if (has_d && inside) {
+            emit_normal<NT>(g, s, o, d, D, dv, mn, act, Y);
+            ok = emit_identity<NT>(g, s, o, d, P, pm, eta_d, own, Y) && ok;
+        }
+    }
+    if (!ok) atomicOr(health, 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1282,6 +1478,13 @@ hipError_t launch_batch_passes(const BatchLaunch& b, int n_iters, bool prologue,
 
 static dim3 grid2d(const Geo& g, dim3 b) { return dim3((g.W + b.x - 1) / b.x, (g.H + b.y - 1) / b.y); }
 static const dim3 kBlock(64, 1);
+static const dim3 kSplitBlock(64, 4);
+// One workgroup of four waves per CU, a wave per SIMD: up to there the split
+// pass is faster (frames of 20 iterations, 24 row segments: 248 against 388 us;
+// 256: 321 against 384), from there on its repeated parts share SIMDs (288:
+// 391 against 394; 384: 427 against 418; 576: 609 against 473).
+constexpr long kSplitSegments = 256;
+static bool use_split(const Geo& g) { return (long)((g.W + 63) / 64) * g.H <= kSplitSegments; }
 hipError_t launch_frame_prep(const Geo& g, const float* src, long src_pitch, float* It, float* Gx, float* Gy,
                              hipStream_t st, int* clear) {
     hipLaunchKernelGGL(k_frame_prep, grid2d(g, kBlock), kBlock, 0, st, g, src, src_pitch, It, Gx, Gy, clear);
@@ -1331,7 +1534,14 @@ hipError_t launch_fu_prologue(const Geo& g, const Strengths& s, const Inputs& in
 
 hipError_t launch_fu_iterate(const Geo& g, const Strengths& s, const Inputs& in, const float* X, float* Y,
                              bool final_pass, float* var_ll, float* valid, int* health, hipStream_t st) {
-    if (final_pass)
+    if (use_split(g)) {
+        if (final_pass)
+            hipLaunchKernelGGL((k_fu_split<true, false>), grid2d(g, kBlock), kSplitBlock, 0, st, g, s, in, X, Y, Tape{},
+                               var_ll, valid, health);
+        else
+            hipLaunchKernelGGL((k_fu_split<false, false>), grid2d(g, kBlock), kSplitBlock, 0, st, g, s, in, X, Y,
+                               Tape{}, var_ll, valid, health);
+    } else if (final_pass)
         hipLaunchKernelGGL(k_fu_iterate<true>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, Y, var_ll, valid, health);
     else
         hipLaunchKernelGGL(k_fu_iterate<false>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, Y, var_ll, valid,
@@ -1349,12 +1559,18 @@ hipError_t launch_fu_segment_tape(const Geo& g, const Strengths& s, const Inputs
     float* t[2] = {tA, tB};
     for (int k = 0; k < len; ++k) {
         const Tape tape{bel + bel_stride * k, seg + seg_stride * (k + 1), marg + marg_stride * (k + 1)};
-        if (k + 1 < len)
-            hipLaunchKernelGGL(k_fu_tape<false>, grid, kBlock, 0, st, g, s, in, t[k & 1], t[(k + 1) & 1], tape, var_ll,
+        const float* src = t[k & 1];
+        float* dst = t[(k + 1) & 1];
+        if (use_split(g) && k + 1 < len)
+            hipLaunchKernelGGL((k_fu_split<false, true>), grid, kSplitBlock, 0, st, g, s, in, src, dst, tape, var_ll,
                                valid, health);
+        else if (use_split(g))
+            hipLaunchKernelGGL((k_fu_split<true, true>), grid, kSplitBlock, 0, st, g, s, in, src, dst, tape, var_ll,
+                               valid, health);
+        else if (k + 1 < len)
+            hipLaunchKernelGGL(k_fu_tape<false>, grid, kBlock, 0, st, g, s, in, src, dst, tape, var_ll, valid, health);
         else
-            hipLaunchKernelGGL(k_fu_tape<true>, grid, kBlock, 0, st, g, s, in, t[k & 1], t[(k + 1) & 1], tape, var_ll,
-                               valid, health);
+            hipLaunchKernelGGL(k_fu_tape<true>, grid, kBlock, 0, st, g, s, in, src, dst, tape, var_ll, valid, health);
     }
     return hipGetLastError();
 }
