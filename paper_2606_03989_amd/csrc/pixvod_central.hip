@@ -57,9 +57,12 @@ constexpr int kThreads = 256;      // 64 x 4 pixel blocks
 constexpr int kLinPartials = 29;   // A (21), g_xi (6), r.r, valid count
 constexpr int kCgPartials = 9;     // r.u, w.u, r.r, sum b_i u_i (6)
 constexpr int kCgThreads = 256;    // work-items per workgroup of the CG launches
-constexpr int kCgPx = 2;           // pixels per work-item and round in those launches
 constexpr int kCgMaxBlocks = 768;  // most workgroups of those launches (a multiple of 8): three per CU
-constexpr int kCgChunk = 16;       // CG iterations launched between convergence checks
+// CG iterations launched between convergence checks. The launches that follow
+// the last needed one, up to two chunks, take 10 us each for nothing; a check
+// costs about 2 us (640 x 480, 385 iterations in three solves: chunks of 16
+// 7.10 ms, 8 6.72, 4 6.64, 2 6.84).
+constexpr int kCgChunk = 4;
 
 // solver state in device memory
 struct CgState {
@@ -331,57 +334,77 @@ __global__ __launch_bounds__(kThreads) void k_c_lin_final(Strengths s, int nb, c
     *rec0 = st;
 }
 
-// The CG launches: kCgThreads work-items per workgroup, kCgPx pixels per
-// work-item and round (range base + j * kCgThreads + work-item). Workgroup b
-// takes range (b mod 8) * (nbx / 8) + b / 8 (nbx, the grid, a multiple of 8):
-// workgroups are dealt to the eight XCDs in turn, so each XCD gets adjacent
-// ranges and finds most of their vertical neighbours in its own L2. Rounds
-// stride over the image when the grid is smaller than it.
+// The CG launches: kCgThreads work-items per workgroup, each with two pixels
+// of a column, v even and v + 1, per round (item base + work-item, along row
+// pairs): either is the other's vertical neighbour, so that a pair needs two
+// recomputed neighbours and not four. Workgroup b takes range
+// (b mod 8) * (nbx / 8) + b / 8 (nbx, the grid, a multiple of 8): workgroups are
+// dealt to the eight XCDs in turn, so each XCD gets adjacent ranges and finds
+// most of their vertical neighbours in its own L2. Rounds stride over the image
+// when the grid is smaller than it.
 //
 // Since D u = r, w = M u needs no diagonal: w = r - lamN sum u_j + b.u_pose,
 // and 1 / D_ii is kept instead of it. A pixel's horizontal neighbours are the
-// adjacent lanes (pixels of a range are consecutive), whose new u comes by a
-// lane exchange; the lanes at the ends of a wave and the vertical neighbours'
-// u are recomputed from their stored r, w, s.
+// adjacent lanes (the items of a range are consecutive), whose new u comes by a
+// lane exchange; the lanes at the ends of a wave and the pairs above and below
+// are recomputed from their stored r, w, s.
 
 __device__ inline int cg_range(int b, int nbx) { return (b & 7) * (nbx >> 3) + (b >> 3); }
 
-struct CgPix {             // what an iteration needs of one pixel
-    int act;
-    long pi;
-    double x, p, r, w, s, idiag, b[6];
-    // r, w, s, 1 / D of the vertical neighbours and (first and last lane of a
-    // wave) of the left or right one
-    double nr[3], nw[3], ns[3], nd[3];
+struct CgOther {           // what a neighbour's new u is computed from
+    double r, w, s, idiag;
 };
 
+struct CgPair {            // what an iteration needs of an item's two pixels
+    int act[2];
+    long pi[2];
+    bool in[2];            // whether there is such a pixel
+    double x[2], p[2], r[2], w[2], s[2], idiag[2], b[2][6];
+    CgOther up, down;      // the pixels above and below the pair
+    CgOther side[2];       // first and last lane of a wave: the left or right neighbours
+};
+
+__device__ inline CgOther cg_other(const Planes& P, int cur, bool first, long pj) {
+    return {P.r[cur][pj], P.w[cur][pj], first ? 0.0 : P.s[cur][pj], P.idiag[pj]};
+}
+
+__device__ inline int cg_items(const Geo& g) { return g.W * ((g.H + 1) / 2); }
+
+// loads item i of n; one past the end repeats the last, a missing pixel or
+// neighbour reads one that is there, and its value is not used
 __device__ inline void cg_load(const Geo& g, const Planes& P, const unsigned char* __restrict__ act, int cur,
-                               bool first, int i, int N, CgPix& a) {
-    const int ic = i < N ? i : N - 1;
-    const int u = ic % g.W, v = ic / g.W;
-    const long pi = pix_of(g, u, v);
-    a.pi = pi;
-    a.act = act[pi];
-    a.r = P.r[cur][pi];
-    a.w = P.w[cur][pi];
-    a.s = first ? 0.0 : P.s[cur][pi];
-    a.idiag = P.idiag[pi];
-    // a missing neighbour's loads read the pixel itself; its value is not used
-    const int lane = threadIdx.x & 63;
-    const long pj[3] = {v > 0 ? pi - g.pitch : pi, v + 1 < g.H ? pi + g.pitch : pi,
-                        lane == 0 ? (u > 0 ? pi - 1 : pi) : (u + 1 < g.W ? pi + 1 : pi)};
+                               bool first, int i, int n, CgPair& a) {
+    const int ic = i < n ? i : n - 1;
+    const int u = ic % g.W, v = ic / g.W * 2;
+    a.pi[0] = pix_of(g, u, v);
+    a.in[0] = i < n;
+    a.in[1] = i < n && v + 1 < g.H;
+    a.pi[1] = v + 1 < g.H ? a.pi[0] + g.pitch : a.pi[0];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        if (k == 2 && lane != 0 && lane != 63) break;
-        a.nr[k] = P.r[cur][pj[k]];
-        a.nw[k] = P.w[cur][pj[k]];
-        a.ns[k] = first ? 0.0 : P.s[cur][pj[k]];
-        a.nd[k] = P.idiag[pj[k]];
+    for (int j = 0; j < 2; ++j) {
+        const long pi = a.pi[j];
+        a.act[j] = act[pi];
+        a.r[j] = P.r[cur][pi];
+        a.w[j] = P.w[cur][pi];
+        a.s[j] = first ? 0.0 : P.s[cur][pi];
+        a.idiag[j] = P.idiag[pi];
     }
-    a.x = P.x[pi];
-    a.p = first ? 0.0 : P.p[pi];
+    a.up = cg_other(P, cur, first, v > 0 ? a.pi[0] - g.pitch : a.pi[0]);
+    a.down = cg_other(P, cur, first, v + 2 < g.H ? a.pi[0] + 2 * g.pitch : a.pi[1]);
+    const int lane = threadIdx.x & 63;
+    if (lane == 0 || lane == 63) {
+        const int step = lane == 0 ? (u > 0 ? -1 : 0) : (u + 1 < g.W ? 1 : 0);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) a.b[k] = P.b[(long)k * g.plane + pi];
+        for (int j = 0; j < 2; ++j) a.side[j] = cg_other(P, cur, first, a.pi[j] + step);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const long pi = a.pi[j];
+        a.x[j] = P.x[pi];
+        a.p[j] = first ? 0.0 : P.p[pi];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) a.b[j][k] = P.b[(long)k * g.plane + pi];
+    }
 }
 
 // one pixel's new residual from its stored r, w, s (explicit FMAs, so that a
@@ -474,15 +497,21 @@ __device__ inline void cg_apply_pixel(const double b[6], const double un[4], int
     red[2] = fma(r, r, red[2]);
 }
 
-// the four neighbours' u at a wave's pixels from the own u and the loaded
-// neighbours' (DIR_U, DIR_D, edge lane)
-__device__ inline void cg_neighbours(double u, const double uv[3], double un[4]) {
+// the four neighbours' u of a pair's pixels, from the pair's own and the
+// recomputed ones above, below and (edge lanes) beside it
+__device__ inline void cg_neighbours(const double u[2], double up, double down, const double side[2],
+                                     double un[2][4]) {
     const int lane = threadIdx.x & 63;
-    const double l = __shfl_up(u, 1, 64), r = __shfl_down(u, 1, 64);
-    un[DIR_L] = lane == 0 ? uv[2] : l;
-    un[DIR_R] = lane == 63 ? uv[2] : r;
-    un[DIR_U] = uv[0];
-    un[DIR_D] = uv[1];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const double l = __shfl_up(u[j], 1, 64), r = __shfl_down(u[j], 1, 64);
+        un[j][DIR_L] = lane == 0 ? side[j] : l;
+        un[j][DIR_R] = lane == 63 ? side[j] : r;
+    }
+    un[0][DIR_U] = up;
+    un[0][DIR_D] = u[1];
+    un[1][DIR_U] = u[0];
+    un[1][DIR_D] = down;
 }
 
 // CG start: u_0 = P^-1 r_0 and w_0 = M u_0 (planes of set 0), partial sums
@@ -504,22 +533,23 @@ __global__ __launch_bounds__(kCgThreads) void k_c_cg_init(Geo g, Strengths s, Pl
     double red[kCgPartials];
 #pragma unroll
     for (int k = 0; k < kCgPartials; ++k) red[k] = 0.0;
-    const int N = g.H * g.W;
-    const int round = kCgThreads * kCgPx;
-    for (int rb = cg_range(blockIdx.x, gridDim.x); rb * round < N; rb += gridDim.x) {
+    const int n = cg_items(g);
+    for (int rb = cg_range(blockIdx.x, gridDim.x); rb * kCgThreads < n; rb += gridDim.x) {
+        CgPair c;
+        cg_load(g, P, act, 0, true, rb * kCgThreads + threadIdx.x, n, c);
+        double u[2], un[2][4], side[2];
 #pragma unroll
-        for (int j = 0; j < kCgPx; ++j) {
-            const int i = rb * round + j * kCgThreads + threadIdx.x;
-            CgPix c;
-            cg_load(g, P, act, 0, true, i, N, c);
-            double uv[3], un[4], w;
+        for (int j = 0; j < 2; ++j) {
+            u[j] = c.r[j] * c.idiag[j];
+            side[j] = c.side[j].r * c.side[j].idiag;
+        }
+        cg_neighbours(u, c.up.r * c.up.idiag, c.down.r * c.down.idiag, side, un);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) uv[k] = c.nr[k] * c.nd[k];
-            const double u = c.r * c.idiag;
-            cg_neighbours(u, uv, un);
-            if (i >= N) continue;
-            cg_apply_pixel(c.b, un, s.lamN > 0.0 ? c.act : 0, s.lamN, up, c.r, u, w, red);
-            P.w[0][c.pi] = w;
+        for (int j = 0; j < 2; ++j) {
+            if (!c.in[j]) continue;
+            double w;
+            cg_apply_pixel(c.b[j], un[j], s.lamN > 0.0 ? c.act[j] : 0, s.lamN, up, c.r[j], u[j], w, red);
+            P.w[0][c.pi[j]] = w;
         }
     }
     cg_block_reduce(red, part_out, blockIdx.x);
@@ -532,12 +562,14 @@ __global__ __launch_bounds__(kCgThreads) void k_c_cg_init(Geo g, Strengths s, Pl
 // then p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s, u = P^-1 r,
 // w = M u and the partial sums for the next step. The scalar step runs on the
 // first wave of each workgroup, a lane per pose component, and reaches the
-// others via LDS. Every load of the launch (the previous partial sums, the pose block and its
-// inverse, the scalar record, the first round's pixels and neighbours) is
-// issued before the first wait: the launch is bound by its chain of latencies
-// (the waves wait on memory for 71% of their life), not by the 42 MB that it
-// moves at 640 x 480: 14.7 us per launch, 15.4 us with the scalar step in one
-// lane, its record loaded after the partial sums and 1 / D formed by division.
+// others via LDS. Every load of the launch (the previous partial sums, the pose
+// block and its inverse, the scalar record, the first round's pixels and
+// neighbours) is issued before the first wait. The launch is bound by its chain
+// of latencies (the waves wait on memory for 71% of their life) and by the 42 MB
+// that it moves at 640 x 480: 14.7 us per launch there and 7.5 us at 32 x 24;
+// 640 x 480 took 15.1 us with a pixel at a time (four recomputed neighbours per
+// two pixels), 15.9 with the scalar step in one lane, its record loaded after
+// the partial sums and 1 / D formed by division as well.
 __global__ __launch_bounds__(kCgThreads, 3) void k_c_cg_iter(Geo g, Strengths s, const CgState* __restrict__ cs,
                                                              Planes P, const unsigned char* __restrict__ act,
                                                              const CgIter* __restrict__ rin,
@@ -556,13 +588,10 @@ __global__ __launch_bounds__(kCgThreads, 3) void k_c_cg_iter(Geo g, Strengths s,
     if (wv == 2 && lane < (int)(sizeof(CgIter) / 8))
         reinterpret_cast<double*>(&sh_st)[lane] = reinterpret_cast<const double*>(rin)[lane];
     cg_totals(part_in, gridDim.x, sh_tot);
-    const int N = g.H * g.W;
-    const int round = kCgThreads * kCgPx;
+    const int n = cg_items(g);
     int rb = cg_range(blockIdx.x, gridDim.x);
-    CgPix a[kCgPx];
-#pragma unroll
-    for (int j = 0; j < kCgPx; ++j)
-        cg_load(g, P, act, cur, first != 0, rb * round + j * kCgThreads + tid, N, a[j]);
+    CgPair c;
+    cg_load(g, P, act, cur, first != 0, rb * kCgThreads + tid, n, c);
     const double rr0 = cs->rr0;
     __syncthreads();
     if (wv == 0) {
@@ -632,32 +661,35 @@ __global__ __launch_bounds__(kCgThreads, 3) void k_c_cg_iter(Geo g, Strengths s,
     double red[kCgPartials];
 #pragma unroll
     for (int k = 0; k < kCgPartials; ++k) red[k] = 0.0;
+    const auto other = [&](const CgOther& o) {
+        double sn;
+        return cg_new_r(o.r, o.w, o.s, alpha, beta, sn) * o.idiag;
+    };
     while (true) {
+        double u[2], r[2], sv[2], un[2][4], side[2];
 #pragma unroll
-        for (int j = 0; j < kCgPx; ++j) {
-            const int i = rb * round + j * kCgThreads + tid;
-            const CgPix& c = a[j];
-            double uv[3], un[4], sj;
+        for (int j = 0; j < 2; ++j) {
+            r[j] = cg_new_r(c.r[j], c.w[j], c.s[j], alpha, beta, sv[j]);
+            u[j] = r[j] * c.idiag[j];
+            side[j] = other(c.side[j]);
+        }
+        cg_neighbours(u, other(c.up), other(c.down), side, un);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) uv[k] = cg_new_r(c.nr[k], c.nw[k], c.ns[k], alpha, beta, sj) * c.nd[k];
-            const double pn = fma(beta, c.p, c.r * c.idiag);
-            double sv, w;
-            const double r = cg_new_r(c.r, c.w, c.s, alpha, beta, sv);
-            const double u = r * c.idiag;
-            cg_neighbours(u, uv, un);
-            if (i >= N) continue;
-            cg_apply_pixel(c.b, un, lamN > 0.0 ? c.act : 0, lamN, up, r, u, w, red);
-            P.x[c.pi] = fma(alpha, pn, c.x);
-            P.p[c.pi] = pn;
-            P.s[nxt][c.pi] = sv;
-            P.r[nxt][c.pi] = r;
-            P.w[nxt][c.pi] = w;
+        for (int j = 0; j < 2; ++j) {
+            if (!c.in[j]) continue;
+            const long pi = c.pi[j];
+            const double pn = fma(beta, c.p[j], c.r[j] * c.idiag[j]);
+            double w;
+            cg_apply_pixel(c.b[j], un[j], lamN > 0.0 ? c.act[j] : 0, lamN, up, r[j], u[j], w, red);
+            P.x[pi] = fma(alpha, pn, c.x[j]);
+            P.p[pi] = pn;
+            P.s[nxt][pi] = sv[j];
+            P.r[nxt][pi] = r[j];
+            P.w[nxt][pi] = w;
         }
         rb += gridDim.x;
-        if (rb * round >= N) break;
-#pragma unroll
-        for (int j = 0; j < kCgPx; ++j)
-            cg_load(g, P, act, cur, first != 0, rb * round + j * kCgThreads + tid, N, a[j]);
+        if (rb * kCgThreads >= n) break;
+        cg_load(g, P, act, cur, first != 0, rb * kCgThreads + tid, n, c);
     }
     cg_block_reduce(red, part_out, blockIdx.x);
 }
@@ -1026,8 +1058,8 @@ int pixvod_central_track(pixvod_central* c, const float* frame, int where, int n
     const Planes P = cplanes(c);
     const dim3 gr = cgrid(g), blk(64, 4);
     const double tol2 = c->tol * c->tol;
-    const long round = (long)kCgThreads * kCgPx;
-    const int nbx = (int)std::min<long>(((long)N + 8 * round - 1) / (8 * round) * 8, kCgMaxBlocks);
+    const long items = (long)c->W * ((c->H + 1) / 2), per = 8L * kCgThreads;
+    const int nbx = (int)std::min<long>((items + per - 1) / per * 8, kCgMaxBlocks);
     double* part[2] = {c->part_cg, c->part_cg + (size_t)kCgMaxBlocks * kCgPartials};
     const hipStream_t st = c->stream;
     hipLaunchKernelGGL(k_c_reset_total, dim3(1), dim3(64), 0, st, c->cs);
