@@ -19,12 +19,11 @@ hipError_t launch_keyframe_prep(const Geo& g, const float* img, const float* nor
 hipError_t launch_init_state(const Geo& g, float* X, float ell0, hipStream_t st);
 hipError_t launch_pf_iteration(const Geo& g, const Strengths& s, const Inputs& in, float* X, double* marg,
                                double* M, float* var_ll, float* valid, int* health, hipStream_t st);
-// n_iters damped iterations (message damping beta) from the canonical state
-// X[cur]; it ends in X[cur ^ (n_iters & 1)]. marg: two buffers of 29 FP64
-// planes. One linearisation, then one pass per iteration.
-hipError_t launch_damped(const Geo& g, const Strengths& s, const Inputs& in, float* const X[2], int cur,
-                         double* const marg[2], int n_iters, float beta, float* var_ll, float* valid, int* health,
-                         hipStream_t st);
+// n_iters damped iterations (message damping beta) of the canonical state X, in
+// place. part: two state-sized work buffers. One prologue, then one pass per
+// iteration.
+hipError_t launch_damped(const Geo& g, const Strengths& s, const Inputs& in, float* X, float* const part[2],
+                         int n_iters, float beta, float* var_ll, float* valid, int* health, hipStream_t st);
 hipError_t launch_fu_prologue(const Geo& g, const Strengths& s, const Inputs& in, const float* X, float* Y,
                               int* health, hipStream_t st);
 hipError_t launch_fu_iterate(const Geo& g, const Strengths& s, const Inputs& in, const float* X, float* Y,

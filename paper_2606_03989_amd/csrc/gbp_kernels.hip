@@ -29,29 +29,43 @@ namespace pv {
 // are loaded straight from memory without passing through registers (63 planes
 // of 64 lanes, 16 KB per wave: eight waves fit a CU's 160 KB), the fourth and
 // everything else in registers: at most 256 registers, so that two waves share
-// a SIMD and fill each other's waits. Every lane reads only what it loaded
-// itself, so no barrier is needed.
-constexpr int LDS_DIRS = 3;
-constexpr int LDS_PLANES = LDS_DIRS * 21;
-constexpr int LDS_WAVE = LDS_PLANES * 64;   // floats per wave
+// a SIMD and fill each other's waits. Passes that also store the messages of
+// each iteration (with a tape, damped) spilled at that, and a spilled value's
+// load waits for every store before it; they keep 78 planes in LDS, as much as
+// eight waves can have (320 x 240: with tape, beside the reverse kernels, 54.5 us
+// against 66.5; damped 34.5 against 41.4), which costs the other passes 2% (256 x
+// 256: 20.25 us against 19.75). Every lane reads only what it loaded itself, so
+// no barrier is needed.
+constexpr int LDS_PLANES = 63, LDS_PLANES_STORING = 78;
 
+template <int PLANES>
 struct Messages {
+    static constexpr int kPlanes = PLANES, kRest = 4 * 21 - PLANES, kFloats = PLANES * 64;   // LDS floats per wave
     float eta[4][6];     // identity messages
-    float lam3[21];      // information of direction 3
+    float rest[kRest];   // information: what LDS does not hold, the end of direction 3's
     float mn[4][2];      // normal messages: eta, lambda
-    const float* lds;    // information of directions 0 .. 2: this lane's column of the wave's LDS planes
+    float* lds;          // information, direction by direction: this lane's column of the wave's LDS planes
 
-    __device__ inline float lam(int d, int k) const { return d < LDS_DIRS ? lds[(d * 21 + k) * 64] : lam3[k]; }
+    __device__ inline float lam(int d, int k) const {
+        const int i = d * 21 + k;
+        return i < PLANES ? lds[i * 64] : rest[i - PLANES];
+    }
+    __device__ inline void set_lam(int d, int k, float x) {
+        const int i = d * 21 + k;
+        if (i < PLANES) lds[i * 64] = x;
+        else rest[i - PLANES] = x;
+    }
 };
 
-// issues the loads of a pixel's messages but the information of direction 3.
+// issues the loads of a pixel's messages but the information that LDS
+// does not hold.
 // at_: where each slot is read, the pixel itself for stored messages and the
 // neighbour that sends it for partials in flight (a missing neighbour's is the
 // pixel's own: finite and not used). buf: the wave's LDS planes, lane: the lane
-// of the wave. The information matrices of the LDS directions may be read after
-// wait_lds_loads() only.
+// of the wave. The information may be read after wait_lds_loads() only.
+template <int PLANES>
 __device__ inline void load_messages(const float* X, const Geo& g, const unsigned at_[4], float* buf, int lane,
-                                     Messages& m) {
+                                     Messages<PLANES>& m) {
     GFloat* b = plane_of(X, (long)P_MID * g.plane);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
@@ -61,14 +75,12 @@ __device__ inline void load_messages(const float* X, const Geo& g, const unsigne
             m.eta[d][k] = *at(b, o);
             b = next(g, b);
         }
-        if (d < LDS_DIRS) {
 #pragma unroll
-            for (int k = 0; k < 21; ++k) {
-                __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(b, o),
-                                                 (__attribute__((address_space(3))) void*)(buf + (d * 21 + k) * 64), 4,
-                                                 0, 0);
-                b = next(g, b);
-            }
+        for (int k = 0; k < 21 && d * 21 + k < PLANES; ++k) {
+            __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)at(b, o),
+                                             (__attribute__((address_space(3))) void*)(buf + (d * 21 + k) * 64), 4, 0,
+                                             0);
+            b = next(g, b);
         }
     }
     b = plane_of(X, (long)P_MN * g.plane);
@@ -83,20 +95,22 @@ __device__ inline void load_messages(const float* X, const Geo& g, const unsigne
     m.lds = buf + lane;
 }
 
-// issues the loads of direction 3's information: late, so that they are not
-// held in registers beside the linearisation
-__device__ inline void load_lam3(const float* X, const Geo& g, unsigned o, Messages& m) {
-    GFloat* b = plane_of(X, (long)(P_MID + 3 * MID_STRIDE + 6) * g.plane);
+// issues the loads of the rest: late, so that they are not held in registers
+// beside the linearisation
+template <int PLANES>
+__device__ inline void load_rest(const float* X, const Geo& g, unsigned o, Messages<PLANES>& m) {
+    GFloat* b = plane_of(X, (long)(P_MID + 4 * MID_STRIDE - m.kRest) * g.plane);
     o = here(o);
 #pragma unroll
-    for (int k = 0; k < 21; ++k) {
-        m.lam3[k] = *at(b, o);
+    for (int k = 0; k < m.kRest; ++k) {
+        m.rest[k] = *at(b, o);
         b = next(g, b);
     }
 }
 
 // B += a stored message (embedded: identity -> pose block, normal -> depth entry)
-__device__ inline void add_message(double L[28], double eta[7], const Messages& m, int d) {
+template <class M>
+__device__ inline void add_message(double L[28], double eta[7], const M& m, int d) {
 #pragma unroll
     for (int a = 0; a < 6; ++a) eta[a] += (double)m.eta[d][a];
 #pragma unroll
@@ -125,7 +139,8 @@ __device__ inline void transport(float eta[6], float mn[2], Lam lam, const doubl
     for (int a = 0; a < 6; ++a) eta[a] = (float)e[a];
     mn[0] = (float)fma(-(double)mn[1], m[6], (double)mn[0]);
 }
-__device__ inline void transport_message(Messages& ms, int d, const double m[7]) {
+template <class M>
+__device__ inline void transport_message(M& ms, int d, const double m[7]) {
     transport(ms.eta[d], ms.mn[d], [&](int k) { return ms.lam(d, k); }, m);
 }
 
@@ -166,15 +181,15 @@ __device__ inline void store_point(float* Y, const Geo& g, unsigned o, const dou
     put<NT>(at(b, o), (float)ell);
 }
 
-template <bool NT = false>
-__device__ inline void store_messages(float* Y, const Geo& g, unsigned o, const Messages& m, const bool has[4]) {
+template <bool NT = false, class M>
+__device__ inline void store_messages(float* Y, const Geo& g, unsigned o, const M& m) {
     GFloat* b = plane_of(Y, (long)P_MID * g.plane);
     o = here(o);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
 #pragma unroll
         for (int k = 0; k < 27; ++k) {
-            put<NT>(at(b, o), k < 6 ? m.eta[d][k] : (has[d] ? m.lam(d, k - 6) : 0.0f));
+            put<NT>(at(b, o), k < 6 ? m.eta[d][k] : m.lam(d, k - 6));
             b = next(g, b);
         }
     }
@@ -376,7 +391,7 @@ __global__ __launch_bounds__(256, 2) void k_pf_messages(Geo g, Strengths s, Inpu
 __global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs in, float* __restrict__ X,
                                                      const double* __restrict__ M, float* __restrict__ var_ll,
                                                      float* __restrict__ valid, int* __restrict__ health) {
-    __shared__ float buf[LDS_WAVE];
+    __shared__ float buf[Messages<LDS_PLANES>::kFloats];
     int u, v;
     segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
@@ -388,9 +403,8 @@ __global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs 
     const bool val = unary_factors(g, s, in, u, v, tau, q, R, t, ell, load_pixel_inputs(g, s, in, u, v), L, eta);
     // the new messages: added to the belief in FP64, kept at storage precision
     // (the information matrices are at storage precision already)
-    Messages ms;
-    float* lds = buf + threadIdx.x;
-    ms.lds = lds;
+    Messages<LDS_PLANES> ms;
+    ms.lds = buf + threadIdx.x;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         const double* md = M + (long)(d * 29) * g.plane + p;
@@ -406,8 +420,7 @@ __global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs 
             for (int c = r; c < 6; ++c) {
                 const double l = md[(6 + s6(r, c)) * g.plane];
                 L[s7(r, c)] += l;
-                if (d < LDS_DIRS) lds[(d * 21 + s6(r, c)) * 64] = (float)l;
-                else ms.lam3[s6(r, c)] = (float)l;
+                ms.set_lam(d, s6(r, c), (float)l);
             }
         const double ne = md[27 * g.plane], nl = md[28 * g.plane];
         eta[6] += ne;
@@ -422,9 +435,8 @@ __global__ __launch_bounds__(64, 2) void k_pf_update(Geo g, Strengths s, Inputs 
     round_point(tau, ell);
 #pragma unroll
     for (int d = 0; d < 4; ++d) transport_message(ms, d, m);
-    const bool has[4] = {true, true, true, true};
     store_point(X, g, off_of(g, u, v), tau, ell);
-    store_messages(X, g, off_of(g, u, v), ms, has);
+    store_messages(X, g, off_of(g, u, v), ms);
     var_ll[p] = (float)var;
     valid[p] = val ? 1.0f : 0.0f;
     if (!ok) atomicOr(health, 1);
@@ -471,9 +483,9 @@ __device__ inline bool emit_identity(const Geo& g, const Strengths& s, unsigned 
     return ok;
 }
 
-template <bool NT, bool TAPE>
+template <bool NT, bool TAPE, class M>
 __device__ inline bool emit_partials(const Geo& g, const Strengths& s, unsigned o, const bool has[4], const bool act[4],
-                                     const double L[28], const double eta[7], const Messages& ms,
+                                     const double L[28], const double eta[7], const M& ms,
                                      float* __restrict__ Y, double* __restrict__ marg) {
     double P[21], pm[6], D, dv, l66 = L[s7(6, 6)];
     bool ok = depth_marginal(L, eta, D, dv);
@@ -502,7 +514,7 @@ __device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& 
                                                                      int u, int v, float* buf, int lane,
                                                                      double* __restrict__ marg) {
     const unsigned o = off_of(g, u, v);
-    Messages ms;
+    Messages<LDS_PLANES> ms;
     bool has[4];
     unsigned on[4];
     float c[4], pt[7];
@@ -517,7 +529,7 @@ __device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& 
     pose_rotation(q, R);
     unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
     wait_lds_loads();
-    load_lam3(X, g, o, ms);
+    load_rest(X, g, o, ms);
 #pragma unroll
     for (int d = 0; d < 4; ++d) add_message(L, eta, ms, d);
     bool act[4];
@@ -538,17 +550,29 @@ __device__ __attribute__((always_inline)) inline void prologue_pixel(const Geo& 
 // used again before the pass ends, and what is left in the L2 has to be written
 // back then (256 x 256: 19.7 us against 21.2; 1920 x 1080: 459 against 475; 64
 // mixed sequences: 1,747 against 1,785). Beside the reverse kernels, which read
-// the state soon, it is not (320 x 240: the pass with tape 66.5 us, 71 with).
-template <bool FINAL, bool TAPE>
+// the state soon, it is not (320 x 240: the pass with tape 66.5 us, 71 with);
+// neither is a damped state, which the next pass updates (34.5 us, 35.5 with).
+// DAMPED: a new message is mixed with the one that the receiver holds, whose
+// stored form is kept beside the partials (damp.state, updated in place: a pixel
+// reads and writes its own).
+struct Damp {
+    float* state;
+    float beta;
+};
+
+constexpr int iterate_planes(bool tape, bool damped) { return tape || damped ? LDS_PLANES_STORING : LDS_PLANES; }
+
+template <bool FINAL, bool TAPE, bool DAMPED = false>
 __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g, const Strengths& s, const Inputs& in,
                                                                     const float* __restrict__ X,
                                                                     float* __restrict__ Y, float* __restrict__ var_ll,
                                                                     float* __restrict__ valid,
                                                                     int* __restrict__ health, int u, int v, float* buf,
-                                                                    int lane, const Tape& tape) {
-    constexpr bool NT = !TAPE;
+                                                                    int lane, const Tape& tape,
+                                                                    const Damp& damp = Damp{}) {
+    constexpr bool NT = !TAPE && !DAMPED;
     const unsigned o = off_of(g, u, v);
-    Messages ms;
+    Messages<iterate_planes(TAPE, DAMPED)> ms;
     bool has[4];
     unsigned on[4];
     float c[4], pt[7], npt[4][7];
@@ -568,7 +592,10 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 
     // --- complete the partials in flight with the residuals at both points
     wait_lds_loads();
-    load_lam3(X, g, on[3], ms);
+    load_rest(X, g, on[3], ms);
+    if constexpr (FINAL || TAPE || DAMPED)
+#pragma unroll
+        for (int k = 0; k < ms.kRest; ++k) ms.rest[k] = has[3] ? ms.rest[k] : 0.0f;
     bool act[4];
     active_edges(s, c, act);
 #pragma unroll
@@ -577,6 +604,9 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 #pragma unroll
             for (int k = 0; k < 6; ++k) ms.eta[d][k] = 0.0f;
             ms.mn[d][0] = ms.mn[d][1] = 0.0f;
+            if constexpr (FINAL || TAPE || DAMPED)   // what is stored of it
+#pragma unroll
+                for (int k = 0; k < 21 && d * 21 + k < ms.kPlanes; ++k) ms.set_lam(d, k, 0.0f);
             continue;
         }
         double tj[6], ellj, qj[4], trj[3], r[6], e[6];
@@ -590,6 +620,27 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
             rn = normal_residual_c(c[d], d, ell, ellj);
             nl = ms.mn[d][1];
             ne = fma(-(double)nl, rn, (double)ms.mn[d][0]);
+        }
+        if constexpr (DAMPED) {
+            // the blended information is rounded to storage precision like
+            // every stored one
+            const double b1 = (double)damp.beta, a1 = 1.0 - b1;
+            GFloat* b = plane_of(damp.state, (long)(P_MID + d * MID_STRIDE) * g.plane);
+            const unsigned oh = here(o);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                e[k] = fma(a1, e[k], b1 * (double)*at(b, oh));
+                b = next(g, b);
+            }
+#pragma unroll
+            for (int k = 0; k < 21; ++k) {
+                const float l = (float)fma(a1, (double)ms.lam(d, k), b1 * (double)*at(b, oh));
+                b = next(g, b);
+                ms.set_lam(d, k, l);
+            }
+            b = plane_of(damp.state, (long)(P_MN + 2 * d) * g.plane);
+            ne = fma(a1, ne, b1 * (double)*at(b, oh));
+            nl = (float)fma(a1, (double)nl, b1 * (double)*at(next(g, b), oh));
         }
 #pragma unroll
         for (int a = 0; a < 6; ++a) {
@@ -626,8 +677,9 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
         if (has[d]) transport_message(ms, d, m);
     reread_lds();
     if constexpr (FINAL) {
-        store_point<NT>(Y, g, o, tau, ell);
-        store_messages<NT>(Y, g, o, ms, has);
+        float* out = DAMPED ? damp.state : Y;
+        store_point<NT>(out, g, o, tau, ell);
+        store_messages<NT>(out, g, o, ms);
         *at((GFloat*)var_ll, o) = (float)var;
         *at((GFloat*)valid, o) = val ? 1.0f : 0.0f;
     } else {
@@ -638,8 +690,9 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
         store_point<NT>(Y, g, o, tau, ell);
         if constexpr (TAPE) {
             store_point(tape.canonical, g, o, tau, ell);
-            store_messages(tape.canonical, g, o, ms, has);
+            store_messages(tape.canonical, g, o, ms);
         }
+        if constexpr (DAMPED) store_messages<NT>(damp.state, g, o, ms);
 #pragma unroll
         for (int d = 0; d < 4; ++d)
             if (has[d]) add_message(L, eta, ms, d);
@@ -658,7 +711,7 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 // before; the smallest images take k_fu_split).
 __global__ __launch_bounds__(64, 2) void k_fu_prologue(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                        float* __restrict__ Y, int* __restrict__ health) {
-    __shared__ float buf[LDS_WAVE];
+    __shared__ float buf[Messages<LDS_PLANES>::kFloats];
     int u, v;
     segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
@@ -669,7 +722,7 @@ template <bool FINAL>
 __global__ __launch_bounds__(64, 2) void k_fu_iterate(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                       float* __restrict__ Y, float* __restrict__ var_ll,
                                                       float* __restrict__ valid, int* __restrict__ health) {
-    __shared__ float buf[LDS_WAVE];
+    __shared__ float buf[Messages<LDS_PLANES>::kFloats];
     int u, v;
     segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
@@ -682,7 +735,7 @@ __global__ __launch_bounds__(64, 2) void k_fu_iterate(Geo g, Strengths s, Inputs
 __global__ __launch_bounds__(64, 2) void k_fu_prologue_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                             float* __restrict__ Y, double* __restrict__ marg,
                                                             int* __restrict__ health) {
-    __shared__ float buf[LDS_WAVE];
+    __shared__ float buf[Messages<LDS_PLANES>::kFloats];
     int u, v;
     segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
@@ -694,14 +747,14 @@ __global__ __launch_bounds__(64, 2) void k_fu_prologue_tape(Geo g, Strengths s, 
 // tape.canonical) and the prologue of iteration k + 1 (partials into Y, depth
 // marginal and belief into tape.marg) in one pass; the same arithmetic as the
 // final form followed by k_fu_prologue_tape on the canonical state. Bound by its
-// stores: 320 x 240, beside the reverse kernels, 68.5 us with 1,560 bytes
-// written per pixel; 76.9 with 2,128 (the messages' information and the pose
-// marginal on the tape as well).
+// stores, 1,560 bytes per pixel: 320 x 240, beside the reverse kernels, 54.5 us
+// (2,128 bytes, with the messages' information and the pose marginal on the tape
+// as well, took 8 us more).
 template <bool FINAL>
 __global__ __launch_bounds__(64, 2) void k_fu_tape(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                    float* __restrict__ Y, Tape tape, float* __restrict__ var_ll,
                                                    float* __restrict__ valid, int* __restrict__ health) {
-    __shared__ float buf[LDS_WAVE];
+    __shared__ float buf[Messages<LDS_PLANES_STORING>::kFloats];
     int u, v;
     segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
@@ -893,179 +946,22 @@ __global__ __launch_bounds__(256, 2) void k_fu_split(Geo g, Strengths s, Inputs 
 // ---------------------------------------------------------------------------
 // damped iterations
 //
-// A damped message mixes the new one with the one that the receiver holds, so
-// it cannot travel as a partial; the receiver computes it from the sender's
-// marginals (FP64 planes, as k_pf_linearise leaves them). One pass per
-// iteration: the pixel's four messages, its update and transport, and the
-// marginals of the new state for the next pass; state and marginals alternate
-// between two buffers. The per-factor kernels' arithmetic without their
-// message planes (928 bytes per pixel written and read back) and second
-// linearisation: 41 us per iteration at 320 x 240, where the three launches
-// took 87 us (72 with this pass's algebra). Bound by the latency of the four
-// senders' gathered loads: 1,200 waves on 1,024 SIMDs.
+// The fused pass with the receiver's stored messages beside the partials: what
+// a sender contributes to a damped message still travels as a partial. Bound by
+// memory and, below two waves per SIMD, by one wave's chain: 320 x 240, 34.5 us
+// per iteration; 41 us as a pass that gathered the senders' FP64 marginals, 87 us
+// as three launches per iteration.
 template <bool FINAL>
 __global__ __launch_bounds__(64, 2) void k_damped_iterate(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
-                                                          const double* __restrict__ marg, float* __restrict__ Y,
-                                                          double* __restrict__ marg_next, float beta,
+                                                          float* __restrict__ Y, float* state, float beta,
                                                           float* __restrict__ var_ll, float* __restrict__ valid,
                                                           int* __restrict__ health) {
-    __shared__ float buf[LDS_WAVE];
+    __shared__ float buf[Messages<LDS_PLANES_STORING>::kFloats];
     int u, v;
     segment_pixel(threadIdx.x, u, v);
     if (u >= g.W) return;
-    const unsigned o = off_of(g, u, v);
-    bool has[4], act[4];
-    unsigned on[4];
-    float c[4], pt[7];
-    load_point_at(X, g, o, pt);
-    const PixelInputs pin = load_inputs_at(s, in, o);
-    edges_of(g, in, u, v, has, on, c);
-    active_edges(s, c, act);
-    double tau[6], ell, q[4], R[9], t[3], L[28], eta[7];
-    point_of(pt, tau, ell);
-    pose_exp(tau, q, t);
-    // the sum of the new messages first: the linearisation's registers come after
-    double Lm[28], em[7];
-#pragma unroll
-    for (int k = 0; k < 28; ++k) Lm[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 7; ++k) em[k] = 0.0;
-    bool ok = true;
-    Messages ms;
-    float* lds = buf + threadIdx.x;
-    ms.lds = lds;
-    const double b1 = (double)beta, a1 = 1.0 - b1;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        float lam[21];
-#pragma unroll
-        for (int k = 0; k < 21; ++k) lam[k] = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) ms.eta[d][k] = 0.0f;
-        ms.mn[d][0] = ms.mn[d][1] = 0.0f;
-        if (has[d]) {
-            const int slot = opposite(d);
-            const unsigned oj = here(on[d]), oi = here(o);
-            float npt[7];
-            load_point_at(X, g, oj, npt);
-            // the sender's variable-to-factor message: its marginals less the
-            // message it holds from this factor
-            double V[21], vv[6], Lp[21], h[6], D, dv;
-            GDouble* mb = plane_of(const_cast<double*>(marg));
-            GFloat* xb = plane_of(X, (long)(P_MID + slot * MID_STRIDE + 6) * g.plane);
-#pragma unroll
-            for (int k = 0; k < 21; ++k) {
-                V[k] = *at(mb, oj) - (double)*at(xb, oj);
-                mb = next(g, mb);
-                xb = next(g, xb);
-            }
-            xb = plane_of(X, (long)(P_MID + slot * MID_STRIDE) * g.plane);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                vv[k] = *at(mb, oj) - (double)*at(xb, oj);
-                mb = next(g, mb);
-                xb = next(g, xb);
-            }
-            xb = plane_of(X, (long)(P_MN + 2 * slot) * g.plane);
-            D = *at(mb, oj) - (double)*at(next(g, xb), oj);
-            dv = *at(next(g, mb), oj) - (double)*at(xb, oj);
-            ok = identity_partial(s.lamR, V, vv, Lp, h) && ok;
-            float part[27];
-#pragma unroll
-            for (int k = 0; k < 27; ++k) part[k] = k < 6 ? (float)h[k] : (float)Lp[k - 6];
-            double tj[6], ellj, qj[4], trj[3], r[6], e[6];
-            point_of(npt, tj, ellj);
-            pose_exp(tj, qj, trj);
-            pose_between(qj, trj, q, t, r);
-            complete_eta(part, [&](int k) { return part[6 + k]; }, r, e);
-            double ne = 0.0;
-            float nl = 0.0f;
-            if (act[d]) {
-                double lp, hn;
-                normal_partial(s.lamN, D, dv, lp, hn);
-                nl = (float)lp;
-                ne = fma(-(double)nl, normal_residual_c(c[d], d, ell, ellj), (double)(float)hn);
-            }
-            // damping towards the stored message; the blended information is
-            // rounded to storage precision like every stored one
-            xb = plane_of(X, (long)(P_MID + d * MID_STRIDE) * g.plane);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                e[k] = fma(a1, e[k], b1 * (double)*at(xb, oi));
-                xb = next(g, xb);
-                em[k] += e[k];
-                ms.eta[d][k] = (float)e[k];
-            }
-#pragma unroll
-            for (int k = 0; k < 21; ++k) {
-                lam[k] = (float)fma(a1, (double)part[6 + k], b1 * (double)*at(xb, oi));
-                xb = next(g, xb);
-            }
-            xb = plane_of(X, (long)(P_MN + 2 * d) * g.plane);
-            ne = fma(a1, ne, b1 * (double)*at(xb, oi));
-            nl = (float)fma(a1, (double)nl, b1 * (double)*at(next(g, xb), oi));
-#pragma unroll
-            for (int i = 0; i < 6; ++i)
-#pragma unroll
-                for (int k = i; k < 6; ++k) Lm[s7(i, k)] += (double)lam[s6(i, k)];
-            em[6] += ne;
-            Lm[s7(6, 6)] += (double)nl;
-            ms.mn[d][0] = (float)ne;
-            ms.mn[d][1] = nl;
-        }
-#pragma unroll
-        for (int k = 0; k < 21; ++k) {
-            if (d < LDS_DIRS) lds[(d * 21 + k) * 64] = lam[k];
-            else ms.lam3[k] = lam[k];
-        }
-        // kept as FP32 (and not as the FP64 values that its readers convert to)
-#pragma unroll
-        for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(ms.eta[d][k]));
-        asm volatile("" : "+v"(ms.mn[d][0]), "+v"(ms.mn[d][1]));
-        if (d == 3)
-#pragma unroll
-            for (int k = 0; k < 21; ++k) asm volatile("" : "+v"(ms.lam3[k]));
-        reread_lds();
-    }
-    pose_rotation(q, R);
-    const bool val = unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
-#pragma unroll
-    for (int k = 0; k < 28; ++k) L[k] += Lm[k];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) eta[k] += em[k];
-    double m[7], var;
-    ok = ldl7_solve(L, eta, m, var) && ok;
-    pose_retract(q, t, m, tau);
-    ell += m[6];
-    round_point(tau, ell);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) transport_message(ms, d, m);
-    reread_lds();
-    if constexpr (FINAL) {
-        *at((GFloat*)var_ll, o) = (float)var;
-        *at((GFloat*)valid, o) = val ? 1.0f : 0.0f;
-    } else {
-        pose_exp(tau, q, t);
-        pose_rotation(q, R);
-        unary_factors(g, s, in, u, v, tau, q, R, t, ell, pin, L, eta);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) add_message(L, eta, ms, d);
-        double D, dv, P[21], pm[6], l66 = L[s7(6, 6)];
-        ok = depth_marginal(L, eta, D, dv) && ok;
-        asm volatile("" : "+v"(l66), "+v"(D), "+v"(dv));
-        pose_marginal(L, eta, l66, P, pm);
-        GDouble* mb = plane_of(marg_next);
-        const unsigned oh = here(o);
-#pragma unroll
-        for (int k = 0; k < 29; ++k) {
-            *at(mb, oh) = k < 21 ? P[k] : k < 27 ? pm[k - 21] : k == 27 ? D : dv;
-            mb = next(g, mb);
-        }
-    }
-    const bool all[4] = {true, true, true, true};
-    store_point(Y, g, o, tau, ell);
-    store_messages(Y, g, o, ms, all);
-    if (!ok) atomicOr(health, 1);
+    iterate_pixel<FINAL, false, true>(g, s, in, X, Y, var_ll, valid, health, u, v, buf, threadIdx.x,
+                                      Tape{}, Damp{state, beta});
 }
 
 // ---------------------------------------------------------------------------
@@ -1231,11 +1127,11 @@ __device__ inline float* batch_buf(int& lane) {
     extern __shared__ float batch_lds_[];
     const int tid = threadIdx.y * blockDim.x + threadIdx.x;
     lane = tid & 63;
-    return batch_lds_ + __builtin_amdgcn_readfirstlane(tid >> 6) * LDS_WAVE;
+    return batch_lds_ + __builtin_amdgcn_readfirstlane(tid >> 6) * Messages<LDS_PLANES>::kFloats;
 }
 
 static size_t batch_lds(int tile_x, int tile_y) {
-    return (size_t)((tile_x * tile_y + 63) / 64) * LDS_WAVE * sizeof(float);
+    return (size_t)((tile_x * tile_y + 63) / 64) * Messages<LDS_PLANES>::kFloats * sizeof(float);
 }
 
 __global__ __launch_bounds__(256, 2) void k_batch_prologue(const SeqDesc* __restrict__ seqs, const int2* __restrict__ work,
@@ -1502,18 +1398,19 @@ hipError_t launch_init_state(const Geo& g, float* X, float ell0, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_damped(const Geo& g, const Strengths& s, const Inputs& in, float* const X[2], int cur,
-                         double* const marg[2], int n_iters, float beta, float* var_ll, float* valid, int* health,
-                         hipStream_t st) {
+hipError_t launch_damped(const Geo& g, const Strengths& s, const Inputs& in, float* X, float* const part[2],
+                         int n_iters, float beta, float* var_ll, float* valid, int* health, hipStream_t st) {
     if (n_iters < 1) return hipSuccess;
-    hipLaunchKernelGGL(k_pf_linearise, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X[cur], marg[0], valid, health);
-    for (int it = 0; it < n_iters; ++it, cur ^= 1) {
+    hipLaunchKernelGGL(k_fu_prologue, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X, part[0], health);
+    for (int it = 0; it < n_iters; ++it) {
+        const float* src = part[it & 1];
+        float* dst = part[(it & 1) ^ 1];
         if (it + 1 < n_iters)
-            hipLaunchKernelGGL(k_damped_iterate<false>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X[cur],
-                               marg[it & 1], X[cur ^ 1], marg[(it & 1) ^ 1], beta, var_ll, valid, health);
+            hipLaunchKernelGGL(k_damped_iterate<false>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, src, dst, X, beta,
+                               var_ll, valid, health);
         else
-            hipLaunchKernelGGL(k_damped_iterate<true>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, X[cur],
-                               marg[it & 1], X[cur ^ 1], marg[(it & 1) ^ 1], beta, var_ll, valid, health);
+            hipLaunchKernelGGL(k_damped_iterate<true>, grid2d(g, kBlock), kBlock, 0, st, g, s, in, src, dst, X, beta,
+                               var_ll, valid, health);
     }
     return hipGetLastError();
 }

@@ -566,10 +566,9 @@ __global__ __launch_bounds__(kCgThreads) void k_c_cg_init(Geo g, Strengths s, Pl
 // block and its inverse, the scalar record, the first round's pixels and
 // neighbours) is issued before the first wait. The launch is bound by its chain
 // of latencies (the waves wait on memory for 71% of their life) and by the 42 MB
-// that it moves at 640 x 480: 14.7 us per launch there and 7.5 us at 32 x 24;
-// 640 x 480 took 15.1 us with a pixel at a time (four recomputed neighbours per
-// two pixels), 15.9 with the scalar step in one lane, its record loaded after
-// the partial sums and 1 / D formed by division as well.
+// that it moves at 640 x 480: 14.7 us per launch there, 7.5 us at 32 x 24. Three
+// solves of 385 iterations, 640 x 480: 6.52 ms; 6.67 with a pixel at a time and
+// so four recomputed neighbours per two pixels.
 __global__ __launch_bounds__(kCgThreads, 3) void k_c_cg_iter(Geo g, Strengths s, const CgState* __restrict__ cs,
                                                              Planes P, const unsigned char* __restrict__ act,
                                                              const CgIter* __restrict__ rin,

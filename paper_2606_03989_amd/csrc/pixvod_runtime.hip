@@ -49,6 +49,7 @@ struct pixvod_ctx {
     unsigned* zbuf = nullptr;            // depth-transfer z-buffer (allocated on first use)
     double* marg = nullptr;
     double* msg = nullptr;
+    float* part = nullptr;               // partials of damped iterations (allocated on first use)
     double* partial = nullptr;
     int* health = nullptr;
     double* h_result = nullptr;          // pinned: the frame reductions are written here
@@ -303,7 +304,7 @@ static void prof_collect(pixvod_ctx* c) {
 
 static void release(pixvod_ctx* c) {
     void* bufs[] = {c->X[0], c->X[1], c->NX[0], c->NX[1], c->Is, c->cxt, c->cyt, c->sig, c->It, c->Gx, c->Gy, c->prior_ell, c->var_ll,
-                    c->valid, c->frame_stage, c->kf_stage, c->out_stage, c->dense_state, c->zbuf, c->marg, c->msg,
+                    c->valid, c->frame_stage, c->kf_stage, c->out_stage, c->dense_state, c->zbuf, c->marg, c->msg, c->part,
                     c->partial, c->health};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -681,21 +682,25 @@ static int run_iterations(pixvod_ctx* c, int n) {
         c->cur = src;
     } else if (c->schedule == PIXVOD_SCHED_PER_FACTOR) {
         const size_t pl = (size_t)c->plane;
-        if (!c->marg) {
+        const bool damped = c->P.damping != 0.0f;
+        if (damped && !c->part) {
+            int rc = dev_alloc(c, &c->part, pl * N_PLANES);
+            if (rc) return rc;
+        }
+        if (!damped && !c->marg) {
             int rc = dev_alloc(c, &c->marg, pl * 29);
             if (rc) return rc;
         }
-        if (!c->msg) {
-            // the messages, or (damped) the second copy of the marginals
-            int rc = dev_alloc(c, &c->msg, pl * (c->P.damping != 0.0f ? 29 : 116));
+        if (!damped && !c->msg) {
+            int rc = dev_alloc(c, &c->msg, pl * 116);
             if (rc) return rc;
         }
         hipEvent_t a = prof_begin(c);
-        if (c->P.damping != 0.0f) {
-            double* marg[2] = {c->marg, c->msg};
-            HIP_TRY(c, launch_damped(g, s, in, c->X, c->cur, marg, n, c->P.damping, c->var_ll, c->valid, c->health,
+        if (damped) {
+            // partials alternate between the other state buffer and one of their own
+            float* part[2] = {c->X[1 - c->cur], c->part};
+            HIP_TRY(c, launch_damped(g, s, in, c->X[c->cur], part, n, c->P.damping, c->var_ll, c->valid, c->health,
                                      c->stream));
-            c->cur ^= n & 1;
         } else {
             for (int it = 0; it < n; ++it)
                 HIP_TRY(c, launch_pf_iteration(g, s, in, c->X[c->cur], c->marg, c->msg, c->var_ll, c->valid,
