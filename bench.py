@@ -33,10 +33,11 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, vendor figure
 STATE_PLANES = 123
 BYTES_PER_PX_ITER = STATE_PLANES * 4 * 2 + 4 + 8 + 12
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_fused_iterate_vga.json")
-KERNEL_SOURCES = ["paper_2606_03989_amd/csrc/gbp_kernels.hip", "paper_2606_03989_amd/csrc/gbp_device.hpp"]
+KERNEL_SOURCES = ["paper_2606_03989_amd/csrc/gbp_kernels.hip", "paper_2606_03989_amd/csrc/gbp_device.hpp",
+                  "paper_2606_03989_amd/csrc/gbp_planes.hpp"]
 TREE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_quadtree_iterate_vga.json")
 TREE_KERNEL_SOURCES = ["paper_2606_03989_amd/csrc/gbp_tree.hip", "paper_2606_03989_amd/csrc/gbp_tree.h",
-                       "paper_2606_03989_amd/csrc/gbp_device.hpp"]
+                       "paper_2606_03989_amd/csrc/gbp_device.hpp", "paper_2606_03989_amd/csrc/gbp_planes.hpp"]
 
 
 def kernel_source_hash(sources=KERNEL_SOURCES) -> str:

@@ -283,19 +283,6 @@ __device__ inline void se3_compose(const double Ra[9], const double ta[3], const
     }
 }
 
-// Log([Rj | tj]^-1 [Ri | ti]): the identity-factor residual of Eq. (regul)
-__device__ inline void se3_between(const double Rj[9], const double tj[3], const double Ri[9],
-                                   const double ti[3], double r[6]) {
-    double R[9], t[3], d[3] = {ti[0] - tj[0], ti[1] - tj[1], ti[2] - tj[2]};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) R[a * 3 + c] = Rj[a] * Ri[c] + Rj[3 + a] * Ri[3 + c] + Rj[6 + a] * Ri[6 + c];
-        t[a] = Rj[a] * d[0] + Rj[3 + a] * d[1] + Rj[6 + a] * d[2];
-    }
-    se3_log(R, t, r);
-}
-
 // ---------------------------------------------------------------------------
 // poses of the iteration kernels: unit quaternion q = (vector 3, scalar) and
 // translation t. An Exp is 39 FP64 operations and the residual between two
@@ -589,10 +576,6 @@ __device__ inline bool ldl6_solve(double L[21], double eta[6], double m[6]) {
 
 // ---------------------------------------------------------------------------
 // photometric and prior factors
-
-__device__ inline float plane_at(const float* p, const Geo& g, int u, int v) {
-    return p[(long)v * g.pitch + u];
-}
 
 constexpr double WARP_EPS = 1e-3;
 
