@@ -32,7 +32,7 @@ hipError_t launch_fu_iterate(const Geo& g, const Strengths& s, const Inputs& in,
 // state X0, with the tape of every iteration k: the depth marginal (2 FP64
 // planes) followed by the belief it comes from (35) at marg + k * marg_stride
 // and the belief of the update (35 FP64) at bel + k * bel_stride. The canonical
-// states after iterations 1 .. len - 1 go to seg + k * seg_stride; tA and tB
+// state after iteration k < len - 1 goes to seg + k * seg_stride; tA and tB
 // are state-sized work buffers, and the last canonical state is left in tB if
 // len is odd, in tA if it is even. One prologue, len - 1 rotated passes (update of k and prologue of k + 1) and a
 // final pass.

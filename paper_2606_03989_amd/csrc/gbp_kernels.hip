@@ -1455,7 +1455,7 @@ hipError_t launch_fu_segment_tape(const Geo& g, const Strengths& s, const Inputs
     hipLaunchKernelGGL(k_fu_prologue_tape, grid, kBlock, 0, st, g, s, in, X0, tA, marg, health);
     float* t[2] = {tA, tB};
     for (int k = 0; k < len; ++k) {
-        const Tape tape{bel + bel_stride * k, seg + seg_stride * (k + 1), marg + marg_stride * (k + 1)};
+        const Tape tape{bel + bel_stride * k, seg + seg_stride * k, marg + marg_stride * (k + 1)};
         const float* src = t[k & 1];
         float* dst = t[(k + 1) & 1];
         if (use_split(g) && k + 1 < len)

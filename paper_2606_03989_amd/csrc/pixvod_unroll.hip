@@ -2,9 +2,9 @@
 // include/pixvod.h, "Differentiation").
 //
 // Forward: the fused schedule in segments of at most ckpt_every iterations;
-// every segment starts from a canonical state, which is copied to the tape
-// (per-factor and fused schedules are the same iteration bit for bit, so the
-// tape holds exactly the per-factor states).
+// every segment starts from a canonical state on the tape and its final pass
+// writes the next one there (per-factor and fused schedules are the same
+// iteration bit for bit, so the tape holds exactly the per-factor states).
 // Backward, for frames and segments in reverse: recompute the segment's
 // states from its checkpoint, one prologue + final pass per state, which also
 // keep each state's marginals and new messages; then run the three reverse
@@ -147,8 +147,8 @@ static void urelease(pixvod_unroll* u) {
     if (u->own_stream) (void)hipStreamDestroy(u->own_stream);
 }
 
-// canonical state after n fused iterations from src; returns the buffer that
-// holds it (src is left unchanged when n >= 1; a and b are the work buffers)
+// n >= 1 fused iterations from the canonical state src to dst (a and b are work
+// buffers)
 static int fused_run(pixvod_unroll* u, const Geo& g, const Strengths& s, const Inputs& in, const float* src,
                      float* a, float* b, float* dst, int n) {
     // prologue src -> a, passes alternate a <-> b, the last one writes dst
@@ -212,19 +212,20 @@ int pixvod_unroll_create(int H, int W, const pixvod_intrinsics* K, const pixvod_
     u->sigma_N = P.sigma_N;
     u->huber_k = P.huber_k;
     const size_t pl = (size_t)u->plane, N = (size_t)H * W, S = state_floats(u);
+    const size_t n_seg = ckpt_every > 1 ? (size_t)ckpt_every - 1 : 1;   // recomputed states of a segment
     const int nb = stats_blocks(ugeo(u)) > sum2_blocks(ugeo(u)) ? stats_blocks(ugeo(u)) : sum2_blocks(ugeo(u));
     bool ok = ualloc(&u->Is, pl) && ualloc(&u->cxt, pl) && ualloc(&u->cyt, pl) && ualloc(&u->sig, pl) &&
               ualloc(&u->It, pl) && ualloc(&u->Gx, pl) && ualloc(&u->Gy, pl) &&
               ualloc(&u->frames, N * (size_t)max_frames) && ualloc(&u->stage, N * 4) && ualloc(&u->X0, S) &&
               ualloc(&u->Xw[0], S) && ualloc(&u->Xw[1], S) && ualloc(&u->tape, S * (size_t)max_frames * spf) &&
-              ualloc(&u->Xend, S) && ualloc(&u->seg, S * (size_t)ckpt_every) && ualloc(&u->var_ll, pl) &&
+              ualloc(&u->Xend, S) && ualloc(&u->seg, S * n_seg) && ualloc(&u->var_ll, pl) &&
               ualloc(&u->valid, pl) && ualloc(&u->marg, pl * MARG_PLANES * (size_t)ckpt_every) &&
               ualloc(&u->bel, pl * BEL_PLANES * (size_t)ckpt_every) &&
               ualloc(&u->Mb, pl * MSG_PLANES) && ualloc(&u->Ub, pl * UB_PLANES) && ualloc(&u->Eb, pl * EB_PLANES) &&
               ualloc(&u->Xb[0], S) && ualloc(&u->Xb[1], S) && ualloc(&u->gsig, pl) && ualloc(&u->gN, pl) &&
               ualloc(&u->gk, pl) && ualloc(&u->partial, (size_t)nb * 8) &&
               ualloc(&u->Cb[0], pl * CB_PLANES) && ualloc(&u->Cb[1], pl * CB_PLANES) &&
-              ualloc(&u->seg2, S * (size_t)ckpt_every) && ualloc(&u->tmp2, S) && ualloc(&u->sink2, S) &&
+              ualloc(&u->seg2, S * n_seg) && ualloc(&u->tmp2, S) && ualloc(&u->sink2, S) &&
               ualloc(&u->It2, pl) && ualloc(&u->Gx2, pl) && ualloc(&u->Gy2, pl) &&
               ualloc(&u->marg2, pl * MARG_PLANES * (size_t)ckpt_every) &&
               ualloc(&u->bel2, pl * BEL_PLANES * (size_t)ckpt_every) &&
@@ -329,16 +330,17 @@ int pixvod_unroll_forward(pixvod_unroll* u, const float* frames, int n_frames, i
     const Inputs in = uinputs(u);
     UHIP(hipEventRecord(u->ev[0], u->stream));
     UHIP(hipMemsetAsync(u->health, 0, sizeof(int), u->stream));
-    UHIP(hipMemcpyAsync(u->Xw[0], u->X0, S * sizeof(float), hipMemcpyDeviceToDevice, u->stream));
-    float* cur = u->Xw[0];
+    float* cur = ckpt(u, 0, 0);
+    UHIP(hipMemcpyAsync(cur, u->X0, S * sizeof(float), hipMemcpyDeviceToDevice, u->stream));
     for (int f = 0; f < n_frames; ++f) {
         UHIP(launch_frame_prep(g, u->frames + N * f, u->W, u->It, u->Gx, u->Gy, u->stream));
         for (int sg = 0; sg < u->seg_per_frame; ++sg) {
-            float* ck = ckpt(u, f, sg);
-            UHIP(hipMemcpyAsync(ck, cur, S * sizeof(float), hipMemcpyDeviceToDevice, u->stream));
-            // the tape copy is the segment's source; the result lands in cur
-            rc = fused_run(u, g, s, in, ck, u->Xw[0] == cur ? u->Xw[1] : u->Xw[0], u->seg, cur, seg_len(u, sg));
+            float* next = sg + 1 < u->seg_per_frame ? ckpt(u, f, sg + 1)
+                          : f + 1 < n_frames        ? ckpt(u, f + 1, 0)
+                                                    : u->Xend;
+            rc = fused_run(u, g, s, in, cur, u->Xw[0], u->Xw[1], next, seg_len(u, sg));
             if (rc) return rc;
+            cur = next;
         }
         UHIP(launch_frame_stats(g, cur, u->valid, 0, u->partial, u->stats + 8 * f, u->stream));
         if (inv_depth_out) {
@@ -349,7 +351,6 @@ int pixvod_unroll_forward(pixvod_unroll* u, const float* frames, int n_frames, i
                                     u->stream));
         }
     }
-    UHIP(hipMemcpyAsync(u->Xend, cur, S * sizeof(float), hipMemcpyDeviceToDevice, u->stream));
     UHIP(hipEventRecord(u->ev[1], u->stream));
     UHIP(hipMemcpyAsync(u->h_stats, u->stats, (size_t)n_frames * 8 * sizeof(double), hipMemcpyDeviceToHost,
                         u->stream));
@@ -427,13 +428,12 @@ int pixvod_unroll_backward(pixvod_unroll* u, const double* xi_bar, const float* 
         if (sg == S_ - 1)
             UHIP(launch_frame_prep(g, u->frames + N * f, u->W, const_cast<float*>(I.It), const_cast<float*>(I.Gx),
                                    const_cast<float*>(I.Gy), u->side));
-        // states of the segment: seg[0] = checkpoint, seg[i] after i
+        // states of the segment: its checkpoint, then seg[i] after i + 1
         // iterations; the recompute also keeps, per iteration, the beliefs of
         // its emission and its update (one prologue, then one rotated pass per
         // iteration; the last state stays in a work buffer of the set)
         const int len = seg_len(u, sg);
-        UHIP(hipMemcpyAsync(B.seg, ckpt(u, f, sg), S * sizeof(float), hipMemcpyDeviceToDevice, u->side));
-        UHIP(launch_fu_segment_tape(g, s, I, B.seg, B.seg, (long)S, len, B.tmp, B.sink, B.marg,
+        UHIP(launch_fu_segment_tape(g, s, I, ckpt(u, f, sg), B.seg, (long)S, len, B.tmp, B.sink, B.marg,
                                     (long)(pl * MARG_PLANES), B.bel, (long)(pl * BEL_PLANES), u->var_ll, u->valid, u->health, u->side));
         UHIP(hipEventRecord(evC[i], u->side));
         return PIXVOD_OK;
@@ -468,9 +468,9 @@ int pixvod_unroll_backward(pixvod_unroll* u, const double* xi_bar, const float* 
         UHIP(hipStreamWaitEvent(u->stream, evC[i], 0));
         const int len = seg_len(u, sg);
         for (int k = len - 1; k >= 0; --k) {
-            const float* X = B.seg + S * k;
+            const float* X = k > 0 ? B.seg + S * (k - 1) : ckpt(u, f, sg);
             // the state after the iteration: its messages' information is the new messages'
-            const float* Xn = k + 1 < len ? X + S : (len & 1 ? B.sink : B.tmp);
+            const float* Xn = k + 1 < len ? B.seg + S * k : (len & 1 ? B.sink : B.tmp);
             const double* marg = B.marg + pl * MARG_PLANES * k;
             const double* bel = B.bel + pl * BEL_PLANES * k;
             UHIP(launch_adj_update(g, s, I, X, Xn, bel, u->Xb[cur], u->Cb[cur], u->Mb, u->Ub, u->stream));
