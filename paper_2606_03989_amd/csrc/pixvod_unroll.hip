@@ -202,7 +202,7 @@ int pixvod_unroll_create(int H, int W, const pixvod_intrinsics* K, const pixvod_
     u->H = H;
     u->W = W;
     u->pitch = (W + 63) / 64 * 64;
-    u->plane = (long)H * u->pitch;
+    u->plane = plane_elements(H, u->pitch);
     u->K = *K;
     u->P = P;
     u->max_frames = max_frames;
