@@ -48,7 +48,7 @@ __host__ __device__ constexpr long plane_elements(int H, int pitch) { return (lo
 struct Geo {
     int H, W;
     int pitch;            // floats per row of every plane
-    long plane;           // floats per plane (H * pitch)
+    long plane;           // floats from a plane to the next (plane_elements)
     double fx, fy, cx, cy;
     double ifx, ify;      // 1 / fx, 1 / fy
 };

@@ -570,7 +570,7 @@ int pixvod_set_keyframe_transfer_noalloc(pixvod_ctx* c, const float* img, const 
     if (!img || !normals) return fail(c, PIXVOD_EINVAL, "img and normals are required");
     if (where != PIXVOD_HOST && where != PIXVOD_DEVICE) return fail(c, PIXVOD_EINVAL, "bad location");
     if (!c->have_track) return fail(c, PIXVOD_ESTATE, "no tracked frame since the keyframe");
-    if (c->plane > kTransferScratchMax)
+    if ((long)c->H * c->pitch > kTransferScratchMax)
         return fail(c, PIXVOD_EINVAL, "frame too large for the static z-buffer (H * pitch > 2^21)");
     unsigned* zb = transfer_scratch(c->device);
     if (!zb) return fail(c, PIXVOD_ESTATE, "static z-buffer not set up on this device");

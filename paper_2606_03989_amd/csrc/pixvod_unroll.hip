@@ -292,11 +292,11 @@ int pixvod_unroll_set_state(pixvod_unroll* u, const float* state, int where) {
     if (!state) return ufail(PIXVOD_EINVAL, "state is NULL");
     if (where != PIXVOD_HOST && where != PIXVOD_DEVICE) return ufail(PIXVOD_EINVAL, "bad location");
     if (!u->have_kf) return ufail(PIXVOD_ESTATE, "pixvod_unroll_set_state before pixvod_unroll_set_keyframe");
-    const size_t S = state_floats(u);
+    const size_t dense = (size_t)N_PLANES * u->H * u->W;   // the caller's planes are not padded
     const float* d = state;
     if (where == PIXVOD_HOST) {
         // staged through the first work buffer, which no forward pass needs kept
-        UHIP(hipMemcpyAsync(u->Xw[1], state, S * sizeof(float), hipMemcpyHostToDevice, u->stream));
+        UHIP(hipMemcpyAsync(u->Xw[1], state, dense * sizeof(float), hipMemcpyHostToDevice, u->stream));
         d = u->Xw[1];
     }
     UHIP(launch_pack_state(ugeo(u), u->X0, const_cast<float*>(d), 0, u->stream));
