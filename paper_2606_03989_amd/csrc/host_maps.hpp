@@ -11,11 +11,14 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <thread>
+#include <vector>
 
 namespace pv {
 
@@ -54,6 +57,14 @@ struct MapJob {
     const float* src;
     size_t n;
 };
+
+// whether any two destinations have memory in common (sorts them)
+inline bool destinations_overlap(std::vector<MapJob>& maps) {
+    std::sort(maps.begin(), maps.end(), [](const MapJob& a, const MapJob& b) { return std::less<float*>()(a.dst, b.dst); });
+    for (size_t i = 1; i < maps.size(); ++i)
+        if (std::less<float*>()(maps[i].dst, maps[i - 1].dst + maps[i - 1].n)) return true;
+    return false;
+}
 
 // Copies maps from pinned memory to where they belong. The workers are started
 // before the wait for the device (so that it hides their start) and wait for

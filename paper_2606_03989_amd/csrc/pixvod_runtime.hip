@@ -1115,6 +1115,7 @@ struct pixvod_batch {
     unsigned *d_flags = nullptr, *h_flags = nullptr;
     MapStage maps;                       // output maps on their way to host memory
     std::vector<MapJob> jobs;            // their copies of the present step (room for two per sequence)
+    std::vector<MapJob> dev_maps;        // maps in the caller's device memory (likewise)
     bool persistent = false;             // iteration block as one cooperative launch
     int persistent_grid = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -1310,6 +1311,7 @@ int pixvod_batch_create(int n, const int* H, const int* W, const pixvod_intrinsi
     b->P = P;
     b->seq.resize(n);
     b->jobs.reserve(2 * (size_t)n);
+    b->dev_maps.reserve(2 * (size_t)n);
     int rc = PIXVOD_OK;
     auto alloc = [&](float** p, size_t cnt) {
         if (rc) return;
@@ -1500,6 +1502,7 @@ static int batch_step(pixvod_batch* b, const float* const* frames, const float* 
     // where the step's output maps go: device memory as given, host memory
     // through the batch's pinned memory or (no room there) device staging
     b->jobs.clear();
+    b->dev_maps.clear();
     size_t n_host = 0;
     bool any_maps = false;
     for (int i = 0; i < b->n; ++i) {
@@ -1517,7 +1520,11 @@ static int batch_step(pixvod_batch* b, const float* const* frames, const float* 
         const size_t N = (size_t)q.H * q.W;
         d.inv_depth = o.inv_depth;
         d.inv_var = o.inv_depth_var;
-        if (o.out_where != PIXVOD_HOST) continue;
+        if (o.out_where != PIXVOD_HOST) {
+            if (o.inv_depth) b->dev_maps.push_back({o.inv_depth, nullptr, N});
+            if (o.inv_depth_var) b->dev_maps.push_back({o.inv_depth_var, nullptr, N});
+            continue;
+        }
         float* const host[2] = {o.inv_depth, o.inv_depth_var};
         float** const dev[2] = {&d.inv_depth, &d.inv_var};
         for (int k = 0; k < 2; ++k) {
@@ -1552,8 +1559,20 @@ static int batch_step(pixvod_batch* b, const float* const* frames, const float* 
     HIP_TRY_B(b, hipMemcpyAsync(b->h_health, b->d_health, sizeof(int), hipMemcpyDeviceToHost, b->stream));
     HIP_TRY_B(b, hipMemcpyAsync(b->h_flags, b->d_flags, sizeof(unsigned) * b->n, hipMemcpyDeviceToHost, b->stream));
     // re-anchoring keeps the log-depths and the variance plane: the maps are
-    // those of the frame just tracked
-    if (any_maps) HIP_TRY_B(b, launch_batch_outputs(batch_launch_args(b), b->parity, b->stream));
+    // those of the frame just tracked. One launch forms them all, in no order
+    // among the sequences; device maps that overlap are written in the order of
+    // the sequences, so that the last one stays.
+    if (any_maps && !destinations_overlap(b->dev_maps)) {
+        HIP_TRY_B(b, launch_batch_outputs(batch_launch_args(b), b->parity, b->stream));
+    } else if (any_maps) {
+        for (int i = 0; i < b->n; ++i) {
+            const BatchSeq& q = b->seq[i];
+            const SeqDesc& d = b->descs[i];
+            if (d.inv_depth || d.inv_var)
+                HIP_TRY_B(b, launch_outputs(geo_of_seq(q), q.X[b->parity], q.var_ll, 1, d.inv_depth, d.inv_var,
+                                            b->stream));
+        }
+    }
     for (int i = 0; i < b->n && !staged; ++i) {
         const BatchSeq& q = b->seq[i];
         const pixvod_track_out* o = &outs[i];
