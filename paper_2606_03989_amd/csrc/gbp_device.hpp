@@ -45,6 +45,13 @@ __host__ __device__ constexpr int s7(int r, int c) {
 // reverse of the update, 320 x 240: 36.8 against 39.3).
 __host__ __device__ constexpr long plane_elements(int H, int pitch) { return (long)H * pitch + 64; }
 
+// The passes address a pixel by a 32-bit byte offset into its plane
+// (gbp_planes.hpp), which reaches 2^30 elements of padded rows. (A state of that
+// size, 123 planes in two copies, is 984 GiB.)
+__host__ __device__ constexpr bool plane_addressable(int H, int W) {
+    return (long)H * ((W + 63L) / 64 * 64) <= 1L << 30;
+}
+
 struct Geo {
     int H, W;
     int pitch;            // floats per row of every plane

@@ -25,10 +25,10 @@ __device__ inline void segment_pixel(int lane, int& u, int& v) {
 // Plane access of the fused passes: the plane's base is uniform (scalar
 // registers and scalar arithmetic), the pixel a 32-bit byte offset, and a
 // neighbour's slot the same offset from a base moved by one element or one
-// row. (H * pitch is at most 2^28 elements.) A base runs through consecutive
-// planes and is opaque to the compiler at each, which otherwise forms 64-bit
-// addresses per lane (about 300 vector instructions more per pass).
-__device__ inline unsigned off_of(const Geo& g, int u, int v) { return (unsigned)((v * g.pitch + u) * 4); }
+// row. (plane_addressable bounds a plane at 2^30 elements.) A base runs through
+// consecutive planes and is opaque to the compiler at each, which otherwise
+// forms 64-bit addresses per lane (about 300 vector instructions more per pass).
+__device__ inline unsigned off_of(const Geo& g, int u, int v) { return (unsigned)(v * g.pitch + u) * 4u; }
 __device__ inline long step_of(const Geo& g, int d) {
     return d == DIR_L ? -1 : d == DIR_R ? 1 : d == DIR_U ? -(long)g.pitch : (long)g.pitch;
 }

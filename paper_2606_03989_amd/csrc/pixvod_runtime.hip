@@ -350,7 +350,8 @@ int pixvod_create(int H, int W, const pixvod_intrinsics* K, const pixvod_params*
     if (!out) return fail(nullptr, PIXVOD_EINVAL, "out_ctx is NULL");
     *out = nullptr;
     if (H < 2 || W < 2) return fail(nullptr, PIXVOD_EINVAL, "H and W must be >= 2");
-    if ((long)H * (long)W > (1L << 28)) return fail(nullptr, PIXVOD_EINVAL, "image too large");
+    if ((long)H * (long)W > (1L << 28) || !plane_addressable(H, W))
+        return fail(nullptr, PIXVOD_EINVAL, "image too large");
     if (!K || !(K->fx > 0) || !(K->fy > 0) || !std::isfinite(K->cx) || !std::isfinite(K->cy))
         return fail(nullptr, PIXVOD_EINVAL, "intrinsics must be finite with fx, fy > 0");
     pixvod_params P;
@@ -1289,6 +1290,7 @@ int pixvod_batch_create(int n, const int* H, const int* W, const pixvod_intrinsi
         if (H[i] < 2 || W[i] < 2) return bfail(nullptr, PIXVOD_EINVAL, "H and W must be >= 2");
         if (!(K[i].fx > 0) || !(K[i].fy > 0) || !std::isfinite(K[i].cx) || !std::isfinite(K[i].cy))
             return bfail(nullptr, PIXVOD_EINVAL, "intrinsics must be finite with fx, fy > 0");
+        if (!plane_addressable(H[i], W[i])) return bfail(nullptr, PIXVOD_EINVAL, "image too large");
         total += (long)H[i] * W[i];
     }
     if (total > (1L << 30)) return bfail(nullptr, PIXVOD_EINVAL, "batch too large");

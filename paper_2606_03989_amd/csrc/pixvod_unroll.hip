@@ -176,7 +176,7 @@ int pixvod_unroll_create(int H, int W, const pixvod_intrinsics* K, const pixvod_
     if (!out) return ufail(PIXVOD_EINVAL, "out_unroll is NULL");
     *out = nullptr;
     if (H < 2 || W < 2) return ufail(PIXVOD_EINVAL, "H and W must be >= 2");
-    if ((long)H * (long)W > (1L << 26)) return ufail(PIXVOD_EINVAL, "image too large");
+    if ((long)H * (long)W > (1L << 26) || !plane_addressable(H, W)) return ufail(PIXVOD_EINVAL, "image too large");
     if (max_frames < 1 || n_iters < 1 || ckpt_every < 1)
         return ufail(PIXVOD_EINVAL, "max_frames, n_iters and ckpt_every must be >= 1");
     if (!K || !(K->fx > 0) || !(K->fy > 0) || !std::isfinite(K->cx) || !std::isfinite(K->cy))
