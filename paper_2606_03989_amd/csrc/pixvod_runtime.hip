@@ -757,6 +757,8 @@ static std::vector<unsigned char> track_graph_key(const pixvod_ctx* c, int n_ite
     key_put(k, g.fy);
     key_put(k, g.cx);
     key_put(k, g.cy);
+    key_put(k, g.ifx);
+    key_put(k, g.ify);
     const Strengths s = strengths_of(c);
     key_put(k, s.lamP);
     key_put(k, s.lamR);
@@ -767,6 +769,8 @@ static std::vector<unsigned char> track_graph_key(const pixvod_ctx* c, int n_ite
     key_put(k, s.prior_ell);
     key_put(k, s.prior_R);
     key_put(k, s.prior_t);
+    key_put(k, s.prior_q);
+    key_put(k, s.prior_p);
     key_put(k, s.prior_is_identity);
     key_put(k, s.has_sigma_map);
     key_put(k, s.has_prior_map);
