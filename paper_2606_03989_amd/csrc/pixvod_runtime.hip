@@ -917,28 +917,28 @@ int pixvod_track(pixvod_ctx* c, const float* frame, int where, int n_iters, pixv
     MapJob jobs[2];
     int n_jobs = 0;
     if (out->inv_depth || out->inv_depth_var) {
-        float* d_inv = out->inv_depth;
-        float* d_var = out->inv_depth_var;
-        bool staged = false;
+        float* const dst[2] = {out->inv_depth, out->inv_depth_var};
+        float* to[2] = {dst[0], dst[1]};   // where the kernel writes them
+        bool copied[2] = {false, false};
         if (out->out_where == PIXVOD_HOST) {
-            // the maps in pinned memory, or in device memory and copied
-            float* pinned = c->maps.reserve(2 * N);
-            staged = pinned != nullptr;
-            float* stage = staged ? pinned : c->out_stage;
-            d_inv = out->inv_depth ? stage : nullptr;
-            d_var = out->inv_depth_var ? stage + N : nullptr;
-            if (staged && d_inv) jobs[n_jobs++] = {out->inv_depth, d_inv, N};
-            if (staged && d_var) jobs[n_jobs++] = {out->inv_depth_var, d_var, N};
+            // a map in pinned memory, or in device memory and copied
+            bool direct[2], stage = false;
+            for (int k = 0; k < 2; ++k) {
+                direct[k] = dst[k] && copied_directly(dst[k], N);
+                stage = stage || (dst[k] && !direct[k]);
+            }
+            float* pinned = stage ? c->maps.reserve(2 * N) : nullptr;
+            for (int k = 0; k < 2; ++k) {
+                if (!dst[k]) continue;
+                copied[k] = direct[k] || !pinned;
+                to[k] = (copied[k] ? c->out_stage : pinned) + k * N;
+                if (!copied[k]) jobs[n_jobs++] = {dst[k], to[k], N};
+            }
         }
-        HIP_TRY(c, launch_outputs(g, c->X[c->cur], c->var_ll, c->have_var ? 1 : 0, d_inv, d_var, c->stream));
-        if (out->out_where == PIXVOD_HOST && !staged) {
-            if (out->inv_depth)
-                HIP_TRY(c, hipMemcpyAsync(out->inv_depth, c->out_stage, N * sizeof(float), hipMemcpyDeviceToHost,
-                                          c->stream));
-            if (out->inv_depth_var)
-                HIP_TRY(c, hipMemcpyAsync(out->inv_depth_var, c->out_stage + N, N * sizeof(float),
-                                          hipMemcpyDeviceToHost, c->stream));
-        }
+        HIP_TRY(c, launch_outputs(g, c->X[c->cur], c->var_ll, c->have_var ? 1 : 0, to[0], to[1], c->stream));
+        for (int k = 0; k < 2; ++k)
+            if (copied[k])
+                HIP_TRY(c, hipMemcpyAsync(dst[k], to[k], N * sizeof(float), hipMemcpyDeviceToHost, c->stream));
     }
     MapCopier copier(jobs, n_jobs);
     HIP_TRY(c, hipStreamSynchronize(c->stream));

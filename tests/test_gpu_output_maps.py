@@ -1,11 +1,14 @@
 """Output maps of a frame step in device and host memory, at the edges of the
 ways they take there."""
 
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
-from test_gpu_host_maps import _batch, _step
+import synth
+from test_gpu_host_maps import PARAMS, _batch, _step
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +34,27 @@ def test_overlapping_device_maps_keep_the_order_of_the_sequences(shapes):
     for a, w in zip(at, want):
         exp[:, a:a + w.shape[1]] = w
     assert np.array_equal(one.cpu().numpy(), exp)
+
+
+# on both sides of the size from which a map goes to pinned memory by a copy of its own (2^17 pixels)
+@pytest.mark.parametrize("shape", [(3, 65), (256, 511), (256, 512), (517, 641)])
+@pytest.mark.parametrize("pinned", [(True, True), (True, False), (False, True), (True, None), (None, True)])
+def test_frame_maps_in_pinned_memory(shape, pinned):
+    """pinned: per map (inverse depth, variance) pinned or pageable host memory, or None: not asked for."""
+    import paper_2606_03989_amd as pv
+    H, W = shape
+    p = synth.tiny_pair(0, H=H, W=W, inv_depth=0.5, rotvec=[0.001, -0.002, 0.001], trans=[0.004, -0.002, 0.003])
+    t = pv.Tracker(H, W, (p["cam"].fx, p["cam"].fy, p["cam"].cx, p["cam"].cy), **PARAMS)
+    t.set_keyframe(p["I_s"], p["normals_s"])
+    frame = np.ascontiguousarray(p["I_t"], np.float32)
+    state = t.get_state()
+    r = t.track(frame, 2, out_device=True)
+    want = [r[k].cpu().numpy() for k in ("inv_depth", "inv_depth_var")]
+    for _ in range(2):   # the second time with the memory that the first one took
+        t.set_state(state)
+        maps = [torch.full((H, W), -1.0, pin_memory=bool(k)) for k in pinned]
+        out = pv.TrackOut(out_where=pv.HOST)
+        out.inv_depth, out.inv_depth_var = [m.data_ptr() if k is not None else None for m, k in zip(maps, pinned)]
+        assert pv.lib().pixvod_track(t._h, C.c_void_p(frame.ctypes.data), pv.HOST, 2, C.byref(out)) == 0
+        for m, k, w in zip(maps, pinned, want):
+            assert np.array_equal(m.numpy(), w) if k is not None else bool((m == -1.0).all())
