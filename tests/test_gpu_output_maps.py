@@ -58,3 +58,18 @@ def test_frame_maps_in_pinned_memory(shape, pinned):
         assert pv.lib().pixvod_track(t._h, C.c_void_p(frame.ctypes.data), pv.HOST, 2, C.byref(out)) == 0
         for m, k, w in zip(maps, pinned, want):
             assert np.array_equal(m.numpy(), w) if k is not None else bool((m == -1.0).all())
+
+
+# few large sequences, whose maps are formed by more workgroups each than those of many; 33 sequences: the line
+@pytest.mark.parametrize("shapes", [[(1030, 1027)], [(700, 701), (3, 5)], [(40, 67)] * 32, [(40, 67)] * 33])
+def test_device_maps_of_few_and_many_sequences(shapes):
+    import paper_2606_03989_amd as pv
+    b, frames = _batch(shapes)
+    dev = [torch.full((2, H, W), -1.0, device="cuda") for H, W in shapes]
+    _step(b, frames, [(pv.DEVICE, d[0].data_ptr(), d[1].data_ptr()) for d in dev])
+    for i, d in enumerate(dev):
+        # inverse depth of the state's log-depth, rounded once to FP32 (half an ulp; two for a libm of another ulp)
+        want = np.exp(-b.get_state(i)[6].astype(np.float64))
+        assert np.abs(d[0].cpu().numpy() - want).max() <= 2 * 2.0 ** -24 * want.max()
+        var = d[1].cpu().numpy()
+        assert np.isfinite(var).all() and (var > 0).all()
