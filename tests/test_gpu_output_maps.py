@@ -73,3 +73,48 @@ def test_device_maps_of_few_and_many_sequences(shapes):
         assert np.abs(d[0].cpu().numpy() - want).max() <= 2 * 2.0 ** -24 * want.max()
         var = d[1].cpu().numpy()
         assert np.isfinite(var).all() and (var > 0).all()
+
+
+def _textured(H, W, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    a = torch.rand((1, 1, H // 16 + 2, W // 16 + 2), device="cuda", generator=g)
+    a = torch.nn.functional.interpolate(a, scale_factor=16, mode="bilinear")[0, 0, :H, :W].contiguous()
+    n = torch.zeros((H, W, 3), device="cuda")
+    n[..., 2] = -1.0
+    return a, n
+
+
+# more floats of maps for host memory than a context pins (2^26): they go through device memory
+def test_maps_of_a_frame_beyond_the_pinned_memory():
+    import paper_2606_03989_amd as pv
+    H, W = 5793, 5795
+    img, nrm = _textured(H, W, 1)
+    r = []
+    for device in (True, False):
+        t = pv.Tracker(H, W, (0.9 * W, 0.9 * W, W / 2, H / 2), **PARAMS)
+        t.set_keyframe(img, nrm)
+        r.append(t.track(img, 1, out_device=device))
+        t.close()
+    for k in ("inv_depth", "inv_depth_var"):
+        assert np.isfinite(r[1][k]).all() and np.array_equal(r[0][k].cpu().numpy(), r[1][k])
+
+
+def test_maps_of_a_batch_beyond_the_pinned_memory():
+    import paper_2606_03989_amd as pv
+    shapes = [(4097, 4099), (3, 65), (4097, 4097)]
+    pairs = [_textured(H, W, k) for k, (H, W) in enumerate(shapes)]
+    r = []
+    for where in (pv.DEVICE, pv.HOST):
+        b = pv.Batch(shapes, [(0.9 * W, 0.9 * W, W / 2, H / 2) for H, W in shapes], **PARAMS)
+        b.set_keyframes(list(range(len(shapes))), [p[0] for p in pairs], [p[1] for p in pairs])
+        maps = [torch.full((2, H, W), -1.0, device="cuda" if where == pv.DEVICE else "cpu") for H, W in shapes]
+        outs = (pv.TrackOut * b.n)()
+        for o, m in zip(outs, maps):
+            o.out_where, o.inv_depth, o.inv_depth_var = where, m[0].data_ptr(), m[1].data_ptr()
+        torch.cuda.synchronize()
+        frames = (C.c_void_p * b.n)(*[p[0].data_ptr() for p in pairs])
+        assert pv.lib().pixvod_batch_track(b._h, frames, pv.DEVICE, 1, outs) == 0
+        b.close()
+        r.append([m.cpu().numpy() for m in maps])
+    for d, h in zip(*r):
+        assert np.isfinite(h).all() and (h[0] > 0).all() and np.array_equal(d, h)
