@@ -1380,11 +1380,20 @@ static dim3 grid2d(const Geo& g, dim3 b) { return dim3((g.W + b.x - 1) / b.x, (g
 static const dim3 kBlock(64, 1);
 static const dim3 kSplitBlock(64, 4);
 // One workgroup of four waves per CU, a wave per SIMD: up to there the split
-// pass is faster (frames of 20 iterations, 24 row segments: 248 against 388 us;
-// 256: 321 against 384), from there on its repeated parts share SIMDs (288:
-// 391 against 394; 384: 427 against 418; 576: 609 against 473).
-constexpr long kSplitSegments = 256;
-static bool use_split(const Geo& g) { return (long)((g.W + 63) / 64) * g.H <= kSplitSegments; }
+// pass is faster (256 CUs, frames of 20 iterations, 24 row segments: 248 against
+// 388 us; 256: 321 against 384), from there on its repeated parts share SIMDs
+// (288: 391 against 394; 384: 427 against 418; 576: 609 against 473).
+static bool use_split(const Geo& g) {
+    static const int n_cu = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+            n = 256;
+        return n;
+    }();
+    return (long)((g.W + 63) / 64) * g.H <= n_cu;
+}
+
 hipError_t launch_frame_prep(const Geo& g, const float* src, long src_pitch, float* It, float* Gx, float* Gy,
                              hipStream_t st, int* clear) {
     hipLaunchKernelGGL(k_frame_prep, grid2d(g, kBlock), kBlock, 0, st, g, src, src_pitch, It, Gx, Gy, clear);
@@ -1456,16 +1465,17 @@ hipError_t launch_fu_segment_tape(const Geo& g, const Strengths& s, const Inputs
                                   hipStream_t st) {
     if (len < 1) return hipSuccess;
     const dim3 grid = grid2d(g, kBlock);
+    const bool split = use_split(g);
     hipLaunchKernelGGL(k_fu_prologue_tape, grid, kBlock, 0, st, g, s, in, X0, tA, marg, health);
     float* t[2] = {tA, tB};
     for (int k = 0; k < len; ++k) {
         const Tape tape{bel + bel_stride * k, seg + seg_stride * k, marg + marg_stride * (k + 1)};
         const float* src = t[k & 1];
         float* dst = t[(k + 1) & 1];
-        if (use_split(g) && k + 1 < len)
+        if (split && k + 1 < len)
             hipLaunchKernelGGL((k_fu_split<false, true>), grid, kSplitBlock, 0, st, g, s, in, src, dst, tape, var_ll,
                                valid, health);
-        else if (use_split(g))
+        else if (split)
             hipLaunchKernelGGL((k_fu_split<true, true>), grid, kSplitBlock, 0, st, g, s, in, src, dst, tape, var_ll,
                                valid, health);
         else if (k + 1 < len)
