@@ -20,9 +20,8 @@ struct PoseBar {
 // existing slot of Xb by its reader
 // Xn: the canonical state after the iteration, whose messages hold the new
 // messages' information
-hipError_t launch_adj_update(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const float* Xn,
-                             const double* bel, const float* Xb, const float* Cb, float* Mb, float* Ub,
-                             hipStream_t st);
+hipError_t launch_adj_update(const Geo& g, const float* X, const float* Xn, const double* bel, const float* Xb,
+                             const float* Cb, float* Mb, float* Ub, hipStream_t st);
 hipError_t launch_adj_edges(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const double* marg,
                             const float* Xn, const float* Mb, float* Xbo, float* Eb, double* gN, hipStream_t st);
 hipError_t launch_adj_belief(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const double* marg,

@@ -102,9 +102,8 @@ __device__ inline void store_planes(float* base, long stride, unsigned o, const 
 // the transport's sums, which do not need the solve, stand under the belief's
 // loads. 320 x 240, beside the recompute: 40.4 us, 51.3 with the loads behind
 // the solve and Cholesky factors.
-__global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, Strengths s, Inputs in, const float* X, const float* Xn,
-                                                      const double* bel, const float* Xb, const float* Cb, float* Mb,
-                                                      float* Ub) {
+__global__ __launch_bounds__(64, 2) void k_adj_update(Geo g, const float* X, const float* Xn, const double* bel,
+                                                      const float* Xb, const float* Cb, float* Mb, float* Ub) {
     __shared__ float buf[84 * 64];
     int u, v;
     segment_pixel(threadIdx.x, u, v);
@@ -572,10 +571,9 @@ __global__ void k_plane_to_dense(Geo g, const double* __restrict__ src, float* _
 static const dim3 kAdjBlock(64, 4);
 static dim3 adj_grid(const Geo& g) { return dim3((g.W + 63) / 64, (g.H + 3) / 4); }
 
-hipError_t launch_adj_update(const Geo& g, const Strengths& s, const Inputs& in, const float* X, const float* Xn,
-                             const double* bel, const float* Xb, const float* Cb, float* Mb, float* Ub,
-                             hipStream_t st) {
-    hipLaunchKernelGGL(k_adj_update, dim3((g.W + 63) / 64, g.H), dim3(64), 0, st, g, s, in, X, Xn, bel, Xb, Cb, Mb, Ub);
+hipError_t launch_adj_update(const Geo& g, const float* X, const float* Xn, const double* bel, const float* Xb,
+                             const float* Cb, float* Mb, float* Ub, hipStream_t st) {
+    hipLaunchKernelGGL(k_adj_update, dim3((g.W + 63) / 64, g.H), dim3(64), 0, st, g, X, Xn, bel, Xb, Cb, Mb, Ub);
     return hipGetLastError();
 }
 

@@ -473,7 +473,7 @@ int pixvod_unroll_backward(pixvod_unroll* u, const double* xi_bar, const float* 
             const float* Xn = k + 1 < len ? B.seg + S * k : (len & 1 ? B.sink : B.tmp);
             const double* marg = B.marg + pl * MARG_PLANES * k;
             const double* bel = B.bel + pl * BEL_PLANES * k;
-            UHIP(launch_adj_update(g, s, I, X, Xn, bel, u->Xb[cur], u->Cb[cur], u->Mb, u->Ub, u->stream));
+            UHIP(launch_adj_update(g, X, Xn, bel, u->Xb[cur], u->Cb[cur], u->Mb, u->Ub, u->stream));
             UHIP(launch_adj_edges(g, s, I, X, marg, Xn, u->Mb, u->Xb[cur ^ 1], u->Eb, u->gN, u->stream));
             UHIP(launch_adj_belief(g, s, I, X, marg, u->Ub, u->Eb, u->Xb[cur ^ 1], u->Cb[cur ^ 1], u->gsig, u->gk,
                                    u->stream));
