@@ -103,7 +103,13 @@ typedef struct {
     float* inv_depth_var;      /* caller buffer (H*W) or NULL: delta-method
                                 * variance of the inverse depth from the final
                                 * belief; NaN when n_iters == 0 */
-    int32_t out_where;         /* PIXVOD_HOST / PIXVOD_DEVICE for the two maps */
+    int32_t out_where;         /* PIXVOD_HOST / PIXVOD_DEVICE for the two maps.
+                                * Maps for host memory go through pinned host
+                                * memory, up to 256 MB of which a context or
+                                * batch takes when it is first asked for them
+                                * and keeps until it is destroyed; larger ones
+                                * and large ones for pinned memory are copied
+                                * from device memory. */
     float valid_fraction;      /* pixels whose warp landed in the image during
                                 * the last iteration */
     int32_t frames_since_keyframe;
@@ -119,6 +125,7 @@ void pixvod_default_params(pixvod_params* params);
  * by the context: 123 float32 planes per pixel (pose 6, log-depth 1, four
  * identity messages of 27 values and four normal messages of 2 values) in
  * two ping-pong copies, plus the keyframe and frame inputs. Returns
+ * PIXVOD_EINVAL for more than 2^28 pixels or 2^30 with each row padded to 64,
  * PIXVOD_ENODEV without a usable GPU, PIXVOD_ENOMEM if allocation fails. */
 int pixvod_create(int H, int W, const pixvod_intrinsics* K, const pixvod_params* params,
                   pixvod_ctx** out_ctx);
@@ -289,7 +296,8 @@ int pixvod_batch_set_keyframes(pixvod_batch* b, int m, const int* seq_ids, const
 
 /* One frame per sequence (frames[i], H[i]*W[i]); n_iters >= 1 iterations for
  * all sequences; outs[i] receives sequence i's result (maps written when its
- * pointers are set). Requires every sequence to have a keyframe. */
+ * pointers are set; where maps of several sequences share memory, the last
+ * sequence's stay). Requires every sequence to have a keyframe. */
 int pixvod_batch_track(pixvod_batch* b, const float* const* frames, int where, int n_iters,
                        pixvod_track_out* outs);
 
@@ -306,9 +314,9 @@ int pixvod_batch_track(pixvod_batch* b, const float* const* frames, int where, i
 int pixvod_batch_track_reanchor(pixvod_batch* b, const float* const* frames, const float* const* normals,
                                 int where, int n_iters, pixvod_track_out* outs);
 
-/* Runs the iteration block of each frame step (prologue and n_iters passes)
- * as one persistent cooperative launch with a grid-wide barrier between the
- * passes (enable = 1) instead of one captured launch per pass (0, default).
+/* Runs the first n_iters - 1 passes of each frame step as one persistent
+ * cooperative launch with a grid-wide barrier between the passes (enable = 1)
+ * instead of one captured launch per pass (0, default).
  * Results are identical; the grid is the co-resident maximum for the tile. */
 int pixvod_batch_set_persistent(pixvod_batch* b, int enable);
 
@@ -355,8 +363,11 @@ typedef struct pixvod_unroll pixvod_unroll;
 
 /* H, W >= 2; 1 <= n_iters; 1 <= ckpt_every; 1 <= max_frames. Device memory
  * holds max_frames * ceil(n_iters / ckpt_every) checkpoints of the state
- * (123 * H * W floats each, rows padded to 64 floats) and ckpt_every states of
- * one recomputed segment. */
+ * (123 * H * W floats each, rows padded to 64 floats), two states (the first and
+ * the last), the state's cotangent in two copies and 252 FP32 planes of
+ * intermediate cotangents; and for the recompute, which runs one segment ahead
+ * of the reverse, twice max(ckpt_every - 1, 1) + 2 states and 72 * ckpt_every
+ * FP64 planes. PIXVOD_EINVAL as for pixvod_create. */
 int pixvod_unroll_create(int H, int W, const pixvod_intrinsics* K, const pixvod_params* params, int max_frames,
                          int n_iters, int ckpt_every, pixvod_unroll** out_unroll);
 int pixvod_unroll_destroy(pixvod_unroll* u);
@@ -435,7 +446,7 @@ int pixvod_central_get_point(pixvod_central* c, double xi[6], double* log_depth)
 /* n_iters >= 0 IRLS iterations on `frame` (H*W) from the current point
  * (warm start); xi_out (host, may be NULL), inv_depth (H*W at out_where, may
  * be NULL), stats (may be NULL). ESTATE before a keyframe. Synchronous: the
- * host reads the CG stop test between chunks of 16 CG iterations on the
+ * host reads the CG stop test between chunks of 4 CG iterations on the
  * solver's stream. */
 int pixvod_central_track(pixvod_central* c, const float* frame, int where, int n_iters, double xi_out[6],
                          float* inv_depth, int out_where, pixvod_central_stats* stats);

@@ -416,8 +416,10 @@ __global__ __launch_bounds__(256, 3) void k_adj_edges(Geo g, Strengths s, Inputs
 
 // reverse of the marginals and of the unary factors; completes Xbo (point
 // planes) and writes the slot-common part Cbo. Two phases (marginals, unary),
-// each with its own loads, so that the kernel fits 256 registers and two waves
-// share a SIMD (24.2 us at 320 x 240, beside the recompute; 36.2 with 400).
+// each with its own loads, so that two waves share a SIMD: 256 registers and
+// six values in scratch (28 bytes per lane), whose reloads wait for the stores of
+// Cbo before them; those stores behind the loads gained nothing (24.2 us at 320 x
+// 240, beside the recompute; 36.2 with 400 registers).
 __global__ __launch_bounds__(64, 2) void k_adj_belief(Geo g, Strengths s, Inputs in, const float* X,
                                                       const double* marg, const float* Ub, const float* Eb, float* Xbo,
                                                       float* Cbo, double* gsig, double* gk) {

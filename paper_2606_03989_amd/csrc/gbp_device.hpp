@@ -38,7 +38,6 @@ __host__ __device__ constexpr int s7(int r, int c) {
 }
 
 // ---------------------------------------------------------------------------
-// frame geometry and factor strengths, passed by value to every kernel
 // Elements from a plane of the state to the next. The padding of 64 keeps planes
 // whose size is a large power of two's multiple off the same memory channels
 // (640 x 480: 78.6 us per pass against 80.8; 256 x 256: 19.5 against 19.7; the
@@ -52,6 +51,7 @@ __host__ __device__ constexpr bool plane_addressable(int H, int W) {
     return (long)H * ((W + 63L) / 64 * 64) <= 1L << 30;
 }
 
+// frame geometry and factor strengths, passed by value to every kernel
 struct Geo {
     int H, W;
     int pitch;            // floats per row of every plane

@@ -31,11 +31,11 @@ namespace pv {
 // everything else in registers: at most 256 registers, so that two waves share
 // a SIMD and fill each other's waits. Passes that also store the messages of
 // each iteration (with a tape, damped) spilled at that, and a spilled value's
-// load waits for every store before it; they keep 78 planes in LDS, as much as
-// eight waves can have (320 x 240: with tape, beside the reverse kernels, 54.5 us
-// against 66.5; damped 34.5 against 41.4), which costs the other passes 2% (256 x
-// 256: 20.25 us against 19.75). Every lane reads only what it loaded itself, so
-// no barrier is needed.
+// load waits for every store before it; they keep 78 planes in LDS, which is
+// enough for none (160 KB would give eight waves 80; 320 x 240: with tape, beside
+// the reverse kernels, 54.5 us against 66.5; damped 34.5 against 41.4), but costs
+// the other passes 2% (256 x 256: 20.25 us against 19.75). Every lane reads only
+// what it loaded itself, so no barrier is needed.
 constexpr int LDS_PLANES = 63, LDS_PLANES_STORING = 78;
 
 template <int PLANES>
@@ -703,12 +703,13 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 
 // Fused passes of one image: one wave per workgroup, 64 pixels of a row, so
 // that a SIMD takes the next row segment as soon as one of its two waves ends.
-// Bound by memory where the image fills the chip (640 x 480: 80 us per pass,
-// 302 MB of algorithmic bytes, whose copy at this card's 4.74 TB/s takes 64 us;
-// 1920 x 1080: 459 us, copy 431; 127 us at 640 x 480 before, as one wave per SIMD of a persistent workgroup with 504
-// registers) and by one wave's chain of instructions and loads where it does
-// not (256 x 256: 19.7 us, 27 before; 4,218 vector instructions per wave, 6,234
-// before; the smallest images take k_fu_split).
+// Bound by memory where the image fills the chip (640 x 480: 74 to 82 us per
+// pass, 310 MB of algorithmic bytes, whose copy at this card's 4.74 TB/s takes 65
+// us; 1920 x 1080: 455 us, copy 441; 127 us at 640 x 480 before, as one wave per
+// SIMD of a persistent workgroup with 504 registers) and by one wave's chain of
+// instructions and loads where it does not (256 x 256: 19.7 us, 27 before; 4,223
+// vector instructions per wave, 6,234 before; the smallest images take
+// k_fu_split).
 __global__ __launch_bounds__(64, 2) void k_fu_prologue(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
                                                        float* __restrict__ Y, int* __restrict__ health) {
     __shared__ float buf[Messages<LDS_PLANES>::kFloats];

@@ -15,8 +15,10 @@
 // partials towards its children, stay in the sender's own slots (coalesced
 // writes from the wide lower levels; the parent gathers four children from
 // two adjacent rows). Normal-integration partials go into the receiver's
-// slot, as on the grid. At frame ends the same slots hold the canonical
-// messages, each stored at the variable that receives it.
+// slot: 8 of 42 planes, for which the sender's slot, as on the grid, gains
+// nothing (65.9 us per iteration at 640 x 480, 65.5 so). At frame ends the same
+// slots hold the canonical messages, each stored at the variable that receives
+// it.
 #include "gbp_tree.h"
 #include "gbp_device.hpp"
 #include "gbp_planes.hpp"

@@ -4,9 +4,9 @@
 // at a time, and the first touch of a new buffer's pages is taken by one
 // thread. Here the kernel that forms the maps writes them to pinned memory that
 // the context keeps, and after the step's one wait the maps are copied out, by
-// several threads if they are large. 64 mixed sequences, 59 MB of maps: 31.6 ms
-// per frame step, 25.9 without maps, 42 with a copy per map (36 with one thread
-// beside the caller, 32.8 with three, 31.2 with fifteen).
+// several threads if they are large. 64 mixed sequences, 59 MB of maps into new
+// arrays: 32.9 ms per frame step, 26.5 without maps, 40.8 with a copy per map
+// (36.7 with one thread beside the caller, 34.1 with three, 31.6 with fifteen).
 #pragma once
 
 #include <hip/hip_runtime.h>

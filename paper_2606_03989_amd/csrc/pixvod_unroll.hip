@@ -6,8 +6,10 @@
 // writes the next one there (per-factor and fused schedules are the same
 // iteration bit for bit, so the tape holds exactly the per-factor states).
 // Backward, for frames and segments in reverse: recompute the segment's
-// states from its checkpoint, one prologue + final pass per state, which also
-// keep each state's marginals and new messages; then run the three reverse
+// states from its checkpoint, one prologue and one rotated pass per iteration,
+// which also keep the depth marginal and belief of each emission and the belief
+// of each update (the new messages' information is read from the state after
+// the iteration, which holds it); then run the three reverse
 // kernels for each state from last to first.
 #include <hip/hip_runtime.h>
 
@@ -25,7 +27,7 @@
 using namespace pv;
 
 namespace {
-constexpr int MSG_PLANES = 116;  // 4 x (eta 6, Lambda 21, normal eta, normal lambda): cotangents (FP64)
+constexpr int MSG_PLANES = 116;  // 4 x (eta 6, Lambda 21, normal eta, normal lambda): cotangents (FP32)
 constexpr int MARG_PLANES = 37;  // depth marginal 2, its belief 28 + 7
 constexpr int BEL_PLANES = 35;   // belief of the update: 28 + 7
 constexpr int UB_PLANES = 42;
