@@ -707,7 +707,7 @@ __device__ __attribute__((always_inline)) inline void iterate_pixel(const Geo& g
 // pass, 310 MB of algorithmic bytes, whose copy at this card's 4.74 TB/s takes 65
 // us; 1920 x 1080: 455 us, copy 441; 127 us at 640 x 480 before, as one wave per
 // SIMD of a persistent workgroup with 504 registers) and by one wave's chain of
-// instructions and loads where it does not (256 x 256: 19.7 us, 27 before; 4,223
+// instructions and loads where it does not (256 x 256: 19.7 us, 27 before; 4,303
 // vector instructions per wave, 6,234 before; the smallest images take
 // k_fu_split).
 __global__ __launch_bounds__(64, 2) void k_fu_prologue(Geo g, Strengths s, Inputs in, const float* __restrict__ X,
